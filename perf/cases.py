@@ -195,6 +195,7 @@ def _prepare_batch(case, seed):
         if case["op"] != "call":
             # a loader's first batch runs directly: the recording takes its grid from that batch's hit counts
             other = W.seed_batch(sp, g, m + case["members"])
+            torch.cuda.synchronize()                     # the context's stream does not wait for the one that made them
             h.prepare_batch(other, _fan(case), rs + 1, *_args(bufs))
             h.sync()
             for t in (bufs.unique, bufs.inverse, bufs.miss_pos, bufs.miss_id, bufs.miss_slot, bufs.out):
