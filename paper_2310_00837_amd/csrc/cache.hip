@@ -4,9 +4,9 @@
 //
 // lookup_partition: one thread per ID reads rank[id] (one random 4-byte read),
 // classifies it into the HBM tier, the host tier or a miss by two compares, and
-// the three classes are compacted *stably* in one pass: a thread takes four
-// consecutive IDs, a workgroup scan gives the in-tile ranks and a three-counter
-// chained scan (scan.hpp) the ranks across workgroups.  The two hit lists (position, slot)
+// the three classes are compacted *stably* in one pass: wave ballots and a scan of
+// the waves' totals give the ranks inside a tile and a three-counter
+// chained scan (TileScan in scan.hpp) the ranks across workgroups.  The two hit lists (position, slot)
 // feed the row-copy kernels; the miss list (position, id, slot) is the request
 // list of the storage tier and comes out ascending in position.
 #include "kernels.hpp"
@@ -52,77 +52,74 @@ struct PartitionArgs {
     int32_t* err;
 };
 
-__global__ __launch_bounds__(kBlock) void lookup_partition_kernel(PartitionArgs a) {
-    __shared__ uint32_t s_wave[kWavesPerBlock + 1];
-    __shared__ uint32_t s_ticket, s_agg[3], s_excl[3];
-    __shared__ ScanLookbackLds<3> s_look;
-    const int64_t n = a.n.get();
-    const int64_t n_tiles = (n + kTileItems - 1) / kTileItems;
+// Bound like a stage of the compaction (compact_dev.hpp) by its chain of dependent steps, and built like it.
+template <int K>
+__global__ __launch_bounds__(kScanBlock) void lookup_partition_kernel(PartitionArgs a) {
+    using Scan = TileScan<2, 3, K>;
+    __shared__ typename Scan::Lds lds;
+    const ScanState scan = scan_resolve(a.scan);
+    const uint32_t n = static_cast<uint32_t>(a.n.get());
+    const uint32_t n_tiles = (n + K * kScanBlock - 1) / (K * kScanBlock);
     if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
         a.lists.count[0] = a.lists.count[1] = a.lists.count[2] = 0;
         if (a.stats_out) { a.stats_out[0] = 0; a.stats_out[1] = 0; a.stats_out[2] = 0; a.stats_out[3] = 0; }
     }
-    if (static_cast<int64_t>(blockIdx.x) >= n_tiles) return;
-    const uint32_t tile = scan_take_ticket(a.scan, static_cast<uint32_t>(n_tiles), &s_ticket);
-
-    // a thread takes four consecutive IDs: all four rank reads are in flight together
-    const int64_t j0 = static_cast<int64_t>(tile) * kTileItems + static_cast<int64_t>(threadIdx.x) * kItemsPerThread;
-    int32_t id[kItemsPerThread], slot[kItemsPerThread];
-    int tier[kItemsPerThread];               // -1: no ID here (tail of the last tile, or a bad ID)
+    if (blockIdx.x >= n_tiles) return;
+    const uint32_t n_wgs = gridDim.x < n_tiles ? gridDim.x : n_tiles;
+    for (uint32_t tile = Scan::take_ticket(scan, n_tiles, n_wgs, lds); tile < n_tiles;
+         tile = n_wgs < n_tiles ? Scan::take_ticket(scan, n_tiles, n_wgs, lds) : n_tiles) {
+        const uint32_t j0 = tile * (K * kScanBlock) + threadIdx.x;
+        int32_t id[K], r[K];
 #pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) id[k] = j0 + k < n ? a.ids[j0 + k] : -1;
-    int64_t r[kItemsPerThread];
+        for (int k = 0; k < K; ++k) id[k] = a.ids[j0 + k * kScanBlock < n ? j0 + k * kScanBlock : 0];
 #pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) {
-        const bool ok = id[k] >= 0 && static_cast<int64_t>(id[k]) < a.n_nodes;
-        if (j0 + k < n && !ok) raise(a.err, kErrData);
-        r[k] = ok ? static_cast<int64_t>(a.rank[id[k]]) : -1;
-    }
-    uint32_t c_hbm = 0, c_host = 0, c_miss = 0;
-#pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) {
-        tier[k] = -1;
-        slot[k] = 0;
-        if (r[k] >= 0) {
-            if (r[k] < a.n_hbm) { tier[k] = 0; slot[k] = static_cast<int32_t>(r[k]); ++c_hbm; }
-            else if (r[k] < a.n_hbm + a.n_host) { tier[k] = 1; slot[k] = static_cast<int32_t>(r[k] - a.n_hbm); ++c_host; }
-            else { tier[k] = 2; slot[k] = static_cast<int32_t>(r[k] - a.n_hbm - a.n_host); ++c_miss; }
+        for (int k = 0; k < K; ++k) {
+            const bool here = j0 + k * kScanBlock < n, ok = here && id[k] >= 0 && static_cast<int64_t>(id[k]) < a.n_nodes;
+            if (here && !ok) raise(a.err, kErrData);
+            const int32_t got = a.rank[ok ? id[k] : 0];          // all reads in flight together
+            r[k] = ok ? got : -1;                                // -1: no ID here, a bad ID, or a node that the order left out
         }
-    }
-    // ranks inside the workgroup: the two hit classes share one scan (16 bits each, a tile has 1024 IDs)
-    uint32_t tot_hits, tot_miss;
-    const uint32_t before_hits = block_exclusive_scan(c_hbm | (c_host << 16), s_wave, tot_hits);
-    const uint32_t before_miss = block_exclusive_scan(c_miss, s_wave, tot_miss);
-    if (threadIdx.x == 0) {
-        s_agg[0] = tot_hits & 0xffffu;
-        s_agg[1] = tot_hits >> 16;
-        s_agg[2] = tot_miss;
-    }
-    scan_chained_prefix<3>(a.scan, tile, s_agg, s_excl, &s_look, a.err);
-    int64_t at[3] = {static_cast<int64_t>(s_excl[0]) + (before_hits & 0xffffu),
-                     static_cast<int64_t>(s_excl[1]) + (before_hits >> 16),
-                     static_cast<int64_t>(s_excl[2]) + before_miss};
+        const uint32_t n_hbm = static_cast<uint32_t>(a.n_hbm), n_cached = static_cast<uint32_t>(a.n_hbm + a.n_host);
+        uint32_t totals[2][K], before[2][K], in_class[K], in_hits[K];
 #pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) {
-        if (tier[k] < 0) continue;
-        const int64_t w = tier[k] == 0 ? at[0]++ : tier[k] == 1 ? at[1]++ : at[2]++;
-        if (tier[k] < 2) {
-            a.lists.pos[tier[k]][w] = static_cast<int32_t>(j0 + k);
-            a.lists.slot[tier[k]][w] = slot[k];
-        } else if (w < a.miss_cap) {
-            a.miss_pos[w] = static_cast<int32_t>(j0 + k);
-            a.miss_id[w] = id[k];
-            a.miss_slot[w] = slot[k];
+        for (int k = 0; k < K; ++k) {
+            const uint32_t ur = static_cast<uint32_t>(r[k]);     // -1 is in none of the three classes
+            const uint64_t hbm = __ballot(ur < n_hbm), host = __ballot(ur >= n_hbm && ur < n_cached), miss = __ballot(r[k] >= 0 && ur >= n_cached);
+            totals[0][k] = static_cast<uint32_t>(__popcll(miss));
+            totals[1][k] = static_cast<uint32_t>(__popcll(hbm)) | (static_cast<uint32_t>(__popcll(host)) << 16);
+            in_class[k] = rank_in_mask(miss);
+            in_hits[k] = rank_in_mask(hbm) | (rank_in_mask(host) << 16);
         }
-    }
-    if (static_cast<int64_t>(tile) == n_tiles - 1 && threadIdx.x == 0) {
-        const int64_t c0 = static_cast<int64_t>(s_excl[0]) + s_agg[0];
-        const int64_t c1 = static_cast<int64_t>(s_excl[1]) + s_agg[1];
-        const int64_t c2 = static_cast<int64_t>(s_excl[2]) + s_agg[2];
-        a.lists.count[0] = c0; a.lists.count[1] = c1; a.lists.count[2] = c2;
-        if (a.stats_out) { a.stats_out[0] = n; a.stats_out[1] = c0; a.stats_out[2] = c1; a.stats_out[3] = c2; }
-        if (a.learn) { a.learn[0] = n; a.learn[1] = c0; a.learn[2] = c1; a.learn[3] = c2; }
-        if (c2 > a.miss_cap) raise(a.err, kErrCapacity);
+        Scan::run(scan, tile, totals, before, lds, a.err);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (r[k] < 0) continue;
+            const uint32_t ur = static_cast<uint32_t>(r[k]);
+            const int32_t j = static_cast<int32_t>(j0 + k * kScanBlock);
+            const uint32_t hits = before[1][k] + in_hits[k];
+            if (ur < n_cached) {
+                const bool host = ur >= n_hbm;
+                const uint32_t w = host ? lds.excl[2] + (hits >> 16) : lds.excl[1] + (hits & 0xffffu);
+                (host ? a.lists.pos[1] : a.lists.pos[0])[w] = j;
+                (host ? a.lists.slot[1] : a.lists.slot[0])[w] = static_cast<int32_t>(host ? ur - n_hbm : ur);
+            } else {
+                const int64_t w = static_cast<int64_t>(lds.excl[0]) + before[0][k] + in_class[k];
+                if (w < a.miss_cap) {
+                    a.miss_pos[w] = j;
+                    a.miss_id[w] = id[k];
+                    a.miss_slot[w] = static_cast<int32_t>(ur - n_cached);
+                }
+            }
+        }
+        if (tile == n_tiles - 1 && threadIdx.x == 0) {
+            const int64_t c0 = static_cast<int64_t>(lds.excl[1]) + lds.agg[1];
+            const int64_t c1 = static_cast<int64_t>(lds.excl[2]) + lds.agg[2];
+            const int64_t c2 = static_cast<int64_t>(lds.excl[0]) + lds.agg[0];
+            a.lists.count[0] = c0; a.lists.count[1] = c1; a.lists.count[2] = c2;
+            if (a.stats_out) { a.stats_out[0] = n; a.stats_out[1] = c0; a.stats_out[2] = c1; a.stats_out[3] = c2; }
+            if (a.learn) { a.learn[0] = n; a.learn[1] = c0; a.learn[2] = c1; a.learn[3] = c2; }
+            if (c2 > a.miss_cap) raise(a.err, kErrCapacity);
+        }
     }
 }
 
@@ -150,9 +147,9 @@ hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, Count
                                    const ScanState& scan, int32_t* err) {
     PartitionArgs a{ids, n, rank, n_nodes, n_hbm, n_host, lists, miss_pos, miss_id, miss_slot, miss_cap,
                     stats_out, learn, scan, err};
-    int64_t tiles = (n_max + kTileItems - 1) / kTileItems;
-    if (tiles < 1) tiles = 1;
-    hipLaunchKernelGGL(lookup_partition_kernel, dim3(static_cast<unsigned>(tiles)), dim3(kBlock), 0, stream, a);
+    const dim3 grid(scan_workgroups(n_max, kScanMaxWorkgroups)), block(kScanBlock);
+    if (n_max <= kScanOneItemMax) hipLaunchKernelGGL(lookup_partition_kernel<1>, grid, block, 0, stream, a);
+    else hipLaunchKernelGGL(lookup_partition_kernel<kScanMaxItems>, grid, block, 0, stream, a);
     return hipGetLastError();
 }
 

@@ -123,10 +123,26 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
     return base + inc - v;
 }
 
-// Scan kernels give every thread kItemsPerThread consecutive items, so a tile is 1024 items and a
-// launch has few tiles (each tile costs a ticket, see scan.hpp).
-constexpr int kItemsPerThread = 4;
-constexpr int kTileItems = kBlock * kItemsPerThread;
+// The same scan by DPP moves, without a trip through LDS per step: four shifts inside the rows of 16 lanes, then
+// the last lane of a row is carried into the rows after it.
+__device__ __forceinline__ uint32_t dpp_inclusive_scan(uint32_t v) {
+    const auto add = [](uint32_t x, int moved) { return x + static_cast<uint32_t>(moved); };
+    v = add(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x111, 0xf, 0xf, false));      // row_shr:1
+    v = add(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x112, 0xf, 0xf, false));      // row_shr:2
+    v = add(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x114, 0xf, 0xf, false));      // row_shr:4
+    v = add(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x118, 0xf, 0xf, false));      // row_shr:8
+    v = add(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x142, 0xa, 0xf, false));      // row_bcast:15 into rows 1, 3
+    v = add(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x143, 0xc, 0xf, false));      // row_bcast:31 into rows 2, 3
+    return v;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t lane) {      // lane: the same in all lanes
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>(lane)));
+}
+__device__ __forceinline__ uint32_t dpp_sum(uint32_t v) { return lane_value(dpp_inclusive_scan(v), kWave - 1); }
+// how many lanes below this one are set in the mask
+__device__ __forceinline__ uint32_t rank_in_mask(uint64_t mask) {
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
+}
 
 // min(deg(v), fanout): how many samples node v yields at a hop.  A value that is no node ID, or a
 // row of 2^31 entries or more, is reported and yields nothing.

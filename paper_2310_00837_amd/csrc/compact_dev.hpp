@@ -1,8 +1,8 @@
 // Device code of the second pass of the order-preserving de-duplication (see dedup.hip for the
 // whole scheme): the inputs have been inserted into a hash table that keeps, per distinct ID, the
 // smallest input position holding it, and the slot of every input is remembered.  Input j is a
-// first occurrence iff its slot's position is j.  A thread takes four consecutive inputs; the flags
-// are scanned in the workgroup and chained across workgroups (scan.hpp), so `unique` comes out in
+// first occurrence iff its slot's position is j.  The flags are counted by wave ballots, summed in the
+// workgroup and chained across workgroups (TileScan in scan.hpp), so `unique` comes out in
 // input order.  The pass has the new unique IDs in registers, so two things that need them ride on
 // it instead of being kernels of their own:
 //   kCompactNextHop  the unique list is the frontier of the next hop: read every new frontier node's
@@ -24,8 +24,6 @@
 #include "common.hpp"
 #include "hashtable.hpp"
 #include "scan.hpp"
-
-#define HELIOS_KERNELS_MAX_SEG 9
 
 namespace helios {
 
@@ -53,15 +51,6 @@ struct BatchTables {
     __device__ __forceinline__ uint32_t pick(const BatchVars* vars) const { return vars ? vars->table % kBatchTables : which; }
     __device__ __forceinline__ unsigned long long* table(uint32_t t) const { return table0 + t * table_stride; }
     __device__ __forceinline__ int32_t* iof(uint32_t t) const { return iof0 + t * iof_stride; }
-};
-
-// The lengths of up to HELIOS_KERNELS_MAX_SEG segments whose concatenation is de-duplicated (each may be
-// known only on the device).  The stage handles the segments [first_here, n_seg); those before it only
-// fix where it begins.
-struct SegLens {
-    Count len[HELIOS_KERNELS_MAX_SEG];
-    int n_seg;
-    int first_here;
 };
 
 // What the de-duplication between two hops also computes for the hop that follows: the sample
@@ -97,12 +86,15 @@ struct LookupOut {
 constexpr int kStageUnique = 0, kStageHbm = 1, kStageHost = 2;      // unique IDs, HBM hits, host hits so far
 constexpr int kStageHbmCopy = 3, kStageHostCopy = 4;                // list entries that may be copied (none of a stage
                                                                     // whose part of `unique` did not fit its capacity)
+constexpr int kStageEnd = 5;                                        // inputs compacted so far: where the next stage begins
 constexpr int kStageWords = 8;
 
 struct CompactArgs {
     const int32_t* ids;
-    SegLens lens;
-    int64_t n_max;               // bound on the inputs of this stage
+    uint32_t n_nodes;            // IDs from here on are never used as an index
+    Count len;                   // inputs of this stage: len + fixed
+    uint32_t fixed;
+    uint32_t n_max;              // bound on them
     int64_t* n_total_dev;        // receives begin + n: the inputs compacted so far (nullable)
     DedupScratch s;              // table / index_of_first are overridden by `batch` when that is set
     BatchTables batch;
@@ -124,37 +116,180 @@ struct CompactArgs {
     Stamps stamps;
 };
 
+// K items per thread (see scan.hpp).  What bounds a stage: nothing but the chain itself -- counts of the stages before,
+// ticket, slot and ID, table word and rank / row bounds, tile scan, look-back, stores.  Every load of a step is issued for
+// all items before the first is used, and unconditionally (an item that is not there reads entry 0), because a guarded load
+// makes the compiler wait for it at the end of its branch.
+template <int MODE, int K>
+__device__ __forceinline__ void compact_tiles(const CompactArgs& a, const DedupScratch& s, const ScanState& scan, const int64_t (&prev)[kStageWords],
+                                              uint32_t begin, uint32_t n, uint32_t rb, uint32_t nrb) {
+    constexpr int NP = MODE == kCompactPlain ? 1 : 2;
+    constexpr int NC = MODE == kCompactNextHop ? 2 : MODE == kCompactLookup ? 3 : 1;
+    using Scan = TileScan<NP, NC, K>;
+    __shared__ typename Scan::Lds lds;
+    const uint32_t end = begin + n;
+    const int64_t base[3] = {prev[kStageUnique], prev[kStageHbm], prev[kStageHost]};
+    const uint32_t n_tiles = (n + K * kScanBlock - 1) / (K * kScanBlock);
+    if (rb >= n_tiles) return;
+    const uint32_t n_wgs = nrb < n_tiles ? nrb : n_tiles;
+    for (uint32_t tile = Scan::take_ticket(scan, n_tiles, n_wgs, lds); tile < n_tiles;
+         tile = n_wgs < n_tiles ? Scan::take_ticket(scan, n_tiles, n_wgs, lds) : n_tiles) {
+        const uint32_t j0 = begin + tile * (K * kScanBlock) + threadIdx.x;
+        int32_t slot[K], id[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint32_t j = j0 + k * kScanBlock;
+            const uint32_t at = j < end ? j : begin;
+            slot[k] = s.slot_of[at];
+            id[k] = a.ids[at];
+        }
+        // The table word and the row bounds / the rank are fetched together: those of a repeated ID are
+        // read for nothing, but they are in cache and nobody waits for the flag first.  (A slot >= 0
+        // means the insert pass found the ID to be a node ID.)
+        unsigned long long word[K];
+        int64_t lo[K], hi[K];
+        int32_t r[K];
+        bool live[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            // (both checked: a caller that overwrites its seeds while they are being sampled leaves places of the list
+            // unwritten, and what they hold then must not become an address)
+            live[k] = j0 + k * kScanBlock < end && static_cast<uint32_t>(slot[k]) < s.n_slots && static_cast<uint32_t>(id[k]) < a.n_nodes;
+            const uint32_t at = live[k] ? static_cast<uint32_t>(slot[k]) : 0u, node = live[k] ? static_cast<uint32_t>(id[k]) : 0u;
+            word[k] = s.table[at];
+            if (MODE == kCompactNextHop) { lo[k] = a.next.offsets[node]; hi[k] = a.next.offsets[node + 1]; }
+            if (MODE == kCompactLookup) r[k] = a.look.rank[node];
+        }
+        uint32_t totals[NP][K], before[NP][K], local[K], local2[K], cnt[K];
+        bool first[K];
+        int tier[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            first[k] = live[k] && static_cast<uint32_t>(word[k]) == j0 + k * kScanBlock;
+            const uint64_t firsts = __ballot(first[k]);
+            totals[0][k] = static_cast<uint32_t>(__popcll(firsts));
+            local[k] = rank_in_mask(firsts);
+            if (MODE == kCompactNextHop) {
+                const int64_t d = hi[k] - lo[k];
+                const bool bad = d < 0 || d > 0x7fffffffLL;
+                if (live[k] && bad) raise(a.err, kErrData);
+                const int64_t f = a.next.fanout > 0 ? a.next.fanout : 0;
+                cnt[k] = !first[k] || bad ? 0u : static_cast<uint32_t>(d < f ? d : f);
+                const uint32_t inc = dpp_inclusive_scan(cnt[k]);
+                totals[NP - 1][k] = lane_value(inc, kWave - 1);
+                local2[k] = inc - cnt[k];
+            }
+            if (MODE == kCompactLookup) {
+                // a negative rank (the hotness order was no permutation; reported when the map was built, and
+                // here) counts as a miss whose slot no table has
+                if (first[k] && r[k] < 0) raise(a.err, kErrData);
+                const uint32_t ur = static_cast<uint32_t>(r[k]);
+                tier[k] = ur < static_cast<uint32_t>(a.look.n_hbm) ? 0 : ur < static_cast<uint32_t>(a.look.n_hbm + a.look.n_host) ? 1 : 2;
+                const uint64_t hbm = __ballot(first[k] && tier[k] == 0), host = __ballot(first[k] && tier[k] == 1);
+                totals[NP - 1][k] = static_cast<uint32_t>(__popcll(hbm)) | (static_cast<uint32_t>(__popcll(host)) << 16);
+                local2[k] = rank_in_mask(hbm) | (rank_in_mask(host) << 16);
+            }
+        }
+        Scan::run(scan, tile, totals, before, lds, a.err);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (!first[k]) continue;
+            const uint32_t j = j0 + k * kScanBlock;
+            const int64_t at = base[0] + lds.excl[0] + before[0][k] + local[k];
+            if (s.index_of_first) s.index_of_first[j] = static_cast<int32_t>(at);
+            if (MODE == kCompactNextHop) {
+                const int64_t at_cnt = static_cast<int64_t>(lds.excl[NC - 1]) + before[NP - 1][k] + local2[k];
+                if (at <= a.unique_cap) a.next.indptr[at] = at_cnt;
+                // the frontier is cut off here: the next hop samples the nodes that fit, and its sample list
+                // ends where this node's samples would have begun
+                if (at == a.unique_cap) *a.next.n_flat_dev = at_cnt;
+            }
+            if (at >= a.unique_cap) continue;
+            a.unique[at] = id[k];
+            if (MODE == kCompactLookup) {
+                const uint32_t in_tile = before[NP - 1][k] + local2[k];          // no carry between the halves: a tile has at most 4096 items
+                const int64_t at_hbm = base[1] + lds.excl[NC - 2] + (in_tile & 0xffffu);
+                const int64_t at_host = base[2] + lds.excl[NC - 1] + (in_tile >> 16);
+                if (tier[k] < 2) {
+                    const int64_t w = tier[k] == 0 ? at_hbm : at_host;
+                    (tier[k] == 0 ? a.look.lists.pos[0] : a.look.lists.pos[1])[w] = static_cast<int32_t>(at);
+                    (tier[k] == 0 ? a.look.lists.slot[0] : a.look.lists.slot[1])[w] =
+                        r[k] - (tier[k] == 0 ? 0 : static_cast<int32_t>(a.look.n_hbm));
+                } else {
+                    const int64_t w = at - at_hbm - at_host;                     // every unique ID is in exactly one class
+                    if (w < a.look.miss_cap) {
+                        a.look.miss_pos[w] = static_cast<int32_t>(at);
+                        a.look.miss_id[w] = id[k];
+                        a.look.miss_slot[w] = r[k] < 0 ? -1 : r[k] - static_cast<int32_t>(a.look.n_hbm + a.look.n_host);
+                    }
+                }
+            }
+        }
+        if (tile == n_tiles - 1 && threadIdx.x == 0) {
+            const int64_t total = base[0] + lds.excl[0] + lds.agg[0];
+            const bool fits = total <= a.unique_cap;
+            if (a.last) {
+                *a.n_unique_dev = total;
+                if (a.n_unique_out) *a.n_unique_out = total;
+            }
+            if (!fits) raise(a.err, kErrCapacity);
+            if (a.mine) a.mine[kStageUnique] = total;
+            if (MODE == kCompactNextHop) {
+                const int64_t total_cnt = static_cast<int64_t>(lds.excl[NC - 1]) + lds.agg[NC - 1];
+                if (fits) {                          // else the thread at the cut has written both
+                    a.next.indptr[total] = total_cnt;
+                    *a.next.n_flat_dev = total_cnt;
+                }
+                if (a.next.size_out) { a.next.size_out[0] = total; a.next.size_out[1] = total_cnt; }
+                if (total_cnt > a.next.flat_cap) raise(a.err, kErrCapacity);
+            }
+            if (MODE == kCompactLookup) {
+                const int64_t c0 = base[1] + lds.excl[NC - 2] + lds.agg[NC - 2];
+                const int64_t c1 = base[2] + lds.excl[NC - 1] + lds.agg[NC - 1];
+                const int64_t c2 = total - c0 - c1;
+                // if `unique` overflowed, list entries past its capacity were not written: this stage's are not copied
+                const int64_t copy0 = fits ? c0 : prev[kStageHbmCopy];
+                const int64_t copy1 = fits ? c1 : prev[kStageHostCopy];
+                if (a.mine) {
+                    a.mine[kStageHbm] = c0; a.mine[kStageHost] = c1;
+                    a.mine[kStageHbmCopy] = copy0; a.mine[kStageHostCopy] = copy1;
+                }
+                if (a.last) {
+                    a.look.lists.count[0] = copy0; a.look.lists.count[1] = copy1; a.look.lists.count[2] = fits ? c2 : 0;
+                    if (a.look.stats_out) { a.look.stats_out[0] = total; a.look.stats_out[1] = c0; a.look.stats_out[2] = c1; a.look.stats_out[3] = c2; }
+                    if (a.look.learn) { a.look.learn[0] = total; a.look.learn[1] = c0; a.look.learn[2] = c1; a.look.learn[3] = c2; }
+                    if (c2 > a.look.miss_cap) raise(a.err, kErrCapacity);
+                }
+            }
+        }
+    }
+}
+
 template <int MODE>
 __device__ __forceinline__ void compact_role(const CompactArgs& a, uint32_t rb, uint32_t nrb) {
-    constexpr int NC = MODE == kCompactNextHop ? 2 : MODE == kCompactLookup ? 3 : 1;
-    __shared__ uint32_t s_wave[kWavesPerBlock + 1];
-    __shared__ uint32_t s_ticket, s_agg[NC], s_excl[NC];
-    __shared__ ScanLookbackLds<NC> s_look;
     stamp_start(a.stamps, rb);
+    const ScanState scan = scan_resolve(a.scan);
+    const uint32_t which = a.batch.pick(a.vars);
+    const uint32_t n_raw = a.fixed + static_cast<uint32_t>(a.len.get());
+    int64_t prev[kStageWords] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (a.prev) {
+#pragma unroll
+        for (int q = 0; q < kStageWords; ++q) prev[q] = a.prev[q];
+    }
     if (a.batches_run && rb == 0 && threadIdx.x == 0) *a.batches_run += 1;   // every workgroup of the batch's first kernel has read its slot
     DedupScratch s = a.s;
-    if (a.batch.table0) {
-        const uint32_t t = a.batch.pick(a.vars);
-        s = DedupScratch{a.batch.table(t), a.batch.n_slots, a.batch.slot_of, a.batch.iof(t)};
-    }
-    int64_t begin = 0, n = 0;
-#pragma unroll
-    for (int k = 0; k < HELIOS_KERNELS_MAX_SEG; ++k) {
-        if (k < a.lens.first_here) begin += a.lens.len[k].get();
-        else if (k < a.lens.n_seg) n += a.lens.len[k].get();
-    }
-    n = n < a.n_max ? n : a.n_max;
-    const int64_t end = begin + n;
-    int64_t base[3] = {0, 0, 0};
-    if (a.prev) { base[0] = a.prev[kStageUnique]; base[1] = a.prev[kStageHbm]; base[2] = a.prev[kStageHost]; }
-    const int64_t n_tiles = (n + kTileItems - 1) / kTileItems;
+    if (a.batch.table0) s = DedupScratch{a.batch.table(which), a.batch.n_slots, a.batch.slot_of, a.batch.iof(which)};
+    const uint32_t n = n_raw < a.n_max ? n_raw : a.n_max;
+    const uint32_t begin = static_cast<uint32_t>(prev[kStageEnd]), end = begin + n;
+    const int64_t base[3] = {prev[kStageUnique], prev[kStageHbm], prev[kStageHost]};
     if (rb == 0 && threadIdx.x == 0) {
         if (a.n_total_dev) *a.n_total_dev = end;
+        if (a.mine) a.mine[kStageEnd] = end;
         if (n == 0) {                              // an empty stage: the totals pass through
             if (a.mine) {
                 a.mine[kStageUnique] = base[0]; a.mine[kStageHbm] = base[1]; a.mine[kStageHost] = base[2];
-                a.mine[kStageHbmCopy] = a.prev ? a.prev[kStageHbmCopy] : 0;
-                a.mine[kStageHostCopy] = a.prev ? a.prev[kStageHostCopy] : 0;
+                a.mine[kStageHbmCopy] = prev[kStageHbmCopy];
+                a.mine[kStageHostCopy] = prev[kStageHostCopy];
             }
             if (a.last) {
                 *a.n_unique_dev = base[0];
@@ -168,148 +303,16 @@ __device__ __forceinline__ void compact_role(const CompactArgs& a, uint32_t rb, 
             if (MODE == kCompactLookup && a.last) {
                 const int64_t c2 = base[0] - base[1] - base[2];
                 const bool fits = base[0] <= a.unique_cap;
-                a.look.lists.count[0] = a.prev ? a.prev[kStageHbmCopy] : 0;
-                a.look.lists.count[1] = a.prev ? a.prev[kStageHostCopy] : 0;
+                a.look.lists.count[0] = prev[kStageHbmCopy];
+                a.look.lists.count[1] = prev[kStageHostCopy];
                 a.look.lists.count[2] = fits ? c2 : 0;
                 if (a.look.stats_out) { a.look.stats_out[0] = base[0]; a.look.stats_out[1] = base[1]; a.look.stats_out[2] = base[2]; a.look.stats_out[3] = c2; }
             }
         }
     }
-    if (static_cast<int64_t>(rb) >= n_tiles) {
-        stamp_end(a.stamps, rb, nrb);
-        return;
-    }
-    const uint32_t tile = scan_take_ticket(a.scan, static_cast<uint32_t>(n_tiles), &s_ticket);
-    const int64_t j0 = begin + static_cast<int64_t>(tile) * kTileItems + static_cast<int64_t>(threadIdx.x) * kItemsPerThread;
-    int32_t slot[kItemsPerThread], id[kItemsPerThread];
-    uint32_t first[kItemsPerThread], cnt[kItemsPerThread];
-    int64_t r[kItemsPerThread];
-#pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) {
-        slot[k] = j0 + k < end ? s.slot_of[j0 + k] : -1;
-        id[k] = j0 + k < end ? a.ids[j0 + k] : 0;
-    }
-    // The table word and the row bounds / the rank are fetched together: those of a repeated ID are
-    // read for nothing, but they are in cache and nobody waits for the flag first.  (A slot >= 0
-    // means the insert pass found the ID to be a node ID.)
-    unsigned long long word[kItemsPerThread];
-#pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) {
-        if (static_cast<uint32_t>(slot[k]) >= s.n_slots) slot[k] = -1;      // never a slot of this table
-        word[k] = slot[k] >= 0 ? s.table[slot[k]] : ~0ull;
-        cnt[k] = 0;
-        r[k] = 0;
-        if (MODE == kCompactNextHop && slot[k] >= 0) cnt[k] = sample_count(a.next.offsets, a.next.n_nodes, id[k], a.next.fanout, a.err);
-        if (MODE == kCompactLookup && slot[k] >= 0) r[k] = a.look.rank[id[k]];
-    }
-    uint32_t n_first = 0, n_second = 0;          // second counter: sample counts, or hits packed as hbm | host << 16
-    int tier[kItemsPerThread];
-#pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) {
-        first[k] = slot[k] >= 0 && static_cast<uint32_t>(word[k]) == static_cast<uint32_t>(j0 + k) ? 1u : 0u;
-        if (!first[k]) cnt[k] = 0;
-        tier[k] = -1;
-        if (MODE == kCompactLookup && first[k]) {
-            // a negative rank (the hotness order was no permutation; reported when the map was built, and
-            // here) counts as a miss whose slot no table has
-            if (r[k] < 0) raise(a.err, kErrData);
-            tier[k] = r[k] < 0 ? 2 : r[k] < a.look.n_hbm ? 0 : r[k] < a.look.n_hbm + a.look.n_host ? 1 : 2;
-            n_second += tier[k] == 0 ? 1u : tier[k] == 1 ? (1u << 16) : 0u;
-        }
-        n_first += first[k];
-        if (MODE == kCompactNextHop) n_second += cnt[k];
-    }
-
-    uint32_t tile_first, tile_second = 0;
-    const uint32_t local_first = block_exclusive_scan(n_first, s_wave, tile_first);
-    uint32_t local_second = 0;
-    if (MODE != kCompactPlain) local_second = block_exclusive_scan(n_second, s_wave, tile_second);
-    if (threadIdx.x == 0) {
-        s_agg[0] = tile_first;
-        if (MODE == kCompactNextHop) s_agg[NC - 1] = tile_second;
-        if (MODE == kCompactLookup) {
-            s_agg[NC - 2] = tile_second & 0xffffu;
-            s_agg[NC - 1] = tile_second >> 16;
-        }
-    }
-    scan_chained_prefix<NC>(a.scan, tile, s_agg, s_excl, &s_look, a.err);
-    int64_t at = base[0] + static_cast<int64_t>(s_excl[0]) + local_first;
-    int64_t at_cnt = MODE == kCompactNextHop ? static_cast<int64_t>(s_excl[NC - 1]) + local_second : 0;
-    int64_t at_tier[3] = {0, 0, 0};
-    if (MODE == kCompactLookup) {
-        at_tier[0] = base[1] + static_cast<int64_t>(s_excl[NC - 2]) + (local_second & 0xffffu);
-        at_tier[1] = base[2] + static_cast<int64_t>(s_excl[NC - 1]) + (local_second >> 16);
-        at_tier[2] = at - at_tier[0] - at_tier[1];           // every unique ID is in exactly one class
-    }
-#pragma unroll
-    for (int k = 0; k < kItemsPerThread; ++k) {
-        if (first[k]) {
-            if (s.index_of_first) s.index_of_first[j0 + k] = static_cast<int32_t>(at);
-            if (MODE == kCompactNextHop && at == a.unique_cap) {
-                // the frontier is cut off here: the next hop samples the nodes that fit, and its sample list
-                // ends where this node's samples would have begun
-                a.next.indptr[a.unique_cap] = at_cnt;
-                *a.next.n_flat_dev = at_cnt;
-            }
-            if (at < a.unique_cap) {
-                a.unique[at] = id[k];
-                if (MODE == kCompactNextHop) a.next.indptr[at] = at_cnt;
-                if (MODE == kCompactLookup) {
-                    const int t = tier[k];
-                    const int64_t w = at_tier[t];
-                    const int32_t sl = static_cast<int32_t>(t == 0 ? r[k] : t == 1 ? r[k] - a.look.n_hbm
-                                                             : r[k] < 0 ? -1 : r[k] - a.look.n_hbm - a.look.n_host);
-                    if (t < 2) {
-                        a.look.lists.pos[t][w] = static_cast<int32_t>(at);
-                        a.look.lists.slot[t][w] = sl;
-                    } else if (w < a.look.miss_cap) {
-                        a.look.miss_pos[w] = static_cast<int32_t>(at);
-                        a.look.miss_id[w] = id[k];
-                        a.look.miss_slot[w] = sl;
-                    }
-                }
-            }
-            if (MODE == kCompactLookup) at_tier[tier[k]] += 1;
-            at += 1;
-            at_cnt += cnt[k];
-        }
-    }
-    if (static_cast<int64_t>(tile) == n_tiles - 1 && threadIdx.x == 0) {
-        const int64_t total = base[0] + static_cast<int64_t>(s_excl[0]) + tile_first;
-        const bool fits = total <= a.unique_cap;
-        if (a.last) {
-            *a.n_unique_dev = total;
-            if (a.n_unique_out) *a.n_unique_out = total;
-        }
-        if (!fits) raise(a.err, kErrCapacity);
-        if (a.mine) a.mine[kStageUnique] = total;
-        if (MODE == kCompactNextHop) {
-            const int64_t total_cnt = static_cast<int64_t>(s_excl[NC - 1]) + tile_second;
-            if (fits) {                          // else the thread at the cut has written both
-                a.next.indptr[total] = total_cnt;
-                *a.next.n_flat_dev = total_cnt;
-            }
-            if (a.next.size_out) { a.next.size_out[0] = total; a.next.size_out[1] = total_cnt; }
-            if (total_cnt > a.next.flat_cap) raise(a.err, kErrCapacity);
-        }
-        if (MODE == kCompactLookup) {
-            const int64_t c0 = base[1] + static_cast<int64_t>(s_excl[NC - 2]) + (tile_second & 0xffffu);
-            const int64_t c1 = base[2] + static_cast<int64_t>(s_excl[NC - 1]) + (tile_second >> 16);
-            const int64_t c2 = total - c0 - c1;
-            // if `unique` overflowed, list entries past its capacity were not written: this stage's are not copied
-            const int64_t copy0 = fits ? c0 : (a.prev ? a.prev[kStageHbmCopy] : 0);
-            const int64_t copy1 = fits ? c1 : (a.prev ? a.prev[kStageHostCopy] : 0);
-            if (a.mine) {
-                a.mine[kStageHbm] = c0; a.mine[kStageHost] = c1;
-                a.mine[kStageHbmCopy] = copy0; a.mine[kStageHostCopy] = copy1;
-            }
-            if (a.last) {
-                a.look.lists.count[0] = copy0; a.look.lists.count[1] = copy1; a.look.lists.count[2] = fits ? c2 : 0;
-                if (a.look.stats_out) { a.look.stats_out[0] = total; a.look.stats_out[1] = c0; a.look.stats_out[2] = c1; a.look.stats_out[3] = c2; }
-                if (a.look.learn) { a.look.learn[0] = total; a.look.learn[1] = c0; a.look.learn[2] = c1; a.look.learn[3] = c2; }
-                if (c2 > a.look.miss_cap) raise(a.err, kErrCapacity);
-            }
-        }
+    if (static_cast<uint64_t>(rb) * kScanBlock < n) {
+        if (n <= kScanOneItemMax) compact_tiles<MODE, 1>(a, s, scan, prev, begin, n, rb, nrb);
+        else compact_tiles<MODE, kScanMaxItems>(a, s, scan, prev, begin, n, rb, nrb);
     }
     stamp_end(a.stamps, rb, nrb);
 }

@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_kernel(const int32_t* __r
     }
 }
 
-__global__ __launch_bounds__(kBlock) void dedup_compact_kernel(CompactArgs a) {
+__global__ __launch_bounds__(kScanBlock) void dedup_compact_kernel(CompactArgs a) {
     compact_role<kCompactPlain>(a, blockIdx.x, gridDim.x);
 }
 
@@ -68,9 +68,7 @@ hipError_t launch_dedup_insert(hipStream_t stream, const int32_t* ids, Count n, 
 }
 
 hipError_t launch_dedup_compact_plain(hipStream_t stream, const CompactArgs& a, int64_t n_max) {
-    int64_t tiles = (n_max + kTileItems - 1) / kTileItems;
-    if (tiles < 1) tiles = 1;
-    hipLaunchKernelGGL(dedup_compact_kernel, dim3(static_cast<unsigned>(tiles)), dim3(kBlock), 0, stream, a);
+    hipLaunchKernelGGL(dedup_compact_kernel, dim3(scan_workgroups(n_max, kScanMaxWorkgroups)), dim3(kScanBlock), 0, stream, a);
     return hipGetLastError();
 }
 

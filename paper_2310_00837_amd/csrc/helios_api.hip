@@ -95,7 +95,7 @@ int ensure_capacity(helios_ctx* c, int64_t n) {
     c->blocks_ready = false;
     const int64_t cap = (n + 4095) / 4096 * 4096;
     const uint32_t slots = pow2_at_least(2 * cap);
-    const uint32_t stride = static_cast<uint32_t>(cap / kTileItems + 2);
+    const uint32_t stride = scan_row_stride(cap);
     HIP_TRY(c, hipMalloc(&c->batch_tables, sizeof(unsigned long long) * slots * kBatchTables));
     HIP_TRY(c, hipMalloc(&c->batch_iof, sizeof(int32_t) * cap * kBatchTables));
     HIP_TRY(c, hipMalloc(&c->batch_slot_of, sizeof(int32_t) * cap));
@@ -198,11 +198,6 @@ uint32_t dedup_slots(const helios_ctx* c, int64_t n_max) {
     return want < c->table_slots ? want : c->table_slots;
 }
 
-unsigned tiles_for(int64_t n_max) {
-    int64_t tiles = (n_max + kTileItems - 1) / kTileItems;
-    return static_cast<unsigned>(tiles < 1 ? 1 : tiles);
-}
-
 // ---- timing of roles
 constexpr uint64_t kStampWords = 2ull * kMaxRoleBlocks * 16;     // ticks of all timed roles of one batch (8 MiB)
 
@@ -257,6 +252,10 @@ struct BatchOut {                // the outputs of the whole-path call beyond th
     int64_t miss_cap;
     helios_gather_stats* stats;
 };
+
+// The compaction reads entry 0 of these for an item that is not there, so they have to exist in a graph without nodes too.
+const int32_t* rank_or_any(const helios_ctx* c) { return c->g.n_nodes > 0 ? c->rank : reinterpret_cast<const int32_t*>(c->cnt); }
+const int64_t* offsets_or_any(const helios_ctx* c) { return c->g.n_nodes > 0 ? c->g.offsets : c->cnt; }
 
 int64_t* stage_words(const helios_ctx* c, int stage) { return c->cnt + kCntStage + stage * kStageWords; }
 
@@ -391,7 +390,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
         if (!fits) return fail(c, HELIOS_EINTERNAL, "launch bounds of hop %d do not fit its buffers", h);
     }
     if (p.cat_max > c->cap_ids || 2 * p.cat_max > static_cast<int64_t>(c->table_slots) || (b && u_max > b->unique_cap) ||
-        c->scan_stride < static_cast<uint32_t>(p.ids_max / kTileItems + 2))
+        c->scan_stride < scan_row_stride(p.ids_max))
         return fail(c, HELIOS_EINTERNAL, "launch bounds of the batch do not fit the scratch");
 
     const bool fold = n_seeds <= kFoldMaxSeeds;
@@ -405,7 +404,6 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
                                          fanouts[0], hops[0].indptr, hops[0].flat_cap, c->cnt + kCntFlat + 0, sizes,
                                          scan_state(c, epoch, kScanRowsHop), err));
     }
-    Count prev_flat[HELIOS_MAX_HOPS];
     Count nf{nullptr, n_seeds};
     for (int h = 0; h < n_hops; ++h) {
         const bool last = h + 1 == n_hops;
@@ -429,7 +427,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
         ha.batch = bt;
         ha.cat_out = c->cat;
         ha.n_seeds = n_seeds;
-        for (int k = 0; k < h; ++k) ha.prev_flat[k] = prev_flat[k];
+        ha.cat_begin = b && h > 0 ? stage_words(c, h - 1) + kStageEnd : nullptr;
         ha.err = err;
         if (ha.fold) {
             ha.feed = feed;
@@ -438,7 +436,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             ha.n_flat_dev = c->cnt + kCntFlat + 0;
             ha.size_out = sizes;
         }
-        const unsigned hop_blocks = sample_role_blocks(fanouts[h], p.frontier_max[h]);
+        const unsigned hop_blocks = sample_role_blocks(fanouts[h], p.frontier_max[h], c->link_share);
         ha.stamps = take_stamps(c, HELIOS_ROLE_SAMPLE, h, hop_blocks);
         GatherArgs link{};
         unsigned link_blocks = 0;
@@ -452,41 +450,42 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
         }
         int rs = emit_sample(c, SampleJob{ha, hop_blocks, link, link_blocks});
         if (rs) return rs;
-        prev_flat[h] = Count{c->cnt + kCntFlat + h, p.flat_max[h]};
+        const Count flat{c->cnt + kCntFlat + h, p.flat_max[h]};
 
         // ---- compaction: this hop's samples into the next frontier, and stage h of the batch's ID list
         if (last && !b) break;
         uint32_t epoch;
         int rc = next_epoch(c, &epoch);
         if (rc) return rc;
+        const int64_t stage_max = h == 0 ? n_seeds + p.flat_max[0] : p.flat_max[h];     // bound on the inputs of stage h
+        // the compactions of a gang's members run at the same time: they share the workgroups of a launch
+        const unsigned scan_limit = std::min(256u, kScanMaxWorkgroups / static_cast<unsigned>(c->link_share));
         CompactArgs hopc{}, look{};
         unsigned hopc_blocks = 0, look_blocks = 0;
         if (!last) {
             hopc.ids = hops[h].flat;
-            hopc.lens.n_seg = 1;
-            hopc.lens.first_here = 0;
-            hopc.lens.len[0] = prev_flat[h];
-            hopc.n_max = p.flat_max[h];
+            hopc.n_nodes = static_cast<uint32_t>(c->g.n_nodes);
+            hopc.len = flat;
+            hopc.n_max = static_cast<uint32_t>(p.flat_max[h]);
             hopc.n_total_dev = c->cnt + kCntHopTotal;
             hopc.s = DedupScratch{c->hop_table[h % 2], hop_slots[h], c->hop_slot_of, nullptr};
             hopc.unique = hops[h + 1].frontier;
             hopc.unique_cap = hops[h + 1].frontier_cap;
             hopc.last = true;
             hopc.n_unique_dev = c->cnt + kCntFrontier + h + 1;
-            hopc.next = NextHopCount{c->g.offsets, c->g.n_nodes, fanouts[h + 1], hops[h + 1].indptr, hops[h + 1].flat_cap,
+            hopc.next = NextHopCount{offsets_or_any(c), c->g.n_nodes, fanouts[h + 1], hops[h + 1].indptr, hops[h + 1].flat_cap,
                                      c->cnt + kCntFlat + h + 1, sizes ? sizes + 2 * (h + 1) : nullptr};
             hopc.scan = scan_state(c, epoch, kScanRowsHop);
             hopc.err = err;
-            hopc_blocks = tiles_for(p.flat_max[h]);
+            hopc_blocks = scan_workgroups(p.flat_max[h], scan_limit);
             hopc.stamps = take_stamps(c, HELIOS_ROLE_COMPACT_HOP, h, hopc_blocks);
         }
         if (b) {
             look.ids = c->cat;
-            look.lens.n_seg = h + 2;
-            look.lens.first_here = h == 0 ? 0 : h + 1;
-            look.lens.len[0] = Count{nullptr, n_seeds};
-            for (int k = 0; k <= h; ++k) look.lens.len[k + 1] = prev_flat[k];
-            look.n_max = h == 0 ? n_seeds + p.flat_max[0] : p.flat_max[h];
+            look.n_nodes = static_cast<uint32_t>(c->g.n_nodes);
+            look.len = flat;
+            look.fixed = h == 0 ? static_cast<uint32_t>(n_seeds) : 0u;
+            look.n_max = static_cast<uint32_t>(stage_max);
             look.n_total_dev = c->cnt + kCntCat;
             look.batch = bt;
             look.vars = vars;
@@ -497,13 +496,13 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             look.last = last;
             look.n_unique_dev = c->cnt + kCntUnique;
             look.n_unique_out = b->n_unique;
-            look.look = LookupOut{c->rank, c->n_hbm, c->n_host,
+            look.look = LookupOut{rank_or_any(c), c->n_hbm, c->n_host,
                                   TierLists{{c->list_pos[0], c->list_pos[1]}, {c->list_slot[0], c->list_slot[1]}, c->cnt + kCntTier},
                                   b->miss_pos, b->miss_id, b->miss_slot, b->miss_cap, reinterpret_cast<int64_t*>(b->stats), c->learn};
             look.batches_run = rec && h == 0 ? c->batches_run : nullptr;
             look.scan = scan_state(c, epoch, kScanRowsLook);
             look.err = err;
-            look_blocks = tiles_for(look.n_max);
+            look_blocks = scan_workgroups(stage_max, scan_limit);
             look.stamps = take_stamps(c, HELIOS_ROLE_COMPACT_LOOKUP, h, look_blocks);
         }
         rc = emit_compact(c, CompactJob{hopc, hopc_blocks, look, look_blocks});
@@ -976,10 +975,9 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, c->err));
     CompactArgs a{};
     a.ids = ids;
-    a.lens.n_seg = 1;
-    a.lens.first_here = 0;
-    a.lens.len[0] = n;
-    a.n_max = n_ids;
+    a.n_nodes = static_cast<uint32_t>(c->g.n_nodes);
+    a.len = n;
+    a.n_max = static_cast<uint32_t>(n_ids);
     a.n_total_dev = c->cnt + kCntCat;
     a.s = s;
     a.unique = unique;
@@ -1013,7 +1011,7 @@ int helios_gather(helios_ctx* c, const int32_t* ids, int64_t n_ids, void* out, i
     rc = next_epoch(c, &epoch);
     if (rc) return rc;
     const TierLists lists{{c->list_pos[0], c->list_pos[1]}, {c->list_slot[0], c->list_slot[1]}, c->cnt + kCntTier};
-    HIP_TRY(c, launch_lookup_partition(c->stream, ids, Count{nullptr, n_ids}, n_ids, c->rank, c->g.n_nodes, c->n_hbm, c->n_host,
+    HIP_TRY(c, launch_lookup_partition(c->stream, ids, Count{nullptr, n_ids}, n_ids, rank_or_any(c), c->g.n_nodes, c->n_hbm, c->n_host,
                                        lists, miss_pos, miss_id, miss_slot, miss_cap, reinterpret_cast<int64_t*>(stats), c->learn,
                                        scan_state(c, epoch, kScanRowsLook), c->err));
     rc = copy_tiers_split(c, n_ids, out);

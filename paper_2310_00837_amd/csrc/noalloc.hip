@@ -20,7 +20,7 @@ namespace {
 
 constexpr int64_t kMaxIds = HELIOS_DEDUP_NOALLOC_MAX_IDS;
 constexpr uint32_t kSlots = 2u * static_cast<uint32_t>(kMaxIds);              // power of two, twice the inputs
-constexpr uint32_t kStride = static_cast<uint32_t>(kMaxIds / kTileItems + 2);   // tiles the status rows hold
+constexpr uint32_t kStride = static_cast<uint32_t>(kMaxIds / kScanBlock + 2);   // tiles the status rows hold
 static_assert((kSlots & (kSlots - 1)) == 0, "the table size must be a power of two");
 
 // layout of the scratch array, in bytes (every part 256-byte aligned)
@@ -103,10 +103,9 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, c->err));
     CompactArgs a{};
     a.ids = ids;
-    a.lens.n_seg = 1;
-    a.lens.first_here = 0;
-    a.lens.len[0] = n;
-    a.n_max = n_ids;
+    a.n_nodes = static_cast<uint32_t>(c->g.n_nodes);
+    a.len = n;
+    a.n_max = static_cast<uint32_t>(n_ids);
     a.n_total_dev = counters + 0;
     a.s = s;
     a.unique = unique;

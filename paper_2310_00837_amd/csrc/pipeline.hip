@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kBlock) void batch_sample_kernel(SampleGang g) {
     }
 }
 
-__global__ __launch_bounds__(kBlock) void batch_compact_kernel(CompactGang g) {
+__global__ __launch_bounds__(kScanBlock) void batch_compact_kernel(CompactGang g) {
 #pragma unroll 1
     for (int m = 0; m < g.n; ++m) {
         const CompactMember& a = g.m[m];
@@ -178,7 +178,7 @@ hipError_t launch_compact(hipStream_t stream, const CompactJob* jobs, int n) {
         at += jobs[m].hop_blocks;
     }
     if (at == 0) return hipSuccess;
-    hipLaunchKernelGGL(batch_compact_kernel, dim3(at), dim3(kBlock), 0, stream, g);
+    hipLaunchKernelGGL(batch_compact_kernel, dim3(at), dim3(kScanBlock), 0, stream, g);
     return hipGetLastError();
 }
 

@@ -49,7 +49,7 @@ struct HopArgs {
     BatchTables batch;            // de-duplication of [seeds | flat_0 | ...]; position = place in that list
     int32_t* cat_out;             // with batch: receives [seeds | flat_0 | ...]
     int64_t n_seeds;
-    Count prev_flat[HELIOS_KERNELS_MAX_SEG - 1];   // sizes of flat_0 .. flat_{hop-1}
+    const int64_t* cat_begin;     // device word: where flat_hop starts in that list (nullable: hop 0, right after the seeds)
     int32_t* err;
     // folded count pass (hop 0): the outputs that frontier_count_kernel would write
     bool fold;
@@ -160,8 +160,7 @@ __device__ __forceinline__ void sample_role(const HopArgs& a, uint32_t rb, uint3
         tabs.batch_slot_of = a.batch.slot_of;
     }
     const bool seeds_too = tabs.batch_table && a.hop == 0;   // the frontier of hop 0 is the head of the batch's list
-    int64_t cat_base = a.n_seeds;                // where flat_hop starts in [seeds | flat_0 | ...]
-    for (int h = 0; h < a.hop; ++h) cat_base += a.prev_flat[h].get();
+    const int64_t cat_base = a.cat_begin ? *a.cat_begin : a.n_seeds;      // where flat_hop starts in [seeds | flat_0 | ...]
     if (f > 0 || seeds_too) {
         const int64_t step = static_cast<int64_t>(nrb) * kGroups;
         for (int64_t i = static_cast<int64_t>(rb) * kGroups + group; i < n; i += step) {
@@ -259,12 +258,17 @@ __device__ __forceinline__ void sample_role(const HopArgs& a, uint32_t rb, uint3
 
 inline int group_lanes(int32_t fanout) { return fanout <= 8 ? 8 : fanout <= 16 ? 16 : fanout <= 32 ? 32 : 64; }
 
-// workgroups of a sampling role over a frontier of at most n_max nodes
-inline unsigned sample_role_blocks(int32_t fanout, int64_t n_max) {
+// Workgroups of a sampling role over a frontier of at most n_max nodes.  The bound is usually several times the
+// frontier's length, and a workgroup costs about 1 ns of the launch whether it has work or not, so a launch gets no more
+// than the chip holds at once (eight per CU) and they loop.  Measured: second hop of four batches of 41 k samples 14.8 us with
+// one step per workgroup (6400), 11.0 with 2048, 12.6 with 1024; second hop of 10 k seeds, fan-outs 25 and 10, 17.3 us with
+// 15625, 11.8 with 2048, 17.4 with 512.
+constexpr int64_t kSampleMaxWorkgroups = 2048;
+inline unsigned sample_role_blocks(int32_t fanout, int64_t n_max, int share /* roles that run in the same launch */) {
     const int64_t per_block = kBlock / group_lanes(fanout);
     int64_t blocks = (n_max + per_block - 1) / per_block;
     if (blocks < 1) blocks = 1;
-    if (blocks > kMaxRoleBlocks) blocks = kMaxRoleBlocks;
+    if (blocks > kSampleMaxWorkgroups / share) blocks = kSampleMaxWorkgroups / share;
     return static_cast<unsigned>(blocks);
 }
 

@@ -1,0 +1,93 @@
+"""GPU parity at the edges of the scan kernels' tiles (512 items; one item per thread up to 131 072 items, four beyond;
+workgroups loop once a list has more tiles than a grid has workgroups): de-duplication, cache lookup, count pass and the
+compactions of a batch, element by element against the oracle (tolerance zero: indexing and byte copies)."""
+import numpy as np
+import pytest
+import torch
+
+from pathlib_helios import GpuCache, assert_same, gpu_path, oracle_path, to_bytes
+
+pytestmark = pytest.mark.gpu
+ONE_ITEM_MAX = 131_072
+EDGES = [1, 63, 65, 511, 512, 513, 1025, ONE_ITEM_MAX - 1, ONE_ITEM_MAX, ONE_ITEM_MAX + 1, 256 * 2048 + 3]
+
+
+@pytest.fixture(scope="module")
+def helios():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    from paper_2310_00837_amd import helios as hl
+    return hl
+
+
+@pytest.fixture()
+def h(helios):
+    ctx = helios.Helios(0)
+    yield ctx
+    ctx.close()
+
+
+def _graph(rng, n, max_deg):
+    deg = rng.integers(0, max_deg + 1, n)
+    off = np.zeros(n + 1, np.int64)
+    off[1:] = np.cumsum(deg)
+    idx = rng.integers(0, n, int(off[-1])).astype(np.int32)
+    return off, idx
+
+
+@pytest.mark.parametrize("n_ids", EDGES)
+def test_dedup_and_lookup_at_tile_edges(h, oracle, n_ids):
+    print("tile edge", n_ids, flush=True)
+    rng = np.random.default_rng(n_ids)
+    n = 50_000
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    ids = (n * rng.random(n_ids) ** 2).astype(np.int32)
+    t = torch.from_numpy(ids).cuda()
+    wu, wi = oracle.dedup(n, ids)
+    for call in (h.dedup, h.dedup_noalloc) if n_ids <= 262_144 else (h.dedup,):
+        uniq = torch.full((n_ids,), -9, dtype=torch.int32, device="cuda")
+        inv, nu = torch.full_like(uniq, -9), torch.full((1,), -9, dtype=torch.int64).pin_memory()
+        for _ in range(2):
+            call(t, uniq, inv, nu)
+            h.sync()
+            assert int(nu[0]) == wu.size
+            assert np.array_equal(uniq[:wu.size].cpu().numpy(), wu)
+            assert np.array_equal(inv.cpu().numpy(), wi)
+    feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
+    order = torch.from_numpy(rng.permutation(n).astype(np.int32))
+    n_hbm, n_host = 9_000, 21_000
+    cache = GpuCache(h, feats, order, n_hbm, n_host)  # noqa: F841  (keeps the tables alive)
+    out = torch.zeros((n_ids, 16), dtype=torch.uint8, device="cuda")
+    miss = [torch.full((n_ids,), -9, dtype=torch.int32, device="cuda") for _ in range(3)]
+    stats = torch.zeros(4, dtype=torch.int64).pin_memory()
+    h.gather(t, out, *miss, stats)
+    h.sync()
+    by_rank = to_bytes(feats)[order.numpy()]
+    want = np.zeros((n_ids, 16), np.uint8)
+    lists = oracle.gather(ids, oracle.rank_build(order.numpy()), n_hbm, n_host, np.ascontiguousarray(by_rank[:n_hbm]),
+                          np.ascontiguousarray(by_rank[n_hbm:n_hbm + n_host]), want)
+    assert np.array_equal(stats.numpy(), lists[3])
+    assert np.array_equal(out.cpu().numpy(), want)
+    for got, w in zip(miss, lists[:3]):
+        assert np.array_equal(got[:w.size].cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("n_seeds,fanouts", [(2_048, [4, 3]), (2_049, [4, 3]), (ONE_ITEM_MAX + 5, [1, 2]), (60_000, [4, 2])])
+def test_whole_path_with_long_lists(h, helios, oracle, n_seeds, fanouts):
+    """Seed lists on both sides of the folded count pass, and stages and hops longer than one item per thread serves."""
+    print("long lists", n_seeds, fanouts, flush=True)
+    rng = np.random.default_rng(n_seeds)
+    n = 200_000
+    off, idx = _graph(rng, n, 9)
+    seeds = rng.integers(0, n, n_seeds).astype(np.int32)
+    h.csr_load(torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda())
+    feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
+    order = torch.from_numpy(rng.permutation(n).astype(np.int32))
+    n_hbm, n_host = 50_000, 60_000
+    cache = GpuCache(h, feats, order, n_hbm, n_host)  # noqa: F841
+    by_rank = to_bytes(feats)[order.numpy()]
+    tabs = [np.ascontiguousarray(x) for x in (by_rank[:n_hbm], by_rank[n_hbm:n_hbm + n_host], by_rank[n_hbm + n_host:])]
+    want = oracle_path(oracle, off, idx, seeds, fanouts, 99, oracle.rank_build(order.numpy()), n_hbm, n_host, *tabs, 16)
+    for _ in range(2):
+        assert_same(gpu_path(h, helios, torch.from_numpy(seeds), fanouts, 99, fused=True), want)
+    assert_same(gpu_path(h, helios, torch.from_numpy(seeds), fanouts, 99, fused=False), want)
