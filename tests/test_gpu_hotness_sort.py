@@ -1,0 +1,29 @@
+"""GPU parity of the hotness order's radix sort at the edges of its tiles (8192 nodes) and for every set of digits (11 bits) that
+can vary: a pass whose digit is the same in all counts is left out.  Against the oracle, exactly."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+SIZES = [1, 2, 65, 8191, 8192, 8193, 70_001]
+KINDS = {"zero": lambda r, n: np.zeros(n), "equal": lambda r, n: np.full(n, 123_456_789), "low": lambda r, n: r.integers(0, 2048, n),
+         "few": lambda r, n: r.poisson(0.7, n), "middle": lambda r, n: r.integers(0, 2048, n) << 11,
+         "high": lambda r, n: r.integers(0, 512, n) << 22, "low and high": lambda r, n: (r.integers(0, 3, n) << 29) | r.integers(0, 9, n),
+         "all": lambda r, n: r.integers(0, 1 << 31, n), "low and middle": lambda r, n: r.integers(0, 1 << 14, n)}
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_hotness_order_at_tile_edges(oracle, kind):
+    from paper_2310_00837_amd import helios
+    h = helios.Helios(0)
+    for n in SIZES + ([8192 * 512 + 77] if kind in ("few", "all") else []):        # the last: more tiles than workgroups
+        print("hotness order", kind, n, flush=True)
+        counts = KINDS[kind](np.random.default_rng(n), n).astype(np.int32)
+        h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+        t, order = torch.from_numpy(counts).cuda(), torch.full((n,), -9, dtype=torch.int32, device="cuda")
+        for _ in range(2):
+            h.hotness_order(t, order)
+            h.sync()
+            assert np.array_equal(order.cpu().numpy(), oracle.hotness_order(counts))
+            assert np.array_equal(t.cpu().numpy(), counts)
+    h.close()
