@@ -93,38 +93,8 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return v;
 }
 
-// inclusive scan over the 64 lanes of a wave
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        uint32_t t = __shfl_up(v, d, kWave);
-        if (lane >= d) v += t;
-    }
-    return v;
-}
-
-// Exclusive scan of one value per thread over the block; `total` is the block
-// sum (valid in every thread).  `s_wave` is kWavesPerBlock+1 words of LDS.
-// Contains block barriers: call from uniform control flow.
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s_wave, uint32_t& total) {
-    uint32_t inc = wave_inclusive_scan(v);
-    if (lane_id() == kWave - 1) s_wave[wave_id()] = inc;
-    __syncthreads();
-    uint32_t base = 0, sum = 0;
-#pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) {
-        uint32_t t = s_wave[w];
-        if (w < wave_id()) base += t;
-        sum += t;
-    }
-    total = sum;
-    __syncthreads();            // s_wave may be reused by the caller
-    return base + inc - v;
-}
-
-// The same scan by DPP moves, without a trip through LDS per step: four shifts inside the rows of 16 lanes, then
-// the last lane of a row is carried into the rows after it.
+// Inclusive scan over the 64 lanes of a wave by DPP moves, without a trip through LDS per step: four shifts inside the
+// rows of 16 lanes, then the last lane of a row is carried into the rows after it.
 __device__ __forceinline__ uint32_t dpp_inclusive_scan(uint32_t v) {
     const auto add = [](uint32_t x, int moved) { return x + static_cast<uint32_t>(moved); };
     v = add(v, __builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x111, 0xf, 0xf, false));      // row_shr:1
@@ -139,9 +109,35 @@ __device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t lane) {     
     return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>(lane)));
 }
 __device__ __forceinline__ uint32_t dpp_sum(uint32_t v) { return lane_value(dpp_inclusive_scan(v), kWave - 1); }
+// Lane LANE's value for all lanes of its group of G lanes (8 or 16), by DPP.
+template <int G, int LANE>
+__device__ __forceinline__ int32_t group_value(int32_t v) {
+    static_assert((G == 8 || G == 16) && LANE < G, "a row has 16 lanes");
+    if constexpr (G == 16) return __builtin_amdgcn_update_dpp(v, v, 0x150 + LANE, 0xf, 0xf, false);      // row_newbcast
+    const int lower = __builtin_amdgcn_update_dpp(v, v, 0x150 + LANE, 0xf, 0x3, false);                  // into lanes 0-7 of a row
+    return __builtin_amdgcn_update_dpp(lower, v, 0x158 + (LANE & 7), 0xf, 0xc, false);                   // and into lanes 8-15
+}
+// ... of 32 or 64 lanes, by the scalar unit; lane is the same in all lanes
+template <int G>
+__device__ __forceinline__ int32_t group_value(int32_t v, int lane) {
+    static_assert(G == 32 || G == 64, "smaller groups use DPP");
+    if constexpr (G == 64) return __builtin_amdgcn_readlane(v, lane);
+    const int lower = __builtin_amdgcn_readlane(v, lane), upper = __builtin_amdgcn_readlane(v, 32 + lane);
+    return (threadIdx.x & 32) ? upper : lower;
+}
 // how many lanes below this one are set in the mask
 __device__ __forceinline__ uint32_t rank_in_mask(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
+}
+
+// The bounds of a CSR row, read as one 16-byte access (the two words are adjacent, 8-byte aligned).
+struct RowBounds {
+    int64_t lo, hi;
+};
+__device__ __forceinline__ RowBounds row_bounds(const int64_t* offsets, uint32_t v) {
+    typedef int64_t pair __attribute__((ext_vector_type(2), aligned(8)));
+    const pair p = *reinterpret_cast<const pair*>(offsets + v);
+    return RowBounds{p.x, p.y};
 }
 
 // min(deg(v), fanout): how many samples node v yields at a hop.  A value that is no node ID, or a

@@ -13,8 +13,9 @@ __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint3
     constexpr uint32_t W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
-        const uint32_t hi0 = __umulhi(M0, c0), lo0 = M0 * c0;
-        const uint32_t hi1 = __umulhi(M1, c2), lo1 = M1 * c2;
+        const uint64_t p0 = static_cast<uint64_t>(M0) * c0, p1 = static_cast<uint64_t>(M1) * c2;
+        const uint32_t hi0 = static_cast<uint32_t>(p0 >> 32), lo0 = static_cast<uint32_t>(p0);
+        const uint32_t hi1 = static_cast<uint32_t>(p1 >> 32), lo1 = static_cast<uint32_t>(p1);
         c0 = hi1 ^ c1 ^ k0;
         c1 = lo1;
         c2 = hi0 ^ c3 ^ k1;
@@ -36,7 +37,10 @@ __device__ __forceinline__ uint64_t node_draw(uint64_t rng_seed, int32_t node, i
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
-// draw -> [0, n) by the high half of the 128-bit product
-__device__ __forceinline__ uint64_t bounded(uint64_t x, uint64_t n) { return __umul64hi(x, n); }
+// draw -> [0, n): floor(x n / 2^64), for n < 2^32 by two 32 x 32 products
+__device__ __forceinline__ uint32_t bounded(uint64_t x, uint32_t n) {
+    const uint64_t low = (x & 0xffffffffu) * n;
+    return static_cast<uint32_t>(((x >> 32) * n + (low >> 32)) >> 32);
+}
 
 }  // namespace helios

@@ -91,3 +91,24 @@ def test_whole_path_with_long_lists(h, helios, oracle, n_seeds, fanouts):
     for _ in range(2):
         assert_same(gpu_path(h, helios, torch.from_numpy(seeds), fanouts, 99, fused=True), want)
     assert_same(gpu_path(h, helios, torch.from_numpy(seeds), fanouts, 99, fused=False), want)
+
+
+@pytest.mark.parametrize("n_seeds", [1, 255, 256, 257, 1023, 1024, 1025, 2047])
+def test_folded_count_pass_edges(h, helios, oracle, n_seeds):
+    """Seed counts at the edges of the folded count pass (256, 1024, 2048 seeds), with fan-outs that fill a lane group exactly
+    (no lane left for the seed itself) and that do not."""
+    rng = np.random.default_rng(n_seeds)
+    n = 20_000
+    off, idx = _graph(rng, n, 80)
+    seeds = rng.integers(0, n, n_seeds).astype(np.int32)
+    h.csr_load(torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda())
+    feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
+    order = torch.from_numpy(rng.permutation(n).astype(np.int32))
+    cache = GpuCache(h, feats, order, 8_000, 6_000)  # noqa: F841
+    by_rank = to_bytes(feats)[order.numpy()]
+    tabs = [np.ascontiguousarray(x) for x in (by_rank[:8_000], by_rank[8_000:14_000], by_rank[14_000:])]
+    rank = oracle.rank_build(order.numpy())
+    for fanouts in ([8, 3], [7, 8], [16, 2], [9, 16], [32, 2], [25, 10], [64, 2], [40, 1], [70, 2], [0, 3]):
+        print("folded", n_seeds, fanouts, flush=True)
+        want = oracle_path(oracle, off, idx, seeds, fanouts, 7, rank, 8_000, 6_000, *tabs, 16)
+        assert_same(gpu_path(h, helios, torch.from_numpy(seeds), fanouts, 7, fused=True), want)
