@@ -627,15 +627,21 @@ int make_blocks_impl(helios_ctx* c, uint32_t table, uint32_t slots, int64_t n_se
     const DedupScratch s{batch_table(c, table), slots, nullptr, batch_iof(c, table)};
     for (int h = 0; h < n_hops; ++h)
         if (!blocks[h].row_local || !blocks[h].col_local) return fail(c, HELIOS_EINVAL, "hop %d: NULL block buffer", h);
+    LocalIdsList lists[kMaxLocalIdsLists];
+    int64_t n_max[kMaxLocalIdsLists];
+    static_assert(kMaxLocalIdsLists >= 2 * HELIOS_MAX_HOPS, "two lists per hop");
     for (int h = 0; h < n_hops; ++h) {
         // the sizes of the batch: the caller's size array if there is one (it belongs to the batch's buffers), else
         // the context's counters, which hold those of the context's last batch
         const Count nf = h == 0 ? Count{nullptr, n_seeds}
                                 : Count{sizes ? sizes + 2 * h : c->cnt + kCntFrontier + h, frontier_max[h]};
         const Count nfl{sizes ? sizes + 2 * h + 1 : c->cnt + kCntFlat + h, flat_max[h]};
-        HIP_TRY(c, launch_local_ids(c->stream, hops[h].frontier, nf, frontier_max[h], s, blocks[h].row_local, err));
-        HIP_TRY(c, launch_local_ids(c->stream, hops[h].flat, nfl, flat_max[h], s, blocks[h].col_local, err));
+        lists[2 * h] = LocalIdsList{hops[h].frontier, nf, blocks[h].row_local};
+        lists[2 * h + 1] = LocalIdsList{hops[h].flat, nfl, blocks[h].col_local};
+        n_max[2 * h] = frontier_max[h];
+        n_max[2 * h + 1] = flat_max[h];
     }
+    HIP_TRY(c, launch_local_ids(c->stream, lists, n_max, 2 * n_hops, s, err));
     return HELIOS_OK;
 }
 

@@ -140,10 +140,16 @@ hipError_t launch_gather_rows(hipStream_t stream, const GatherArgs& a, int64_t n
                               unsigned* blocks_out);
 
 // ---- blocks.hip
-// out[j] = index in a de-duplication's unique list of ids[j] (s = the scratch that de-duplication used,
-// untouched since); an ID that is not in the list raises kErrData.
-hipError_t launch_local_ids(hipStream_t stream, const int32_t* ids, Count n, int64_t n_max, const DedupScratch& s,
-                            int32_t* out, int32_t* err);
+// For every list: out[j] = index in a de-duplication's unique list of ids[j] (s = the scratch that de-duplication used,
+// untouched since); an ID that is not in the list raises kErrData.  n_max[k] bounds list k.
+struct LocalIdsList {
+    const int32_t* ids;
+    Count n;
+    int32_t* out;
+};
+constexpr int kMaxLocalIdsLists = 16;        // frontier and samples of up to eight hops
+hipError_t launch_local_ids(hipStream_t stream, const LocalIdsList* lists, const int64_t* n_max, int n_lists, const DedupScratch& s,
+                            int32_t* err);
 
 // ---- hotness.hip
 hipError_t launch_hotness_add(hipStream_t stream, const int32_t* ids, Count n, int64_t n_max, int64_t n_nodes,
