@@ -147,7 +147,7 @@ int helios_dedup(helios_ctx *ctx, const int32_t *ids, int64_t n_ids,
  * is a fixed array of about 6 MiB in the library's device image, which every
  * GPU the library runs on holds until the process ends.  At most
  * HELIOS_DEDUP_NOALLOC_MAX_IDS IDs per call, more is HELIOS_EINVAL.  All
- * contexts of a GPU share that array and each call starts by resetting it, so
+ * contexts of a GPU share that array, which every call leaves empty, so
  * calls that overlap on one GPU (different streams or host threads) race: the
  * caller serialises them.  It does not touch the scratch of helios_dedup or of
  * the batch calls. */

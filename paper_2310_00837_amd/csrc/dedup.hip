@@ -50,7 +50,23 @@ __global__ __launch_bounds__(kScanBlock) void dedup_compact_kernel(CompactArgs a
     compact_role<kCompactPlain>(a, blockIdx.x, gridDim.x);
 }
 
-__global__ __launch_bounds__(kBlock) void dedup_inverse_kernel(InverseArgs a) { inverse_role(a, blockIdx.x, gridDim.x); }
+// The end of a stand-alone de-duplication: the inverse map, and beside it the emptying of what the call has used.
+struct EndArgs {
+    InverseArgs inv;
+    ClearJob clear;
+    unsigned long long* zero;
+    uint32_t n_zero;
+    Role r_inv, r_clear;
+};
+__global__ __launch_bounds__(kBlock) void dedup_end_kernel(EndArgs a) {
+    if (a.r_inv.mine()) {
+        inverse_role(a.inv, a.r_inv.rb(), a.r_inv.blocks);
+        return;
+    }
+    const uint32_t step = a.r_clear.blocks * kBlock, first = a.r_clear.rb() * kBlock + threadIdx.x;
+    for (uint32_t w = first; a.clear.table && w < a.clear.n_slots; w += step) a.clear.table[w] = kEmptySlot;
+    for (uint32_t w = first; w < a.n_zero; w += step) a.zero[w] = 0ull;
+}
 
 unsigned grid_for(int64_t n_max, unsigned cap_blocks) {
     int64_t b = (n_max + kBlock - 1) / kBlock;
@@ -72,8 +88,16 @@ hipError_t launch_dedup_compact_plain(hipStream_t stream, const CompactArgs& a, 
     return hipGetLastError();
 }
 
-hipError_t launch_dedup_inverse(hipStream_t stream, const InverseArgs& a, int64_t n_max) {
-    hipLaunchKernelGGL(dedup_inverse_kernel, dim3(grid_for(n_max, 4096)), dim3(kBlock), 0, stream, a);
+hipError_t launch_dedup_end(hipStream_t stream, const InverseArgs& inv, int64_t n_max, const ClearJob& clear, unsigned long long* zero,
+                            uint32_t n_zero) {
+    EndArgs a{inv, clear, zero, n_zero, Role{0, 0}, Role{0, 0}};
+    a.r_inv.blocks = inv.inverse ? grid_for(n_max, 2048) : 0u;
+    a.r_clear.first = a.r_inv.blocks;
+    // eight slots per thread up to a grid that fills the chip
+    a.r_clear.blocks = clear.table || n_zero ? grid_for((static_cast<int64_t>(clear.n_slots) + 7) / 8, 1024) : 0u;
+    const unsigned blocks = a.r_inv.blocks + a.r_clear.blocks;
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(dedup_end_kernel, dim3(blocks), dim3(kBlock), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -491,6 +491,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             look.vars = vars;
             look.unique = b->unique;
             look.unique_cap = b->unique_cap;
+            look.inverse = b->inverse;
             look.prev = h > 0 ? stage_words(c, h - 1) : nullptr;
             look.mine = stage_words(c, h);
             look.last = last;
@@ -530,15 +531,15 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
         if (rc) return rc;
     }
     const uint32_t clear_slots = rec ? slots_b : c->batch_dirty[next];
-    InverseArgs inv{Count{c->cnt + kCntCat, p.cat_max}, DedupScratch{nullptr, 0, nullptr, nullptr}, bt, vars, b->inverse, Stamps{nullptr}};
+    InverseArgs inv{Count{c->cnt + kCntCat, p.cat_max}, nullptr, bt, vars, b->inverse, Stamps{nullptr}};
     if (c->split_copies) {
         int rc = copy_tiers_split(c, u_max, b->out);
         if (rc) return rc;
         if (served_max > 0)
             HIP_TRY(c, launch_gather_rows(c->stream, miss_args, served_max, true, true, c->host_blocks, 0, nullptr, nullptr, nullptr));
-        if (b->inverse) HIP_TRY(c, launch_dedup_inverse(c->stream, inv, p.cat_max));
         // (a recording with split copies leaves the emptying of the next table to helios_plan_launch)
-        if (!rec && clear_slots) HIP_TRY(c, launch_clear(c->stream, ClearJob{batch_table(c, next), clear_slots}));
+        const ClearJob clear = !rec && clear_slots ? ClearJob{batch_table(c, next), clear_slots} : ClearJob{nullptr, 0};
+        HIP_TRY(c, launch_dedup_end(c->stream, inv, p.cat_max, clear, nullptr, 0));
     } else {
         const int stage = n_hops - 1;
         GatherArgs hbm{}, link{}, miss{};
@@ -820,7 +821,7 @@ int helios_create(helios_ctx** out, int device, void* hip_stream) {
               hipHostMalloc(reinterpret_cast<void**>(&c->clock_host), sizeof(uint64_t) * 2 * kMaxStampRoles,
                             hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess;
     ok = ok && c->err && c->cnt && c->vars && c->scan_ticket && c->batches_run && c->vars_ring && c->learn && c->clock_host;
-    ok = ok && noalloc_init(device) == HELIOS_OK;      // address of this device's static scratch (helios_dedup_noalloc)
+    ok = ok && noalloc_init(device, c->stream) == HELIOS_OK;      // this device's static scratch (helios_dedup_noalloc)
     if (ok) {
         int khz = 0;
         if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) c->clock_khz = khz;
@@ -991,14 +992,15 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     a.last = true;
     a.n_unique_dev = c->cnt + kCntUnique;
     a.n_unique_out = n_unique;
+    a.inverse = inverse;
     a.scan = scan_state(c, epoch, kScanRowsLook);
     a.err = c->err;
     HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
-    if (inverse) {
-        const InverseArgs inv{Count{c->cnt + kCntCat, n_ids}, s, BatchTables{nullptr, 0, nullptr, 0, 0, nullptr, 0}, nullptr, inverse,
-                              Stamps{nullptr}};
-        HIP_TRY(c, launch_dedup_inverse(c->stream, inv, n_ids));
-    }
+    // the call leaves its table as it found it: empty
+    const InverseArgs inv{Count{c->cnt + kCntCat, n_ids}, s.index_of_first, BatchTables{nullptr, 0, nullptr, 0, 0, nullptr, 0}, nullptr, inverse,
+                          Stamps{nullptr}};
+    HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{s.table, s.n_slots}, nullptr, 0));
+    c->batch_dirty[which] = 0;
     return HELIOS_OK;
 }
 

@@ -117,9 +117,12 @@ hipError_t launch_clock_publish(hipStream_t stream, const uint64_t* clock, const
 // into s.table, which must be empty.
 hipError_t launch_dedup_insert(hipStream_t stream, const int32_t* ids, Count n, int64_t n_max, int64_t n_nodes,
                                const DedupScratch& s, int32_t* err);
-// Second pass over the whole list, and the optional third pass.
+// Second pass over the whole list.
 hipError_t launch_dedup_compact_plain(hipStream_t stream, const CompactArgs& a, int64_t n_max);
-hipError_t launch_dedup_inverse(hipStream_t stream, const InverseArgs& a, int64_t n_max);
+// The optional third pass (inv.inverse nullable), and in the same launch the emptying of a table and the zeroing of n_zero words,
+// neither of which that pass reads.
+hipError_t launch_dedup_end(hipStream_t stream, const InverseArgs& inv, int64_t n_max, const ClearJob& clear, unsigned long long* zero,
+                            uint32_t n_zero);
 
 // ---- cache.hip
 hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int32_t* err);

@@ -4,11 +4,13 @@
 // helios_dedup takes its scratch (hash table, slot of every input, unique index of every first
 // occurrence, scan status words, counters) from memory the context allocates and grows.  Here all
 // of it lives in one file-scope device array of fixed size, so the call enqueues kernels and
-// nothing else.  The array exists once per GPU the library runs on and keeps the contents of the
-// last call: every call starts with a fill kernel that empties the table and zeroes the scan
-// status, ticket and counters (a kernel, not a memset: a memset node in a captured graph is not
-// reliable on this platform).  All calls on one GPU share the array, so calls that overlap on one
-// GPU (two streams, two contexts, two host threads) race; callers serialise them.
+// nothing else.  The array exists once per GPU the library runs on.  It is filled once, when the
+// first context of that GPU is created, and every call leaves it as it found it: its last launch
+// empties the table and zeroes the scan status beside the inverse map, which reads neither (a
+// launch of its own at the start of every call took 3 us).  So a captured call can be replayed.
+// Only a call that a launch error has cut short leaves it in use; the next call fills it first.
+// All calls on one GPU share the array, so calls that overlap on one GPU (two streams, two
+// contexts, two host threads) race; callers serialise them.
 #include "context.hpp"
 #include "noalloc.hpp"
 
@@ -38,6 +40,7 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_mu;
 unsigned char* g_ptr[kMaxDevices] = {nullptr};     // device address of `scratch` on every GPU seen so far
+bool g_in_use[kMaxDevices] = {false};              // a call has been cut short: the array has to be filled
 
 // empties the table, zeroes the scan status words and the small block
 __global__ __launch_bounds__(kBlock) void noalloc_reset_kernel(unsigned long long* table, uint32_t n_slots,
@@ -47,16 +50,29 @@ __global__ __launch_bounds__(kBlock) void noalloc_reset_kernel(unsigned long lon
     for (uint32_t w = blockIdx.x * kBlock + threadIdx.x; w < n_zero_words; w += step) zero_from[w] = 0ull;
 }
 
+hipError_t launch_reset(hipStream_t stream, unsigned char* base, uint32_t slots) {
+    const uint32_t zero_words = static_cast<uint32_t>((kStatusBytes + kSmallBytes) / sizeof(unsigned long long));
+    unsigned blocks = (slots + kBlock * 16 - 1) / (kBlock * 16);
+    blocks = blocks < 1 ? 1 : blocks > 1024 ? 1024 : blocks;
+    hipLaunchKernelGGL(noalloc_reset_kernel, dim3(blocks), dim3(kBlock), 0, stream, reinterpret_cast<unsigned long long*>(base + kOffTable),
+                       slots, reinterpret_cast<unsigned long long*>(base + kOffStatus), zero_words);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 namespace helios {
 
-int noalloc_init(int device) {
+int noalloc_init(int device, hipStream_t stream) {
     if (device < 0 || device >= kMaxDevices) return HELIOS_EINVAL;
     std::lock_guard<std::mutex> lk(g_mu);
     if (g_ptr[device]) return HELIOS_OK;
     void* p = nullptr;
     if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) {     // the current device's copy of the array
+        (void)hipGetLastError();
+        return HELIOS_EHIP;
+    }
+    if (launch_reset(stream, static_cast<unsigned char*>(p), kSlots) != hipSuccess || hipStreamSynchronize(stream) != hipSuccess) {
         (void)hipGetLastError();
         return HELIOS_EHIP;
     }
@@ -76,9 +92,12 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
                     (long long)kMaxIds, (long long)n_ids);
     if ((n_ids > 0 && !ids) || (unique_cap > 0 && !unique)) return fail(c, HELIOS_EINVAL, "NULL pointer");
     unsigned char* base = nullptr;
-    {
+    bool fill = false;
+    if (c->device >= 0 && c->device < kMaxDevices) {
         std::lock_guard<std::mutex> lk(g_mu);
-        base = c->device >= 0 && c->device < kMaxDevices ? g_ptr[c->device] : nullptr;
+        base = g_ptr[c->device];
+        fill = g_in_use[c->device];
+        g_in_use[c->device] = true;              // until the last launch has gone out
     }
     if (!base) return fail(c, HELIOS_ESTATE, "the static scratch of device %d was not set up by helios_create", c->device);
     DeviceGuard guard(c->device);
@@ -91,11 +110,7 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     while (static_cast<int64_t>(slots) < 2 * n_ids) slots <<= 1;
     const DedupScratch s{table, slots, reinterpret_cast<int32_t*>(base + kOffSlotOf),
                          reinterpret_cast<int32_t*>(base + kOffIndexOfFirst)};
-    const uint32_t zero_words = static_cast<uint32_t>((kStatusBytes + kSmallBytes) / sizeof(unsigned long long));
-    unsigned reset_blocks = (slots + kBlock * 16 - 1) / (kBlock * 16);
-    reset_blocks = reset_blocks < 1 ? 1 : reset_blocks > 1024 ? 1024 : reset_blocks;
-    hipLaunchKernelGGL(noalloc_reset_kernel, dim3(reset_blocks), dim3(kBlock), 0, c->stream, table, slots, status, zero_words);
-    HIP_TRY(c, hipGetLastError());
+    if (fill) HIP_TRY(c, launch_reset(c->stream, base, kSlots));
     // the status words are zero, so any epoch but zero reads them as unpublished; the same value every
     // call keeps a captured call replayable
     const ScanState scan{status, ticket, kStride, 1u, nullptr};
@@ -113,13 +128,15 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     a.last = true;
     a.n_unique_dev = counters + 1;
     a.n_unique_out = n_unique;
+    a.inverse = inverse;
     a.scan = scan;
     a.err = c->err;
     HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
-    if (inverse) {
-        const InverseArgs inv{Count{counters + 0, n_ids}, s, BatchTables{nullptr, 0, nullptr, 0, 0, nullptr, 0}, nullptr, inverse,
-                              Stamps{nullptr}};
-        HIP_TRY(c, launch_dedup_inverse(c->stream, inv, n_ids));
-    }
+    const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{nullptr, 0, nullptr, 0, 0, nullptr, 0}, nullptr, inverse,
+                          Stamps{nullptr}};
+    HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{table, slots}, status,
+                                static_cast<uint32_t>(kStatusBytes / sizeof(unsigned long long))));
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_in_use[c->device] = false;
     return HELIOS_OK;
 }
