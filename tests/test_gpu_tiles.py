@@ -9,7 +9,7 @@ from pathlib_helios import GpuCache, assert_same, gpu_path, oracle_path, to_byte
 
 pytestmark = pytest.mark.gpu
 ONE_ITEM_MAX = 131_072
-EDGES = [1, 63, 65, 511, 512, 513, 1025, ONE_ITEM_MAX - 1, ONE_ITEM_MAX, ONE_ITEM_MAX + 1, 256 * 2048 + 3]
+EDGES = [1, 63, 65, 511, 512, 513, 1025, ONE_ITEM_MAX - 1, ONE_ITEM_MAX, ONE_ITEM_MAX + 1, 262_144, 262_145, 256 * 2048 + 3]
 
 
 @pytest.fixture(scope="module")
@@ -70,6 +70,29 @@ def test_dedup_and_lookup_at_tile_edges(h, oracle, n_ids):
     assert np.array_equal(out.cpu().numpy(), want)
     for got, w in zip(miss, lists[:3]):
         assert np.array_equal(got[:w.size].cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("n_ids", [1_000, 300_001])
+def test_dedup_reports_bad_ids_and_keeps_the_rest(h, helios, oracle, n_ids):
+    """IDs outside [0, n) in a short and in a long list: reported, left out of unique, -1 in inverse."""
+    rng = np.random.default_rng(n_ids)
+    n = 5_000
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    ids = rng.integers(0, n, n_ids).astype(np.int32)
+    bad = rng.choice(n_ids, 37, replace=False)
+    ids[bad] = rng.choice([-1, -(1 << 31), n, (1 << 31) - 1], 37)
+    uniq = torch.full((n_ids,), -9, dtype=torch.int32, device="cuda")
+    inv, nu = torch.full_like(uniq, -9), torch.zeros(1, dtype=torch.int64).pin_memory()
+    h.dedup(torch.from_numpy(ids).cuda(), uniq, inv, nu)
+    with pytest.raises(helios.HeliosError) as e:
+        h.sync()
+    assert e.value.code == helios.EDATA
+    good = np.ones(n_ids, bool)
+    good[bad] = False
+    wu, wi = oracle.dedup(n, ids[good])
+    assert int(nu[0]) == wu.size and np.array_equal(uniq[:wu.size].cpu().numpy(), wu)
+    got = inv.cpu().numpy()
+    assert np.array_equal(got[good], wi) and (got[bad] == -1).all()
 
 
 @pytest.mark.parametrize("n_seeds,fanouts", [(2_048, [4, 3]), (2_049, [4, 3]), (ONE_ITEM_MAX + 5, [1, 2]), (60_000, [4, 2])])
