@@ -36,7 +36,7 @@ struct BatchVars {
     uint32_t epoch_base;     // added to the per-launch epoch of the chained scans
     uint32_t io_round;       // round number of the miss queue the batch submits to (0 if none)
     uint32_t table;          // which of the rotating batch tables this batch uses
-    uint32_t reserved;
+    uint32_t clear_slots;    // slots in use of the table that the batch's last launch empties (0: it is empty)
 };
 
 // How a recorded batch gets its BatchVars without a copy being part of the recording: the host writes

@@ -17,6 +17,7 @@ constexpr int kCntCat = 32;         // length of [seeds | flat_0 | ...] compacte
 constexpr int kCntUnique = 33;
 constexpr int kCntHopTotal = 34;    // input length of a de-duplication between two hops (a copy of its flat size)
 constexpr int kCntTier = 40;        // [3] list entries to copy from the HBM tier and the host tier, misses to serve
+constexpr int kCntList = 48;        // [kBatchTables] length of the ID list that the table's last batch inserted
 constexpr int kCntStage = 64;       // [HELIOS_MAX_HOPS][kStageWords] totals after every stage of a batch's compaction
 constexpr int kNumCounters = kCntStage + HELIOS_MAX_HOPS * kStageWords;
 constexpr uint32_t kVarsRing = 256;   // batch launches that may be queued on a context without a helios_sync
@@ -95,8 +96,9 @@ struct helios_ctx {
     uint32_t table_slots = 0;                  // slots of every hash table below (power of two >= 2 * cap_ids)
     unsigned long long* batch_tables = nullptr;   // kBatchTables tables of the batch de-duplication, one after the other
     int32_t* batch_iof = nullptr;              // kBatchTables x cap_ids: index in `unique` of a first occurrence
-    int32_t* batch_slot_of = nullptr;          // cap_ids
+    int32_t* batch_slot_of = nullptr;          // kBatchTables x cap_ids: slot of every position in the batch's ID list
     uint32_t batch_dirty[helios::kBatchTables] = {0, 0, 0};   // slots of each batch table that may be non-empty
+    bool batch_listed[helios::kBatchTables] = {false, false, false};   // ... and whether that batch's list names all of them
     uint64_t batch_seq = 0;                    // batches launched so far; batch b uses table b mod kBatchTables
     unsigned long long* hop_table[2] = {nullptr, nullptr};   // de-duplication of one hop's samples, hops alternate
     uint32_t hop_dirty[2] = {0, 0};

@@ -25,7 +25,7 @@ struct helios_plan {
     helios_hop_out hops[HELIOS_MAX_HOPS] = {};
     const int64_t* sizes = nullptr;    // the caller's size array (device-accessible, nullable)
     uint32_t slots = 0;                // slots of the batch table the recording uses
-    uint32_t clear_slots = 0;          // slots of the next batch's table it empties on the way
+    uint32_t clear_slots = 0;          // not 0: its last launch empties the next batch's table
     helios_missq* missq = nullptr;     // the queue attached when the batch was recorded
     hipEvent_t done = nullptr;         // recorded behind every launch
     uint64_t launch_seq = 0;           // the context's launch count at this plan's last launch
@@ -80,6 +80,7 @@ void free_scratch(helios_ctx* c) {
 }
 
 unsigned long long* batch_table(const helios_ctx* c, uint32_t t) { return c->batch_tables + static_cast<size_t>(t) * c->table_slots; }
+int32_t* batch_slots(const helios_ctx* c, uint32_t t) { return c->batch_slot_of + static_cast<size_t>(t) * c->cap_ids; }
 int32_t* batch_iof(const helios_ctx* c, uint32_t t) { return c->batch_iof + static_cast<size_t>(t) * c->cap_ids; }
 
 // Scratch for calls with up to n IDs.  Growing waits for the stream first: the
@@ -98,7 +99,7 @@ int ensure_capacity(helios_ctx* c, int64_t n) {
     const uint32_t stride = scan_row_stride(cap);
     HIP_TRY(c, hipMalloc(&c->batch_tables, sizeof(unsigned long long) * slots * kBatchTables));
     HIP_TRY(c, hipMalloc(&c->batch_iof, sizeof(int32_t) * cap * kBatchTables));
-    HIP_TRY(c, hipMalloc(&c->batch_slot_of, sizeof(int32_t) * cap));
+    HIP_TRY(c, hipMalloc(&c->batch_slot_of, sizeof(int32_t) * cap * kBatchTables));
     HIP_TRY(c, hipMalloc(&c->hop_table[0], sizeof(unsigned long long) * slots));
     HIP_TRY(c, hipMalloc(&c->hop_table[1], sizeof(unsigned long long) * slots));
     HIP_TRY(c, hipMalloc(&c->hop_slot_of, sizeof(int32_t) * cap));
@@ -242,6 +243,15 @@ int clean_for_call(helios_ctx* c, int batch_table_needed /* -1: none */) {
     return HELIOS_OK;
 }
 
+// empties a batch table now, unless the list of its last batch names everything in it
+int clean_unlisted(helios_ctx* c, uint32_t t) {
+    if (c->batch_dirty[t] && !c->batch_listed[t]) {
+        HIP_TRY(c, launch_clear(c->stream, ClearJob{batch_table(c, t), c->batch_dirty[t]}));
+        c->batch_dirty[t] = 0;
+    }
+    return HELIOS_OK;
+}
+
 struct BatchOut {                // the outputs of the whole-path call beyond those of the sampling
     int32_t* unique;
     int64_t unique_cap;
@@ -365,11 +375,12 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
 
     const int64_t batch_max = p.cat_max > 0 ? p.cat_max : 1;
     const uint32_t which = static_cast<uint32_t>(c->batch_seq % kBatchTables), next = (which + 1) % kBatchTables;
-    BatchTables bt{nullptr, 0, nullptr, 0, 0, nullptr, 0};
+    BatchTables bt{};
     uint32_t slots_b = 0;
     if (b) {
         slots_b = dedup_slots(c, batch_max);
-        bt = BatchTables{c->batch_tables, c->table_slots, c->batch_iof, static_cast<uint64_t>(c->cap_ids), slots_b, c->batch_slot_of, which};
+        bt = BatchTables{c->batch_tables, c->table_slots, c->batch_iof, static_cast<uint64_t>(c->cap_ids), c->batch_slot_of, c->cnt + kCntList,
+                         slots_b, which};
     }
     uint32_t hop_slots[HELIOS_MAX_HOPS];
     for (int h = 0; h < n_hops; ++h) hop_slots[h] = dedup_slots(c, p.flat_max[h]);
@@ -378,7 +389,13 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
         if (rc) return rc;
         // until the call has been enqueued completely, its tables count as in use
         for (int h = 0; h + 1 < n_hops; ++h) c->hop_dirty[h % 2] = std::max(c->hop_dirty[h % 2], hop_slots[h]);
-        if (b) c->batch_dirty[which] = slots_b;
+        if (b) {
+            c->batch_dirty[which] = slots_b;
+            c->batch_listed[which] = false;
+            // the last launch empties the next batch's table by its list, if that names everything in it
+            if (!c->split_copies) rc = clean_unlisted(c, next);
+            if (rc) return rc;
+        }
     }
     const int64_t u_max = b ? std::min(p.cat_max, b->unique_cap) : 0;
     // What the kernels' own guards rely on (they bound every index by these): a list never outgrows the buffer it
@@ -564,12 +581,8 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             inv_blocks = inv_blocks < 1 ? 1 : inv_blocks;
             inv.stamps = take_stamps(c, HELIOS_ROLE_INVERSE, stage, inv_blocks);
         }
-        ClearJob clear{nullptr, 0};
-        if (clear_slots) {
-            clear = ClearJob{batch_table(c, next), clear_slots};      // a recording picks the table on the device
-            clear_blocks = std::min(256u, (clear_slots + kBlock * 16 - 1) / (kBlock * 16));
-        }
-        int rf = emit_finish(c, FinishJob{hbm, hbm_blocks, link, link_blocks, miss, miss_blocks, inv, inv_blocks, clear, clear_blocks, bt, vars});
+        if (clear_slots) clear_blocks = std::min(256u, (clear_slots + kBlock * 16 - 1) / (kBlock * 16));      // (a recording learns on the device how much there is)
+        int rf = emit_finish(c, FinishJob{hbm, hbm_blocks, link, link_blocks, miss, miss_blocks, inv, inv_blocks, clear_slots, clear_blocks, bt, vars});
         if (rf) return rf;
     }
     int rc = c->defer ? HELIOS_OK : publish_stamps(c);      // (a gang publishes after its launches have gone out)
@@ -577,6 +590,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
     if (!rec) {
         for (int t = 0; t < 2; ++t) c->hop_dirty[t] = 0;
         c->batch_dirty[next] = 0;
+        c->batch_listed[which] = true;
         c->batch_seq += 1;
         c->blocks_ready = true;
         c->last_table = which;
@@ -615,6 +629,7 @@ int check_error_word(helios_ctx* c, int32_t* word) {
     const int code = *reinterpret_cast<volatile int32_t*>(word);
     if (code != 0) {
         word[0] = 0;
+        for (uint32_t t = 0; t < kBatchTables; ++t) c->batch_listed[t] = false;      // no list is trusted after an error
         return fail(c, code, code == HELIOS_ECAPACITY ? "an output did not fit its capacity"
                              : code == HELIOS_EINTERNAL ? "a workgroup gave up waiting (chained scan, or a miss queue that stopped answering)"
                              : "a node ID outside [0, n_nodes), an order that is not a permutation, or a list entry outside its table");
@@ -716,23 +731,22 @@ int plan_prelaunch(helios_plan* pl, const int32_t* seeds, uint64_t rng_seed, uin
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         c->vars_unsynced = 0;
     }
-    // The recording assumes that its own batch table and both hop tables are empty, and it empties clear_slots slots
-    // of the next batch's table.  What that leaves out is emptied here, by launches of their own (rare: only when
-    // batches of different sizes, or direct and recorded calls, alternate on a context).
+    // The recording assumes that its own batch table and both hop tables are empty, and its last launch empties the next
+    // batch's table, however much of that is in use.  What that leaves out is emptied here, by launches of their own (rare: a
+    // recording with split copies, or a call that failed half way).
     const uint32_t which = static_cast<uint32_t>(c->batch_seq % kBatchTables), next = (which + 1) % kBatchTables;
     int rc = clean_for_call(c, static_cast<int>(which));
     if (rc) return rc;
-    if (c->batch_dirty[next] > pl->clear_slots) {
-        HIP_TRY(c, launch_clear(c->stream, ClearJob{batch_table(c, next), c->batch_dirty[next]}));
-        c->batch_dirty[next] = 0;
-    }
+    if (!pl->clear_slots) c->batch_listed[next] = false;
+    rc = clean_unlisted(c, next);
+    if (rc) return rc;
     BatchVars* slot = c->vars_ring + (c->vars_next % kVarsRing);
     slot->rng_seed = rng_seed;
     slot->seeds = seeds;
     slot->epoch_base = c->epoch;
     slot->io_round = io_round;
     slot->table = which;
-    slot->reserved = 0;
+    slot->clear_slots = c->batch_dirty[next];
     __atomic_thread_fence(__ATOMIC_RELEASE);     // the slot is written before the launch is rung in
     *io_round_out = io_round;
     return HELIOS_OK;
@@ -748,6 +762,7 @@ void plan_postlaunch(helios_plan* pl, uint32_t io_round) {
     c->epoch += pl->n_scans;
     if (pl->missq) missq_commit_round(pl->missq, io_round);
     c->batch_dirty[which] = pl->slots;
+    c->batch_listed[which] = true;
     c->batch_dirty[next] = 0;
     c->batch_seq += 1;
     pl->batch_seq = c->batch_seq;
@@ -976,8 +991,9 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     uint32_t epoch;
     rc = next_epoch(c, &epoch);
     if (rc) return rc;
-    const DedupScratch s{batch_table(c, which), dedup_slots(c, n_ids), c->batch_slot_of, batch_iof(c, which)};
+    const DedupScratch s{batch_table(c, which), dedup_slots(c, n_ids), batch_slots(c, which), batch_iof(c, which)};
     c->batch_dirty[which] = s.n_slots;
+    c->batch_listed[which] = false;
     const Count n{nullptr, n_ids};
     HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, c->err));
     CompactArgs a{};
@@ -997,7 +1013,7 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     a.err = c->err;
     HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
     // the call leaves its table as it found it: empty
-    const InverseArgs inv{Count{c->cnt + kCntCat, n_ids}, s.index_of_first, BatchTables{nullptr, 0, nullptr, 0, 0, nullptr, 0}, nullptr, inverse,
+    const InverseArgs inv{Count{c->cnt + kCntCat, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse,
                           Stamps{nullptr}};
     HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{s.table, s.n_slots}, nullptr, 0));
     c->batch_dirty[which] = 0;

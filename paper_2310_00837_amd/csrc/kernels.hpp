@@ -52,8 +52,8 @@ hipError_t launch_compact(hipStream_t stream, const CompactJob* jobs, int n);
 // The end of a batch in one launch: host-tier copy of the last stage, the rows of the miss list from the
 // storage stand-in (if the batch serves its own misses), HBM-tier copy of all stages, the inverse map,
 // and the emptying of the table that the next batch of the context uses.  Any of the five may be absent
-// (0 workgroups).  With vars (a recorded batch) the table to empty is the one after the batch's
-// own among bt's, whatever clear.table says.  The rows of all members have one size.
+// (0 workgroups).  The table to empty is the one after the batch's own among bt's; clear_slots of its slots are in use (with
+// vars, a recorded batch, the variables say how many).  The rows of all members have one size.
 struct FinishJob {
     GatherArgs hbm;
     unsigned hbm_blocks;
@@ -63,7 +63,7 @@ struct FinishJob {
     unsigned miss_blocks;
     InverseArgs inv;
     unsigned inv_blocks;
-    ClearJob clear;
+    uint32_t clear_slots;
     unsigned clear_blocks;
     BatchTables bt;
     const BatchVars* vars;
@@ -90,9 +90,9 @@ struct CompactGang {
 struct FinishMember {
     GatherArgs hbm, link, miss;
     InverseArgs inv;
-    ClearJob clear;
     BatchTables bt;
     const BatchVars* vars;
+    uint32_t clear_slots;
     Role r_hbm, r_link, r_miss, r_inv, r_clear;
 };
 struct FinishGang {

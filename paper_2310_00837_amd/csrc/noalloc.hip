@@ -132,7 +132,7 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     a.scan = scan;
     a.err = c->err;
     HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
-    const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{nullptr, 0, nullptr, 0, 0, nullptr, 0}, nullptr, inverse,
+    const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse,
                           Stamps{nullptr}};
     HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{table, slots}, status,
                                 static_cast<uint32_t>(kStatusBytes / sizeof(unsigned long long))));

@@ -86,10 +86,7 @@ __global__ __launch_bounds__(kBlock) void batch_finish_kernel(FinishGang g) {
             return;
         }
         if (a.r_clear.mine()) {
-            // the table of the context's next batch; a recorded batch learns only on the device which one that is
-            unsigned long long* table = a.vars ? a.bt.table((a.vars->table + 1) % kBatchTables) : a.clear.table;
-            for (uint32_t w = a.r_clear.rb() * kBlock + threadIdx.x; table && w < a.clear.n_slots; w += a.r_clear.blocks * kBlock)
-                table[w] = kEmptySlot;
+            empty_next_table(a.bt, a.vars, a.clear_slots, a.r_clear.rb(), a.r_clear.blocks);
             return;
         }
     }
@@ -193,7 +190,7 @@ hipError_t launch_finish(hipStream_t stream, const FinishJob* jobs, int n) {
         a.hbm = jobs[m].hbm;
         a.link = jobs[m].link;
         a.inv = jobs[m].inv;
-        a.clear = jobs[m].clear;
+        a.clear_slots = jobs[m].clear_slots;
         a.bt = jobs[m].bt;
         a.vars = jobs[m].vars;
         a.miss = jobs[m].miss;

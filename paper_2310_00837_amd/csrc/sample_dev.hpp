@@ -229,7 +229,7 @@ __device__ __forceinline__ void sample_role(const HopArgs& a, uint32_t rb, uint3
     if (a.batch.table0) {
         tabs.batch_table = a.batch.table(which);
         tabs.batch_mask = a.batch.n_slots - 1;
-        tabs.batch_slot_of = a.batch.slot_of;
+        tabs.batch_slot_of = a.batch.slot_of(which);
     }
     const bool seeds_too = tabs.batch_table && a.hop == 0;   // the frontier of hop 0 is the head of the batch's list
     if (f > 0 || seeds_too) {

@@ -1,0 +1,94 @@
+"""GPU parity over many batches on one context: the hash tables of the de-duplication rotate, and a batch's last launch empties
+the next one's, by the list of the batch that used it (short lists) or in full (long ones).  Direct and recorded batches of two
+sizes, stand-alone de-duplications and batches that report an error follow each other; every result equals the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+from pathlib_helios import GpuCache, assert_same, gpu_path, oracle_path, to_bytes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def helios():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    from paper_2310_00837_amd import helios as hl
+    return hl
+
+
+@pytest.mark.parametrize("max_deg,fanouts", [(2, [25, 10]), (40, [3, 3])])
+def test_tables_over_many_batches(helios, oracle, max_deg, fanouts):
+    rng = np.random.default_rng(max_deg)
+    n = 30_000
+    deg = rng.integers(max_deg // 2, max_deg + 1, n)
+    off = np.zeros(n + 1, np.int64)
+    off[1:] = np.cumsum(deg)
+    idx = rng.integers(0, n, int(off[-1])).astype(np.int32)
+    feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
+    order = torch.from_numpy(rng.permutation(n).astype(np.int32))
+    by_rank = to_bytes(feats)[order.numpy()]
+    tabs = [np.ascontiguousarray(x) for x in (by_rank[:9_000], by_rank[9_000:15_000], by_rank[15_000:])]
+    rank = oracle.rank_build(order.numpy())
+    h = helios.Helios(0, stream=torch.cuda.Stream())
+    off_d, idx_d = torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda()
+    torch.cuda.synchronize()
+    h.csr_load(off_d, idx_d)
+    cache = GpuCache(h, feats, order, 9_000, 6_000)  # noqa: F841
+    sizes = {}
+    h.reserve(700 * (1 + fanouts[0] * (1 + fanouts[1])))
+
+    def plan_of(b):
+        if b not in sizes:
+            dev = h.device
+            hops = helios.alloc_hops(b, fanouts, dev)
+            cap = b + sum(hb.flat.numel() for hb in hops)
+            ints = [torch.empty(cap, dtype=torch.int32, device=dev) for _ in range(5)]
+            bufs = (hops, torch.zeros(2 * len(fanouts), dtype=torch.int64).pin_memory(), ints[0], ints[1],
+                    torch.zeros(1, dtype=torch.int64).pin_memory(), torch.empty((cap, 16), dtype=torch.uint8, device=dev),
+                    ints[2], ints[3], ints[4], torch.zeros(4, dtype=torch.int64).pin_memory())
+            torch.cuda.synchronize()
+            sizes[b] = (h.plan_create(b, fanouts, *bufs), bufs)
+        return sizes[b]
+
+    def want_of(seeds, rs):
+        return oracle_path(oracle, off, idx, seeds, fanouts, rs, rank, 9_000, 6_000, *tabs, 16)
+
+    for k, what in enumerate("direct plan plan dedup plan bad direct plan small plan small bad plan direct dedup small direct".split()):
+        print(k, what, flush=True)
+        b = 90 if what == "small" else 700
+        seeds = rng.integers(0, n, b).astype(np.int32)
+        if what == "dedup":
+            ids = rng.integers(0, n, 5_000).astype(np.int32)
+            t = torch.from_numpy(ids).cuda()
+            uq, inv, nu = torch.empty_like(t), torch.empty_like(t), torch.zeros(1, dtype=torch.int64).pin_memory()
+            torch.cuda.synchronize()
+            h.dedup(t, uq, inv, nu)
+            h.sync()
+            wu, wi = oracle.dedup(n, ids)
+            assert np.array_equal(uq[:wu.size].cpu().numpy(), wu) and np.array_equal(inv.cpu().numpy(), wi)
+            continue
+        if what == "bad":
+            seeds[5] = n + 7
+        s = torch.from_numpy(seeds).cuda()
+        torch.cuda.synchronize()
+        if what == "direct":
+            assert_same(gpu_path(h, helios, s, fanouts, k, fused=True), want_of(seeds, k))
+            continue
+        plan, bufs = plan_of(b)
+        plan.launch(s, k)
+        if what == "bad":
+            with pytest.raises(helios.HeliosError) as e:
+                plan.wait()
+            assert e.value.code == helios.EDATA
+            continue
+        plan.wait()
+        want = want_of(seeds, k)
+        u = want["unique"].size
+        assert int(bufs[4][0]) == u and np.array_equal(bufs[2][:u].cpu().numpy(), want["unique"])
+        assert np.array_equal(bufs[3][:want["inverse"].size].cpu().numpy(), want["inverse"])
+        assert np.array_equal(bufs[9].numpy(), want["stats"])
+        for hb, (fr, ip, fl) in zip(bufs[0], want["hops"]):
+            assert np.array_equal(hb.frontier[:fr.size].cpu().numpy(), fr) and np.array_equal(hb.flat[:fl.size].cpu().numpy(), fl)
+    h.close()
