@@ -7,7 +7,8 @@
 // the three classes are compacted *stably* in one pass: wave ballots and a scan of
 // the waves' totals give the ranks inside a tile and a three-counter
 // chained scan (TileScan in scan.hpp) the ranks across workgroups.  The two hit lists (position, slot)
-// feed the row-copy kernels; the miss list (position, id, slot) is the request
+// feed the row-copy kernels (helios_gather copies the HBM tier's rows without one, in
+// the same launch); the miss list (position, id, slot) is the request
 // list of the storage tier and comes out ascending in position.
 #include "kernels.hpp"
 
@@ -48,24 +49,25 @@ struct PartitionArgs {
     int64_t miss_cap;
     int64_t* stats_out;          // device-accessible int64[4], nullable
     int64_t* learn;              // pinned int64[4], nullable: a copy of the stats for the host's grid sizing
+    bool hbm_direct;             // no list is wanted for the HBM tier
     ScanState scan;
     int32_t* err;
 };
 
 // Bound like a stage of the compaction (compact_dev.hpp) by its chain of dependent steps, and built like it.
 template <int K>
-__global__ __launch_bounds__(kScanBlock) void lookup_partition_kernel(PartitionArgs a) {
+__device__ __forceinline__ void partition_role(const PartitionArgs& a, uint32_t rb, uint32_t nrb) {
     using Scan = TileScan<2, 3, K>;
     __shared__ typename Scan::Lds lds;
     const ScanState scan = scan_resolve(a.scan);
     const uint32_t n = static_cast<uint32_t>(a.n.get());
     const uint32_t n_tiles = (n + K * kScanBlock - 1) / (K * kScanBlock);
-    if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+    if (n == 0 && rb == 0 && threadIdx.x == 0) {
         a.lists.count[0] = a.lists.count[1] = a.lists.count[2] = 0;
         if (a.stats_out) { a.stats_out[0] = 0; a.stats_out[1] = 0; a.stats_out[2] = 0; a.stats_out[3] = 0; }
     }
-    if (blockIdx.x >= n_tiles) return;
-    const uint32_t n_wgs = gridDim.x < n_tiles ? gridDim.x : n_tiles;
+    if (rb >= n_tiles) return;
+    const uint32_t n_wgs = nrb < n_tiles ? nrb : n_tiles;
     for (uint32_t tile = Scan::take_ticket(scan, n_tiles, n_wgs, lds); tile < n_tiles;
          tile = n_wgs < n_tiles ? Scan::take_ticket(scan, n_tiles, n_wgs, lds) : n_tiles) {
         const uint32_t j0 = tile * (K * kScanBlock) + threadIdx.x;
@@ -98,10 +100,15 @@ __global__ __launch_bounds__(kScanBlock) void lookup_partition_kernel(PartitionA
             const int32_t j = static_cast<int32_t>(j0 + k * kScanBlock);
             const uint32_t hits = before[1][k] + in_hits[k];
             if (ur < n_cached) {
-                const bool host = ur >= n_hbm;
-                const uint32_t w = host ? lds.excl[2] + (hits >> 16) : lds.excl[1] + (hits & 0xffffu);
-                (host ? a.lists.pos[1] : a.lists.pos[0])[w] = j;
-                (host ? a.lists.slot[1] : a.lists.slot[0])[w] = static_cast<int32_t>(host ? ur - n_hbm : ur);
+                if (ur >= n_hbm) {
+                    const uint32_t w = lds.excl[2] + (hits >> 16);
+                    a.lists.pos[1][w] = j;
+                    a.lists.slot[1][w] = static_cast<int32_t>(ur - n_hbm);
+                } else if (!a.hbm_direct) {                  // (else copied without a list)
+                    const uint32_t w = lds.excl[1] + (hits & 0xffffu);
+                    a.lists.pos[0][w] = j;
+                    a.lists.slot[0][w] = static_cast<int32_t>(ur);
+                }
             } else {
                 const int64_t w = static_cast<int64_t>(lds.excl[0]) + before[0][k] + in_class[k];
                 if (w < a.miss_cap) {
@@ -123,6 +130,54 @@ __global__ __launch_bounds__(kScanBlock) void lookup_partition_kernel(PartitionA
     }
 }
 
+// The HBM tier's rows without a list: out[j, :] = table[rank[ids[j]], :] for the IDs whose rank is in the tier.  A group of L
+// lanes owns a row, as in copy_rows (gather_dev.hpp); it reads the ID and its rank by itself, so the copy need not wait for the
+// partition, which makes the other lists in the same launch.
+struct DirectArgs {
+    const int32_t* ids;
+    const int32_t* rank;
+    uint32_t n, n_nodes, n_hbm;
+    const chunk16* table;
+    chunk16* out;
+    int32_t chunks;
+};
+template <int L, int CPL>
+__device__ __forceinline__ void direct_rows(const DirectArgs& a, uint32_t rb, uint32_t nrb) {
+    constexpr int kLanes = L == 0 ? kWave : L, kGroups = kScanBlock / kLanes;
+    const int l = threadIdx.x % kLanes;
+    for (uint32_t j = rb * kGroups + threadIdx.x / kLanes; j < a.n; j += nrb * kGroups) {
+        const uint32_t id = static_cast<uint32_t>(a.ids[j]);
+        if (id >= a.n_nodes) continue;                           // reported by the partition
+        const uint32_t r = static_cast<uint32_t>(a.rank[id]);
+        if (r >= a.n_hbm) continue;
+        const chunk16* src = a.table + static_cast<int64_t>(r) * a.chunks;
+        chunk16* o = a.out + static_cast<int64_t>(j) * a.chunks;
+        if constexpr (L == 0) {
+            for (int c = l; c < a.chunks; c += kWave) store16(o + c, load16(src + c));
+        } else {
+            chunk16 v[CPL == 0 ? 1 : CPL];
+#pragma unroll
+            for (int c = 0; c < CPL; ++c)
+                if (l + c * L < a.chunks) v[c] = load16(src + l + c * L);
+#pragma unroll
+            for (int c = 0; c < CPL; ++c)
+                if (l + c * L < a.chunks) store16(o + l + c * L, v[c]);
+        }
+    }
+}
+
+// Lookup and partition, and beside it, if r_copy has workgroups, the copy of the HBM tier's rows.  As two launches the copy
+// waited 8 to 13 us for lists it does not need: 243 k rows of 2 KB 179.1 -> 174.5 us for the call, 100 k rows of 64 bytes
+// 15.0 -> 12.0.  (One row per group and step: with two 177.0 and 13.4 us, with four 184.2 and 13.7.)
+template <int K, int L, int CPL>
+__global__ __launch_bounds__(kScanBlock) void lookup_copy_kernel(PartitionArgs a, DirectArgs d, Role r_part, Role r_copy) {
+    if (r_part.mine()) {
+        partition_role<K>(a, r_part.rb(), r_part.blocks);
+        return;
+    }
+    direct_rows<L, CPL>(d, r_copy.rb(), r_copy.blocks);
+}
+
 unsigned grid_for(int64_t n, unsigned cap_blocks) {
     int64_t b = (n + kBlock - 1) / kBlock;
     if (b < 1) b = 1;
@@ -140,16 +195,33 @@ hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n
     return hipGetLastError();
 }
 
-hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, Count n, int64_t n_max,
+hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, int64_t n,
                                    const int32_t* rank, int64_t n_nodes, int64_t n_hbm, int64_t n_host,
                                    const TierLists& lists, int32_t* miss_pos, int32_t* miss_id,
                                    int32_t* miss_slot, int64_t miss_cap, int64_t* stats_out, int64_t* learn,
-                                   const ScanState& scan, int32_t* err) {
-    PartitionArgs a{ids, n, rank, n_nodes, n_hbm, n_host, lists, miss_pos, miss_id, miss_slot, miss_cap,
-                    stats_out, learn, scan, err};
-    const dim3 grid(scan_workgroups(n_max, kScanMaxWorkgroups)), block(kScanBlock);
-    if (n_max <= kScanOneItemMax) hipLaunchKernelGGL(lookup_partition_kernel<1>, grid, block, 0, stream, a);
-    else hipLaunchKernelGGL(lookup_partition_kernel<kScanMaxItems>, grid, block, 0, stream, a);
+                                   const ScanState& scan, int32_t* err, const chunk16* copy_table, chunk16* copy_out, int32_t chunks,
+                                   unsigned copy_limit) {
+    const bool copy = copy_table && n > 0 && n_hbm > 0;
+    const PartitionArgs a{ids, Count{nullptr, n}, rank, n_nodes, n_hbm, n_host, lists, miss_pos, miss_id, miss_slot, miss_cap,
+                          stats_out, learn, copy, scan, err};
+    const DirectArgs d{ids, rank, static_cast<uint32_t>(n), static_cast<uint32_t>(n_nodes), static_cast<uint32_t>(n_hbm), copy_table, copy_out, chunks};
+    const Role r_part{0, scan_workgroups(n, kScanMaxWorkgroups)};
+    const dim3 block(kScanBlock);
+    // One row per group and step, and as many workgroups as the list has steps: short-lived workgroups on consecutive rows copy
+    // fastest (gather_dev.hpp).
+#define HELIOS_CALL_(L, CPL, R)                                                                                              \
+    do {                                                                                                                     \
+        constexpr int64_t step = kScanBlock / ((L) == 0 ? kWave : (L));                                                     \
+        int64_t nb = copy ? (n + step - 1) / step : 0;                                                                       \
+        if (copy_limit > 0 && nb > copy_limit) nb = copy_limit;                                                              \
+        if (nb > kMaxRoleBlocks) nb = kMaxRoleBlocks;                                                                        \
+        const Role r_copy{r_part.blocks, static_cast<uint32_t>(nb)};                                                         \
+        const dim3 grid(r_part.blocks + r_copy.blocks);                                                                      \
+        if (n <= kScanOneItemMax) hipLaunchKernelGGL((lookup_copy_kernel<1, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy); \
+        else hipLaunchKernelGGL((lookup_copy_kernel<kScanMaxItems, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy);  \
+    } while (0)
+    HELIOS_COPY_SHAPE_SWITCH(copy ? chunks : 1, false, HELIOS_CALL_);
+#undef HELIOS_CALL_
     return hipGetLastError();
 }
 

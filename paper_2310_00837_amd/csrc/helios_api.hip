@@ -307,10 +307,11 @@ unsigned hbm_role_blocks(const helios_ctx* c, int64_t n_max) {
 }
 
 // The two row copies as kernels of their own over the per-tier lists that a lookup has left behind
-// (helios_gather, and the whole-path call with split copies); n_max bounds the lists.
-int copy_tiers_split(helios_ctx* c, int64_t n_max, void* out) {
+// (helios_gather, which has copied the HBM tier already unless it is timed, and the whole-path call with split copies);
+// n_max bounds the lists.
+int copy_tiers_split(helios_ctx* c, int64_t n_max, void* out, bool hbm_too) {
     const bool events = c->timing > 1 && !c->recording;
-    if (c->n_hbm > 0 && n_max > 0) {
+    if (hbm_too && c->n_hbm > 0 && n_max > 0) {
         const int64_t expected = expected_hbm_rows(c);
         const unsigned nb = copy_role_blocks(c->row_bytes / 16, false, n_max, c->hbm_blocks, expected);
         const GatherArgs a = tier_copy_args(c, 0, nullptr, Count{c->cnt + kCntTier + 0, n_max}, out, take_stamps(c, HELIOS_ROLE_COPY_HBM, 0, nb));
@@ -550,7 +551,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
     const uint32_t clear_slots = rec ? slots_b : c->batch_dirty[next];
     InverseArgs inv{Count{c->cnt + kCntCat, p.cat_max}, nullptr, bt, vars, b->inverse, Stamps{nullptr}};
     if (c->split_copies) {
-        int rc = copy_tiers_split(c, u_max, b->out);
+        int rc = copy_tiers_split(c, u_max, b->out, true);
         if (rc) return rc;
         if (served_max > 0)
             HIP_TRY(c, launch_gather_rows(c->stream, miss_args, served_max, true, true, c->host_blocks, 0, nullptr, nullptr, nullptr));
@@ -1035,10 +1036,14 @@ int helios_gather(helios_ctx* c, const int32_t* ids, int64_t n_ids, void* out, i
     rc = next_epoch(c, &epoch);
     if (rc) return rc;
     const TierLists lists{{c->list_pos[0], c->list_pos[1]}, {c->list_slot[0], c->list_slot[1]}, c->cnt + kCntTier};
-    HIP_TRY(c, launch_lookup_partition(c->stream, ids, Count{nullptr, n_ids}, n_ids, rank_or_any(c), c->g.n_nodes, c->n_hbm, c->n_host,
+    // Timed calls keep the copy in a kernel of its own, whose time it then is.
+    const bool direct = c->timing == 0 && c->n_hbm > 0;
+    HIP_TRY(c, launch_lookup_partition(c->stream, ids, n_ids, rank_or_any(c), c->g.n_nodes, c->n_hbm, c->n_host,
                                        lists, miss_pos, miss_id, miss_slot, miss_cap, reinterpret_cast<int64_t*>(stats), c->learn,
-                                       scan_state(c, epoch, kScanRowsLook), c->err));
-    rc = copy_tiers_split(c, n_ids, out);
+                                       scan_state(c, epoch, kScanRowsLook), c->err,
+                                       direct ? static_cast<const chunk16*>(c->hbm_table) : nullptr, static_cast<chunk16*>(out),
+                                       c->row_bytes / 16, c->hbm_blocks));
+    rc = copy_tiers_split(c, n_ids, out, !direct);
     if (rc) return rc;
     return publish_stamps(c);
 }
