@@ -142,11 +142,8 @@ __device__ __forceinline__ void copy_rows_long(const GatherArgs& a, uint32_t rb,
         }                                                               \
     } while (0)
 
-// Rows per step of the far shape where it shares a kernel with the near one that copies the row with L lanes and CPL
-// pieces per lane.  Two for 512-byte rows too, where the stand-alone copy takes four: four rows cost that kernel 78 registers,
-// and with them a quarter of the waves of the copy from HBM (last launch of a gang of four 34.5 -> 33.0 us, of a
-// batch of 71 k rows of 400 bytes 24.0 -> 22.1 us; a launch bound by the link takes the same 224 us with either).
-constexpr int far_rows_per_step(int L, int CPL) { return L == 0 ? 0 : CPL >= 4 ? 1 : 2; }
+// rows per step of the far shape for a row that the near shape copies with L lanes and CPL pieces per lane
+constexpr int far_rows_per_step(int L, int CPL) { return L == 0 ? 0 : L <= 16 ? 2 : L == 32 ? 4 : CPL >= 4 ? 1 : 2; }
 
 // The copy with the shape chosen on the device: for roles that ride on another kernel (a host-link
 // copy beside a sampling pass), where one instantiation has to serve every row size.  The loop is

@@ -219,9 +219,18 @@ hipError_t launch_finish(hipStream_t stream, const FinishJob* jobs, int n) {
     if (at == 0) return hipSuccess;
     if (chunks == 0) chunks = 1;
     const dim3 grid(at), block(kBlock);
-    // the two copies move rows of the same size; their loops differ in the rows a group takes per step
-#define HELIOS_CALL_(L, CPL, R) \
-    hipLaunchKernelGGL((batch_finish_kernel<L, CPL, R, far_rows_per_step(L, CPL)>), grid, block, 0, stream, g)
+    // The two copies move rows of the same size; their loops differ in the rows a group takes per step.  The four rows of the
+    // host-tier copy of 512-byte rows cost the kernel 78 registers, and with them a quarter of the waves of the copy from HBM, so a
+    // launch without a copy over the link takes an instance with one: last launch of a gang of four 34.5 -> 33.0 us, of a
+    // batch of 71 k rows of 400 bytes 24.0 -> 22.1.  A launch with one is bound by the link and better off with the four
+    // rows (three gangs of the paper's shape in flight 266.7 us with four, 268.3 with two).
+    bool over_link = false;
+    for (int m = 0; m < n; ++m) over_link = over_link || jobs[m].link_blocks > 0 || jobs[m].miss_blocks > 0;
+#define HELIOS_CALL_(L, CPL, R)                                                                                        \
+    do {                                                                                                               \
+        if ((L) == 32 && !over_link) hipLaunchKernelGGL((batch_finish_kernel<L, CPL, R, 1>), grid, block, 0, stream, g); \
+        else hipLaunchKernelGGL((batch_finish_kernel<L, CPL, R, far_rows_per_step(L, CPL)>), grid, block, 0, stream, g); \
+    } while (0)
     HELIOS_COPY_SHAPE_SWITCH(chunks, false, HELIOS_CALL_);
 #undef HELIOS_CALL_
     return hipGetLastError();
