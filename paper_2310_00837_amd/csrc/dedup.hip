@@ -10,16 +10,21 @@
 //   2. compact (compact_dev.hpp): input j is a first occurrence iff its slot's
 //      position is j; the flags are scanned in-workgroup and chained across
 //      workgroups, so the unique list comes out in input order in the same pass.
-//   3. inverse (optional): every input looks up the unique index of its ID's
-//      first occurrence.
+//   3. inverse (optional): the compaction writes it for first occurrences and
+//      marks a repeat with the place of its first occurrence; a last pass over
+//      the list turns the marks into unique indices.  It reads neither slots nor
+//      table, so its launch empties the table for the next call as well.
 // The table has at least twice as many slots as inputs and is empty before the
 // first insert; at the sizes of one mini-batch (at most 32 MB) it stays in L2 /
-// MALL.  It is not staged through LDS.  Measured on the power-law workloads
-// (dedup_probe.py): 15-21 % of a batch's list entries repeat an earlier entry,
-// but only 0.5-4.4 % repeat one within the same 4096 entries (0.1-1.2 % within
-// 1024), because the hubs that repeat are spread over the whole list.  A
-// per-workgroup LDS table would take that little off the global table, while
-// every entry paid an LDS probe and a barrier more.
+// MALL.  The inserts of the sampling kernel are not staged through LDS.
+// Measured on the power-law workloads (dedup_probe.py): 15-21 % of a batch's
+// list entries repeat an earlier entry, but only 0.5-4.4 % repeat one within
+// the same 4096 entries (0.1-1.2 % within 1024), because the hubs that repeat
+// are spread over the whole list.  A per-workgroup LDS table would take that
+// little off the global table, while every entry paid an LDS probe and a
+// barrier more.  A long stand-alone list is another matter: there a workgroup
+// goes through many steps of the list and remembers what it has met
+// (dedup_insert_long_kernel).
 #include "kernels.hpp"
 
 namespace helios {
