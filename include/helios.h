@@ -50,8 +50,9 @@ typedef enum {
     HELIOS_ESTATE = -4,    /* call order: graph or cache not loaded yet              */
     HELIOS_EDATA = -5,     /* a node ID outside [0, N), or an order that is not a
                               permutation (from helios_sync)                         */
-    HELIOS_EINTERNAL = -6  /* a bounded device-side wait ran out (from helios_sync);
-                              the results of that call are invalid                   */
+    HELIOS_EINTERNAL = -6  /* a bounded device-side wait ran out, or a hash table of
+                              the library was full (from helios_sync); the results
+                              of that call are invalid                               */
 } helios_status;
 
 #define HELIOS_MAX_HOPS 8

@@ -47,7 +47,9 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_kernel(const int32_t* __r
             s.slot_of[j] = -1;
             continue;
         }
-        s.slot_of[j] = static_cast<int32_t>(table_insert(s.table, mask, static_cast<uint32_t>(id), static_cast<uint32_t>(j)));
+        const uint32_t slot = table_insert(s.table, mask, static_cast<uint32_t>(id), static_cast<uint32_t>(j));
+        if (slot == kNoSlot) raise(err, kErrInternal);
+        s.slot_of[j] = static_cast<int32_t>(slot);
     }
 }
 
@@ -81,6 +83,7 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_long_kernel(const int32_t
                 slot = static_cast<int32_t>(static_cast<uint32_t>(seen));
             } else {
                 slot = static_cast<int32_t>(table_insert(s.table, mask, static_cast<uint32_t>(id), j));
+                if (slot < 0) raise(err, kErrInternal);
                 recent[(home >> 16) % kRecent] = (static_cast<unsigned long long>(static_cast<uint32_t>(id)) << 32) | static_cast<uint32_t>(slot);
             }
             s.slot_of[j] = slot;

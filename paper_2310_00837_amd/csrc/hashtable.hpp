@@ -3,11 +3,13 @@
 // with a 64-bit atomic minimum (the ID is in the high half, so the minimum orders by position), which
 // leaves in every slot the first position that holds its ID however the threads were scheduled.
 #pragma once
-#include "common.hpp"
+#include <hip/hip_runtime.h>
+#include <stdint.h>
 
 namespace helios {
 
 constexpr unsigned long long kEmptySlot = ~0ull;
+constexpr uint32_t kNoSlot = ~0u;      // (-1 where slots are kept as int32)
 
 __device__ __forceinline__ uint32_t hash_id(uint32_t id, uint32_t mask) {
     uint32_t h = id * 0x9E3779B1u;
@@ -18,21 +20,22 @@ __device__ __forceinline__ uint32_t hash_id(uint32_t id, uint32_t mask) {
 }
 
 // Inserts (id, pos) and returns the slot of the ID.  The table has at least twice as many slots as
-// insertions, so an empty slot is always reached.
+// insertions, so an empty slot is reached; should it be full all the same (words left behind by a caller that
+// broke the rules of the call), kNoSlot comes back once every slot has been looked at.
 __device__ __forceinline__ uint32_t table_insert(unsigned long long* table, uint32_t mask, uint32_t id, uint32_t pos) {
     const unsigned long long mine = (static_cast<unsigned long long>(id) << 32) | pos;
     uint32_t slot = hash_id(id, mask);
-    while (true) {
+    for (uint32_t probes = 0; probes <= mask; ++probes) {
         // try to claim straight away: one round trip when the slot is free (the common case)
         const unsigned long long cur = atomicCAS(table + slot, kEmptySlot, mine);
-        if (cur == kEmptySlot) break;                               // claimed
+        if (cur == kEmptySlot) return slot;                         // claimed
         if (static_cast<uint32_t>(cur >> 32) == id) {
             if (mine < cur) atomicMin(table + slot, mine);
-            break;
+            return slot;
         }
         slot = (slot + 1) & mask;
     }
-    return slot;
+    return kNoSlot;
 }
 
 // A table that a producing kernel inserts its outputs into as it writes them, so that the

@@ -632,7 +632,7 @@ int check_error_word(helios_ctx* c, int32_t* word) {
         word[0] = 0;
         for (uint32_t t = 0; t < kBatchTables; ++t) c->batch_listed[t] = false;      // no list is trusted after an error
         return fail(c, code, code == HELIOS_ECAPACITY ? "an output did not fit its capacity"
-                             : code == HELIOS_EINTERNAL ? "a workgroup gave up waiting (chained scan, or a miss queue that stopped answering)"
+                             : code == HELIOS_EINTERNAL ? "a workgroup gave up waiting (chained scan, or a miss queue that stopped answering), or a hash table was full"
                              : "a node ID outside [0, n_nodes), an order that is not a permutation, or a list entry outside its table");
     }
     return HELIOS_OK;

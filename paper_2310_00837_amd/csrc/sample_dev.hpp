@@ -69,6 +69,13 @@ struct SampleTables {
     int32_t* cat_out;
 };
 
+// The slot of a node ID in a table, as it is kept per position; a full table is reported.
+__device__ __forceinline__ int32_t insert_id(unsigned long long* table, uint32_t mask, uint32_t id, uint32_t pos, int32_t* err) {
+    const uint32_t slot = table_insert(table, mask, id, pos);
+    if (slot == kNoSlot) raise(err, kErrInternal);
+    return static_cast<int32_t>(slot);
+}
+
 // id goes to place `at` of flat, if it is a sample and not a seed, to place cat_at of [seeds | flat_0 | ...], and
 // into the tables of the de-duplications that follow.  (One table after the other: with both first tries in flight together, and
 // with a plain read before each, the passes took 0.5 to 2 us longer.)
@@ -79,11 +86,11 @@ __device__ __forceinline__ void put_id(const SampleTables& t, int64_t n_nodes, i
     if (sample) {
         flat[at] = id;
         if (!node) raise(err, kErrData);                 // (a seed that is no node has been reported by the count pass)
-        if (t.hop.table) t.hop.slot_of[at] = node ? static_cast<int32_t>(table_insert(t.hop.table, t.hop.n_slots - 1, uid, at)) : -1;
+        if (t.hop.table) t.hop.slot_of[at] = node ? insert_id(t.hop.table, t.hop.n_slots - 1, uid, at, err) : -1;
     }
     if (t.batch_table) {
         t.cat_out[cat_at] = id;
-        t.batch_slot_of[cat_at] = node ? static_cast<int32_t>(table_insert(t.batch_table, t.batch_mask, uid, cat_at)) : -1;
+        t.batch_slot_of[cat_at] = node ? insert_id(t.batch_table, t.batch_mask, uid, cat_at, err) : -1;
     }
 }
 
