@@ -7,8 +7,8 @@
 // the three classes are compacted *stably* in one pass: wave ballots and a scan of
 // the waves' totals give the ranks inside a tile and a three-counter
 // chained scan (TileScan in scan.hpp) the ranks across workgroups.  The two hit lists (position, slot)
-// feed the row-copy kernels (helios_gather copies the HBM tier's rows without one, in
-// the same launch); the miss list (position, id, slot) is the request
+// feed the row-copy kernels (where it is quicker, helios_gather copies the HBM tier's rows
+// without one, in the same launch); the miss list (position, id, slot) is the request
 // list of the storage tier and comes out ascending in position.
 #include "kernels.hpp"
 
@@ -168,7 +168,8 @@ __device__ __forceinline__ void direct_rows(const DirectArgs& a, uint32_t rb, ui
 
 // Lookup and partition, and beside it, if r_copy has workgroups, the copy of the HBM tier's rows.  As two launches the copy
 // waited 8 to 13 us for lists it does not need: 243 k rows of 2 KB 179.1 -> 174.5 us for the call, 100 k rows of 64 bytes
-// 15.0 -> 12.0.  (One row per group and step: with two 177.0 and 13.4 us, with four 184.2 and 13.7.)
+// 15.0 -> 12.0.  (One row per group and step: with two 177.0 and 13.4 us, with four 184.2 and 13.7.)  When it does not pay:
+// copy_beside_lookup below.
 template <int K, int L, int CPL>
 __global__ __launch_bounds__(kScanBlock) void lookup_copy_kernel(PartitionArgs a, DirectArgs d, Role r_part, Role r_copy) {
     if (r_part.mine()) {
@@ -195,12 +196,31 @@ hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n
     return hipGetLastError();
 }
 
+// The copy beside the lookup takes a step for every ID, hit or not, while the one by list takes steps for hits only and knows
+// their rows already.  So it pays as long as the steps are few enough to be over while the partition runs, or nearly all of
+// them are hits.  What share of the IDs hits is known once they have been looked up; the tier's share of the nodes, below
+// which a tier of the hottest nodes does not fall, stands in for it.  Measured, us for the call by list / beside the lookup, IDs
+// drawn uniformly, rows of 64 / 512 / 2048 bytes:
+//   1/100 of the nodes in HBM   4096 steps 18.8/22.2 (524 k IDs)  10.5/8.3  9.9/7.9     8192 steps 33.2/43.5  13.6/17.2  11.2/11.8
+//   7 tenths                    4096 steps 31.4/29.6              19.4/16.7 25.7/20.7   8192 steps 58.0/57.1  31.2/33.5  42.7/38.2
+//   9 tenths                    8192 steps 64.0/60.8  36.3/35.2  51.7/46.3    16384 steps -  59.4/60.1  95.0/93.5   32768 -  104/120  177/172
+//   3 tenths                    8192 steps of 2048 / 4096 bytes: 25.3/25.7  40.7/36.8 (7 tenths 42.7/38.2  77.3/70.8)
+//   all                        16384 steps -          64.0/61.9 103.2/101.5   32768 steps - 112.2/123.0 192.6/186.8  65536 -  216/239  384/379
+// With four pieces per lane (rows of 2 to 4 KB) it stops paying earlier: 4096 bytes, all in HBM, 8192 steps 102.3/97.3, 16384 195.3/199.4.
+bool copy_beside_lookup(int64_t n, int64_t n_nodes, int64_t n_hbm, int32_t chunks) {
+    int64_t lanes = 4;
+    while (lanes < chunks && lanes < kWave) lanes <<= 1;
+    const int64_t steps = (n * lanes + kScanBlock - 1) / kScanBlock;
+    if (10 * n_hbm < 9 * n_nodes) return n <= 262144 && steps <= (chunks >= 128 && 10 * n_hbm >= 3 * n_nodes ? 8192 : 4096);
+    if (chunks > 128 && chunks <= 256) return steps <= 8192;
+    return chunks >= 128 || steps <= (n_hbm < n_nodes ? 8192 : 16384);
+}
+
 hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, int64_t n,
                                    const int32_t* rank, int64_t n_nodes, int64_t n_hbm, int64_t n_host,
                                    const TierLists& lists, int32_t* miss_pos, int32_t* miss_id,
                                    int32_t* miss_slot, int64_t miss_cap, int64_t* stats_out, int64_t* learn,
-                                   const ScanState& scan, int32_t* err, const chunk16* copy_table, chunk16* copy_out, int32_t chunks,
-                                   unsigned copy_limit) {
+                                   const ScanState& scan, int32_t* err, const chunk16* copy_table, chunk16* copy_out, int32_t chunks) {
     const bool copy = copy_table && n > 0 && n_hbm > 0;
     const PartitionArgs a{ids, Count{nullptr, n}, rank, n_nodes, n_hbm, n_host, lists, miss_pos, miss_id, miss_slot, miss_cap,
                           stats_out, learn, copy, scan, err};
@@ -213,7 +233,6 @@ hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, int64
     do {                                                                                                                     \
         constexpr int64_t step = kScanBlock / ((L) == 0 ? kWave : (L));                                                     \
         int64_t nb = copy ? (n + step - 1) / step : 0;                                                                       \
-        if (copy_limit > 0 && nb > copy_limit) nb = copy_limit;                                                              \
         if (nb > kMaxRoleBlocks) nb = kMaxRoleBlocks;                                                                        \
         const Role r_copy{r_part.blocks, static_cast<uint32_t>(nb)};                                                         \
         const dim3 grid(r_part.blocks + r_copy.blocks);                                                                      \

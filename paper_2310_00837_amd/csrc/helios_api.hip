@@ -307,8 +307,8 @@ unsigned hbm_role_blocks(const helios_ctx* c, int64_t n_max) {
 }
 
 // The two row copies as kernels of their own over the per-tier lists that a lookup has left behind
-// (helios_gather, which has copied the HBM tier already unless it is timed, and the whole-path call with split copies);
-// n_max bounds the lists.
+// (helios_gather, unless it has copied the HBM tier beside the lookup, and the whole-path call with split copies); n_max
+// bounds the lists.
 int copy_tiers_split(helios_ctx* c, int64_t n_max, void* out, bool hbm_too) {
     const bool events = c->timing > 1 && !c->recording;
     if (hbm_too && c->n_hbm > 0 && n_max > 0) {
@@ -1036,13 +1036,14 @@ int helios_gather(helios_ctx* c, const int32_t* ids, int64_t n_ids, void* out, i
     rc = next_epoch(c, &epoch);
     if (rc) return rc;
     const TierLists lists{{c->list_pos[0], c->list_pos[1]}, {c->list_slot[0], c->list_slot[1]}, c->cnt + kCntTier};
-    // Timed calls keep the copy in a kernel of its own, whose time it then is.
-    const bool direct = c->timing == 0 && c->n_hbm > 0;
+    // Timed calls keep the copy in a kernel of its own, whose time it then is; so do calls with a launch shape of the caller's.
+    const bool direct = c->timing == 0 && c->hbm_blocks == 0 && c->n_hbm > 0 &&
+                        copy_beside_lookup(n_ids, c->g.n_nodes, c->n_hbm, c->row_bytes / 16);
     HIP_TRY(c, launch_lookup_partition(c->stream, ids, n_ids, rank_or_any(c), c->g.n_nodes, c->n_hbm, c->n_host,
                                        lists, miss_pos, miss_id, miss_slot, miss_cap, reinterpret_cast<int64_t*>(stats), c->learn,
                                        scan_state(c, epoch, kScanRowsLook), c->err,
                                        direct ? static_cast<const chunk16*>(c->hbm_table) : nullptr, static_cast<chunk16*>(out),
-                                       c->row_bytes / 16, c->hbm_blocks));
+                                       c->row_bytes / 16));
     rc = copy_tiers_split(c, n_ids, out, !direct);
     if (rc) return rc;
     return publish_stamps(c);

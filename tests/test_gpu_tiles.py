@@ -135,3 +135,49 @@ def test_folded_count_pass_edges(h, helios, oracle, n_seeds):
         print("folded", n_seeds, fanouts, flush=True)
         want = oracle_path(oracle, off, idx, seeds, fanouts, 7, rank, 8_000, 6_000, *tabs, 16)
         assert_same(gpu_path(h, helios, torch.from_numpy(seeds), fanouts, 7, fused=True), want)
+
+
+# steps of the copy beside the lookup (rows / (512 / lanes)) on both sides of every line of its rule, for rows of every copy
+# shape, in lists of one item per thread and of four
+@pytest.mark.parametrize("row_bytes,n,n_hbm,sizes", [
+    (16, 600_000, 6_000, [1, 262_144, 262_145, 524_289]), (48, 300_000, 290_000, [131_073, 1_048_577]), (128, 300_000, 90_000, [262_144, 262_145]),
+    (256, 200_000, 60_000, [131_072, 131_073]), (400, 200_000, 190_000, [131_072, 131_073]), (512, 200_000, 60_000, [65_536, 65_537]),
+    (512, 140_000, 140_000, [262_144, 262_145]), (1024, 100_000, 30_000, [32_768, 32_769]), (1040, 60_000, 57_000, [65_536, 65_537, 131_100]),
+    (2048, 60_000, 54_000, [131_080]),
+    (2048, 60_000, 18_000, [65_536, 65_537]), (2064, 60_000, 60_000, [65_536, 131_100]), (4112, 30_000, 29_000, [8_193, 131_100])])
+def test_gather_by_list_and_beside_the_lookup(h, helios, row_bytes, n, n_hbm, sizes):
+    """helios_gather against torch indexing, exactly; the IDs include some that are no nodes."""
+    gen = torch.Generator(device="cuda").manual_seed(row_bytes + n_hbm)
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    order = torch.randperm(n, device="cuda", generator=gen)
+    rank = torch.empty_like(order)
+    rank[order] = torch.arange(n, device="cuda")
+    table = torch.randint(0, 256, (n_hbm, row_bytes), dtype=torch.uint8, device="cuda", generator=gen)
+    order32 = order.int()
+    h.cache_build(order32, n_hbm, 0, row_bytes, table, None, None)
+    for n_ids in sizes:
+        print("gather", row_bytes, n, n_hbm, n_ids, flush=True)
+        ids = torch.randint(0, n, (n_ids,), device="cuda", generator=gen).int()
+        bad = n_ids > 1000
+        if bad:
+            ids[n_ids // 3], ids[n_ids - 1] = -5, n
+        node = (ids >= 0) & (ids < n)
+        r = rank[ids.clamp(0, n - 1).long()]
+        hit, miss = node & (r < n_hbm), node & (r >= n_hbm)
+        out = torch.full((n_ids, row_bytes), 0xA5, dtype=torch.uint8, device="cuda")
+        lists = [torch.full((n_ids,), -9, dtype=torch.int32, device="cuda") for _ in range(3)]
+        stats = torch.zeros(4, dtype=torch.int64).pin_memory()
+        torch.cuda.synchronize()
+        h.gather(ids, out, *lists, stats)
+        if bad:
+            with pytest.raises(helios.HeliosError) as e:
+                h.sync()
+            assert e.value.code == helios.EDATA
+        else:
+            h.sync()
+        n_miss = int(miss.sum())
+        assert stats.tolist() == [n_ids, int(hit.sum()), 0, n_miss]
+        assert torch.equal(out[hit], table[r[hit]]) and bool((out[~hit] == 0xA5).all())
+        at = miss.nonzero()[:, 0]
+        for got, want in zip(lists, (at, ids[at], r[at] - n_hbm)):
+            assert torch.equal(got[:n_miss].long(), want.long()) and bool((got[n_miss:] == -9).all())
