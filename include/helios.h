@@ -18,6 +18,13 @@
  *    may be device memory or pinned, GPU-mapped host memory (hipHostMalloc);
  *    their contents are valid after helios_sync().
  *  - "host" pointers are ordinary host memory, read during the call only.
+ *  - What a call reads on the device (seeds, ID lists, the graph, the tables)
+ *    is read while its work runs on the stream, not when the call returns: it
+ *    must not change before that work has finished (helios_sync, the wait of a
+ *    plan or gang, or the order of the stream).  A batch whose lists do not fit
+ *    together because something changed under it, or because its buffers
+ *    overlap, has invalid results; if it notices, it reports HELIOS_EDATA.  The
+ *    batches after it are not affected.
  *  - All caller buffers are BORROWED: the library never frees or reallocates
  *    them.  Graph and cache tables must outlive the context (or the next
  *    helios_csr_load / helios_cache_build).
@@ -48,8 +55,9 @@ typedef enum {
     HELIOS_ECAPACITY = -2, /* an output did not fit its capacity (from helios_sync)  */
     HELIOS_EHIP = -3,      /* a HIP runtime call failed                              */
     HELIOS_ESTATE = -4,    /* call order: graph or cache not loaded yet              */
-    HELIOS_EDATA = -5,     /* a node ID outside [0, N), or an order that is not a
-                              permutation (from helios_sync)                         */
+    HELIOS_EDATA = -5,     /* a node ID outside [0, N), an order that is not a
+                              permutation, or an input that changed while a batch
+                              was running (from helios_sync)                         */
     HELIOS_EINTERNAL = -6  /* a bounded device-side wait ran out, or a hash table of
                               the library was full (from helios_sync); the results
                               of that call are invalid                               */

@@ -46,7 +46,7 @@ struct BatchTables {
     int32_t* iof0;               // index_of_first of table t starts at iof0 + t * iof_stride
     uint64_t iof_stride;
     int32_t* slot0;              // slot of every position in the batch's ID list, for table t at slot0 + t * iof_stride
-    int64_t* list_n;             // device [kBatchTables]: length of the ID list that the table's last batch inserted
+    int64_t* list_n;             // device [kBatchTables]: length of the ID list that the table's last batch inserted, or kListIncomplete
     uint32_t n_slots;            // slots in use (power of two)
     uint32_t which;              // the batch's table, unless BatchVars say otherwise
     __device__ __forceinline__ uint32_t pick(const BatchVars* vars) const { return vars ? vars->table % kBatchTables : which; }
@@ -56,7 +56,8 @@ struct BatchTables {
 };
 
 // Empties the table of the context's next batch, of which `slots` slots are in use: the batch before the last used it,
-// and every ID that it inserted has left its slot at its place in the list.  The table is sized for the worst case of a
+// and the slot of every ID that it inserted stands at the ID's place in the list, if the batch's own last launch has found
+// so (check_table_list).  The table is sized for the worst case of a
 // batch, which is several times what batches bring, so emptying the slots of the list is far less memory traffic than
 // emptying the table: 0.25 MB of list against 8 MB per batch with fan-outs 25 and 10.  A scattered 8-byte store takes
 // about 14 ps of the whole chip's time and a streamed one 1.6, so a list longer than an eighth of the table streams.
@@ -66,7 +67,7 @@ __device__ __forceinline__ void empty_next_table(const BatchTables& b, const Bat
     const uint64_t n = static_cast<uint64_t>(b.list_n[t]);
     unsigned long long* table = b.table(t);
     const uint32_t step = nrb * kBlock;
-    if (n * 8 > slots || n > b.iof_stride) {
+    if (n > b.iof_stride || n * 8 > slots) {                   // (kListIncomplete is more than any list)
         for (uint32_t w = rb * kBlock + threadIdx.x; w < slots; w += step) table[w] = ~0ull;
         return;
     }
@@ -75,6 +76,31 @@ __device__ __forceinline__ void empty_next_table(const BatchTables& b, const Bat
         const uint32_t slot = static_cast<uint32_t>(slot_of[j]);
         if (slot < slots) table[slot] = ~0ull;                 // (-1: the entry was no node)
     }
+}
+
+// Whether the list of a batch names every word of its table, by one workgroup once the batch is compacted.  A word counts as a
+// first occurrence at the one place that is its position, and only if the list holds the word's slot there; so if the
+// first occurrences (n_firsts) are as many as the words that the sampling passes have added (the sum of claims), every
+// word is named.  It is not so if what the batch reads has changed while it ran (a caller that refills the seeds too
+// early, buffers that overlap): two samples may then have met at one place, of which the list holds one.  The batch is
+// reported, and its table will be emptied in full whatever is queued behind it.
+constexpr int64_t kListIncomplete = INT64_MAX;
+__device__ __forceinline__ void check_table_list(const BatchTables& b, const BatchVars* vars, const uint32_t* claims, uint32_t n_claims,
+                                                 const int64_t* n_firsts, int32_t* err) {
+    __shared__ uint32_t s_sum[kWavesPerBlock];
+    const uint64_t firsts = static_cast<uint64_t>(*n_firsts);
+    uint32_t sum = 0;
+#pragma unroll 4
+    for (uint32_t w = threadIdx.x; w < n_claims; w += kBlock) sum += claims[w];
+    sum = dpp_sum(sum);
+    if (lane_id() == 0) s_sum[wave_id()] = sum;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    uint64_t words = 0;
+    for (int w = 0; w < kWavesPerBlock; ++w) words += s_sum[w];
+    if (words == firsts) return;
+    b.list_n[b.pick(vars)] = kListIncomplete;
+    raise(err, kErrData);
 }
 
 // What the de-duplication between two hops also computes for the hop that follows: the sample
@@ -183,7 +209,9 @@ __device__ __forceinline__ void compact_tiles(const CompactArgs& a, const DedupS
         for (int k = 0; k < K; ++k) {
             // (both checked: a caller that overwrites its seeds while they are being sampled leaves places of the list
             // unwritten, and what they hold then must not become an address)
-            live[k] = j0 + k * kScanBlock < end && static_cast<uint32_t>(slot[k]) < s.n_slots && static_cast<uint32_t>(id[k]) < a.n_nodes;
+            const bool real = j0 + k * kScanBlock < end && static_cast<uint32_t>(id[k]) < a.n_nodes;
+            live[k] = real && static_cast<uint32_t>(slot[k]) < s.n_slots;
+            if (real && !live[k]) raise(a.err, kErrInternal);      // kNoSlot: its table was full
             const uint32_t at = live[k] ? static_cast<uint32_t>(slot[k]) : 0u, node = live[k] ? static_cast<uint32_t>(id[k]) : 0u;
             word[k] = s.table[at];
             if (MODE == kCompactNextHop) { lo[k] = a.next.offsets[node]; hi[k] = a.next.offsets[node + 1]; }

@@ -17,7 +17,7 @@ constexpr int kCntCat = 32;         // length of [seeds | flat_0 | ...] compacte
 constexpr int kCntUnique = 33;
 constexpr int kCntHopTotal = 34;    // input length of a de-duplication between two hops (a copy of its flat size)
 constexpr int kCntTier = 40;        // [3] list entries to copy from the HBM tier and the host tier, misses to serve
-constexpr int kCntList = 48;        // [kBatchTables] length of the ID list that the table's last batch inserted
+constexpr int kCntList = 48;        // [kBatchTables] length of the ID list that the table's last batch inserted, or kListIncomplete
 constexpr int kCntStage = 64;       // [HELIOS_MAX_HOPS][kStageWords] totals after every stage of a batch's compaction
 constexpr int kNumCounters = kCntStage + HELIOS_MAX_HOPS * kStageWords;
 constexpr uint32_t kVarsRing = 256;   // batch launches that may be queued on a context without a helios_sync
@@ -88,6 +88,8 @@ struct helios_ctx {
     int32_t* err = nullptr;                    // pinned, GPU-mapped int32[2]: the context's device-side error word
     int32_t* err_now = nullptr;                // where kernels being launched report: err, or the word of the plan being recorded
     int64_t* cnt = nullptr;                    // device int64[kNumCounters]
+    uint32_t* claims = nullptr;                // device [HELIOS_MAX_HOPS * kSampleMaxWorkgroups * kWavesPerBlock]: words that every wave of the
+                                               // batch's sampling passes has added to the batch's table
     int64_t* learn = nullptr;                  // pinned int64[4]: {unique, HBM hits, host hits, misses} of the last finished lookup;
                                                // read without waiting, to size the copy grids of the calls that follow
 
@@ -98,7 +100,7 @@ struct helios_ctx {
     int32_t* batch_iof = nullptr;              // kBatchTables x cap_ids: index in `unique` of a first occurrence
     int32_t* batch_slot_of = nullptr;          // kBatchTables x cap_ids: slot of every position in the batch's ID list
     uint32_t batch_dirty[helios::kBatchTables] = {0, 0, 0};   // slots of each batch table that may be non-empty
-    bool batch_listed[helios::kBatchTables] = {false, false, false};   // ... and whether that batch's list names all of them
+    bool batch_listed[helios::kBatchTables] = {false, false, false};   // ... and whether that batch's list is to be gone by (its last launch has checked it)
     uint64_t batch_seq = 0;                    // batches launched so far; batch b uses table b mod kBatchTables
     unsigned long long* hop_table[2] = {nullptr, nullptr};   // de-duplication of one hop's samples, hops alternate
     uint32_t hop_dirty[2] = {0, 0};

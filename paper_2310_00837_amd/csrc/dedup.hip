@@ -40,6 +40,7 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_kernel(const int32_t* __r
     if (j0 < n_in.host) early = ids[j0];
     const int64_t n = n_in.get();
     const uint32_t mask = s.n_slots - 1;
+    uint32_t claims = 0;
     for (int64_t j = j0; j < n; j += static_cast<int64_t>(gridDim.x) * kBlock) {
         const int32_t id = j == j0 ? early : ids[j];
         if (id < 0 || static_cast<int64_t>(id) >= n_nodes) {
@@ -47,9 +48,7 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_kernel(const int32_t* __r
             s.slot_of[j] = -1;
             continue;
         }
-        const uint32_t slot = table_insert(s.table, mask, static_cast<uint32_t>(id), static_cast<uint32_t>(j));
-        if (slot == kNoSlot) raise(err, kErrInternal);
-        s.slot_of[j] = static_cast<int32_t>(slot);
+        s.slot_of[j] = static_cast<int32_t>(table_insert(s.table, mask, static_cast<uint32_t>(id), static_cast<uint32_t>(j), claims));
     }
 }
 
@@ -67,6 +66,7 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_long_kernel(const int32_t
     __shared__ unsigned long long recent[kRecent];        // {id : 32 | slot : 32}
     for (int w = threadIdx.x; w < kRecent; w += kBlock) recent[w] = kEmptySlot;
     const uint32_t n = static_cast<uint32_t>(n_in.get()), mask = s.n_slots - 1, step = gridDim.x * kBlock;
+    uint32_t claims = 0;
     __syncthreads();
     for (uint32_t j0 = blockIdx.x * kBlock; j0 < n; j0 += step) {
         const uint32_t j = j0 + threadIdx.x;
@@ -82,8 +82,7 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_long_kernel(const int32_t
             } else if (static_cast<uint32_t>(seen >> 32) == static_cast<uint32_t>(id)) {
                 slot = static_cast<int32_t>(static_cast<uint32_t>(seen));
             } else {
-                slot = static_cast<int32_t>(table_insert(s.table, mask, static_cast<uint32_t>(id), j));
-                if (slot < 0) raise(err, kErrInternal);
+                slot = static_cast<int32_t>(table_insert(s.table, mask, static_cast<uint32_t>(id), j, claims));
                 recent[(home >> 16) % kRecent] = (static_cast<unsigned long long>(static_cast<uint32_t>(id)) << 32) | static_cast<uint32_t>(slot);
             }
             s.slot_of[j] = slot;

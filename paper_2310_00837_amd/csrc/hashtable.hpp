@@ -19,22 +19,27 @@ __device__ __forceinline__ uint32_t hash_id(uint32_t id, uint32_t mask) {
     return h & mask;
 }
 
-// Inserts (id, pos) and returns the slot of the ID.  The table has at least twice as many slots as
-// insertions, so an empty slot is reached; should it be full all the same (words left behind by a caller that
-// broke the rules of the call), kNoSlot comes back once every slot has been looked at.
-__device__ __forceinline__ uint32_t table_insert(unsigned long long* table, uint32_t mask, uint32_t id, uint32_t pos) {
+// Inserts (id, pos) and returns the slot of the ID; claims grows by one if the ID was not there yet.  The table has at
+// least twice as many slots as insertions, so an empty slot is reached; should it be full all the same (words left behind
+// by a caller that broke the rules of the call), kNoSlot comes back once every slot has been looked at, which the compaction
+// reports (here it would be one more branch in every insert, 0.3 us of a sampling pass).
+__device__ __forceinline__ uint32_t table_insert(unsigned long long* table, uint32_t mask, uint32_t id, uint32_t pos, uint32_t& claims) {
     const unsigned long long mine = (static_cast<unsigned long long>(id) << 32) | pos;
-    uint32_t slot = hash_id(id, mask);
-    for (uint32_t probes = 0; probes <= mask; ++probes) {
+    const uint32_t home = hash_id(id, mask);
+    uint32_t slot = home;
+    do {
         // try to claim straight away: one round trip when the slot is free (the common case)
         const unsigned long long cur = atomicCAS(table + slot, kEmptySlot, mine);
-        if (cur == kEmptySlot) return slot;                         // claimed
+        if (cur == kEmptySlot) {                                    // claimed
+            claims += 1;
+            return slot;
+        }
         if (static_cast<uint32_t>(cur >> 32) == id) {
             if (mine < cur) atomicMin(table + slot, mine);
             return slot;
         }
         slot = (slot + 1) & mask;
-    }
+    } while (slot != home);
     return kNoSlot;
 }
 

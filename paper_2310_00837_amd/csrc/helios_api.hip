@@ -25,7 +25,7 @@ struct helios_plan {
     helios_hop_out hops[HELIOS_MAX_HOPS] = {};
     const int64_t* sizes = nullptr;    // the caller's size array (device-accessible, nullable)
     uint32_t slots = 0;                // slots of the batch table the recording uses
-    uint32_t clear_slots = 0;          // not 0: its last launch empties the next batch's table
+    uint32_t clear_slots = 0;          // not 0: its last launch checks its list and empties the next batch's table
     helios_missq* missq = nullptr;     // the queue attached when the batch was recorded
     hipEvent_t done = nullptr;         // recorded behind every launch
     uint64_t launch_seq = 0;           // the context's launch count at this plan's last launch
@@ -243,7 +243,7 @@ int clean_for_call(helios_ctx* c, int batch_table_needed /* -1: none */) {
     return HELIOS_OK;
 }
 
-// empties a batch table now, unless the list of its last batch names everything in it
+// empties a batch table now, unless that can be left to the list of its last batch
 int clean_unlisted(helios_ctx* c, uint32_t t) {
     if (c->batch_dirty[t] && !c->batch_listed[t]) {
         HIP_TRY(c, launch_clear(c->stream, ClearJob{batch_table(c, t), c->batch_dirty[t]}));
@@ -393,7 +393,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
         if (b) {
             c->batch_dirty[which] = slots_b;
             c->batch_listed[which] = false;
-            // the last launch empties the next batch's table by its list, if that names everything in it
+            // the last launch empties the next batch's table by its list, if that has been checked
             if (!c->split_copies) rc = clean_unlisted(c, next);
             if (rc) return rc;
         }
@@ -423,6 +423,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
                                          scan_state(c, epoch, kScanRowsHop), err));
     }
     Count nf{nullptr, n_seeds};
+    uint32_t n_claims = 0;
     for (int h = 0; h < n_hops; ++h) {
         const bool last = h + 1 == n_hops;
         // ---- sampling pass of hop h; beside it the host-tier copy of the stage that the compaction before it listed
@@ -455,6 +456,10 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             ha.size_out = sizes;
         }
         const unsigned hop_blocks = sample_role_blocks(fanouts[h], p.frontier_max[h], c->link_share);
+        if (b) {
+            ha.claims = c->claims + n_claims;
+            n_claims += hop_blocks * kWavesPerBlock;
+        }
         ha.stamps = take_stamps(c, HELIOS_ROLE_SAMPLE, h, hop_blocks);
         GatherArgs link{};
         unsigned link_blocks = 0;
@@ -582,8 +587,10 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             inv_blocks = inv_blocks < 1 ? 1 : inv_blocks;
             inv.stamps = take_stamps(c, HELIOS_ROLE_INVERSE, stage, inv_blocks);
         }
-        if (clear_slots) clear_blocks = std::min(256u, (clear_slots + kBlock * 16 - 1) / (kBlock * 16));      // (a recording learns on the device how much there is)
-        int rf = emit_finish(c, FinishJob{hbm, hbm_blocks, link, link_blocks, miss, miss_blocks, inv, inv_blocks, clear_slots, clear_blocks, bt, vars});
+        clear_blocks = 1;
+        if (clear_slots) clear_blocks += std::min(256u, (clear_slots + kBlock * 16 - 1) / (kBlock * 16));      // (a recording learns on the device how much there is)
+        int rf = emit_finish(c, FinishJob{hbm, hbm_blocks, link, link_blocks, miss, miss_blocks, inv, inv_blocks, clear_slots, clear_blocks,
+                                          c->claims, n_claims, stage_words(c, stage) + kStageUnique, err, bt, vars});
         if (rf) return rf;
     }
     int rc = c->defer ? HELIOS_OK : publish_stamps(c);      // (a gang publishes after its launches have gone out)
@@ -591,7 +598,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
     if (!rec) {
         for (int t = 0; t < 2; ++t) c->hop_dirty[t] = 0;
         c->batch_dirty[next] = 0;
-        c->batch_listed[which] = true;
+        c->batch_listed[which] = !c->split_copies;        // (the launch that checks the list is left out then)
         c->batch_seq += 1;
         c->blocks_ready = true;
         c->last_table = which;
@@ -630,10 +637,10 @@ int check_error_word(helios_ctx* c, int32_t* word) {
     const int code = *reinterpret_cast<volatile int32_t*>(word);
     if (code != 0) {
         word[0] = 0;
-        for (uint32_t t = 0; t < kBatchTables; ++t) c->batch_listed[t] = false;      // no list is trusted after an error
         return fail(c, code, code == HELIOS_ECAPACITY ? "an output did not fit its capacity"
                              : code == HELIOS_EINTERNAL ? "a workgroup gave up waiting (chained scan, or a miss queue that stopped answering), or a hash table was full"
-                             : "a node ID outside [0, n_nodes), an order that is not a permutation, or a list entry outside its table");
+                             : "a node ID outside [0, n_nodes), an order that is not a permutation, a list entry outside its table, or an input "
+                               "that changed while a batch was running");
     }
     return HELIOS_OK;
 }
@@ -734,7 +741,7 @@ int plan_prelaunch(helios_plan* pl, const int32_t* seeds, uint64_t rng_seed, uin
     }
     // The recording assumes that its own batch table and both hop tables are empty, and its last launch empties the next
     // batch's table, however much of that is in use.  What that leaves out is emptied here, by launches of their own (rare: a
-    // recording with split copies, or a call that failed half way).
+    // recording with split copies or the batches after it, or a call that failed half way).
     const uint32_t which = static_cast<uint32_t>(c->batch_seq % kBatchTables), next = (which + 1) % kBatchTables;
     int rc = clean_for_call(c, static_cast<int>(which));
     if (rc) return rc;
@@ -763,7 +770,7 @@ void plan_postlaunch(helios_plan* pl, uint32_t io_round) {
     c->epoch += pl->n_scans;
     if (pl->missq) missq_commit_round(pl->missq, io_round);
     c->batch_dirty[which] = pl->slots;
-    c->batch_listed[which] = true;
+    c->batch_listed[which] = pl->clear_slots != 0;
     c->batch_dirty[next] = 0;
     c->batch_seq += 1;
     pl->batch_seq = c->batch_seq;
@@ -828,6 +835,7 @@ int helios_create(helios_ctx** out, int device, void* hip_stream) {
               hipEventCreate(&c->t_host[0]) == hipSuccess && hipEventCreate(&c->t_host[1]) == hipSuccess &&
               hipHostMalloc(reinterpret_cast<void**>(&c->err), 64, hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
               hipMalloc(&c->cnt, sizeof(int64_t) * kNumCounters) == hipSuccess &&
+              hipMalloc(&c->claims, sizeof(uint32_t) * HELIOS_MAX_HOPS * kSampleMaxWorkgroups * kWavesPerBlock) == hipSuccess &&
               hipMalloc(&c->vars, sizeof(BatchVars)) == hipSuccess &&
               hipMalloc(&c->scan_ticket, 128) == hipSuccess &&
               hipMalloc(&c->batches_run, 64) == hipSuccess &&
@@ -836,7 +844,7 @@ int helios_create(helios_ctx** out, int device, void* hip_stream) {
               hipHostMalloc(reinterpret_cast<void**>(&c->learn), 64, hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
               hipHostMalloc(reinterpret_cast<void**>(&c->clock_host), sizeof(uint64_t) * 2 * kMaxStampRoles,
                             hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess;
-    ok = ok && c->err && c->cnt && c->vars && c->scan_ticket && c->batches_run && c->vars_ring && c->learn && c->clock_host;
+    ok = ok && c->err && c->cnt && c->claims && c->vars && c->scan_ticket && c->batches_run && c->vars_ring && c->learn && c->clock_host;
     ok = ok && noalloc_init(device, c->stream) == HELIOS_OK;      // this device's static scratch (helios_dedup_noalloc)
     if (ok) {
         int khz = 0;
@@ -866,6 +874,7 @@ int helios_destroy(helios_ctx* c) {
     free_scratch(c);
     (void)hipFree(c->rank);
     (void)hipFree(c->cnt);
+    (void)hipFree(c->claims);
     (void)hipFree(c->vars);
     (void)hipFree(c->scan_ticket);
     (void)hipFree(c->batches_run);

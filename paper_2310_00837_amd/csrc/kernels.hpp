@@ -64,7 +64,11 @@ struct FinishJob {
     InverseArgs inv;
     unsigned inv_blocks;
     uint32_t clear_slots;
-    unsigned clear_blocks;
+    unsigned clear_blocks;       // its first workgroup checks the batch's own list (check_table_list), the others empty
+    const uint32_t* claims;
+    uint32_t n_claims;
+    const int64_t* n_firsts;
+    int32_t* err;
     BatchTables bt;
     const BatchVars* vars;
 };
@@ -92,7 +96,10 @@ struct FinishMember {
     InverseArgs inv;
     BatchTables bt;
     const BatchVars* vars;
-    uint32_t clear_slots;
+    const uint32_t* claims;
+    const int64_t* n_firsts;
+    int32_t* err;
+    uint32_t clear_slots, n_claims;
     Role r_hbm, r_link, r_miss, r_inv, r_clear;
 };
 struct FinishGang {

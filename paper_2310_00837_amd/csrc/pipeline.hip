@@ -86,7 +86,8 @@ __global__ __launch_bounds__(kBlock) void batch_finish_kernel(FinishGang g) {
             return;
         }
         if (a.r_clear.mine()) {
-            empty_next_table(a.bt, a.vars, a.clear_slots, a.r_clear.rb(), a.r_clear.blocks);
+            if (a.r_clear.rb() == 0) check_table_list(a.bt, a.vars, a.claims, a.n_claims, a.n_firsts, a.err);
+            else empty_next_table(a.bt, a.vars, a.clear_slots, a.r_clear.rb() - 1, a.r_clear.blocks - 1);
             return;
         }
     }
@@ -191,6 +192,10 @@ hipError_t launch_finish(hipStream_t stream, const FinishJob* jobs, int n) {
         a.link = jobs[m].link;
         a.inv = jobs[m].inv;
         a.clear_slots = jobs[m].clear_slots;
+        a.claims = jobs[m].claims;
+        a.n_claims = jobs[m].n_claims;
+        a.n_firsts = jobs[m].n_firsts;
+        a.err = jobs[m].err;
         a.bt = jobs[m].bt;
         a.vars = jobs[m].vars;
         a.miss = jobs[m].miss;

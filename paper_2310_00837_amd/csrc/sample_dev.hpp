@@ -49,6 +49,7 @@ struct HopArgs {
     BatchTables batch;            // de-duplication of [seeds | flat_0 | ...]; position = place in that list
     int32_t* cat_out;             // with batch: receives [seeds | flat_0 | ...]
     int64_t n_seeds;
+    uint32_t* claims;             // with batch: [workgroups of the role][waves] words that each wave has added to the batch's table
     const int64_t* cat_begin;     // device word: where flat_hop starts in that list (nullable: hop 0, right after the seeds)
     int32_t* err;
     // folded count pass (hop 0): the outputs that frontier_count_kernel would write
@@ -67,30 +68,24 @@ struct SampleTables {
     uint32_t batch_mask;
     int32_t* batch_slot_of;
     int32_t* cat_out;
+    uint32_t hop_claims, batch_claims;   // words this lane has added to the two tables
 };
-
-// The slot of a node ID in a table, as it is kept per position; a full table is reported.
-__device__ __forceinline__ int32_t insert_id(unsigned long long* table, uint32_t mask, uint32_t id, uint32_t pos, int32_t* err) {
-    const uint32_t slot = table_insert(table, mask, id, pos);
-    if (slot == kNoSlot) raise(err, kErrInternal);
-    return static_cast<int32_t>(slot);
-}
 
 // id goes to place `at` of flat, if it is a sample and not a seed, to place cat_at of [seeds | flat_0 | ...], and
 // into the tables of the de-duplications that follow.  (One table after the other: with both first tries in flight together, and
 // with a plain read before each, the passes took 0.5 to 2 us longer.)
-__device__ __forceinline__ void put_id(const SampleTables& t, int64_t n_nodes, int32_t* err, int32_t* flat, int32_t id, bool sample, uint32_t at,
+__device__ __forceinline__ void put_id(SampleTables& t, int64_t n_nodes, int32_t* err, int32_t* flat, int32_t id, bool sample, uint32_t at,
                                        uint32_t cat_at) {
     const uint32_t uid = static_cast<uint32_t>(id);
     const bool node = uid < static_cast<uint32_t>(n_nodes);
     if (sample) {
         flat[at] = id;
         if (!node) raise(err, kErrData);                 // (a seed that is no node has been reported by the count pass)
-        if (t.hop.table) t.hop.slot_of[at] = node ? insert_id(t.hop.table, t.hop.n_slots - 1, uid, at, err) : -1;
+        if (t.hop.table) t.hop.slot_of[at] = node ? static_cast<int32_t>(table_insert(t.hop.table, t.hop.n_slots - 1, uid, at, t.hop_claims)) : -1;
     }
     if (t.batch_table) {
         t.cat_out[cat_at] = id;
-        t.batch_slot_of[cat_at] = node ? insert_id(t.batch_table, t.batch_mask, uid, cat_at, err) : -1;
+        t.batch_slot_of[cat_at] = node ? static_cast<int32_t>(table_insert(t.batch_table, t.batch_mask, uid, cat_at, t.batch_claims)) : -1;
     }
 }
 
@@ -194,6 +189,9 @@ __device__ __forceinline__ void sample_role(const HopArgs& a, uint32_t rb, uint3
 
     stamp_start(a.stamps, rb);
     const int f = a.fanout;
+    // (fetched with the other arguments: at the end of the role, where it is used, the read would be waited for by itself, 0.3 us)
+    uint32_t* claims = a.claims;
+    asm volatile("" : "+s"(claims));
     const int group = threadIdx.x / G;
     const int l = threadIdx.x % G;
     const uint32_t step = nrb * kGroups;
@@ -232,7 +230,7 @@ __device__ __forceinline__ void sample_role(const HopArgs& a, uint32_t rb, uint3
     }
     for (uint32_t w = rb * kBlock + threadIdx.x; a.clear.table && w < a.clear.n_slots; w += nrb * kBlock)
         a.clear.table[w] = kEmptySlot;                    // side job of the role (at its end it would be a tail of its own)
-    SampleTables tabs{a.hop_table, nullptr, 0, nullptr, a.cat_out};
+    SampleTables tabs{a.hop_table, nullptr, 0, nullptr, a.cat_out, 0, 0};
     if (a.batch.table0) {
         tabs.batch_table = a.batch.table(which);
         tabs.batch_mask = a.batch.n_slots - 1;
@@ -329,6 +327,10 @@ __device__ __forceinline__ void sample_role(const HopArgs& a, uint32_t rb, uint3
                 }
             }
         }
+    }
+    if (claims) {
+        const uint32_t sum = dpp_sum(tabs.batch_claims);
+        if (lane_id() == 0) claims[rb * kWavesPerBlock + wave_id()] = sum;
     }
     stamp_end(a.stamps, rb, nrb);
 }

@@ -92,3 +92,65 @@ def test_tables_over_many_batches(helios, oracle, max_deg, fanouts):
         for hb, (fr, ip, fl) in zip(bufs[0], want["hops"]):
             assert np.array_equal(hb.frontier[:fr.size].cpu().numpy(), fr) and np.array_equal(hb.flat[:fl.size].cpu().numpy(), fl)
     h.close()
+
+
+@pytest.mark.parametrize("recorded", [False, True])
+def test_batches_queued_behind_one_whose_buffers_overlap(helios, oracle, recorded):
+    """A batch whose size array lies inside one of its own indptr buffers: two nodes get places that others have, so what the list
+    remembers of the samples that meet there is one of them.  It is reported, and the batches queued behind it, the third of
+    which uses its table again, come out as if it had not been."""
+    rng = np.random.default_rng(5)
+    n, b, fanouts = 400, 64, [25, 10]
+    off = np.arange(n + 1, dtype=np.int64) * 3
+    idx = rng.integers(0, n, 3 * n).astype(np.int32)
+    feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
+    order = torch.from_numpy(rng.permutation(n).astype(np.int32))
+    by_rank = to_bytes(feats)[order.numpy()]
+    tabs = [np.ascontiguousarray(x) for x in (by_rank[:100], by_rank[100:200], by_rank[200:])]
+    rank = oracle.rank_build(order.numpy())
+    h = helios.Helios(0, stream=torch.cuda.Stream())
+    off_d, idx_d = torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda()
+    torch.cuda.synchronize()
+    h.csr_load(off_d, idx_d)
+    cache = GpuCache(h, feats, order, 100, 100)  # noqa: F841
+    h.reserve(b * (1 + fanouts[0] * (1 + fanouts[1])))
+
+    def buffers(overlap):
+        hops = helios.alloc_hops(b, fanouts, h.device)
+        cap = b + sum(hb.flat.numel() for hb in hops)
+        ints = [torch.empty(cap, dtype=torch.int32, device=h.device) for _ in range(5)]
+        sizes = hops[1].indptr[3:7] if overlap else torch.zeros(4, dtype=torch.int64).pin_memory()
+        return (hops, sizes, ints[0], ints[1], torch.zeros(1, dtype=torch.int64).pin_memory(),
+                torch.full((cap, 16), 0xA5, dtype=torch.uint8, device=h.device), ints[2], ints[3], ints[4],
+                torch.zeros(4, dtype=torch.int64).pin_memory())
+
+    sets = [buffers(k == 0) for k in range(5)]
+    torch.cuda.synchronize()
+    plans = [h.plan_create(b, fanouts, *s) for s in sets] if recorded else []
+    for k in range(6):
+        print("overlap", recorded, k, flush=True)
+        seeds = [rng.integers(0, n, b).astype(np.int32) for _ in sets]
+        seeds_d = [torch.from_numpy(s).cuda() for s in seeds]
+        torch.cuda.synchronize()
+        for m in range(5):
+            if recorded:
+                plans[m].launch(seeds_d[m], 10 * k + m)
+            else:
+                h.prepare_batch(seeds_d[m], fanouts, 10 * k + m, *sets[m])
+        with pytest.raises(helios.HeliosError) as e:
+            plans[0].wait() if recorded else h.sync()
+        assert e.value.code == helios.EDATA
+        h.sync()
+        for m in range(1, 5):
+            hops, sizes, unique, inverse, nu, out, mp, mi, ms, stats = sets[m]
+            want = oracle_path(oracle, off, idx, seeds[m], fanouts, 10 * k + m, rank, 100, 100, *tabs, 16)
+            u, nm = int(nu[0]), int(stats[3])
+            assert u == want["unique"].size, (k, m)
+            got = dict(hops=[(hb.frontier[:fr.size].cpu().numpy(), hb.indptr[:ip.size].cpu().numpy(), hb.flat[:fl.size].cpu().numpy())
+                             for hb, (fr, ip, fl) in zip(hops, want["hops"])],
+                       unique=unique[:u].cpu().numpy(), inverse=inverse[:want["inverse"].size].cpu().numpy(), stats=stats.numpy().copy(),
+                       miss_pos=mp[:nm].cpu().numpy(), miss_id=mi[:nm].cpu().numpy(), miss_slot=ms[:nm].cpu().numpy())
+            assert_same(got, want)
+            hit = np.setdiff1d(np.arange(u), got["miss_pos"])
+            assert np.array_equal(out[:u].cpu().numpy()[hit], want["out_before_miss"][hit])
+    h.close()

@@ -30,21 +30,22 @@ int main() {
     for (uint32_t slots : {1u, 8u, 1024u}) {
         std::vector<unsigned long long> t(slots, kEmptySlot);
         std::vector<bool> taken(slots, false);
+        uint32_t claims = 0;
         for (uint32_t k = 0; k < slots; ++k) {                 // fills up: every ID gets a slot of its own
-            const uint32_t s = table_insert(t.data(), slots - 1, 1000 + 7 * k, 2 * k + 5);
-            if (s >= slots || taken[s]) return 1;
+            const uint32_t s = table_insert(t.data(), slots - 1, 1000 + 7 * k, 2 * k + 5, claims);
+            if (s >= slots || taken[s] || claims != k + 1) return 1;
             taken[s] = true;
         }
         for (uint32_t k = 0; k < slots; ++k) {                 // IDs that are there: the same slot, the smaller position
-            const uint32_t a = table_insert(t.data(), slots - 1, 1000 + 7 * k, 2 * k + 9);
+            const uint32_t a = table_insert(t.data(), slots - 1, 1000 + 7 * k, 2 * k + 9, claims);
             if (t[a] != ((1000ull + 7 * k) << 32 | (2 * k + 5))) return 2;
-            if (table_insert(t.data(), slots - 1, 1000 + 7 * k, 2 * k + 1) != a) return 3;
+            if (table_insert(t.data(), slots - 1, 1000 + 7 * k, 2 * k + 1, claims) != a) return 3;
             if (t[a] != ((1000ull + 7 * k) << 32 | (2 * k + 1))) return 4;
         }
         const std::vector<unsigned long long> before = t;
         for (uint32_t k = 0; k < 64; ++k)                      // no room and not there: ends, and changes nothing
-            if (table_insert(t.data(), slots - 1, 5 + k, 0) < slots) return 5;
-        if (t != before) return 6;
+            if (table_insert(t.data(), slots - 1, 5 + k, 0, claims) < slots) return 5;
+        if (t != before || claims != slots) return 6;
     }
     std::puts("ok");
     return 0;
