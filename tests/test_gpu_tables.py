@@ -100,9 +100,9 @@ def test_batches_queued_behind_one_whose_buffers_overlap(helios, oracle, recorde
     remembers of the samples that meet there is one of them.  It is reported, and the batches queued behind it, the third of
     which uses its table again, come out as if it had not been."""
     rng = np.random.default_rng(5)
-    n, b, fanouts = 400, 64, [25, 10]
-    off = np.arange(n + 1, dtype=np.int64) * 3
-    idx = rng.integers(0, n, 3 * n).astype(np.int32)
+    n, b, fanouts = 2000, 8, [30, 20]               # short lists against the worst case: emptied by list
+    off = np.arange(n + 1, dtype=np.int64) * 12
+    idx = rng.integers(0, n, 12 * n).astype(np.int32)
     feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
     order = torch.from_numpy(rng.permutation(n).astype(np.int32))
     by_rank = to_bytes(feats)[order.numpy()]
