@@ -400,7 +400,8 @@ __device__ __forceinline__ void inverse_role(const InverseArgs& a, uint32_t rb, 
     const uint32_t n = static_cast<uint32_t>(a.n.get());
     for (uint32_t j = rb * kBlock + threadIdx.x; j < n; j += nrb * kBlock) {
         const int32_t mark = a.inverse[j];
-        if (mark < -1) a.inverse[j] = iof[static_cast<uint32_t>(-2 - mark)];
+        const uint32_t of = static_cast<uint32_t>(-2 - mark);
+        if (mark < -1 && of < n) a.inverse[j] = iof[of];       // (the marks stand in a buffer of the caller's: never an address unchecked)
     }
     stamp_end(a.stamps, rb, nrb);
 }

@@ -154,3 +154,40 @@ def test_batches_queued_behind_one_whose_buffers_overlap(helios, oracle, recorde
             hit = np.setdiff1d(np.arange(u), got["miss_pos"])
             assert np.array_equal(out[:u].cpu().numpy()[hit], want["out_before_miss"][hit])
     h.close()
+
+
+def test_inverse_marks_are_range_checked(helios, oracle):
+    """The compaction leaves marks in the caller's inverse buffer, which the last launch looks up.  Here the samples of hop 1
+    are written over them (overlapping buffers), and some are no node IDs but large negative numbers."""
+    rng = np.random.default_rng(8)
+    n, b, fanouts = 400, 64, [25, 10]
+    off = np.arange(n + 1, dtype=np.int64) * 3
+    idx = rng.integers(0, n, 3 * n).astype(np.int32)
+    bad = idx.copy()
+    bad[::7] = rng.integers(-(1 << 31), -(1 << 30), bad[::7].size)
+    feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
+    h = helios.Helios(0)
+    off_d, idx_d, bad_d = torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda(), torch.from_numpy(bad).cuda()
+    seeds = rng.integers(0, n, b).astype(np.int32)
+    order = torch.from_numpy(rng.permutation(n).astype(np.int32))
+    h.csr_load(off_d, bad_d)
+    cache = GpuCache(h, feats, order, n, 0)
+    hops = helios.alloc_hops(b, fanouts, h.device)
+    cap = b + sum(hb.flat.numel() for hb in hops)
+    unique, inverse, mp, mi, ms = [torch.empty(cap, dtype=torch.int32, device=h.device) for _ in range(5)]
+    hops[1] = helios.HopBuffers(hops[1].frontier, hops[1].indptr, inverse[:b * 25 * 10])
+    sizes, nu, stats = [torch.zeros(k, dtype=torch.int64).pin_memory() for k in (4, 1, 4)]
+    h.prepare_batch(torch.from_numpy(seeds).cuda(), fanouts, 3, hops, sizes, unique, inverse, nu,
+                    torch.empty((cap, 16), dtype=torch.uint8, device=h.device), mp, mi, ms, stats)
+    with pytest.raises(helios.HeliosError) as e:
+        h.sync()
+    assert e.value.code == helios.EDATA
+    first_stage = b + int(sizes[1])
+    assert (inverse[:first_stage] < -(1 << 30)).any()              # what is no mark of the list stays as it is
+    h.csr_load(off_d, idx_d)
+    h.cache_build(cache.order, n, 0, 16, cache.hbm, cache.host, cache.standin)
+    tab = np.ascontiguousarray(to_bytes(feats)[order.numpy()])
+    want = oracle_path(oracle, off, idx, seeds, fanouts, 3, oracle.rank_build(order.numpy()), n, 0, tab, tab[:0], tab[:0], 16)
+    for _ in range(4):
+        assert_same(gpu_path(h, helios, torch.from_numpy(seeds), fanouts, 3, fused=True), want)
+    h.close()
