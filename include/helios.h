@@ -158,7 +158,8 @@ int helios_dedup(helios_ctx *ctx, const int32_t *ids, int64_t n_ids,
  * HELIOS_DEDUP_NOALLOC_MAX_IDS IDs per call, more is HELIOS_EINVAL.  All
  * contexts of a GPU share that array, which every call leaves empty, so
  * calls that overlap on one GPU (different streams or host threads) race: the
- * caller serialises them.  It does not touch the scratch of helios_dedup or of
+ * caller serialises them (calls that do overlap have invalid results and may
+ * report HELIOS_EINTERNAL; calls after them are not affected).  It does not touch the scratch of helios_dedup or of
  * the batch calls. */
 #define HELIOS_DEDUP_NOALLOC_MAX_IDS 262144
 int helios_dedup_noalloc(helios_ctx *ctx, const int32_t *ids, int64_t n_ids,

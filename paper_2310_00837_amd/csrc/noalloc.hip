@@ -6,11 +6,14 @@
 // of it lives in one file-scope device array of fixed size, so the call enqueues kernels and
 // nothing else.  The array exists once per GPU the library runs on.  It is filled once, when the
 // first context of that GPU is created, and every call leaves it as it found it: its last launch
-// empties the table and zeroes the scan status beside the inverse map, which reads neither (a
-// launch of its own at the start of every call took 3 us).  So a captured call can be replayed.
+// empties the table and zeroes the scan status and the ticket beside the inverse map, which reads none
+// of them (a launch of its own at the start of every call took 3 us).  So a captured call can be replayed.
 // Only a call that a launch error has cut short leaves it in use; the next call fills it first.
 // All calls on one GPU share the array, so calls that overlap on one GPU (two streams, two
-// contexts, two host threads) race; callers serialise them.
+// contexts, two host threads) race; callers serialise them.  Calls that did overlap spoil each other and no
+// later one: whatever a call has put into the array, also while another was at work in it, its own last launch,
+// which is behind its own writes on its stream, takes out again (the ticket above all: two scans that draw
+// from it at the same time may both miss the draw that puts it back to zero).
 #include "context.hpp"
 #include "noalloc.hpp"
 
@@ -33,6 +36,11 @@ constexpr size_t kOffStatus = kOffIndexOfFirst + sizeof(int32_t) * kMaxIds;
 constexpr size_t kStatusBytes = (sizeof(unsigned long long) * 3 * kStride + 255) / 256 * 256;
 constexpr size_t kOffSmall = kOffStatus + kStatusBytes;     // ticket (uint32) at +0, counters (int64[2]) at +64
 constexpr size_t kSmallBytes = 256;
+constexpr size_t kOffTicket = kOffSmall, kOffCounters = kOffSmall + 64;
+// what the last launch of a call zeroes: the scan status and the ticket right behind it (not the counters, which it reads)
+constexpr uint32_t kEndZeroWords = static_cast<uint32_t>((kOffTicket + sizeof(unsigned long long) - kOffStatus) / sizeof(unsigned long long));
+static_assert(kOffStatus + kEndZeroWords * sizeof(unsigned long long) >= kOffTicket + sizeof(uint32_t) &&
+              kOffStatus + kEndZeroWords * sizeof(unsigned long long) <= kOffCounters, "the ticket is in, the counters are not");
 constexpr size_t kScratchBytes = kOffSmall + kSmallBytes;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -103,8 +111,8 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     DeviceGuard guard(c->device);
     unsigned long long* table = reinterpret_cast<unsigned long long*>(base + kOffTable);
     unsigned long long* status = reinterpret_cast<unsigned long long*>(base + kOffStatus);
-    uint32_t* ticket = reinterpret_cast<uint32_t*>(base + kOffSmall);
-    int64_t* counters = reinterpret_cast<int64_t*>(base + kOffSmall + 64);
+    uint32_t* ticket = reinterpret_cast<uint32_t*>(base + kOffTicket);
+    int64_t* counters = reinterpret_cast<int64_t*>(base + kOffCounters);
     // a table no larger than this call needs: cheaper to empty, and it stays in cache
     uint32_t slots = 1024;
     while (static_cast<int64_t>(slots) < 2 * n_ids) slots <<= 1;
@@ -134,8 +142,7 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
     const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse,
                           Stamps{nullptr}};
-    HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{table, slots}, status,
-                                static_cast<uint32_t>(kStatusBytes / sizeof(unsigned long long))));
+    HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{table, slots}, status, kEndZeroWords));
     std::lock_guard<std::mutex> lk(g_mu);
     g_in_use[c->device] = false;
     return HELIOS_OK;

@@ -91,3 +91,58 @@ def test_noalloc_dedup_on_two_contexts_and_errors(helios):
     finally:
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("n", [300, 1_025, 41_237, 262_144])
+def test_captured_noalloc_dedup_replayed_between_direct_calls(helios, oracle, n):
+    """The call in a HIP graph, replayed with new IDs, with direct calls of other lengths (one tile, several, the longest) on the
+    shared array in between: every result is the oracle's."""
+    n_nodes = 50_000
+    rng = np.random.default_rng(n)
+    stream = torch.cuda.Stream()
+    h = helios.Helios(0, stream=stream)
+    try:
+        off, idx = torch.zeros(n_nodes + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+        h.csr_load(off, idx)
+
+        def buffers(m):
+            return (torch.zeros(m, dtype=torch.int32, device="cuda"), torch.full((m,), -3, dtype=torch.int32, device="cuda"),
+                    torch.full((m,), -3, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int64).pin_memory())
+
+        def fill(t):
+            ids = (n_nodes * rng.random(t.numel()) ** 2).astype(np.int32)
+            t.copy_(torch.from_numpy(ids))
+            torch.cuda.synchronize()
+            return ids
+
+        def check(ids, bufs):
+            want_u, want_inv = oracle.dedup(n_nodes, ids)
+            u = int(bufs[3][0])
+            assert u == want_u.size and np.array_equal(bufs[1][:u].cpu().numpy(), want_u) and np.array_equal(bufs[2].cpu().numpy(), want_inv)
+
+        captured, graph = buffers(n), torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            h.dedup_noalloc(*captured)
+        for k, m in enumerate([700, 5_000, 262_144, 1, 70_001]):
+            print("captured noalloc dedup", n, k, m, flush=True)
+            ids = fill(captured[0])
+            with torch.cuda.stream(stream):
+                graph.replay()
+            h.sync()
+            check(ids, captured)
+            direct = buffers(m)
+            ids = fill(direct[0])
+            h.dedup_noalloc(*direct)
+            h.sync()
+            check(ids, direct)
+            if k == 2:                                             # twice in a row without a wait
+                ids = fill(captured[0])
+                with torch.cuda.stream(stream):
+                    graph.replay()
+                    graph.replay()
+                h.sync()
+                check(ids, captured)
+    finally:
+        h.close()
