@@ -143,7 +143,11 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse,
                           Stamps{nullptr}};
     HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{table, slots}, status, kEndZeroWords));
+    // A call that is being captured has not run.  It found the array clean, and leaves it so, unless the filling was
+    // captured with it: then the next call still has to do that.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (fill && hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
     std::lock_guard<std::mutex> lk(g_mu);
-    g_in_use[c->device] = false;
+    g_in_use[c->device] = capture != hipStreamCaptureStatusNone;
     return HELIOS_OK;
 }
