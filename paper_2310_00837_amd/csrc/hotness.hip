@@ -374,6 +374,14 @@ hipError_t launch_hotness_order(hipStream_t stream, const int32_t* counts, int64
     a.tile_bits = reinterpret_cast<uint32_t*>(p + at.bits);
     a.varying = reinterpret_cast<uint32_t*>(p + at.varying);
     a.err = err;
+    // With one pass or three the first one already writes to `order`.  If that is (part of) the counters' own memory, the pass
+    // reads a copy, in the buffer that no pass writes before the second has begun.
+    const uintptr_t c0 = reinterpret_cast<uintptr_t>(counts), o0 = reinterpret_cast<uintptr_t>(order), len = sizeof(int32_t) * a.n;
+    if (c0 < o0 + len && o0 < c0 + len) {
+        const hipError_t e = hipMemcpyAsync(a.keys[1], counts, len, hipMemcpyDefault, stream);
+        if (e != hipSuccess) return e;
+        a.counts = a.keys[1];
+    }
     const dim3 tiles(a.n_tiles < kSortMaxWorkgroups ? a.n_tiles : kSortMaxWorkgroups), block(kSortBlock);
     for (int pass = 0; pass < kSortPasses; ++pass) {
         a.pass = pass;

@@ -27,3 +27,21 @@ def test_hotness_order_at_tile_edges(oracle, kind):
             assert np.array_equal(order.cpu().numpy(), oracle.hotness_order(counts))
             assert np.array_equal(t.cpu().numpy(), counts)
     h.close()
+
+
+@pytest.mark.parametrize("kind", ["zero", "low", "low and middle", "high", "all"])          # one pass, two, three
+@pytest.mark.parametrize("n", [8193, 8192 * 600 + 5])               # the second: more tiles than workgroups
+def test_hotness_order_in_the_memory_of_the_counts(oracle, kind, n):
+    from paper_2310_00837_amd import helios
+    h = helios.Helios(0)
+    counts = KINDS[kind](np.random.default_rng(n), n).astype(np.int32)
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    want = oracle.hotness_order(counts)
+    for shift in (0, 1000, -1000):                                 # order = counts, behind it, before it
+        t = torch.zeros(n + 2000, dtype=torch.int32, device="cuda")
+        t[1000:1000 + n] = torch.from_numpy(counts)
+        order = t[1000 + shift:1000 + shift + n]
+        h.hotness_order(t[1000:1000 + n], order)
+        h.sync()
+        assert np.array_equal(order.cpu().numpy(), want)
+    h.close()
