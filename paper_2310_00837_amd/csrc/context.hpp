@@ -160,6 +160,12 @@ inline int fail(helios_ctx* c, int code, const char* fmt, ...) {
         if (e_ != hipSuccess) return fail((c), HELIOS_EHIP, "%s: %s", #expr, hipGetErrorString(e_)); \
     } while (0)
 
+// whether two buffers of a call share memory
+inline bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
+    return a_bytes > 0 && b_bytes > 0 && a0 < b0 + static_cast<uintptr_t>(b_bytes) && b0 < a0 + static_cast<uintptr_t>(a_bytes);
+}
+
 // keeps the caller's current device
 struct DeviceGuard {
     int prev = -1;

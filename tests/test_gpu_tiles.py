@@ -181,3 +181,31 @@ def test_gather_by_list_and_beside_the_lookup(h, helios, row_bytes, n, n_hbm, si
         at = miss.nonzero()[:, 0]
         for got, want in zip(lists, (at, ids[at], r[at] - n_hbm)):
             assert torch.equal(got[:n_miss].long(), want.long()) and bool((got[n_miss:] == -9).all())
+
+
+@pytest.mark.parametrize("which", [0, 1, 2])
+@pytest.mark.parametrize("n_ids", [3_000, 130_000])
+def test_gather_with_its_miss_list_in_the_memory_of_the_ids(h, which, n_ids):
+    rng = np.random.default_rng(n_ids + which)
+    n, n_hbm = 40_000, 20_000
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    order = torch.from_numpy(rng.permutation(n).astype(np.int32)).cuda()
+    rank = torch.empty(n, dtype=torch.int64, device="cuda")
+    rank[order.long()] = torch.arange(n, device="cuda")
+    table = torch.from_numpy(rng.integers(0, 256, (n_hbm, 512)).astype(np.uint8)).cuda()
+    h.cache_build(order, n_hbm, 0, 512, table, None, None)
+    for _ in range(5):
+        ids = torch.from_numpy(rng.integers(0, n, n_ids).astype(np.int32)).cuda()
+        r = rank[ids.long()]
+        at = (r >= n_hbm).nonzero()[:, 0]
+        want = (at, ids[at].long(), r[at] - n_hbm)
+        lists = [torch.empty(n_ids, dtype=torch.int32, device="cuda") for _ in range(3)]
+        lists[which] = ids
+        out, stats = torch.full((n_ids, 512), 0xA5, dtype=torch.uint8, device="cuda"), torch.zeros(4, dtype=torch.int64).pin_memory()
+        torch.cuda.synchronize()
+        h.gather(ids, out, *lists, stats)
+        h.sync()
+        assert stats.tolist() == [n_ids, n_ids - at.numel(), 0, at.numel()]
+        assert torch.equal(out[r < n_hbm], table[r[r < n_hbm]]) and bool((out[at] == 0xA5).all())
+        for got, w in zip(lists, want):
+            assert torch.equal(got[:at.numel()].long(), w)
