@@ -665,7 +665,19 @@ int make_blocks_impl(helios_ctx* c, uint32_t table, uint32_t slots, int64_t n_se
         n_max[2 * h] = frontier_max[h];
         n_max[2 * h + 1] = flat_max[h];
     }
-    HIP_TRY(c, launch_local_ids(c->stream, lists, n_max, 2 * n_hops, s, err));
+    // The lists go out together, unless a buffer that one is written to is read or written by another (the buffers of a hop that is
+    // done may be given as those of the next one): such a list starts a launch of its own.
+    const int n_lists = 2 * n_hops;
+    const auto bytes = [&](int k) { return static_cast<int64_t>(sizeof(int32_t)) * n_max[k]; };
+    for (int first = 0, k = 1; first < n_lists; ++k) {
+        bool apart = k == n_lists;
+        for (int q = first; q < k && !apart; ++q)
+            apart = overlap(lists[k].out, bytes(k), lists[q].ids, bytes(q)) || overlap(lists[k].out, bytes(k), lists[q].out, bytes(q)) ||
+                    overlap(lists[k].ids, bytes(k), lists[q].out, bytes(q));
+        if (!apart) continue;
+        HIP_TRY(c, launch_local_ids(c->stream, lists + first, n_max + first, k - first, s, err));
+        first = k;
+    }
     return HELIOS_OK;
 }
 

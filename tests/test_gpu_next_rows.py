@@ -235,3 +235,36 @@ def test_topology_in_pinned_host_memory(helios, oracle, small, cfg):
                            n_host, *tabs, sp.row_bytes)
         assert_same(gpu_path(h, helios, seeds, sp.fanouts, rs, fused=True), want)
     h.close()
+
+
+def test_blocks_in_the_buffers_of_hops_that_are_done(helios, oracle):
+    """Every block buffer is one of the batch's own: the rows of a hop where the samples of the hop before were, the columns in the
+    place of the samples themselves (the lists are relabelled in order: frontier 0, samples 0, frontier 1, ...)."""
+    rng = np.random.default_rng(31)
+    n, b, fanouts = 300_000, 1500, [12, 8, 3]
+    off = np.arange(n + 1, dtype=np.int64) * 12
+    idx = rng.integers(0, n, 12 * n).astype(np.int32)
+    h = helios.Helios(0)
+    h.csr_load(torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda())
+    feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
+    cache = GpuCache(h, feats, torch.from_numpy(rng.permutation(n).astype(np.int32)), n, 0)  # noqa: F841
+    hops = helios.alloc_hops(b, fanouts, h.device)
+    cap = b + sum(hb.flat.numel() for hb in hops)
+    unique, inverse, mp, mi, ms = [torch.empty(cap, dtype=torch.int32, device=h.device) for _ in range(5)]
+    out = torch.empty((cap, 16), dtype=torch.uint8, device=h.device)
+    sizes, nu, stats = [torch.zeros(k, dtype=torch.int64).pin_memory() for k in (6, 1, 4)]
+    for k in range(4):
+        h.prepare_batch(torch.from_numpy(rng.integers(0, n, b).astype(np.int32)).cuda(), fanouts, k, hops, sizes, unique, inverse, nu, out,
+                        mp, mi, ms, stats)
+        h.sync()
+        uniq = unique[:int(nu[0])].cpu().numpy()
+        want = [[oracle.local_ids(n, uniq, t[:int(sizes[2 * q + w])].cpu().numpy()) for w, t in enumerate((hb.frontier, hb.flat))]
+                for q, hb in enumerate(hops)]
+        rows = [hops[0].frontier, hops[0].flat, hops[1].flat]
+        cols = [torch.empty_like(hops[0].flat), torch.empty_like(hops[1].flat), hops[2].flat]
+        h.make_blocks(hops, rows, cols)
+        h.sync()
+        for q in range(3):
+            assert np.array_equal(rows[q][:want[q][0].size].cpu().numpy(), want[q][0]), (k, q)
+            assert np.array_equal(cols[q][:want[q][1].size].cpu().numpy(), want[q][1]), (k, q)
+    h.close()
