@@ -387,18 +387,30 @@ struct InverseArgs {
     BatchTables batch;
     const BatchVars* vars;
     int32_t* inverse;
+    bool by_table;               // batch only: the compaction has not been given `inverse`, so there are no marks
     Stamps stamps;
 };
 
 // Third pass (optional): inverse[j] = index in unique of input j.  The compaction has written it for every first occurrence,
 // which most inputs are, and marked the repeats, so the pass streams over the list and looks up only those; it needs
 // neither the slots nor the table (which may be emptied beside it).  1.1 M IDs, a third of them distinct: 11.3 us with the emptying of a 33 MB table beside it, 17.6 + 10.0 us when
-// every input looked its slot, its table word and its index up.
+// every input looked its slot, its table word and its index up (by_table: the way for an inverse in the memory of a buffer that
+// the batch still needs after its compactions have begun).
 __device__ __forceinline__ void inverse_role(const InverseArgs& a, uint32_t rb, uint32_t nrb) {
     stamp_start(a.stamps, rb);
-    const int32_t* iof = a.batch.table0 ? a.batch.iof(a.batch.pick(a.vars)) : a.iof;
+    const uint32_t which = a.batch.pick(a.vars);
+    const int32_t* iof = a.batch.table0 ? a.batch.iof(which) : a.iof;
     const uint32_t n = static_cast<uint32_t>(a.n.get());
-    for (uint32_t j = rb * kBlock + threadIdx.x; j < n; j += nrb * kBlock) {
+    if (a.by_table) {
+        const unsigned long long* table = a.batch.table(which);
+        const int32_t* slot_of = a.batch.slot_of(which);
+        for (uint32_t j = rb * kBlock + threadIdx.x; j < n; j += nrb * kBlock) {
+            const uint32_t slot = static_cast<uint32_t>(slot_of[j]);
+            const uint32_t of = slot < a.batch.n_slots ? static_cast<uint32_t>(table[slot]) : ~0u;
+            a.inverse[j] = of < n ? iof[of] : -1;
+        }
+    }
+    for (uint32_t j = rb * kBlock + threadIdx.x; j < n && !a.by_table; j += nrb * kBlock) {
         const int32_t mark = a.inverse[j];
         const uint32_t of = static_cast<uint32_t>(-2 - mark);
         if (mark < -1 && of < n) a.inverse[j] = iof[of];       // (the marks stand in a buffer of the caller's: never an address unchecked)

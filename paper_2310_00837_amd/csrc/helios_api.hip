@@ -411,6 +411,16 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
         c->scan_stride < scan_row_stride(p.ids_max))
         return fail(c, HELIOS_EINTERNAL, "launch bounds of the batch do not fit the scratch");
 
+    // The compactions write the inverse map while later hops are still to come.  If it shares memory with a buffer of the hops,
+    // the last launch works it out by itself.
+    bool inverse_late = false;
+    for (int h = 0; b && b->inverse && h < n_hops; ++h) {
+        const int64_t bytes = static_cast<int64_t>(sizeof(int32_t)) * p.cat_max;
+        inverse_late = inverse_late || overlap(b->inverse, bytes, hops[h].frontier, static_cast<int64_t>(sizeof(int32_t)) * hops[h].frontier_cap) ||
+                       overlap(b->inverse, bytes, hops[h].indptr, static_cast<int64_t>(sizeof(int64_t)) * (hops[h].frontier_cap + 1)) ||
+                       overlap(b->inverse, bytes, hops[h].flat, static_cast<int64_t>(sizeof(int32_t)) * hops[h].flat_cap);
+    }
+
     const bool fold = n_seeds <= kFoldMaxSeeds;
     if (c->defer && (!fold || !b || c->split_copies || c->missq || c->timing > 1))
         return fail(c, HELIOS_EINTERNAL, "this call cannot be part of a gang");       // (refused earlier, with the reason)
@@ -514,7 +524,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             look.vars = vars;
             look.unique = b->unique;
             look.unique_cap = b->unique_cap;
-            look.inverse = b->inverse;
+            look.inverse = inverse_late ? nullptr : b->inverse;
             look.prev = h > 0 ? stage_words(c, h - 1) : nullptr;
             look.mine = stage_words(c, h);
             look.last = last;
@@ -554,7 +564,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
         if (rc) return rc;
     }
     const uint32_t clear_slots = rec ? slots_b : c->batch_dirty[next];
-    InverseArgs inv{Count{c->cnt + kCntCat, p.cat_max}, nullptr, bt, vars, b->inverse, Stamps{nullptr}};
+    InverseArgs inv{Count{c->cnt + kCntCat, p.cat_max}, nullptr, bt, vars, b->inverse, inverse_late, Stamps{nullptr}};
     if (c->split_copies) {
         int rc = copy_tiers_split(c, u_max, b->out, true);
         if (rc) return rc;
@@ -1035,7 +1045,7 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     a.err = c->err;
     HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
     // the call leaves its table as it found it: empty
-    const InverseArgs inv{Count{c->cnt + kCntCat, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse,
+    const InverseArgs inv{Count{c->cnt + kCntCat, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse, false,
                           Stamps{nullptr}};
     HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{s.table, s.n_slots}, nullptr, 0));
     c->batch_dirty[which] = 0;

@@ -140,7 +140,7 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     a.scan = scan;
     a.err = c->err;
     HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
-    const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse,
+    const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse, false,
                           Stamps{nullptr}};
     HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{table, slots}, status, kEndZeroWords));
     // A call that is being captured has not run.  It found the array clean, and leaves it so, unless the filling was

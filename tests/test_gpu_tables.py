@@ -156,38 +156,58 @@ def test_batches_queued_behind_one_whose_buffers_overlap(helios, oracle, recorde
     h.close()
 
 
-def test_inverse_marks_are_range_checked(helios, oracle):
-    """The compaction leaves marks in the caller's inverse buffer, which the last launch looks up.  Here the samples of hop 1
-    are written over them (overlapping buffers), and some are no node IDs but large negative numbers."""
+@pytest.mark.parametrize("where", ["frontier 0", "frontier 1", "indptr 1", "flat 0", "flat 1"])
+@pytest.mark.parametrize("recorded", [False, True])
+@pytest.mark.parametrize("bad", [False, True])
+def test_inverse_in_the_memory_of_a_hop(helios, oracle, where, recorded, bad):
+    """The inverse map over a buffer of the hops, whose content is lost in its favour; with a graph that holds no node IDs in
+    places, what stands there meanwhile may be any number."""
     rng = np.random.default_rng(8)
-    n, b, fanouts = 400, 64, [25, 10]
-    off = np.arange(n + 1, dtype=np.int64) * 3
-    idx = rng.integers(0, n, 3 * n).astype(np.int32)
-    bad = idx.copy()
-    bad[::7] = rng.integers(-(1 << 31), -(1 << 30), bad[::7].size)
+    n, b, fanouts = 9_000, 600, [7, 4]
+    off = np.arange(n + 1, dtype=np.int64) * 6
+    idx = rng.integers(0, n, 6 * n).astype(np.int32)
     feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
-    h = helios.Helios(0)
-    off_d, idx_d, bad_d = torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda(), torch.from_numpy(bad).cuda()
-    seeds = rng.integers(0, n, b).astype(np.int32)
     order = torch.from_numpy(rng.permutation(n).astype(np.int32))
-    h.csr_load(off_d, bad_d)
-    cache = GpuCache(h, feats, order, n, 0)
+    seeds = rng.integers(0, n, b).astype(np.int32)
+    h = helios.Helios(0, stream=torch.cuda.Stream())
+    graph = idx.copy()
+    if bad:
+        graph[::7] = rng.integers(-(1 << 31), -(1 << 30), graph[::7].size)
+    off_d, graph_d, seeds_d = torch.from_numpy(off).cuda(), torch.from_numpy(graph).cuda(), torch.from_numpy(seeds).cuda()
+    torch.cuda.synchronize()
+    h.csr_load(off_d, graph_d)
+    cache = GpuCache(h, feats, order, n, 0)  # noqa: F841
     hops = helios.alloc_hops(b, fanouts, h.device)
     cap = b + sum(hb.flat.numel() for hb in hops)
     unique, inverse, mp, mi, ms = [torch.empty(cap, dtype=torch.int32, device=h.device) for _ in range(5)]
-    hops[1] = helios.HopBuffers(hops[1].frontier, hops[1].indptr, inverse[:b * 25 * 10])
-    sizes, nu, stats = [torch.zeros(k, dtype=torch.int64).pin_memory() for k in (4, 1, 4)]
-    h.prepare_batch(torch.from_numpy(seeds).cuda(), fanouts, 3, hops, sizes, unique, inverse, nu,
-                    torch.empty((cap, 16), dtype=torch.uint8, device=h.device), mp, mi, ms, stats)
-    with pytest.raises(helios.HeliosError) as e:
-        h.sync()
-    assert e.value.code == helios.EDATA
-    first_stage = b + int(sizes[1])
-    assert (inverse[:first_stage] < -(1 << 30)).any()              # what is no mark of the list stays as it is
-    h.csr_load(off_d, idx_d)
-    h.cache_build(cache.order, n, 0, 16, cache.hbm, cache.host, cache.standin)
+    what, k = where.split()[0], int(where[-1])
+    fr, ip, fl = hops[k].frontier, hops[k].indptr, hops[k].flat
+    if what == "frontier":
+        fr = inverse[:fr.numel()]
+    elif what == "indptr":
+        ip = inverse[:2 * ip.numel()].view(torch.int64)
+    else:
+        fl = inverse[:fl.numel()]
+    hops[k] = helios.HopBuffers(fr, ip, fl)
+    sizes, nu, stats = [torch.zeros(m, dtype=torch.int64).pin_memory() for m in (4, 1, 4)]
+    bufs = (hops, sizes, unique, inverse, nu, torch.empty((cap, 16), dtype=torch.uint8, device=h.device), mp, mi, ms, stats)
+    torch.cuda.synchronize()
+    plan = h.plan_create(b, fanouts, *bufs) if recorded else None
     tab = np.ascontiguousarray(to_bytes(feats)[order.numpy()])
-    want = oracle_path(oracle, off, idx, seeds, fanouts, 3, oracle.rank_build(order.numpy()), n, 0, tab, tab[:0], tab[:0], 16)
-    for _ in range(4):
-        assert_same(gpu_path(h, helios, torch.from_numpy(seeds), fanouts, 3, fused=True), want)
+    for rs in range(3):
+        print("inverse over", where, recorded, bad, rs, flush=True)
+        if recorded:
+            plan.launch(seeds_d, rs)
+        else:
+            h.prepare_batch(seeds_d, fanouts, rs, *bufs)
+        if bad:
+            with pytest.raises(helios.HeliosError) as e:
+                h.sync()
+            assert e.value.code == helios.EDATA
+            continue
+        h.sync()
+        want = oracle_path(oracle, off, idx, seeds, fanouts, rs, oracle.rank_build(order.numpy()), n, 0, tab, tab[:0], tab[:0], 16)
+        assert int(nu[0]) == want["unique"].size and np.array_equal(unique[:int(nu[0])].cpu().numpy(), want["unique"])
+        assert np.array_equal(inverse[:want["inverse"].size].cpu().numpy(), want["inverse"])
+        assert [int(x) for x in sizes] == [x for hop in want["hops"] for x in (hop[0].size, hop[2].size)]
     h.close()
