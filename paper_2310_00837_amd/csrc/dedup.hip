@@ -73,7 +73,9 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_long_kernel(const int32_t
         const int32_t id = j < n ? ids[j] : -1;
         const bool node = id >= 0 && static_cast<int64_t>(id) < n_nodes;
         const uint32_t home = hash_id(static_cast<uint32_t>(id), 0xffffffffu);
-        const unsigned long long seen = recent[(home >> 16) % kRecent];
+        // (a cell is read and written whole: two IDs that meet in one must not leave the slot of the other behind)
+        unsigned long long* cell = recent + (home >> 16) % kRecent;
+        const unsigned long long seen = __hip_atomic_load(cell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __syncthreads();
         if (j < n) {
             int32_t slot = -1;
@@ -83,7 +85,8 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_long_kernel(const int32_t
                 slot = static_cast<int32_t>(static_cast<uint32_t>(seen));
             } else {
                 slot = static_cast<int32_t>(table_insert(s.table, mask, static_cast<uint32_t>(id), j, claims));
-                recent[(home >> 16) % kRecent] = (static_cast<unsigned long long>(static_cast<uint32_t>(id)) << 32) | static_cast<uint32_t>(slot);
+                const unsigned long long met = (static_cast<unsigned long long>(static_cast<uint32_t>(id)) << 32) | static_cast<uint32_t>(slot);
+                __hip_atomic_store(cell, met, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             s.slot_of[j] = slot;
         }
