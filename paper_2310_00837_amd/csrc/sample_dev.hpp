@@ -189,9 +189,6 @@ __device__ __forceinline__ void sample_role(const HopArgs& a, uint32_t rb, uint3
 
     stamp_start(a.stamps, rb);
     const int f = a.fanout;
-    // (fetched with the other arguments: at the end of the role, where it is used, the read would be waited for by itself, 0.3 us)
-    uint32_t* claims = a.claims;
-    asm volatile("" : "+s"(claims));
     const int group = threadIdx.x / G;
     const int l = threadIdx.x % G;
     const uint32_t step = nrb * kGroups;
@@ -236,6 +233,9 @@ __device__ __forceinline__ void sample_role(const HopArgs& a, uint32_t rb, uint3
         tabs.batch_mask = a.batch.n_slots - 1;
         tabs.batch_slot_of = a.batch.slot_of(which);
     }
+    // (fetched with the arguments above: at the end of the role, where it is used, the read would be waited for by itself, 0.3 us)
+    uint32_t* claims = a.claims;
+    asm volatile("" : "+s"(claims));
     const bool seeds_too = tabs.batch_table && a.hop == 0;   // the frontier of hop 0 is the head of the batch's list
     if (f > 0 || seeds_too) {
         for (bool again = false; i < n; i += step, again = true) {
