@@ -239,7 +239,7 @@ hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, int64
         if (n <= kScanOneItemMax) hipLaunchKernelGGL((lookup_copy_kernel<1, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy); \
         else hipLaunchKernelGGL((lookup_copy_kernel<kScanMaxItems, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy);  \
     } while (0)
-    HELIOS_COPY_SHAPE_SWITCH(copy ? chunks : 1, false, HELIOS_CALL_);
+    HELIOS_COPY_NEAR_SHAPE(copy ? chunks : 1, HELIOS_CALL_);
 #undef HELIOS_CALL_
     return hipGetLastError();
 }

@@ -53,14 +53,16 @@ hipError_t launch_calibration_copy(hipStream_t stream, const void* src, void* ds
 hipError_t launch_gather_rows(hipStream_t stream, const GatherArgs& a, int64_t n_max, bool far_source, bool standin,
                               unsigned blocks_limit, int64_t expected, hipEvent_t t_start, hipEvent_t t_stop, unsigned* blocks_out) {
     const unsigned nb = copy_role_blocks(a.chunks, far_source, n_max, blocks_limit, expected);
-#define HELIOS_CALL_(L, CPL, R)                                                          \
-    do {                                                                                 \
-        if (!far_source) launch_one<L, CPL, R, 0>(stream, a, nb, t_start, t_stop);       \
-        else if (!standin) launch_one<L, CPL, R, 1>(stream, a, nb, t_start, t_stop);     \
-        else launch_one<L, CPL, R, 2>(stream, a, nb, t_start, t_stop);                   \
-    } while (0)
-    HELIOS_COPY_SHAPE_SWITCH(a.chunks, far_source, HELIOS_CALL_);
+    if (!far_source) {
+#define HELIOS_CALL_(L, CPL, R) (launch_one<L, CPL, R, 0>(stream, a, nb, t_start, t_stop))
+        HELIOS_COPY_NEAR_SHAPE(a.chunks, HELIOS_CALL_);
 #undef HELIOS_CALL_
+    } else {
+#define HELIOS_CALL_(L, CPL, R) \
+    (standin ? launch_one<L, CPL, R, 2>(stream, a, nb, t_start, t_stop) : launch_one<L, CPL, R, 1>(stream, a, nb, t_start, t_stop))
+        HELIOS_COPY_FAR_SHAPE(a.chunks, HELIOS_CALL_);
+#undef HELIOS_CALL_
+    }
     if (blocks_out) *blocks_out = nb;
     return hipGetLastError();
 }

@@ -118,28 +118,34 @@ __device__ __forceinline__ void copy_rows_long(const GatherArgs& a, uint32_t rb,
 // The shape of the copy loop for a row of `chunks` pieces.  far: the source is behind the host link (more
 // rows in flight per group, because each takes microseconds); an HBM source is quickest with one row per group
 // and step (measured: 2 KB rows 166 / 170 us with one / two rows, 512 B rows 181 / 186 / 193 us with 1 / 2 / 4).
-#define HELIOS_COPY_SHAPE_SWITCH(chunks, far, CALL)                     \
+#define HELIOS_COPY_FAR_SHAPE(chunks, CALL)                             \
     do {                                                                \
         const int c_ = (chunks);                                        \
-        if (far) {                                                      \
-            if (c_ <= 4) { CALL(4, 1, 2); }                             \
-            else if (c_ <= 8) { CALL(8, 1, 2); }                        \
-            else if (c_ <= 16) { CALL(16, 1, 2); }                      \
-            else if (c_ <= 32) { CALL(32, 1, 4); }                      \
-            else if (c_ <= 64) { CALL(64, 1, 2); }                      \
-            else if (c_ <= 128) { CALL(64, 2, 2); }                     \
-            else if (c_ <= 256) { CALL(64, 4, 1); }                     \
-            else { CALL(0, 0, 0); }                                     \
-        } else {                                                        \
-            if (c_ <= 4) { CALL(4, 1, 1); }                             \
-            else if (c_ <= 8) { CALL(8, 1, 1); }                        \
-            else if (c_ <= 16) { CALL(16, 1, 1); }                      \
-            else if (c_ <= 32) { CALL(32, 1, 1); }                      \
-            else if (c_ <= 64) { CALL(64, 1, 1); }                      \
-            else if (c_ <= 128) { CALL(64, 2, 1); }                     \
-            else if (c_ <= 256) { CALL(64, 4, 1); }                     \
-            else { CALL(0, 0, 0); }                                     \
-        }                                                               \
+        if (c_ <= 4) { CALL(4, 1, 2); }                                 \
+        else if (c_ <= 8) { CALL(8, 1, 2); }                            \
+        else if (c_ <= 16) { CALL(16, 1, 2); }                          \
+        else if (c_ <= 32) { CALL(32, 1, 4); }                          \
+        else if (c_ <= 64) { CALL(64, 1, 2); }                          \
+        else if (c_ <= 128) { CALL(64, 2, 2); }                         \
+        else if (c_ <= 256) { CALL(64, 4, 1); }                         \
+        else { CALL(0, 0, 0); }                                         \
+    } while (0)
+#define HELIOS_COPY_NEAR_SHAPE(chunks, CALL)                            \
+    do {                                                                \
+        const int c_ = (chunks);                                        \
+        if (c_ <= 4) { CALL(4, 1, 1); }                                 \
+        else if (c_ <= 8) { CALL(8, 1, 1); }                            \
+        else if (c_ <= 16) { CALL(16, 1, 1); }                          \
+        else if (c_ <= 32) { CALL(32, 1, 1); }                          \
+        else if (c_ <= 64) { CALL(64, 1, 1); }                          \
+        else if (c_ <= 128) { CALL(64, 2, 1); }                         \
+        else if (c_ <= 256) { CALL(64, 4, 1); }                         \
+        else { CALL(0, 0, 0); }                                         \
+    } while (0)
+#define HELIOS_COPY_SHAPE_SWITCH(chunks, far, CALL)                     \
+    do {                                                                \
+        if (far) HELIOS_COPY_FAR_SHAPE(chunks, CALL);                   \
+        else HELIOS_COPY_NEAR_SHAPE(chunks, CALL);                      \
     } while (0)
 
 // rows per step of the far shape for a row that the near shape copies with L lanes and CPL pieces per lane
@@ -148,11 +154,11 @@ constexpr int far_rows_per_step(int L, int CPL) { return L == 0 ? 0 : L <= 16 ? 
 // The copy with the shape chosen on the device: for roles that ride on another kernel (a host-link
 // copy beside a sampling pass), where one instantiation has to serve every row size.  The loop is
 // bound by the link, not by its instruction count.
-__device__ __forceinline__ void copy_rows_any(const GatherArgs& a, uint32_t rb, uint32_t nrb, bool far) {
+__device__ __forceinline__ void copy_far_rows_any(const GatherArgs& a, uint32_t rb, uint32_t nrb) {
 #define HELIOS_CALL_(L, CPL, R)                                         \
     if constexpr ((L) == 0) copy_rows_long(a, rb, nrb);                 \
     else copy_rows<(L) == 0 ? 64 : (L), (CPL) == 0 ? 1 : (CPL), (R) == 0 ? 1 : (R)>(a, rb, nrb)
-    HELIOS_COPY_SHAPE_SWITCH(a.chunks, far, HELIOS_CALL_);
+    HELIOS_COPY_FAR_SHAPE(a.chunks, HELIOS_CALL_);
 #undef HELIOS_CALL_
 }
 

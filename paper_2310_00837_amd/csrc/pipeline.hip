@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kBlock) void batch_sample_kernel(SampleGang g) {
     for (int m = 0; m < g.n; ++m) {
         const SampleMember& a = g.m[m];
         if (a.r_link.mine()) {
-            copy_rows_any(a.link, a.r_link.rb(), a.r_link.blocks, true);
+            copy_far_rows_any(a.link, a.r_link.rb(), a.r_link.blocks);
             return;
         }
         if (a.r_hop.mine()) {
@@ -180,6 +180,24 @@ hipError_t launch_compact(hipStream_t stream, const CompactJob* jobs, int n) {
     return hipGetLastError();
 }
 
+// The two copies move rows of the same size; their loops differ in the rows a group takes per step.  The four rows of the
+// host-tier copy of 512-byte rows cost the kernel 78 registers, and with them a quarter of the waves of the copy from HBM, so a
+// launch of such rows without a copy over the link takes an instance with one: last launch of a gang of four 34.5 -> 33.0 us, of
+// a batch of 71 k rows of 400 bytes 24.0 -> 22.1.  A launch with a copy over the link is bound by that and keeps the four rows
+// that the link's copy has everywhere: with one or two, three gangs of the paper's shape in flight differ by less than two runs of
+// one side do.
+template <int L, int CPL, int R>
+void launch_finish_shape(hipStream_t stream, dim3 grid, const FinishGang& g, bool over_link) {
+    constexpr int RF = far_rows_per_step(L, CPL);
+    if constexpr (RF > 2) {
+        if (!over_link) {
+            hipLaunchKernelGGL((batch_finish_kernel<L, CPL, R, 1>), grid, dim3(kBlock), 0, stream, g);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((batch_finish_kernel<L, CPL, R, RF>), grid, dim3(kBlock), 0, stream, g);
+}
+
 hipError_t launch_finish(hipStream_t stream, const FinishJob* jobs, int n) {
     if (n < 1 || n > kMaxGang) return hipErrorInvalidValue;
     FinishGang g{};
@@ -223,20 +241,11 @@ hipError_t launch_finish(hipStream_t stream, const FinishJob* jobs, int n) {
     }
     if (at == 0) return hipSuccess;
     if (chunks == 0) chunks = 1;
-    const dim3 grid(at), block(kBlock);
-    // The two copies move rows of the same size; their loops differ in the rows a group takes per step.  The four rows of the
-    // host-tier copy of 512-byte rows cost the kernel 78 registers, and with them a quarter of the waves of the copy from HBM, so a
-    // launch without a copy over the link takes an instance with one: last launch of a gang of four 34.5 -> 33.0 us, of a
-    // batch of 71 k rows of 400 bytes 24.0 -> 22.1.  A launch with one is bound by the link and better off with the four
-    // rows (three gangs of the paper's shape in flight 266.7 us with four, 268.3 with two).
+    const dim3 grid(at);
     bool over_link = false;
     for (int m = 0; m < n; ++m) over_link = over_link || jobs[m].link_blocks > 0 || jobs[m].miss_blocks > 0;
-#define HELIOS_CALL_(L, CPL, R)                                                                                        \
-    do {                                                                                                               \
-        if ((L) == 32 && !over_link) hipLaunchKernelGGL((batch_finish_kernel<L, CPL, R, 1>), grid, block, 0, stream, g); \
-        else hipLaunchKernelGGL((batch_finish_kernel<L, CPL, R, far_rows_per_step(L, CPL)>), grid, block, 0, stream, g); \
-    } while (0)
-    HELIOS_COPY_SHAPE_SWITCH(chunks, false, HELIOS_CALL_);
+#define HELIOS_CALL_(L, CPL, R) (launch_finish_shape<L, CPL, R>(stream, grid, g, over_link))
+    HELIOS_COPY_NEAR_SHAPE(chunks, HELIOS_CALL_);
 #undef HELIOS_CALL_
     return hipGetLastError();
 }
