@@ -276,7 +276,7 @@ __device__ __forceinline__ void compact_tiles(const CompactArgs& a, const DedupS
             if (at >= a.unique_cap) continue;
             a.unique[at] = id[k];
             if (MODE == kCompactLookup) {
-                const uint32_t in_tile = before[NP - 1][k] + local2[k];          // no carry between the halves: a tile has at most 4096 items
+                const uint32_t in_tile = before[NP - 1][k] + local2[k];          // no carry between the halves: a tile has at most 2048 items
                 const int64_t at_hbm = base[1] + lds.excl[NC - 2] + (in_tile & 0xffffu);
                 const int64_t at_host = base[2] + lds.excl[NC - 1] + (in_tile >> 16);
                 if (tier[k] < 2) {

@@ -24,6 +24,9 @@
 // (its 64 MB would take 11 us), and 2-4 us for each launch of a pass that is left
 // out; 96 us in all.  Sixteen two-bit splits by chained scan, which this
 // replaces, took 2 300 us (138 each: 3 900 tickets on one address).
+//
+// One workgroup of the scatter runs per CU: it takes 81 984 bytes of LDS, 64 more than half of what a CU has, and 87 registers
+// where two workgroups of 16 waves would have to do with 64.  So of a grid of 512 half start when the others end.
 #include "kernels.hpp"
 
 namespace helios {
@@ -39,7 +42,7 @@ constexpr int kBins = 1 << kDigitBits;
 constexpr int kSortPasses = 3;
 constexpr int kScanBins = 16;                             // bins per workgroup of the scan
 constexpr int kWalkers = kSortBlock / kScanBins;          // each takes a share of the tiles
-constexpr unsigned kSortMaxWorkgroups = 512;              // two fit a CU (80 KB of LDS each); they loop over the tiles
+constexpr unsigned kSortMaxWorkgroups = 512;              // they loop over the tiles (see the end of the head comment)
 static_assert(kWalkers == kWave && kSortWaves == kScanBins, "one wave scans the walkers of one bin");
 
 __global__ __launch_bounds__(kBlock) void hotness_add_kernel(const int32_t* __restrict__ ids, Count n_in, int64_t n_nodes,

@@ -135,7 +135,7 @@ __device__ __forceinline__ uint32_t scan_lookback(const ScanState& st, uint32_t 
 }
 
 // NP rows of per-wave totals feed NC counters: counter c is row c, except that with NC == NP + 1 the last row holds two
-// counters of 16 bits (a tile has at most 4096 items).
+// counters of 16 bits (a tile has at most 2048 items).
 template <int NP, int NC, int K>
 struct TileScan {
     static_assert(NC == NP || NC == NP + 1, "one row may be a pair");

@@ -449,7 +449,7 @@ def test_three_batches_in_flight(helios, oracle, workloads):
 
 
 def test_many_streams_with_large_scans(helios, oracle):
-    """Six contexts on six streams, each with scan kernels of about 1500 tiles queued back to back:
+    """Six contexts on six streams, each with scan kernels of about 700 tiles queued back to back:
     more waiting workgroups than the chip holds at once.  Every tile must still only wait for tiles
     that have started (no HELIOS_EINTERNAL, no hang), and every result must match the oracle."""
     dev = torch.device("cuda", 0)
