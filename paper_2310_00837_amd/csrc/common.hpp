@@ -140,21 +140,4 @@ __device__ __forceinline__ RowBounds row_bounds(const int64_t* offsets, uint32_t
     return RowBounds{p.x, p.y};
 }
 
-// min(deg(v), fanout): how many samples node v yields at a hop.  A value that is no node ID, or a
-// row of 2^31 entries or more, is reported and yields nothing.
-__device__ __forceinline__ uint32_t sample_count(const int64_t* offsets, int64_t n_nodes, int32_t v, int32_t fanout,
-                                                 int32_t* err) {
-    if (v < 0 || static_cast<int64_t>(v) >= n_nodes) {
-        raise(err, kErrData);
-        return 0;
-    }
-    const int64_t d = offsets[v + 1] - offsets[v];
-    if (d < 0 || d > 0x7fffffffLL) {
-        raise(err, kErrData);
-        return 0;
-    }
-    const int64_t f = fanout > 0 ? fanout : 0;
-    return static_cast<uint32_t>(d < f ? d : f);
-}
-
 }  // namespace helios

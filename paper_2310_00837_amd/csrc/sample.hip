@@ -31,13 +31,14 @@ __global__ __launch_bounds__(kScanBlock) void frontier_count_kernel(CountArgs a)
     // A recorded batch starts here: every workgroup reads the batch's variables from the slot of the host's ring
     // that the count of batches run so far selects, and the first workgroup leaves them in device memory for the
     // kernels that follow (the batch's first compaction advances the count).
-    BatchVars bv{};
-    if (a.feed.ring) bv = a.feed.ring[*a.feed.batches_run % a.feed.ring_slots];
+    const int32_t* frontier = a.frontier;
     ScanState scan = a.scan;
     if (a.feed.ring) {
+        const BatchVars* bv = a.feed.ring + *a.feed.batches_run % a.feed.ring_slots;
+        frontier = bv->seeds;
         scan.vars = nullptr;
-        scan.epoch += bv.epoch_base;
-        if (blockIdx.x == 0 && threadIdx.x == 0) *a.feed.vars_out = bv;
+        scan.epoch += bv->epoch_base;
+        if (blockIdx.x == 0 && threadIdx.x == 0) *a.feed.vars_out = *bv;
     }
     const uint32_t n = static_cast<uint32_t>(a.n.get());
     const uint32_t n_tiles = (n + K * kScanBlock - 1) / (K * kScanBlock);
@@ -53,20 +54,29 @@ __global__ __launch_bounds__(kScanBlock) void frontier_count_kernel(CountArgs a)
     const uint32_t n_wgs = gridDim.x < n_tiles ? gridDim.x : n_tiles;
     for (uint32_t tile = Scan::take_ticket(scan, n_tiles, n_wgs, lds); tile < n_tiles;
          tile = n_wgs < n_tiles ? Scan::take_ticket(scan, n_tiles, n_wgs, lds) : n_tiles) {
-        const int32_t* frontier = a.feed.ring ? bv.seeds : a.frontier;
         const uint32_t j0 = tile * (K * kScanBlock) + threadIdx.x;
         int32_t v[K];
         uint32_t totals[1][K], before[1][K], local[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) v[k] = frontier[j0 + k * kScanBlock < n ? j0 + k * kScanBlock : 0];
+        // (all row bounds are asked for before the first is used, unguarded: a node that is none reads row 0)
+        RowBounds row[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const bool ok = v[k] >= 0 && static_cast<int64_t>(v[k]) < a.n_nodes;
+            row[k] = RowBounds{0, 0};
+            if (a.n_nodes > 0) row[k] = row_bounds(a.offsets, ok ? static_cast<uint32_t>(v[k]) : 0u);      // (uniform guard)
+        }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const uint32_t j = j0 + k * kScanBlock;
-            uint32_t cnt = 0;
-            if (j < n) {
-                if (a.frontier_out && a.frontier_out != frontier) a.frontier_out[j] = v[k];
-                cnt = sample_count(a.offsets, a.n_nodes, v[k], a.fanout, a.err);
-            }
+            const bool ok = v[k] >= 0 && static_cast<int64_t>(v[k]) < a.n_nodes;
+            const int64_t d = ok ? row[k].hi - row[k].lo : 0;
+            const bool bad = d < 0 || d > 0x7fffffffLL;
+            if (j < n && a.frontier_out && a.frontier_out != frontier) a.frontier_out[j] = v[k];
+            if (j < n && (!ok || bad)) raise(a.err, kErrData);
+            const int64_t f = a.fanout > 0 ? a.fanout : 0;
+            const uint32_t cnt = j >= n || bad ? 0u : static_cast<uint32_t>(d < f ? d : f);
             const uint32_t inc = dpp_inclusive_scan(cnt);
             totals[0][k] = lane_value(inc, kWave - 1);
             local[k] = inc - cnt;
