@@ -213,8 +213,8 @@ __device__ __forceinline__ void compact_tiles(const CompactArgs& a, const DedupS
         bool live[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            // (both checked: a caller that overwrites its seeds while they are being sampled leaves places of the list
-            // unwritten, and what they hold then must not become an address)
+            // (both checked: an input that changes while the batch runs leaves places of the list unwritten, and what they
+            // hold then must not become an address)
             const bool real = j0 + k * kScanBlock < end && static_cast<uint32_t>(id[k]) < a.n_nodes;
             live[k] = real && static_cast<uint32_t>(slot[k]) < s.n_slots;
             if (real && !live[k]) raise(a.err, kErrInternal);      // kNoSlot: its table was full

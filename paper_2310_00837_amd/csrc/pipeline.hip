@@ -13,7 +13,8 @@
 //   compact    flat_0 -> frontier_1 + indptr_1   |  [seeds | flat_0] -> stage 0 of unique, tier lists, miss list
 //   sample     hop 1                             |  host-tier copy of stage 0
 //   compact    flat_1 -> stage 1 (the last) of unique, tier lists, miss list, stats
-//   finish     host-tier copy of stage 1  |  HBM-tier copy of all stages  |  inverse  |  emptying of the next batch's table
+//   finish     host-tier copy of stage 1  |  HBM-tier copy of all stages  |  inverse  |  check of the batch's list, emptying of
+//              the next batch's table
 //              (|  the rows of the miss list from the storage stand-in, if the batch serves its own misses)
 //
 // Five launches; the host link is busy from the end of the first compaction on, except while a
