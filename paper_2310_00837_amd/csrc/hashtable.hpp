@@ -25,9 +25,8 @@ __device__ __forceinline__ uint32_t hash_id(uint32_t id, uint32_t mask) {
 // reports (here it would be one more branch in every insert, 0.3 us of a sampling pass).
 __device__ __forceinline__ uint32_t table_insert(unsigned long long* table, uint32_t mask, uint32_t id, uint32_t pos, uint32_t& claims) {
     const unsigned long long mine = (static_cast<unsigned long long>(id) << 32) | pos;
-    const uint32_t home = hash_id(id, mask);
-    uint32_t slot = home;
-    do {
+    uint32_t slot = hash_id(id, mask);
+    for (uint32_t left = mask;; --left) {                           // (the same in all lanes: counted by the scalar unit)
         // try to claim straight away: one round trip when the slot is free (the common case)
         const unsigned long long cur = atomicCAS(table + slot, kEmptySlot, mine);
         if (cur == kEmptySlot) {                                    // claimed
@@ -39,8 +38,8 @@ __device__ __forceinline__ uint32_t table_insert(unsigned long long* table, uint
             return slot;
         }
         slot = (slot + 1) & mask;
-    } while (slot != home);
-    return kNoSlot;
+        if (left == 0) return kNoSlot;
+    }
 }
 
 // A table that a producing kernel inserts its outputs into as it writes them, so that the

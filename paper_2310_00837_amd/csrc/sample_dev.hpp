@@ -228,14 +228,15 @@ __device__ __forceinline__ void sample_role(const HopArgs& a, uint32_t rb, uint3
     for (uint32_t w = rb * kBlock + threadIdx.x; a.clear.table && w < a.clear.n_slots; w += nrb * kBlock)
         a.clear.table[w] = kEmptySlot;                    // side job of the role (at its end it would be a tail of its own)
     SampleTables tabs{a.hop_table, nullptr, 0, nullptr, a.cat_out, 0, 0};
+    uint32_t* claims = nullptr;
     if (a.batch.table0) {
+        // (fetched with the arguments here: at the end of the role, where it is used, the read would be waited for by itself, 0.3 us)
+        claims = a.claims;
+        asm volatile("" : "+s"(claims));
         tabs.batch_table = a.batch.table(which);
         tabs.batch_mask = a.batch.n_slots - 1;
         tabs.batch_slot_of = a.batch.slot_of(which);
     }
-    // (fetched with the arguments above: at the end of the role, where it is used, the read would be waited for by itself, 0.3 us)
-    uint32_t* claims = a.claims;
-    asm volatile("" : "+s"(claims));
     const bool seeds_too = tabs.batch_table && a.hop == 0;   // the frontier of hop 0 is the head of the batch's list
     if (f > 0 || seeds_too) {
         for (bool again = false; i < n; i += step, again = true) {
