@@ -597,8 +597,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             inv_blocks = inv_blocks < 1 ? 1 : inv_blocks;
             inv.stamps = take_stamps(c, HELIOS_ROLE_INVERSE, stage, inv_blocks);
         }
-        clear_blocks = 1;
-        if (clear_slots) clear_blocks += std::min(256u, (clear_slots + kBlock * 16 - 1) / (kBlock * 16));      // (a recording learns on the device how much there is)
+        if (clear_slots) clear_blocks = std::min(256u, (clear_slots + kBlock * 16 - 1) / (kBlock * 16));      // (a recording learns on the device how much there is)
         int rf = emit_finish(c, FinishJob{hbm, hbm_blocks, link, link_blocks, miss, miss_blocks, inv, inv_blocks, clear_slots, clear_blocks,
                                           c->claims, n_claims, stage_words(c, stage) + kStageUnique, err, bt, vars});
         if (rf) return rf;

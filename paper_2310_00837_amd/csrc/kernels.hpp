@@ -51,8 +51,8 @@ struct CompactJob {
 hipError_t launch_compact(hipStream_t stream, const CompactJob* jobs, int n);
 // The end of a batch in one launch: host-tier copy of the last stage, the rows of the miss list from the
 // storage stand-in (if the batch serves its own misses), HBM-tier copy of all stages, the inverse map,
-// and the check of the batch's list with the emptying of the table that the next batch of the context uses.  Any of the
-// five may be absent (0 workgroups).  The table to empty is the one after the batch's own among bt's; clear_slots of its slots are in use (with
+// and the emptying of the table that the next batch of the context uses, any of which may be absent (0 workgroups); and the
+// check of the batch's own list.  The table to empty is the one after the batch's own among bt's; clear_slots of its slots are in use (with
 // vars, a recorded batch, the variables say how many).  The rows of all members have one size.
 struct FinishJob {
     GatherArgs hbm;
@@ -64,8 +64,8 @@ struct FinishJob {
     InverseArgs inv;
     unsigned inv_blocks;
     uint32_t clear_slots;
-    unsigned clear_blocks;       // its first workgroup checks the batch's own list (check_table_list), the others empty
-    const uint32_t* claims;
+    unsigned clear_blocks;
+    const uint32_t* claims;      // for the check of the batch's own list (check_table_list)
     uint32_t n_claims;
     const int64_t* n_firsts;
     int32_t* err;

@@ -64,6 +64,13 @@ __global__ __launch_bounds__(kScanBlock) void batch_compact_kernel(CompactGang g
 // L, CPL, R: the shape of the HBM-tier copy loop for the row size; RF: rows per step of the host-tier copy
 template <int L, int CPL, int R, int RF>
 __global__ __launch_bounds__(kBlock) void batch_finish_kernel(FinishGang g) {
+    // One workgroup per member, the first ones: the check's chain of reads would be a tail behind the thousands of short
+    // workgroups of the copy (0.9 us of a batch of 25 k rows, 58.4 -> 59.3).
+    if (blockIdx.x < static_cast<uint32_t>(g.n)) {
+        const FinishMember& a = g.m[blockIdx.x];
+        check_table_list(a.bt, a.vars, a.claims, a.n_claims, a.n_firsts, a.err);
+        return;
+    }
 #pragma unroll 1
     for (int m = 0; m < g.n; ++m) {
         const FinishMember& a = g.m[m];
@@ -87,8 +94,7 @@ __global__ __launch_bounds__(kBlock) void batch_finish_kernel(FinishGang g) {
             return;
         }
         if (a.r_clear.mine()) {
-            if (a.r_clear.rb() == 0) check_table_list(a.bt, a.vars, a.claims, a.n_claims, a.n_firsts, a.err);
-            else empty_next_table(a.bt, a.vars, a.clear_slots, a.r_clear.rb() - 1, a.r_clear.blocks - 1);
+            empty_next_table(a.bt, a.vars, a.clear_slots, a.r_clear.rb(), a.r_clear.blocks);
             return;
         }
     }
@@ -203,7 +209,7 @@ hipError_t launch_finish(hipStream_t stream, const FinishJob* jobs, int n) {
     if (n < 1 || n > kMaxGang) return hipErrorInvalidValue;
     FinishGang g{};
     g.n = n;
-    unsigned at = 0;
+    unsigned at = static_cast<unsigned>(n);
     int chunks = 0;
     for (int m = 0; m < n; ++m) {
         FinishMember& a = g.m[m];
@@ -240,7 +246,6 @@ hipError_t launch_finish(hipStream_t stream, const FinishJob* jobs, int n) {
         a.r_clear = Role{at, jobs[m].clear_blocks};
         at += jobs[m].clear_blocks;
     }
-    if (at == 0) return hipSuccess;
     if (chunks == 0) chunks = 1;
     const dim3 grid(at);
     bool over_link = false;
