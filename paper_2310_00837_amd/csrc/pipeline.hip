@@ -29,7 +29,8 @@ namespace {
 // contexts that share a stream and go through their steps together), so that the chain of short,
 // latency-bound launches is paid once per gang and not once per batch.  A workgroup looks up which
 // member's role it belongs to; the members' arguments sit side by side in the kernel arguments.
-// The link roles of all members come first in every launch: they start first.
+// The link roles of all members come first in every launch (in the last one after a workgroup per member that checks its
+// list): they start first.
 template <int G>
 __global__ __launch_bounds__(kBlock) void batch_sample_kernel(SampleGang g) {
 #pragma unroll 1
