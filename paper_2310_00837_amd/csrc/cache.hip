@@ -16,7 +16,8 @@ namespace helios {
 
 namespace {
 
-__global__ __launch_bounds__(kBlock) void rank_fill_kernel(int32_t* rank, int64_t n) {
+__global__ __launch_bounds__(kBlock) void rank_fill_kernel(int32_t* rank, int64_t n, int64_t* holes) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *holes = 0;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * kBlock)
         rank[i] = -1;
@@ -33,10 +34,13 @@ __global__ __launch_bounds__(kBlock) void rank_scatter_kernel(const int32_t* __r
 }
 
 // a node that no rank points to means `order` repeated another node
-__global__ __launch_bounds__(kBlock) void rank_check_kernel(const int32_t* __restrict__ rank, int64_t n, int32_t* err) {
+__global__ __launch_bounds__(kBlock) void rank_check_kernel(const int32_t* __restrict__ rank, int64_t n, int64_t* holes, int32_t* err) {
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n;
          i += static_cast<int64_t>(gridDim.x) * kBlock)
-        if (rank[i] < 0) raise(err, kErrData);
+        if (rank[i] < 0) {
+            *holes = 1;
+            raise(err, kErrData);
+        }
 }
 
 struct PartitionArgs {
@@ -50,6 +54,7 @@ struct PartitionArgs {
     int64_t* stats_out;          // device-accessible int64[4], nullable
     int64_t* learn;              // pinned int64[4], nullable: a copy of the stats for the host's grid sizing
     bool hbm_direct;             // no list is wanted for the HBM tier
+    const int64_t* holes;        // device word: not 0 if some node has no rank
     ScanState scan;
     int32_t* err;
 };
@@ -130,6 +135,49 @@ __device__ __forceinline__ void partition_role(const PartitionArgs& a, uint32_t 
     }
 }
 
+// With all nodes in HBM nothing can be listed (no ID has a host row, none can miss), and of the partition only the counts are
+// left: no order, so no tickets and no look-back.  Bound by the chain ID, rank, sums, one atomic per workgroup; the last
+// workgroup to add its count writes the stats and leaves the word at zero.  Where every node has a rank, which the build of the
+// map has found out, the ranks need not be read for it.  Call on 100 k rows of 64 bytes, copied beside it: 12.0 us with the partition,
+// 10.1 with a count that reads the ranks, 7.5 with this; 243 k rows of 2 KB 174.3 -> 167.2.
+constexpr unsigned kCountWorkgroups = 64;              // (a word that all add to takes about 10 ns for each)
+__device__ __forceinline__ void count_role(const PartitionArgs& a, uint32_t rb, uint32_t nrb) {
+    __shared__ uint32_t s_hits[kScanWaves];
+    constexpr int kAhead = 4;
+    const uint32_t n = static_cast<uint32_t>(a.n.get()), step = nrb * kScanBlock;
+    const bool whole = *a.holes == 0;
+    uint32_t hits = 0;
+    for (uint64_t j0 = rb * kScanBlock + threadIdx.x; j0 < n; j0 += static_cast<uint64_t>(kAhead) * step) {
+        int32_t id[kAhead], r[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) id[k] = a.ids[j0 + static_cast<uint64_t>(k) * step < n ? j0 + static_cast<uint64_t>(k) * step : j0];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const bool ok = id[k] >= 0 && static_cast<int64_t>(id[k]) < a.n_nodes;
+            if (!ok) raise(a.err, kErrData);
+            r[k] = ok ? 0 : -1;
+            if (!whole && ok) r[k] = a.rank[id[k]];
+        }
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) hits += j0 + static_cast<uint64_t>(k) * step < n && static_cast<uint32_t>(r[k]) < static_cast<uint32_t>(a.n_hbm) ? 1u : 0u;
+    }
+    const uint32_t sum = dpp_sum(hits);
+    if (lane_id() == 0) s_hits[wave_id()] = sum;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    unsigned long long mine = 1ull << 40;              // {workgroups done : 24 | hits : 40}
+#pragma unroll
+    for (int w = 0; w < kScanWaves; ++w) mine += s_hits[w];
+    unsigned long long* word = reinterpret_cast<unsigned long long*>(a.scan.ticket);       // zero between launches, as the ticket is
+    const unsigned long long all = atomicAdd(word, mine) + mine;
+    if (all >> 40 != nrb) return;
+    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int64_t c0 = static_cast<int64_t>(all & ((1ull << 40) - 1));
+    a.lists.count[0] = c0; a.lists.count[1] = a.lists.count[2] = 0;
+    if (a.stats_out) { a.stats_out[0] = n; a.stats_out[1] = c0; a.stats_out[2] = 0; a.stats_out[3] = 0; }
+    if (a.learn) { a.learn[0] = n; a.learn[1] = c0; a.learn[2] = 0; a.learn[3] = 0; }
+}
+
 // The HBM tier's rows without a list: out[j, :] = table[rank[ids[j]], :] for the IDs whose rank is in the tier.  A group of L
 // lanes owns a row, as in copy_rows (gather_dev.hpp); it reads the ID and its rank by itself, so the copy need not wait for the
 // partition, which makes the other lists in the same launch.
@@ -169,11 +217,12 @@ __device__ __forceinline__ void direct_rows(const DirectArgs& a, uint32_t rb, ui
 // Lookup and partition, and beside it, if r_copy has workgroups, the copy of the HBM tier's rows.  As two launches the copy
 // waited 8 to 13 us for lists it does not need: 243 k rows of 2 KB 179.1 -> 174.5 us for the call, 100 k rows of 64 bytes
 // 15.0 -> 12.0.  (One row per group and step: with two 177.0 and 13.4 us, with four 184.2 and 13.7.)  When it does not pay:
-// copy_beside_lookup below.
+// copy_beside_lookup below.  K = 0: the count in place of the partition.
 template <int K, int L, int CPL>
 __global__ __launch_bounds__(kScanBlock) void lookup_copy_kernel(PartitionArgs a, DirectArgs d, Role r_part, Role r_copy) {
     if (r_part.mine()) {
-        partition_role<K>(a, r_part.rb(), r_part.blocks);
+        if constexpr (K == 0) count_role(a, r_part.rb(), r_part.blocks);
+        else partition_role<K>(a, r_part.rb(), r_part.blocks);
         return;
     }
     direct_rows<L, CPL>(d, r_copy.rb(), r_copy.blocks);
@@ -188,11 +237,11 @@ unsigned grid_for(int64_t n, unsigned cap_blocks) {
 
 }  // namespace
 
-hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int32_t* err) {
+hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int64_t* holes, int32_t* err) {
     const dim3 grid(grid_for(n_nodes, 8192)), block(kBlock);
-    hipLaunchKernelGGL(rank_fill_kernel, grid, block, 0, stream, rank, n_nodes);
+    hipLaunchKernelGGL(rank_fill_kernel, grid, block, 0, stream, rank, n_nodes, holes);
     hipLaunchKernelGGL(rank_scatter_kernel, grid, block, 0, stream, order, n_nodes, rank, err);
-    hipLaunchKernelGGL(rank_check_kernel, grid, block, 0, stream, rank, n_nodes, err);
+    hipLaunchKernelGGL(rank_check_kernel, grid, block, 0, stream, rank, n_nodes, holes, err);
     return hipGetLastError();
 }
 
@@ -205,12 +254,19 @@ hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n
 //   7 tenths                    4096 steps 31.4/29.6              19.4/16.7 25.7/20.7   8192 steps 58.0/57.1  31.2/33.5  42.7/38.2
 //   9 tenths                    8192 steps 64.0/60.8  36.3/35.2  51.7/46.3    16384 steps -  59.4/60.1  95.0/93.5   32768 -  104/120  177/172
 //   3 tenths                    8192 steps of 2048 / 4096 bytes: 25.3/25.7  40.7/36.8 (7 tenths 42.7/38.2  77.3/70.8)
-//   all                        16384 steps -          64.0/61.9 103.2/101.5   32768 steps - 112.2/123.0 192.6/186.8  65536 -  216/239  384/379
-// With four pieces per lane (rows of 2 to 4 KB) it stops paying earlier: 4096 bytes, all in HBM, 8192 steps 102.3/97.3, 16384 195.3/199.4.
+// With four pieces per lane (rows of 2 to 4 KB) it stops paying earlier: 4096 bytes, 9 tenths in HBM, 16384 steps 195.3/199.4.
+// With all nodes in HBM the lookup beside the copy only counts (count_role), and that way is the quicker one for all rows of up to 2 KB
+// and above 4 KB: us for the call by list or beside a partition, whichever the partition leaves quicker / beside the count,
+//   rows of 64     131 k IDs 14.5/7.9   524 k 35.5/24.4  2.1 M 131/86.6
+//   512            65 k 18.6/14.6       262 k 62.6/51.6  1.0 M 220/194
+//   2048           65 k 50.2/47.0       262 k 188/181    524 k 380/362
+//   4096           65 k 97.6/93.7       131 k 193/190    262 k 376/385   (the line)
+//   8192           33 k 95.9/93.9       131 k 375/364
 bool copy_beside_lookup(int64_t n, int64_t n_nodes, int64_t n_hbm, int32_t chunks) {
     int64_t lanes = 4;
     while (lanes < chunks && lanes < kWave) lanes <<= 1;
     const int64_t steps = (n * lanes + kScanBlock - 1) / kScanBlock;
+    if (n_hbm == n_nodes) return chunks <= 128 || chunks > 256 || steps <= 16384;
     if (10 * n_hbm < 9 * n_nodes) return n <= 262144 && steps <= (chunks >= 128 && 10 * n_hbm >= 3 * n_nodes ? 8192 : 4096);
     if (chunks > 128 && chunks <= 256) return steps <= 8192;
     return chunks >= 128 || steps <= (n_hbm < n_nodes ? 8192 : 16384);
@@ -220,12 +276,14 @@ hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, int64
                                    const int32_t* rank, int64_t n_nodes, int64_t n_hbm, int64_t n_host,
                                    const TierLists& lists, int32_t* miss_pos, int32_t* miss_id,
                                    int32_t* miss_slot, int64_t miss_cap, int64_t* stats_out, int64_t* learn,
-                                   const ScanState& scan, int32_t* err, const chunk16* copy_table, chunk16* copy_out, int32_t chunks) {
+                                   const ScanState& scan, const int64_t* holes, int32_t* err, const chunk16* copy_table, chunk16* copy_out,
+                                   int32_t chunks) {
     const bool copy = copy_table && n > 0 && n_hbm > 0;
     const PartitionArgs a{ids, Count{nullptr, n}, rank, n_nodes, n_hbm, n_host, lists, miss_pos, miss_id, miss_slot, miss_cap,
-                          stats_out, learn, copy, scan, err};
+                          stats_out, learn, copy, holes, scan, err};
     const DirectArgs d{ids, rank, static_cast<uint32_t>(n), static_cast<uint32_t>(n_nodes), static_cast<uint32_t>(n_hbm), copy_table, copy_out, chunks};
-    const Role r_part{0, scan_workgroups(n, kScanMaxWorkgroups)};
+    const bool count_only = copy && n_hbm == n_nodes;
+    const Role r_part{0, scan_workgroups(n, count_only ? kCountWorkgroups : kScanMaxWorkgroups)};
     const dim3 block(kScanBlock);
     // One row per group and step, and as many workgroups as the list has steps: short-lived workgroups on consecutive rows copy
     // fastest (gather_dev.hpp).
@@ -236,7 +294,8 @@ hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, int64
         if (nb > kMaxRoleBlocks) nb = kMaxRoleBlocks;                                                                        \
         const Role r_copy{r_part.blocks, static_cast<uint32_t>(nb)};                                                         \
         const dim3 grid(r_part.blocks + r_copy.blocks);                                                                      \
-        if (n <= kScanOneItemMax) hipLaunchKernelGGL((lookup_copy_kernel<1, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy); \
+        if (count_only) hipLaunchKernelGGL((lookup_copy_kernel<0, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy);   \
+        else if (n <= kScanOneItemMax) hipLaunchKernelGGL((lookup_copy_kernel<1, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy); \
         else hipLaunchKernelGGL((lookup_copy_kernel<kScanMaxItems, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy);  \
     } while (0)
     HELIOS_COPY_NEAR_SHAPE(copy ? chunks : 1, HELIOS_CALL_);

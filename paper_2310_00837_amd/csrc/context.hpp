@@ -18,6 +18,7 @@ constexpr int kCntUnique = 33;
 constexpr int kCntHopTotal = 34;    // input length of a de-duplication between two hops (a copy of its flat size)
 constexpr int kCntTier = 40;        // [3] list entries to copy from the HBM tier and the host tier, misses to serve
 constexpr int kCntList = 48;        // [kBatchTables] length of the ID list that the table's last batch inserted, or kListIncomplete
+constexpr int kCntHoles = 56;       // not 0: the hotness order left a node without a rank
 constexpr int kCntStage = 64;       // [HELIOS_MAX_HOPS][kStageWords] totals after every stage of a batch's compaction
 constexpr int kNumCounters = kCntStage + HELIOS_MAX_HOPS * kStageWords;
 constexpr uint32_t kVarsRing = 256;   // batch launches that may be queued on a context without a helios_sync

@@ -966,7 +966,7 @@ int helios_cache_build(helios_ctx* c, const int32_t* order, int64_t hbm_rows, in
         HIP_TRY(c, hipMalloc(&c->rank, sizeof(int32_t) * (n > 0 ? n : 1)));
         c->rank_cap = n;
     }
-    if (n > 0) HIP_TRY(c, launch_rank_build(c->stream, order, n, c->rank, c->err));
+    if (n > 0) HIP_TRY(c, launch_rank_build(c->stream, order, n, c->rank, c->cnt + kCntHoles, c->err));
     c->n_hbm = hbm_rows;
     c->n_host = host_rows;
     c->row_bytes = row_bytes;
@@ -1075,7 +1075,7 @@ int helios_gather(helios_ctx* c, const int32_t* ids, int64_t n_ids, void* out, i
                         copy_beside_lookup(n_ids, c->g.n_nodes, c->n_hbm, c->row_bytes / 16);
     HIP_TRY(c, launch_lookup_partition(c->stream, ids, n_ids, rank_or_any(c), c->g.n_nodes, c->n_hbm, c->n_host,
                                        lists, miss_pos, miss_id, miss_slot, miss_cap, reinterpret_cast<int64_t*>(stats), c->learn,
-                                       scan_state(c, epoch, kScanRowsLook), c->err,
+                                       scan_state(c, epoch, kScanRowsLook), c->cnt + kCntHoles, c->err,
                                        direct ? static_cast<const chunk16*>(c->hbm_table) : nullptr, static_cast<chunk16*>(out),
                                        c->row_bytes / 16));
     rc = copy_tiers_split(c, n_ids, out, !direct);

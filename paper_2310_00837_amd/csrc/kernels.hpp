@@ -132,7 +132,8 @@ hipError_t launch_dedup_end(hipStream_t stream, const InverseArgs& inv, int64_t 
                             uint32_t n_zero);
 
 // ---- cache.hip
-hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int32_t* err);
+// rank[order[r]] = r; *holes (device) = 1 if that leaves a node without a rank, else 0
+hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int64_t* holes, int32_t* err);
 
 // Lookup of ids[0, n) and partition into the per-tier lists and the miss list.  With copy_table, the rows of the HBM tier are copied
 // in the same launch (out[j] = copy_table[rank[ids[j]]], rows of `chunks` 16-byte pieces), and that tier gets no list; its count
@@ -142,7 +143,8 @@ hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, int64
                                    const int32_t* rank, int64_t n_nodes, int64_t n_hbm, int64_t n_host,
                                    const TierLists& lists, int32_t* miss_pos, int32_t* miss_id,
                                    int32_t* miss_slot, int64_t miss_cap, int64_t* stats_out, int64_t* learn,
-                                   const ScanState& scan, int32_t* err, const chunk16* copy_table, chunk16* copy_out, int32_t chunks);
+                                   const ScanState& scan, const int64_t* holes, int32_t* err, const chunk16* copy_table, chunk16* copy_out,
+                                   int32_t chunks);
 
 // ---- gather.hip
 // The row copy as a kernel of its own.  far_source selects the launch shape for a source behind the host

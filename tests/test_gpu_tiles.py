@@ -210,6 +210,44 @@ def test_gather_by_list_and_beside_the_lookup(h, helios, row_bytes, n, n_hbm, si
             assert torch.equal(got[:n_miss].long(), want.long()) and bool((got[n_miss:] == -9).all())
 
 
+@pytest.mark.parametrize("n_ids", [1, 512, 513, 64 * 512 + 1, 5 * 64 * 512 + 77])
+@pytest.mark.parametrize("whole", [True, False])
+def test_gather_counts_with_all_nodes_in_hbm(h, helios, n_ids, whole):
+    """Stats and rows where the lookup only counts, at the edges of its steps (64 workgroups of 512, four steps read ahead); with
+    an order that leaves nodes out, which are then in no class."""
+    gen = torch.Generator(device="cuda").manual_seed(n_ids)
+    n = 30_000
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    order = torch.randperm(n, device="cuda", generator=gen)
+    if not whole:
+        order[7::1000] = order[6]
+    table = torch.randint(0, 256, (n, 64), dtype=torch.uint8, device="cuda", generator=gen)
+    order32 = order.int()
+    h.cache_build(order32, n, 0, 64, table, None, None)
+    if not whole:
+        with pytest.raises(helios.HeliosError):
+            h.sync()
+    known = torch.zeros(n, dtype=torch.bool, device="cuda")
+    known[order] = True
+    ids = torch.randint(0, n, (n_ids,), device="cuda", generator=gen).int()
+    lists = [torch.full((n_ids,), -9, dtype=torch.int32, device="cuda") for _ in range(3)]
+    once = torch.ones(n, dtype=torch.bool, device="cuda")
+    once[order[6]] = whole                                    # (which of its ranks a repeated node has is open)
+    rank = torch.empty(n, dtype=torch.int64, device="cuda")
+    rank[order] = torch.arange(n, device="cuda")
+    for _ in range(3):
+        out = torch.full((n_ids, 64), 0xA5, dtype=torch.uint8, device="cuda")
+        stats = torch.zeros(4, dtype=torch.int64).pin_memory()
+        torch.cuda.synchronize()
+        h.gather(ids, out, *lists, stats)
+        h.sync()
+        there = known[ids.long()]
+        assert stats.tolist() == [n_ids, int(there.sum()), 0, 0]
+        look = there & once[ids.long()]
+        assert torch.equal(out[look], table[rank[ids.long()[look]]]) and bool((out[~there] == 0xA5).all())
+        assert all(bool((x == -9).all()) for x in lists)
+
+
 @pytest.mark.parametrize("which", [0, 1, 2])
 @pytest.mark.parametrize("n_ids", [3_000, 130_000])
 def test_gather_with_its_miss_list_in_the_memory_of_the_ids(h, which, n_ids):
