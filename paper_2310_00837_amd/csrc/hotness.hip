@@ -11,39 +11,50 @@
 // of the counts finds out which bits vary, and every kernel of the later passes
 // looks there.  Counters of a pre-sampling epoch are at most its number of
 // batches, so that one pass is the rule up to 2048 batches.  A pass is three launches:
-//   count    every tile of 8192 pairs counts its digits (LDS);
-//   scan     per digit, a prefix sum over the tiles, 16 digits to a workgroup;
-//   scatter  a tile ranks its pairs (wave ballots find the lanes with the same
-//            digit, a counter per wave and digit in LDS carries the rank along),
-//            puts them into order in LDS and writes them out as runs.
+//   count    every group of consecutive tiles of 8192 pairs counts its digits (LDS);
+//   scan     per digit, a prefix sum over the groups, 16 digits to a workgroup;
+//   scatter  a group goes through its tiles: a tile ranks its pairs (wave ballots find
+//            the lanes with the same digit, a counter per wave and digit in LDS carries
+//            the rank along), puts their places into order in LDS and writes them out as runs.
 // Bins are numbered from the highest digit down, so each pass goes out in
 // descending digit order.  Nothing waits for another workgroup.
 //
 // What bounds it: the scatter's ballots and LDS traffic first, memory second.
-// Measured at 8 M nodes with counts up to 512: count 17 us, scan 9, scatter 45
+// Measured at 8 M nodes with counts up to 512: count 10 us, scan 7.5, scatter 35
 // (its 64 MB would take 11 us), and 2-4 us for each launch of a pass that is left
-// out; 96 us in all.  Sixteen two-bit splits by chained scan, which this
-// replaces, took 2 300 us (138 each: 3 900 tickets on one address).
+// out; 64 us in all, three passes 225, 111 M nodes 565.  With a row of counters per
+// tile, one copy of the count's counters and a scatter of one workgroup per CU it took
+// 82 (17, 9.6 and 45), 287 and 858 us.
 //
-// One workgroup of the scatter runs per CU: it takes 81 984 bytes of LDS, 64 more than half of what a CU has, and 87 registers
-// where two workgroups of 16 waves would have to do with 64.  So of a grid of 512 half start when the others end.
+// Why groups of tiles: one row of counters per group, of which there are at most 512, keeps the table at 4 MB whatever the
+// length of the list, and a scan thread has its rows in registers.
+// Why 512 threads with 16 pairs each in the scatter: its counters then take 32 KB (16 waves of 8 pairs: 64 KB), and with the
+// order kept as {digit, place in the tile}, 4 bytes a pair, two workgroups fit a CU (74 KB and 128 registers each), so that one has
+// its memory traffic while the other ranks.  A digit's bit costs the ranking five instructions of a wave for 64 pairs; as branches that
+// leave out the bits that do not vary it was slower (52 us).  1024 groups, or tiles of 4096, made no difference or 5 us more.
 #include "kernels.hpp"
 
 namespace helios {
 
 namespace {
 
-constexpr int kSortBlock = 1024;
+constexpr int kSortBlock = 1024;                          // count and scan
 constexpr int kSortWaves = kSortBlock / kWave;
-constexpr int kSortItems = 8;                             // pairs per thread
-constexpr int kSortTile = kSortBlock * kSortItems;        // 8192
+constexpr int kSortTile = 8192;                           // pairs
+constexpr int kCountItems = kSortTile / kSortBlock;
+constexpr int kPlaceBlock = 512;                          // scatter
+constexpr int kPlaceWaves = kPlaceBlock / kWave;
+constexpr int kPlaceItems = kSortTile / kPlaceBlock;
+constexpr int kPlaceBits = 13;                            // a place in the tile
 constexpr int kDigitBits = 11;
 constexpr int kBins = 1 << kDigitBits;
 constexpr int kSortPasses = 3;
 constexpr int kScanBins = 16;                             // bins per workgroup of the scan
-constexpr int kWalkers = kSortBlock / kScanBins;          // each takes a share of the tiles
-constexpr unsigned kSortMaxWorkgroups = 512;              // they loop over the tiles (see the end of the head comment)
+constexpr int kWalkers = kSortBlock / kScanBins;          // each takes a share of the groups
+constexpr uint32_t kSortMaxGroups = 512;
+constexpr int kCopies = 4;                                // of the count's counters: lanes that meet on a digit spread over them
 static_assert(kWalkers == kWave && kSortWaves == kScanBins, "one wave scans the walkers of one bin");
+static_assert(kSortTile == 1 << kPlaceBits && kBins == 4 * kPlaceBlock, "a thread of the scatter has four bins");
 
 __global__ __launch_bounds__(kBlock) void hotness_add_kernel(const int32_t* __restrict__ ids, Count n_in, int64_t n_nodes,
                                                              int32_t* counts, int32_t* err) {
@@ -61,9 +72,10 @@ struct SortArgs {
     int32_t *keys[2];            // scratch, by parity of the running pass
     int32_t *vals1, *order;
     uint32_t n, n_tiles;
-    uint32_t* tile_counts;       // [n_tiles][kBins]; after the scan: pairs of the bin in the tiles before
+    uint32_t group_tiles, n_groups;   // group g: the tiles [g * group_tiles, (g + 1) * group_tiles) below n_tiles
+    uint32_t* group_counts;      // [n_groups][kBins]; after the scan: pairs of the bin in the groups before
     uint32_t* totals;            // [kBins]
-    uint32_t* tile_bits;         // [n_tiles][2]: bits set in some count, bits clear in some count
+    uint32_t* group_bits;        // [n_groups][2]: bits set in some count, bits clear in some count
     uint32_t* varying;           // bits that are not the same in all counts (from the first pass's scan on)
     int pass;
     int32_t* err;
@@ -94,62 +106,56 @@ __device__ __forceinline__ uint32_t bin_of(int32_t key, int pass) {
     return kBins - 1 - ((static_cast<uint32_t>(key) >> (pass * kDigitBits)) & (kBins - 1));
 }
 
+// Bound by the LDS atomics: most counts are one of a few small numbers, and lanes that add to one word take their turns.
+// Four copies of the counters, by lane, cut the queues to a quarter: 17.3 -> 10.2 us for 8 M counts (eight copies: no difference).
 __global__ __launch_bounds__(kSortBlock) void sort_count_kernel(SortArgs a) {
-    __shared__ uint32_t s_hist[kBins];
+    __shared__ uint32_t s_hist[kBins * kCopies];
     __shared__ uint32_t s_set, s_clear;
     const SortStep step(a.pass, a.pass == 0 ? 0u : *a.varying);
     if (!step.active) return;
     const int32_t* keys = step.before == 0 ? a.counts : a.keys[(step.before - 1) & 1];
-    for (uint32_t tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
-        for (int q = threadIdx.x; q < kBins; q += kSortBlock) s_hist[q] = 0;
-        if (threadIdx.x == 0) s_set = s_clear = 0;
-        __syncthreads();
+    for (int q = threadIdx.x; q < kBins * kCopies; q += kSortBlock) s_hist[q] = 0;
+    if (threadIdx.x == 0) s_set = s_clear = 0;
+    __syncthreads();
+    const uint32_t tile1 = min((blockIdx.x + 1) * a.group_tiles, a.n_tiles);
+    uint32_t set = 0, clear = 0;
+    for (uint32_t tile = blockIdx.x * a.group_tiles; tile < tile1; ++tile) {
         const uint32_t i0 = tile * kSortTile + threadIdx.x;
-        int32_t key[kSortItems];
+        int32_t key[kCountItems];
 #pragma unroll
-        for (int k = 0; k < kSortItems; ++k) key[k] = keys[i0 + k * kSortBlock < a.n ? i0 + k * kSortBlock : a.n - 1];
-        uint32_t set = 0, clear = 0;
+        for (int k = 0; k < kCountItems; ++k) key[k] = keys[i0 + k * kSortBlock < a.n ? i0 + k * kSortBlock : a.n - 1];
 #pragma unroll
-        for (int k = 0; k < kSortItems; ++k) {
+        for (int k = 0; k < kCountItems; ++k) {
             set |= static_cast<uint32_t>(key[k]);
             clear |= ~static_cast<uint32_t>(key[k]);
-            const uint32_t bin = bin_of(key[k], a.pass);
-            uint64_t rest = __ballot(i0 + k * kSortBlock < a.n);
-            // Most counts are one of a few small numbers: the bins of the first lanes left are counted for the whole
-            // wave at once, so that the lanes do not queue up at one LDS word.
+            if (i0 + k * kSortBlock < a.n) atomicAdd(s_hist + bin_of(key[k], a.pass) * kCopies + threadIdx.x % kCopies, 1u);
+        }
+    }
+    if (a.pass == 0) {
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                if (rest == 0) break;
-                const uint32_t lead = static_cast<uint32_t>(__ffsll(static_cast<long long>(rest)) - 1);
-                const uint32_t lead_bin = lane_value(bin, lead);
-                const uint64_t same = __ballot(bin == lead_bin) & rest;
-                if (static_cast<uint32_t>(lane_id()) == lead) atomicAdd(s_hist + bin, static_cast<uint32_t>(__popcll(same)));
-                rest &= ~same;
-            }
-            if ((rest >> lane_id()) & 1u) atomicAdd(s_hist + bin, 1u);
+        for (int d = 32; d >= 1; d >>= 1) {
+            set |= __shfl_xor(set, d, kWave);
+            clear |= __shfl_xor(clear, d, kWave);
         }
-        if (a.pass == 0) {
+        if (lane_id() == 0) {
+            atomicOr(&s_set, set);
+            atomicOr(&s_clear, clear);
+        }
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < kBins; q += kSortBlock) {
+        uint32_t sum = 0;
 #pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) {
-                set |= __shfl_xor(set, d, kWave);
-                clear |= __shfl_xor(clear, d, kWave);
-            }
-            if (lane_id() == 0) {
-                atomicOr(&s_set, set);
-                atomicOr(&s_clear, clear);
-            }
-        }
-        __syncthreads();
-        for (int q = threadIdx.x; q < kBins; q += kSortBlock) a.tile_counts[static_cast<size_t>(tile) * kBins + q] = s_hist[q];
-        if (a.pass == 0 && threadIdx.x == 0) {
-            a.tile_bits[2 * tile] = s_set;
-            a.tile_bits[2 * tile + 1] = s_clear;
-        }
-        __syncthreads();
+        for (int k = 0; k < kCopies; ++k) sum += s_hist[q * kCopies + k];
+        a.group_counts[static_cast<size_t>(blockIdx.x) * kBins + q] = sum;
+    }
+    if (a.pass == 0 && threadIdx.x == 0) {
+        a.group_bits[2 * blockIdx.x] = s_set;
+        a.group_bits[2 * blockIdx.x + 1] = s_clear;
     }
 }
 
-// Workgroup b: the bins [16 b, 16 b + 16) over all tiles, by 64 walkers that take consecutive tiles each.  In the first
+// Workgroup b: the bins [16 b, 16 b + 16) over all groups, by 64 walkers that take consecutive groups each.  In the first
 // pass one workgroup more gathers which bits vary.
 __global__ __launch_bounds__(kSortBlock) void sort_scan_kernel(SortArgs a) {
     __shared__ uint32_t s_sum[kWalkers][kScanBins + 1];
@@ -158,9 +164,9 @@ __global__ __launch_bounds__(kSortBlock) void sort_scan_kernel(SortArgs a) {
         if (threadIdx.x == 0) s_set = s_clear = 0;
         __syncthreads();
         uint32_t set = 0, clear = 0;
-        for (uint32_t t = threadIdx.x; t < a.n_tiles; t += kSortBlock) {
-            set |= a.tile_bits[2 * t];
-            clear |= a.tile_bits[2 * t + 1];
+        for (uint32_t t = threadIdx.x; t < a.n_groups; t += kSortBlock) {
+            set |= a.group_bits[2 * t];
+            clear |= a.group_bits[2 * t + 1];
         }
         atomicOr(&s_set, set);
         atomicOr(&s_clear, clear);
@@ -170,47 +176,56 @@ __global__ __launch_bounds__(kSortBlock) void sort_scan_kernel(SortArgs a) {
     }
     if (a.pass > 0 && !SortStep(a.pass, *a.varying).active) return;
     const uint32_t walker = threadIdx.x / kScanBins, bin = threadIdx.x % kScanBins;
-    const uint32_t per = (a.n_tiles + kWalkers - 1) / kWalkers;
-    const uint32_t t0 = walker * per < a.n_tiles ? walker * per : a.n_tiles, t1 = t0 + per < a.n_tiles ? t0 + per : a.n_tiles;
-    uint32_t* column = a.tile_counts + blockIdx.x * kScanBins + bin;
-    uint32_t sum = 0;
-#pragma unroll 8
-    for (uint32_t t = t0; t < t1; ++t) sum += column[static_cast<size_t>(t) * kBins];
+    constexpr uint32_t kPer = kSortMaxGroups / kWalkers;
+    uint32_t* column = a.group_counts + blockIdx.x * kScanBins + bin;
+    uint32_t v[kPer], sum = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {            // (unguarded: all in flight together)
+        const uint32_t g = walker * kPer + q;
+        v[q] = column[static_cast<size_t>(g < a.n_groups ? g : 0) * kBins];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        if (walker * kPer + q >= a.n_groups) v[q] = 0;
+        sum += v[q];
+    }
     s_sum[walker][bin] = sum;
     __syncthreads();
     {
         const uint32_t b = static_cast<uint32_t>(wave_id()), w = static_cast<uint32_t>(lane_id());      // one wave per bin
-        const uint32_t v = s_sum[w][b], inc = dpp_inclusive_scan(v);
-        s_sum[w][b] = inc - v;
+        const uint32_t mine = s_sum[w][b], inc = dpp_inclusive_scan(mine);
+        s_sum[w][b] = inc - mine;
         if (w == kWalkers - 1) a.totals[blockIdx.x * kScanBins + b] = inc;
     }
     __syncthreads();
     uint32_t run = s_sum[walker][bin];
-#pragma unroll 8
-    for (uint32_t t = t0; t < t1; ++t) {
-        const uint32_t v = column[static_cast<size_t>(t) * kBins];
-        column[static_cast<size_t>(t) * kBins] = run;
-        run += v;
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        const uint32_t g = walker * kPer + q;
+        if (g < a.n_groups) column[static_cast<size_t>(g) * kBins] = run;
+        run += v[q];
     }
 }
 
-__global__ __launch_bounds__(kSortBlock) void sort_scatter_kernel(SortArgs a) {
+__global__ __launch_bounds__(kPlaceBlock) void sort_scatter_kernel(SortArgs a) {
     // the ranks' counters (one per wave and bin) and, once the ranks are known, the tile in order share their memory
+    // (pointers by condition and no a.keys[i], or the arguments end up in scratch memory)
     __shared__ union {
-        uint16_t count[kSortWaves][kBins];
-        struct { int32_t key[kSortTile], val[kSortTile]; } out;
+        uint16_t count[kPlaceWaves][kBins];
+        unsigned long long four[kPlaceWaves][kBins / 4];      // a thread's bins
+        uint32_t out[kSortTile];                              // {bin : 11 | place in the tile : 13}
     } s;
-    __shared__ uint32_t s_start[kBins];          // where a bin begins in the tile in order
-    __shared__ uint32_t s_to[kBins];             // ... and in the output, minus that
-    __shared__ uint32_t s_wave[kSortWaves];
+    __shared__ uint32_t s_to[kBins];                          // where a bin goes in the output, minus where it begins in the tile
+    __shared__ int32_t s_word[kSortTile];
+    __shared__ uint32_t s_wave[kPlaceWaves];
     const SortStep step(a.pass, *a.varying);
     if (!step.active) return;
-    const int32_t* keys_in = step.before == 0 ? a.counts : a.keys[(step.before - 1) & 1];
+    const int32_t* keys_in = step.before == 0 ? a.counts : step.before == 1 ? a.keys[0] : a.keys[1];
     const int32_t* vals_in = step.before == 0 ? nullptr : step.to_order ? a.vals1 : a.order;
-    int32_t* keys_out = step.last ? nullptr : a.keys[step.before & 1];
+    int32_t* keys_out = step.last ? nullptr : step.before == 0 ? a.keys[0] : a.keys[1];
     int32_t* vals_out = step.to_order ? a.order : a.vals1;
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(wave_id())), lane = static_cast<uint32_t>(lane_id());
-    constexpr int kPer = kBins / kSortBlock;     // bins per thread: consecutive ones
+    constexpr int kPer = kBins / kPlaceBlock;    // bins per thread: consecutive ones
     // exclusive sums over the bins of the whole list
     const auto scan_bins = [&](const uint32_t (&v)[kPer], uint32_t (&before)[kPer]) {
         uint32_t mine = 0;
@@ -219,7 +234,7 @@ __global__ __launch_bounds__(kSortBlock) void sort_scatter_kernel(SortArgs a) {
         const uint32_t inc = dpp_inclusive_scan(mine);
         if (lane == kWave - 1) s_wave[wave] = inc;
         __syncthreads();
-        const uint32_t w = lane < kSortWaves ? s_wave[lane] : 0u;
+        const uint32_t w = lane < kPlaceWaves ? s_wave[lane] : 0u;
         const uint32_t upto = dpp_inclusive_scan(w);
         uint32_t at = lane_value(upto, wave) - lane_value(w, wave) + inc - mine;
 #pragma unroll
@@ -229,95 +244,99 @@ __global__ __launch_bounds__(kSortBlock) void sort_scatter_kernel(SortArgs a) {
         }
         __syncthreads();
     };
-    uint32_t total[kPer], base[kPer];
+    const uint32_t n = a.n;
+    uint32_t total[kPer], next[kPer];            // next: where the tile's pairs of the bin go in the output
 #pragma unroll
     for (int q = 0; q < kPer; ++q) total[q] = a.totals[threadIdx.x * kPer + q];
-    scan_bins(total, base);
-    for (uint32_t tile = blockIdx.x; tile < a.n_tiles; tile += gridDim.x) {
-        uint32_t earlier[kPer];                  // pairs of the bin in the tiles before
+    scan_bins(total, next);
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) earlier[q] = a.tile_counts[static_cast<size_t>(tile) * kBins + threadIdx.x * kPer + q];
-        // a wave owns 512 consecutive pairs, 64 per round
-        const uint32_t i0 = tile * kSortTile + wave * (kSortItems * kWave) + lane;
-        int32_t key[kSortItems], val[kSortItems];
+    for (int q = 0; q < kPer; ++q) next[q] += a.group_counts[static_cast<size_t>(blockIdx.x) * kBins + threadIdx.x * kPer + q];
+    const uint32_t tile1 = min((blockIdx.x + 1) * a.group_tiles, a.n_tiles);
+    for (uint32_t tile = blockIdx.x * a.group_tiles; tile < tile1; ++tile) {
+        // a wave owns 1024 consecutive pairs, 64 per round
+        const uint32_t base = tile * kSortTile, here = min(n - base, static_cast<uint32_t>(kSortTile));
+        const uint32_t at0 = wave * (kPlaceItems * kWave) + lane;
+        uint32_t item[kPlaceItems];              // the bin, then {bin : 11 | rank : 13}
 #pragma unroll
-        for (int k = 0; k < kSortItems; ++k) {
-            const uint32_t i = i0 + k * kWave < a.n ? i0 + k * kWave : a.n - 1;
-            key[k] = keys_in[i];
-            val[k] = vals_in ? vals_in[i] : static_cast<int32_t>(i);
-        }
-        for (uint32_t q = threadIdx.x; q < kSortWaves * kBins / 2; q += kSortBlock) reinterpret_cast<uint32_t*>(s.count)[q] = 0;
+        for (int k = 0; k < kPlaceItems; ++k) item[k] = bin_of(keys_in[base + (at0 + k * kWave < here ? at0 + k * kWave : 0)], a.pass);
+#pragma unroll
+        for (int w = 0; w < kPlaceWaves; ++w) s.four[w][threadIdx.x] = 0;
         __syncthreads();
-        uint32_t rank[kSortItems];
 #pragma unroll
-        for (int k = 0; k < kSortItems; ++k) {
-            const uint32_t bin = bin_of(key[k], a.pass);
-            uint64_t peers = __ballot(i0 + k * kWave < a.n);
+        for (int k = 0; k < kPlaceItems; ++k) {
+            const uint32_t bin = item[k];
+            const uint64_t there = __ballot(at0 + k * kWave < here);
+            uint32_t lo = static_cast<uint32_t>(there), hi = static_cast<uint32_t>(there >> 32);
 #pragma unroll
-            for (int b = 0; b < kDigitBits; ++b) {
-                const uint64_t ones = __ballot((bin >> b) & 1u);
-                peers &= (bin >> b) & 1u ? ones : ~ones;
+            for (int b = 0; b < kDigitBits; ++b) {                // peers: the lanes that agree on the bit (four instructions)
+                const uint32_t mine = static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(bin), b, 1));
+                const uint64_t ones = __ballot(mine != 0);
+                lo &= ~(static_cast<uint32_t>(ones) ^ mine);
+                hi &= ~(static_cast<uint32_t>(ones >> 32) ^ mine);
             }
+            const uint64_t peers = (static_cast<uint64_t>(hi) << 32) | lo;
             const uint32_t among = rank_in_mask(peers);
             const uint32_t seen = s.count[wave][bin];
-            rank[k] = seen + among;
+            item[k] = (bin << kPlaceBits) | (seen + among);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            if (among == 0 && i0 + k * kWave < a.n) s.count[wave][bin] = static_cast<uint16_t>(seen + __popcll(peers));
+            if (among == 0 && at0 + k * kWave < here) s.count[wave][bin] = static_cast<uint16_t>(seen + __popcll(peers));
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
-        uint32_t in_tile[kPer], start[kPer];
+        // four counters of 16 bits at a time: their sums over the waves, and where the bins begin, stay below 2^16
+        unsigned long long sum = 0, before[kPlaceWaves];
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const uint32_t bin = threadIdx.x * kPer + q;
-            uint32_t sum = 0;
-#pragma unroll
-            for (int w = 0; w < kSortWaves; ++w) {
-                const uint32_t c = s.count[w][bin];
-                s.count[w][bin] = static_cast<uint16_t>(sum);
-                sum += c;
-            }
-            in_tile[q] = sum;
+        for (int w = 0; w < kPlaceWaves; ++w) {
+            before[w] = sum;
+            sum += s.four[w][threadIdx.x];
         }
+        uint32_t in_tile[kPer], start[kPer];
+        unsigned long long begins = 0;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) in_tile[q] = static_cast<uint32_t>(sum >> (16 * q)) & 0xffffu;
         scan_bins(in_tile, start);
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
-            const uint32_t bin = threadIdx.x * kPer + q;
-            s_start[bin] = start[q];
-            s_to[bin] = base[q] + earlier[q] - start[q];
+            begins |= static_cast<unsigned long long>(start[q]) << (16 * q);
+            s_to[threadIdx.x * kPer + q] = next[q] - start[q];
+            next[q] += in_tile[q];
         }
-        __syncthreads();
-        uint32_t place[kSortItems];
 #pragma unroll
-        for (int k = 0; k < kSortItems; ++k) {
-            const uint32_t bin = bin_of(key[k], a.pass);
-            place[k] = s_start[bin] + s.count[wave][bin] + rank[k];
+        for (int w = 0; w < kPlaceWaves; ++w) s.four[w][threadIdx.x] = before[w] + begins;
+        __syncthreads();
+        uint32_t place[kPlaceItems];
+#pragma unroll
+        for (int k = 0; k < kPlaceItems; ++k) place[k] = s.count[wave][item[k] >> kPlaceBits] + (item[k] & (kSortTile - 1));
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPlaceItems; ++k)
+            if (at0 + k * kWave < here && place[k] < kSortTile) s.out[place[k]] = (item[k] & ~(kSortTile - 1u)) | (at0 + k * kWave);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kPlaceItems; ++k) {
+            const uint32_t p = threadIdx.x + k * kPlaceBlock, e = s.out[p < here ? p : 0], to = s_to[e >> kPlaceBits] + p;
+            if (p < here && to >= n) raise(a.err, kErrInternal);         // never, unless the counts changed between the kernels
+            if (p < here && to < n && !vals_in) vals_out[to] = static_cast<int32_t>(base + (e & (kSortTile - 1)));
         }
-        __syncthreads();
+        // The other words of the pairs, where there are any: read in order, picked from LDS.
+        const auto move = [&](const int32_t* in, int32_t* out) {
 #pragma unroll
-        for (int k = 0; k < kSortItems; ++k) {
-            if (i0 + k * kWave < a.n && place[k] < kSortTile) {
-                s.out.key[place[k]] = key[k];
-                s.out.val[place[k]] = val[k];
+            for (int k = 0; k < kPlaceItems; ++k) {
+                const uint32_t p = threadIdx.x + k * kPlaceBlock;
+                s_word[p] = in[base + (p < here ? p : 0)];
             }
-        }
-        __syncthreads();
-        const uint32_t here = a.n - tile * kSortTile < kSortTile ? a.n - tile * kSortTile : kSortTile;
+            __syncthreads();
 #pragma unroll
-        for (int k = 0; k < kSortItems; ++k) {
-            const uint32_t p = threadIdx.x + k * kSortBlock;
-            if (p >= here) continue;
-            const int32_t kk = s.out.key[p], vv = s.out.val[p];
-            const uint32_t to = s_to[bin_of(kk, a.pass)] + p;
-            if (to < a.n) {                              // always, unless the counts changed between the kernels
-                vals_out[to] = vv;
-                if (keys_out) keys_out[to] = kk;
-            } else {
-                raise(a.err, kErrInternal);
+            for (int k = 0; k < kPlaceItems; ++k) {
+                const uint32_t p = threadIdx.x + k * kPlaceBlock, e = s.out[p < here ? p : 0], to = s_to[e >> kPlaceBits] + p;
+                if (p < here && to < n) out[to] = s_word[e & (kSortTile - 1)];
             }
-        }
+            __syncthreads();
+        };
+        if (vals_in) move(vals_in, vals_out);
+        if (keys_out) move(keys_in, keys_out);
         __syncthreads();
     }
 }
@@ -339,17 +358,19 @@ hipError_t launch_hotness_add(hipStream_t stream, const int32_t* ids, Count n, i
 
 namespace {
 struct SortLayout {              // scratch of the hotness order, in bytes
-    size_t tiles, totals, varying, bits, counts, keys1, keys2, vals1, bytes;
+    size_t tiles, group_tiles, groups, totals, varying, bits, counts, keys1, keys2, vals1, bytes;
     explicit SortLayout(int64_t n) {
         const auto up = [](size_t b) { return (b + 255) / 256 * 256; };
         tiles = static_cast<size_t>((n + kSortTile - 1) / kSortTile);
         if (tiles < 1) tiles = 1;
+        group_tiles = (tiles + kSortMaxGroups - 1) / kSortMaxGroups;
+        groups = (tiles + group_tiles - 1) / group_tiles;
         const size_t ints = up(sizeof(int32_t) * static_cast<size_t>(n));
         totals = 0;
         varying = totals + up(sizeof(uint32_t) * kBins);
         bits = varying + 256;
-        counts = bits + up(sizeof(uint32_t) * 2 * tiles);
-        keys1 = counts + up(sizeof(uint32_t) * kBins * tiles);
+        counts = bits + up(sizeof(uint32_t) * 2 * groups);
+        keys1 = counts + up(sizeof(uint32_t) * kBins * groups);
         keys2 = keys1 + ints;
         vals1 = keys2 + ints;
         bytes = vals1 + ints;
@@ -372,9 +393,11 @@ hipError_t launch_hotness_order(hipStream_t stream, const int32_t* counts, int64
     a.order = order;
     a.n = static_cast<uint32_t>(n_nodes);
     a.n_tiles = static_cast<uint32_t>(at.tiles);
-    a.tile_counts = reinterpret_cast<uint32_t*>(p + at.counts);
+    a.group_tiles = static_cast<uint32_t>(at.group_tiles);
+    a.n_groups = static_cast<uint32_t>(at.groups);
+    a.group_counts = reinterpret_cast<uint32_t*>(p + at.counts);
     a.totals = reinterpret_cast<uint32_t*>(p + at.totals);
-    a.tile_bits = reinterpret_cast<uint32_t*>(p + at.bits);
+    a.group_bits = reinterpret_cast<uint32_t*>(p + at.bits);
     a.varying = reinterpret_cast<uint32_t*>(p + at.varying);
     a.err = err;
     // With one pass or three the first one already writes to `order`.  If that is (part of) the counters' own memory, the pass
@@ -385,12 +408,12 @@ hipError_t launch_hotness_order(hipStream_t stream, const int32_t* counts, int64
         if (e != hipSuccess) return e;
         a.counts = a.keys[1];
     }
-    const dim3 tiles(a.n_tiles < kSortMaxWorkgroups ? a.n_tiles : kSortMaxWorkgroups), block(kSortBlock);
+    const dim3 groups(a.n_groups), block(kSortBlock);
     for (int pass = 0; pass < kSortPasses; ++pass) {
         a.pass = pass;
-        hipLaunchKernelGGL(sort_count_kernel, tiles, block, 0, stream, a);
+        hipLaunchKernelGGL(sort_count_kernel, groups, block, 0, stream, a);
         hipLaunchKernelGGL(sort_scan_kernel, dim3(kBins / kScanBins + (pass == 0 ? 1 : 0)), block, 0, stream, a);
-        hipLaunchKernelGGL(sort_scatter_kernel, tiles, block, 0, stream, a);
+        hipLaunchKernelGGL(sort_scatter_kernel, groups, dim3(kPlaceBlock), 0, stream, a);
     }
     return hipGetLastError();
 }
