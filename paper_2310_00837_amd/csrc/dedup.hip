@@ -24,7 +24,8 @@
 // little off the global table, while every entry paid an LDS probe and a
 // barrier more.  A long stand-alone list is another matter: there a workgroup
 // goes through many steps of the list and remembers what it has met
-// (dedup_insert_long_kernel).
+// (dedup_insert_long_kernel), or the list is taken apart by hash first
+// (dedup_split_kernel).
 #include "kernels.hpp"
 
 namespace helios {
@@ -52,14 +53,12 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_kernel(const int32_t* __r
     }
 }
 
-// The same for a long list: few workgroups go through it in steps, and each remembers the slots of recent IDs in LDS, one per
-// cell; an ID that an earlier step of the workgroup has inserted needs no insertion of its own (the steps go through the list
-// in order, so that occurrence lies before).  Bound by the atomics: 25 random ones per ns, and about 10 ns each for those that
-// meet on one address, as the repeats of a hub do.  Measured, 1.1 M IDs: of a power law 67.6 us with one step for every ID, 54.6
-// with 512 workgroups, 57.7 with 1024, 62.4 with 2048; uniform over 50 M nodes the whole call 103.6 -> 105.4 us; 300 k IDs 50.7
-// -> 45.7 us.  At 140 k IDs (31.9 against 30.4 us) it does not pay any more.
+// The same for a list that is too long to be taken apart (below): few workgroups go through it in steps, and each remembers the slots
+// of recent IDs in LDS, one per cell; an ID that an earlier step of the workgroup has inserted needs no insertion of its own (the
+// steps go through the list in order, so that occurrence lies before).  Bound by the atomics: 25 random ones per ns, and about 10 ns
+// each for those that meet on one address, as the repeats of a hub do.  Measured, 1.1 M IDs of a power law: 67.6 us with one step for
+// every ID, 54.6 with 512 workgroups, 57.7 with 1024, 62.4 with 2048.
 constexpr int kRecent = 2048;
-constexpr int64_t kInsertLong = 262144;
 constexpr unsigned kInsertLongWorkgroups = 512;
 __global__ __launch_bounds__(kBlock) void dedup_insert_long_kernel(const int32_t* __restrict__ ids, Count n_in, int64_t n_nodes, DedupScratch s,
                                                                    int32_t* err) {
@@ -91,6 +90,272 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_long_kernel(const int32_t
             s.slot_of[j] = slot;
         }
         __syncthreads();
+    }
+}
+
+// ---- a long list by parts, without the table
+//
+// The inserts of a long list are bound by the atomics of the memory (25 a ns) and its compaction by as many random reads.  So a
+// list of kPartsMin to kPartsMax IDs is taken apart by hash instead, until a part fits a table in LDS:
+//   split     a tile of 4096 IDs drops its repeats (LDS table), and the rest is put into order of 512 buckets and written out so,
+//             with where the buckets begin;
+//   buckets   a workgroup per bucket gathers its pieces of all tiles, finds the first position of every ID in an LDS table, and
+//             leaves it where it has read the ID;
+//   compact   a tile's first positions go back into input order (LDS), and from there on it is the compaction as above.
+// All of it is streams in pieces of 32 bytes and more.  A tile drops its repeats so that no bucket is much longer than the
+// others: of an ID that fills the list a bucket gets one entry per tile.
+// Measured, whole call, us with the table / by parts, IDs by a power law (uniform ones differ by less than 4):
+//   65 k 23.9/24.5   100 k 26.0/25.2 (the line)   131 k 30.6/25.6   262 k 43/28.5   400 k 54/31.8   1.1 M 102/45.7   2 M 165/68
+// (1.1 M: split 12.2, buckets 14.1, compact 13.4, inverse 5.7); one ID throughout, 131 k: 1900/20.  Above 2 M a bucket would have more
+// IDs than half its table, and the list goes by the table.  256 buckets of 1024 threads with eight entries each, 64-bit words and
+// a second search for the answers: buckets 44 us at 1.1 M; linear probing and 512 threads in the split: 15.
+constexpr int kPartTile = 4096;
+constexpr int kPartBits = 9;
+constexpr int kParts = 1 << kPartBits;
+constexpr int kSplitBlock = 1024;
+constexpr int kSplitItems = kPartTile / kSplitBlock;
+constexpr int kMergeItems = kPartTile / kScanBlock;    // of the compaction
+constexpr int kBucketBlock = 1024;
+constexpr int kBucketItems = 4;                        // entries per thread that stay in registers
+constexpr uint32_t kPartSlots = 8192;                  // of an LDS table: keys, and the lowest position that holds the key
+constexpr uint32_t kPartProbes = 128;                  // more than that at one ID: a bucket's table counts as full
+constexpr uint32_t kBucketClasses = 1024;
+constexpr uint32_t kMaxPartTiles = 512;
+constexpr uint16_t kNoPlace = 0xffff;
+static_assert(kPartBits + 13 + 10 == 32 && kPartSlots == 1u << 13 && kBucketClasses == 1u << 10, "all bits of the hash tell IDs apart");
+static_assert(kPartsMax == static_cast<int64_t>(kMaxPartTiles) * kPartTile && kMaxPartTiles <= kBucketBlock, "a thread per tile");
+static_assert(kParts <= kSplitBlock && kMergeItems * kScanWaves <= kWave, "a thread per bucket; one step scans a tile");
+
+struct PartTable {
+    uint32_t key[kPartSlots], low[kPartSlots];         // ~0: empty (IDs are below 2^31)
+};
+__device__ __forceinline__ void part_clear(PartTable& t, uint32_t threads) {
+    typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+    words4* w = reinterpret_cast<words4*>(&t);
+    for (uint32_t q = threadIdx.x; q < sizeof(PartTable) / 16; q += threads) w[q] = words4{~0u, ~0u, ~0u, ~0u};
+}
+// the whole hash: the highest bits are the bucket, the next the place in the table, the lowest the class
+__device__ __forceinline__ uint32_t part_hash(uint32_t id) { return hash_id(id, 0xffffffffu); }
+// The tables are half full at most, and a wave waits for the longest of its 64 searches: steps of the ID's own, odd ones, which
+// come by every slot, keep those short.
+__device__ __forceinline__ uint32_t part_step(uint32_t h) { return (h << 1) | 1u; }
+// The ID's slot, claimed if need be; kNoSlot after probes_max others.  (A plain read before the atomic: the entries of a hub would
+// take their turns at its word.)
+__device__ __forceinline__ uint32_t part_slot(PartTable& t, uint32_t id, uint32_t h, uint32_t probes_max) {
+    uint32_t slot = (h >> 10) % kPartSlots;
+    for (uint32_t probes = 0; probes < probes_max; ++probes) {
+        uint32_t cur = __hip_atomic_load(t.key + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (cur == ~0u) cur = atomicCAS(t.key + slot, ~0u, id);
+        if (cur == ~0u || cur == id) return slot;
+        slot = (slot + part_step(h)) % kPartSlots;
+    }
+    return kNoSlot;
+}
+__device__ __forceinline__ uint32_t part_low(const PartTable& t, uint32_t slot) {
+    return __hip_atomic_load(t.low + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+__global__ __launch_bounds__(kSplitBlock) void dedup_split_kernel(const int32_t* __restrict__ ids, uint32_t n, int64_t n_nodes, PartScratch s,
+                                                                  int32_t* err) {
+    __shared__ union {
+        PartTable table;
+        struct { int32_t id[kPartTile]; uint16_t pos[kPartTile]; } out;
+    } m;
+    __shared__ uint32_t s_count[kParts], s_wave[kParts / kWave];
+    const uint32_t tile = blockIdx.x, base = tile * kPartTile;
+    int32_t id[kSplitItems];
+    uint32_t slot[kSplitItems], rank[kSplitItems];
+#pragma unroll
+    for (int k = 0; k < kSplitItems; ++k) {
+        const uint32_t j = base + k * kSplitBlock + threadIdx.x;
+        id[k] = ids[j < n ? j : base];
+    }
+    part_clear(m.table, kSplitBlock);
+    if (threadIdx.x < kParts) s_count[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSplitItems; ++k) {
+        const uint32_t p = k * kSplitBlock + threadIdx.x;
+        const bool here = base + p < n, node = id[k] >= 0 && static_cast<int64_t>(id[k]) < n_nodes;
+        if (here && !node) raise(err, kErrData);
+        slot[k] = kNoSlot;
+        if (!here || !node) continue;
+        const uint32_t at = part_slot(m.table, static_cast<uint32_t>(id[k]), part_hash(static_cast<uint32_t>(id[k])), kPartSlots);
+        slot[k] = at;                                  // (there is one: at most 4096 IDs in 8192 slots)
+        if (part_low(m.table, at) > p) atomicMin(m.table.low + at, p);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSplitItems; ++k) {
+        const uint32_t p = k * kSplitBlock + threadIdx.x;
+        const uint32_t low = slot[k] != kNoSlot ? part_low(m.table, slot[k]) : kNoPlace;
+        if (base + p < n) s.local[base + p] = static_cast<uint16_t>(low);
+        slot[k] = low == p ? part_hash(static_cast<uint32_t>(id[k])) >> (32 - kPartBits) : kNoSlot;      // from here on the bucket
+        rank[k] = low == p ? atomicAdd(s_count + slot[k], 1u) : 0u;
+    }
+    __syncthreads();
+    const uint32_t mine = threadIdx.x < kParts ? s_count[threadIdx.x] : 0u, inc = dpp_inclusive_scan(mine);
+    if (threadIdx.x < kParts && lane_id() == kWave - 1) s_wave[wave_id()] = inc;
+    __syncthreads();
+    uint32_t at = inc - mine, there = 0;
+#pragma unroll
+    for (int w = 0; w < kParts / kWave; ++w) {
+        at += w < wave_id() ? s_wave[w] : 0u;
+        there += s_wave[w];
+    }
+    if (threadIdx.x < kParts) {
+        s_count[threadIdx.x] = at;
+        uint16_t* starts = s.starts + static_cast<size_t>(tile) * (kParts + 1);
+        starts[threadIdx.x] = static_cast<uint16_t>(at);
+        if (threadIdx.x == kParts - 1) starts[kParts] = static_cast<uint16_t>(there);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSplitItems; ++k) {
+        if (slot[k] == kNoSlot) continue;
+        const uint32_t to = s_count[slot[k]] + rank[k];
+        m.out.id[to] = id[k];
+        m.out.pos[to] = static_cast<uint16_t>(k * kSplitBlock + threadIdx.x);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kSplitItems; ++k) {
+        const uint32_t p = k * kSplitBlock + threadIdx.x;
+        if (p >= there) continue;
+        s.id[base + p] = m.out.id[p];
+        s.pos[base + p] = m.out.pos[p];
+    }
+}
+
+// One workgroup per bucket.  A bucket with more distinct IDs than its table takes is gone through class by class of the lowest
+// bits of the hash, a class for 2048 entries and then twice as many, until every class fits.  At 1024 classes it does: the hash is
+// one-to-one, so the IDs of a bucket and class then differ in the 13 bits between, which are their places in the table.
+__global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch s, uint32_t n_tiles) {
+    __shared__ PartTable table;
+    __shared__ uint32_t s_before[kMaxPartTiles], s_from[kMaxPartTiles];     // of a tile's piece: entries before it, where it begins
+    __shared__ uint32_t s_wave[kMaxPartTiles / kWave];
+    __shared__ uint32_t s_full;
+    const uint32_t t = threadIdx.x;
+    uint32_t len = 0, from = 0;
+    if (t < n_tiles) {
+        const uint16_t* starts = s.starts + static_cast<size_t>(t) * (kParts + 1) + blockIdx.x;
+        from = starts[0];
+        len = starts[1] - from;
+    }
+    const uint32_t inc = dpp_inclusive_scan(len);
+    if (t < kMaxPartTiles && lane_id() == kWave - 1) s_wave[wave_id()] = inc;
+    __syncthreads();
+    uint32_t at = inc - len, total = 0;
+#pragma unroll
+    for (int w = 0; w < static_cast<int>(kMaxPartTiles) / kWave; ++w) {
+        at += w < wave_id() ? s_wave[w] : 0u;
+        total += s_wave[w];
+    }
+    if (t < kMaxPartTiles) {
+        s_before[t] = t < n_tiles ? at : ~0u;
+        s_from[t] = t * kPartTile + from;
+    }
+    uint32_t place[kBucketItems], pos[kBucketItems], id[kBucketItems], slot[kBucketItems];
+    const uint32_t chunks = (total + kBucketBlock * kBucketItems - 1) / (kBucketBlock * kBucketItems);
+    for (uint32_t classes = 1;;) {
+        __syncthreads();
+        if (t == 0) s_full = 0;
+        for (uint32_t c = 0; c < classes; ++c) {
+            part_clear(table, kBucketBlock);
+            __syncthreads();
+            for (uint32_t step = 0; step < 2 * chunks; ++step) {            // first all inserts, then all answers
+                const bool answer = step >= chunks;
+                const uint32_t e0 = (answer ? step - chunks : step) * (kBucketBlock * kBucketItems) + t;
+                if (step == chunks) __syncthreads();
+                if (chunks > 1 || (step == 0 && c == 0)) {                  // (one chunk stays in registers)
+#pragma unroll
+                    for (int k = 0; k < kBucketItems; ++k) {
+                        const uint32_t e = e0 + k * kBucketBlock;
+                        uint32_t lo = 0;                                    // the last tile with at most e entries before its piece
+#pragma unroll
+                        for (uint32_t half = kMaxPartTiles / 2; half > 0; half /= 2)
+                            if (s_before[lo + half] <= e) lo += half;
+                        place[k] = e < total ? s_from[lo] + (e - s_before[lo]) : ~0u;
+                        pos[k] = lo * kPartTile;
+                    }
+#pragma unroll
+                    for (int k = 0; k < kBucketItems; ++k) {
+                        const uint32_t p = place[k] != ~0u ? place[k] : 0u;
+                        id[k] = static_cast<uint32_t>(s.id[p]);
+                        pos[k] += s.pos[p];
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < kBucketItems; ++k) {
+                    if (place[k] == ~0u) continue;
+                    const uint32_t h = part_hash(id[k]);
+                    if ((h & (classes - 1)) != c) continue;
+                    if (!answer || chunks > 1) slot[k] = part_slot(table, id[k], h, kPartProbes);
+                    if (slot[k] == kNoSlot) s_full = 1;
+                    else if (answer) s.first[place[k]] = part_low(table, slot[k]);
+                    else if (part_low(table, slot[k]) > pos[k]) atomicMin(table.low + slot[k], pos[k]);
+                }
+            }
+            __syncthreads();
+        }
+        if (s_full == 0) break;                                             // (the same in all threads: behind a barrier)
+        do classes *= 2;
+        while (classes < kBucketClasses && classes * 2048 < total);
+    }
+}
+
+// The compaction of a list that came by parts: like compact_tiles, but the first positions come from the split tile.
+__global__ __launch_bounds__(kScanBlock) void dedup_compact_parts_kernel(CompactArgs a, PartScratch s) {
+    using Scan = TileScan<1, 1, kMergeItems>;
+    __shared__ typename Scan::Lds lds;
+    __shared__ uint32_t s_first[kPartTile];
+    const ScanState scan = scan_resolve(a.scan);
+    const uint32_t n = static_cast<uint32_t>(a.len.get()), n_tiles = (n + kPartTile - 1) / kPartTile;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && a.n_total_dev) *a.n_total_dev = n;
+    const uint32_t tile = Scan::take_ticket(scan, n_tiles, n_tiles, lds);          // (a workgroup per tile)
+    const uint32_t base = tile * kPartTile, there = s.starts[static_cast<size_t>(tile) * (kParts + 1) + kParts];
+    uint32_t first_of[kMergeItems], pos[kMergeItems], in_tile[kMergeItems];
+    int32_t id[kMergeItems];
+#pragma unroll
+    for (int k = 0; k < kMergeItems; ++k) {
+        const uint32_t p = k * kScanBlock + threadIdx.x, at = base + (p < there ? p : 0);
+        first_of[k] = s.first[at];
+        pos[k] = s.pos[at];
+        in_tile[k] = s.local[base + p < n ? base + p : base];
+        id[k] = a.ids[base + p < n ? base + p : base];
+        asm volatile("" : "+v"(id[k]));          // (read before the tile's total goes out: `unique` may lie over the IDs)
+    }
+#pragma unroll
+    for (int k = 0; k < kMergeItems; ++k)
+        if (k * kScanBlock + threadIdx.x < there) s_first[pos[k] % kPartTile] = first_of[k];
+    __syncthreads();
+    uint32_t totals[1][kMergeItems], before[1][kMergeItems], local[kMergeItems];
+    bool first[kMergeItems];
+#pragma unroll
+    for (int k = 0; k < kMergeItems; ++k) {
+        const uint32_t j = base + k * kScanBlock + threadIdx.x;
+        first_of[k] = in_tile[k] != kNoPlace ? s_first[in_tile[k] % kPartTile] : ~0u;        // (~0: no node)
+        first[k] = j < n && first_of[k] == j;
+        const uint64_t firsts = __ballot(first[k]);
+        totals[0][k] = static_cast<uint32_t>(__popcll(firsts));
+        local[k] = rank_in_mask(firsts);
+    }
+    Scan::run(scan, tile, totals, before, lds, a.err);
+#pragma unroll
+    for (int k = 0; k < kMergeItems; ++k) {
+        const uint32_t j = base + k * kScanBlock + threadIdx.x;
+        if (j >= n) continue;
+        const uint32_t at = lds.excl[0] + before[0][k] + local[k];
+        if (a.inverse) a.inverse[j] = first[k] ? static_cast<int32_t>(at) : first_of[k] < j ? repeat_of(first_of[k]) : -1;
+        if (!first[k]) continue;
+        a.s.index_of_first[j] = static_cast<int32_t>(at);
+        if (at < a.unique_cap) a.unique[at] = id[k];
+    }
+    if (tile == n_tiles - 1 && threadIdx.x == 0) {
+        const int64_t total = static_cast<int64_t>(lds.excl[0]) + lds.agg[0];
+        *a.n_unique_dev = total;
+        if (a.n_unique_out) *a.n_unique_out = total;
+        if (total > a.unique_cap) raise(a.err, kErrCapacity);
     }
 }
 
@@ -127,9 +392,18 @@ unsigned grid_for(int64_t n_max, unsigned cap_blocks) {
 
 hipError_t launch_dedup_insert(hipStream_t stream, const int32_t* ids, Count n, int64_t n_max, int64_t n_nodes,
                                const DedupScratch& s, int32_t* err) {
-    if (n_max > kInsertLong)
+    if (n_max > kPartsMax)
         hipLaunchKernelGGL(dedup_insert_long_kernel, dim3(kInsertLongWorkgroups), dim3(kBlock), 0, stream, ids, n, n_nodes, s, err);
     else hipLaunchKernelGGL(dedup_insert_kernel, dim3(grid_for(n_max, 4096)), dim3(kBlock), 0, stream, ids, n, n_nodes, s, err);
+    return hipGetLastError();
+}
+
+hipError_t launch_dedup_by_parts(hipStream_t stream, const CompactArgs& a, int64_t n, int64_t n_nodes, const PartScratch& s) {
+    if (n < 1 || n > kPartsMax) return hipErrorInvalidValue;
+    const unsigned tiles = static_cast<unsigned>((n + kPartTile - 1) / kPartTile);
+    hipLaunchKernelGGL(dedup_split_kernel, dim3(tiles), dim3(kSplitBlock), 0, stream, a.ids, static_cast<uint32_t>(n), n_nodes, s, a.err);
+    hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, stream, s, tiles);
+    hipLaunchKernelGGL(dedup_compact_parts_kernel, dim3(tiles), dim3(kScanBlock), 0, stream, a, s);
     return hipGetLastError();
 }
 

@@ -1015,18 +1015,16 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     DeviceGuard guard(c->device);
     int rc = ensure_capacity(c, n_ids);
     if (rc) return rc;
-    // the table that the context's next batch would use: not one that helios_make_blocks may still need
+    // the table (and its lists) that the context's next batch would use: not one that helios_make_blocks may still need
     const uint32_t which = static_cast<uint32_t>(c->batch_seq % kBatchTables);
-    rc = clean_for_call(c, static_cast<int>(which));
+    const bool by_parts = n_ids >= kPartsMin && n_ids <= kPartsMax;
+    rc = by_parts ? HELIOS_OK : clean_for_call(c, static_cast<int>(which));
     if (rc) return rc;
     uint32_t epoch;
     rc = next_epoch(c, &epoch);
     if (rc) return rc;
     const DedupScratch s{batch_table(c, which), dedup_slots(c, n_ids), batch_slots(c, which), batch_iof(c, which)};
-    c->batch_dirty[which] = s.n_slots;
-    c->batch_listed[which] = false;
     const Count n{nullptr, n_ids};
-    HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, c->err));
     CompactArgs a{};
     a.ids = ids;
     a.n_nodes = static_cast<uint32_t>(c->g.n_nodes);
@@ -1042,10 +1040,22 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     a.inverse = inverse;
     a.scan = scan_state(c, epoch, kScanRowsLook);
     a.err = c->err;
-    HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
-    // the call leaves its table as it found it: empty
     const InverseArgs inv{Count{c->cnt + kCntCat, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse, false,
                           Stamps{nullptr}};
+    if (by_parts) {
+        // (the tier lists are scratch of a lookup: no call leaves anything in them for another)
+        const PartScratch parts{c->list_slot[0], reinterpret_cast<uint16_t*>(c->list_pos[0]), reinterpret_cast<uint32_t*>(c->list_slot[1]),
+                                reinterpret_cast<uint16_t*>(c->list_pos[0]) + c->cap_ids, reinterpret_cast<uint16_t*>(c->list_pos[1])};
+        if (split_starts_bytes(n_ids) > static_cast<int64_t>(sizeof(int32_t)) * c->cap_ids) return fail(c, HELIOS_EINTERNAL, "scratch too small for a list by parts");
+        HIP_TRY(c, launch_dedup_by_parts(c->stream, a, n_ids, c->g.n_nodes, parts));
+        HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{nullptr, 0}, nullptr, 0));
+        return HELIOS_OK;
+    }
+    c->batch_dirty[which] = s.n_slots;
+    c->batch_listed[which] = false;
+    HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, c->err));
+    HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
+    // the call leaves its table as it found it: empty
     HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{s.table, s.n_slots}, nullptr, 0));
     c->batch_dirty[which] = 0;
     return HELIOS_OK;

@@ -126,6 +126,17 @@ hipError_t launch_dedup_insert(hipStream_t stream, const int32_t* ids, Count n, 
                                const DedupScratch& s, int32_t* err);
 // Second pass over the whole list.
 hipError_t launch_dedup_compact_plain(hipStream_t stream, const CompactArgs& a, int64_t n_max);
+// Both passes for a list of kPartsMin to kPartsMax IDs, without the table (see dedup.hip).  a.len is n, known on the host.
+constexpr int64_t kPartsMin = 98304, kPartsMax = 2097152;
+struct PartScratch {             // all of n entries, but starts: split_starts_bytes(n)
+    int32_t* id;                 // the distinct IDs of every tile in order of bucket
+    uint16_t* pos;               // their places in the tile
+    uint32_t* first;             // the first positions of those IDs in the list
+    uint16_t* local;             // for every input, the place in its tile where its ID is first, or 0xffff
+    uint16_t* starts;            // [tile][513]: where a bucket begins in the tile
+};
+constexpr int64_t split_starts_bytes(int64_t n) { return (n + 4095) / 4096 * 513 * 2; }
+hipError_t launch_dedup_by_parts(hipStream_t stream, const CompactArgs& a, int64_t n, int64_t n_nodes, const PartScratch& s);
 // The optional third pass (inv.inverse nullable), and in the same launch the emptying of a table and the zeroing of n_zero words,
 // neither of which that pass reads.
 hipError_t launch_dedup_end(hipStream_t stream, const InverseArgs& inv, int64_t n_max, const ClearJob& clear, unsigned long long* zero,

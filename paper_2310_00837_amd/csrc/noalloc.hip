@@ -41,7 +41,14 @@ constexpr size_t kOffTicket = kOffSmall, kOffCounters = kOffSmall + 64;
 constexpr uint32_t kEndZeroWords = static_cast<uint32_t>((kOffTicket + sizeof(unsigned long long) - kOffStatus) / sizeof(unsigned long long));
 static_assert(kOffStatus + kEndZeroWords * sizeof(unsigned long long) >= kOffTicket + sizeof(uint32_t) &&
               kOffStatus + kEndZeroWords * sizeof(unsigned long long) <= kOffCounters, "the ticket is in, the counters are not");
-constexpr size_t kScratchBytes = kOffSmall + kSmallBytes;
+// a long list is taken apart by hash in memory of its own (the table stays empty)
+constexpr size_t kOffPartId = kOffSmall + kSmallBytes;
+constexpr size_t kOffPartFirst = kOffPartId + sizeof(int32_t) * kMaxIds;
+constexpr size_t kOffPartPos = kOffPartFirst + sizeof(uint32_t) * kMaxIds;
+constexpr size_t kOffPartLocal = kOffPartPos + sizeof(uint16_t) * kMaxIds;
+constexpr size_t kOffPartStarts = kOffPartLocal + sizeof(uint16_t) * kMaxIds;
+constexpr size_t kScratchBytes = kOffPartStarts + static_cast<size_t>(split_starts_bytes(kMaxIds));
+static_assert(kMaxIds <= kPartsMax, "the longest list can be taken apart");
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -123,7 +130,6 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     // call keeps a captured call replayable
     const ScanState scan{status, ticket, kStride, 1u, nullptr};
     const Count n{nullptr, n_ids};
-    HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, c->err));
     CompactArgs a{};
     a.ids = ids;
     a.n_nodes = static_cast<uint32_t>(c->g.n_nodes);
@@ -139,10 +145,20 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     a.inverse = inverse;
     a.scan = scan;
     a.err = c->err;
-    HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
+    const bool by_parts = n_ids >= kPartsMin;
+    if (by_parts) {
+        const PartScratch parts{reinterpret_cast<int32_t*>(base + kOffPartId), reinterpret_cast<uint16_t*>(base + kOffPartPos),
+                                reinterpret_cast<uint32_t*>(base + kOffPartFirst), reinterpret_cast<uint16_t*>(base + kOffPartLocal),
+                                reinterpret_cast<uint16_t*>(base + kOffPartStarts)};
+        HIP_TRY(c, launch_dedup_by_parts(c->stream, a, n_ids, c->g.n_nodes, parts));
+    } else {
+        HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, c->err));
+        HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
+    }
     const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse, false,
                           Stamps{nullptr}};
-    HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{table, slots}, status, kEndZeroWords));
+    HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, by_parts ? ClearJob{nullptr, 0} : ClearJob{table, slots}, status,
+                                kEndZeroWords));
     // A call that is being captured has not run.  It found the array clean, and leaves it so, unless the filling was
     // captured with it: then the next call still has to do that.
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;

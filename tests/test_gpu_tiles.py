@@ -210,6 +210,60 @@ def test_gather_by_list_and_beside_the_lookup(h, helios, row_bytes, n, n_hbm, si
             assert torch.equal(got[:n_miss].long(), want.long()) and bool((got[n_miss:] == -9).all())
 
 
+def _hash(x):
+    h = x.astype(np.uint32) * np.uint32(0x9E3779B1)
+    h ^= h >> np.uint32(15)
+    h *= np.uint32(0x85EBCA77)
+    return h ^ (h >> np.uint32(13))
+
+
+@pytest.mark.parametrize("kind", ["one", "distinct", "one bucket", "one bucket and class", "bad", "few repeats far apart"])
+@pytest.mark.parametrize("n_ids", [98_303, 98_304, 98_305, 1_000_003, 2_097_152, 2_097_153])
+def test_dedup_of_long_lists_by_parts(h, helios, kind, n_ids):
+    """Long lists (98 304 to 2 097 152 IDs are taken apart by hash) whose parts are as uneven as can be, against numpy."""
+    print("by parts", kind, n_ids, flush=True)
+    rng = np.random.default_rng(n_ids)
+    n = 100_000_000
+    if kind == "one":
+        ids = np.full(n_ids, 77_777)
+    elif kind in ("distinct", "bad"):
+        ids = rng.permutation(n_ids) * 7
+    elif kind == "few repeats far apart":
+        ids = np.concatenate([np.arange(n_ids - n_ids // 9), np.arange(n_ids // 9)[::-1]])
+    else:
+        pool = np.arange(40_000_000)                      # about 78 k of them in a bucket (the hash's highest 9 bits)
+        in_bucket = _hash(pool) >> np.uint32(23) == 5
+        if kind == "one bucket and class":                # (its lowest bits)
+            in_bucket &= _hash(pool) % np.uint32(8) == 3
+        ids = rng.choice(pool[in_bucket], min(n_ids, 1_000_003))
+        ids = np.concatenate([ids, rng.integers(0, n, n_ids - ids.size)])
+    ids = ids.astype(np.int32)
+    if kind == "bad":
+        ids[[0, 5000, n_ids - 1]] = [-1, n, -2**31]
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    node = (ids >= 0) & (ids < n)
+    values, first, back = np.unique(ids[node], return_index=True, return_inverse=True)
+    order = np.argsort(first)
+    place = np.empty_like(order)
+    place[order] = np.arange(order.size)
+    want = np.full(n_ids, -1, np.int64)
+    want[node] = place[back]
+    t = torch.from_numpy(ids).cuda()
+    uniq = torch.full((n_ids,), -9, dtype=torch.int32, device="cuda")
+    inv, nu = torch.full_like(uniq, -9), torch.full((1,), -9, dtype=torch.int64).pin_memory()
+    for _ in range(2):
+        h.dedup(t, uniq, inv, nu)
+        if kind == "bad":
+            with pytest.raises(helios.HeliosError) as e:
+                h.sync()
+            assert e.value.code == helios.EDATA
+        else:
+            h.sync()
+        assert int(nu[0]) == values.size
+        assert np.array_equal(uniq[:values.size].cpu().numpy(), values[order])
+        assert np.array_equal(inv.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("n_ids", [1, 512, 513, 64 * 512 + 1, 5 * 64 * 512 + 77])
 @pytest.mark.parametrize("whole", [True, False])
 def test_gather_counts_with_all_nodes_in_hbm(h, helios, n_ids, whole):
