@@ -293,17 +293,19 @@ int64_t expected_hbm_rows(const helios_ctx* c) {
     return v > 0 ? v : 0;
 }
 
-// Workgroups of the HBM-tier copy role over a list of at most n_max rows.  Alone, the copy is quickest with one step
-// per workgroup (a grid that follows the expected length of the list).  The short lists of a gang's members are copied
-// at the same time, and together such grids would be several times what the chip holds at once: each member then
-// takes its share, at least 1024 workgroups, and loops (measured with four members of 34 k rows of 512 B: the four
-// copies take 31 us with 1024 workgroups each against 41 us with 4.4 k each).  A long list fills the chip by itself
-// and keeps its grid.
+// Workgroups of the HBM-tier copy role over a list of at most n_max rows.  By itself the copy is quickest with one step per
+// workgroup (a grid that follows the expected length of the list), but it then holds every place of the chip and fills the memory's
+// queues, and the launches of the batches beside it, chains of dependent reads, stand behind it: in a trace of three gangs in flight
+// every launch that began beside a copy ended when the copy did.  Five workgroups per CU (six for rows of more than 1 KB, which have
+// more in flight) copy as fast and leave room; the members of a gang share them.  Measured, three in flight (and one alone), us
+// with the grid that follows the list / with this one: three hops of 1024 seeds, 243 k rows of 512 bytes 93.7/83.8 (153/148), of 2 KB
+// 188/175 (245/248); 71 k rows of 400 bytes 52.9/50.1 (113/114), of 1 KB 66.1/60.7 (130/127); two members with rows of 1 KB 46.1/44.4, four
+// with rows of 512 bytes 58.5/57.8.  With four per CU 2 KB rows take 257 alone, with eight the 512-byte rows 90.
 unsigned hbm_role_blocks(const helios_ctx* c, int64_t n_max) {
     const int32_t chunks = c->row_bytes / 16;
     const unsigned alone = copy_role_blocks(chunks, false, n_max, c->hbm_blocks, expected_hbm_rows(c));
-    if (c->hbm_blocks > 0 || c->link_share <= 1 || alone >= 16384) return alone;
-    return std::min(alone, std::max(1024u, alone / static_cast<unsigned>(c->link_share)));
+    const unsigned most = chunks > 64 ? 6 * 256 : 5 * 256;
+    return c->hbm_blocks > 0 ? alone : std::min(alone, std::max(384u, most / static_cast<unsigned>(c->link_share)));
 }
 
 // The two row copies as kernels of their own over the per-tier lists that a lookup has left behind
