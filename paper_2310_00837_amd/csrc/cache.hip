@@ -1,6 +1,7 @@
 // Cache map and cache lookup.
 //
-// rank_build: rank[order[r]] = r, with a check that order is a permutation.
+// rank_build: rank[order[r]] = r, with a check that order is a permutation: by scattered stores, or, where there is scratch
+// memory for it, by way of buckets of neighbouring IDs.
 //
 // lookup_partition: one thread per ID reads rank[id] (one random 4-byte read),
 // classifies it into the HBM tier, the host tier or a miss by two compares, and
@@ -41,6 +42,110 @@ __global__ __launch_bounds__(kBlock) void rank_check_kernel(const int32_t* __res
             *holes = 1;
             raise(err, kErrData);
         }
+}
+
+// ---- the map by buckets
+//
+// The scattered stores are bound by the parts of lines that they write: a hotness order has the nodes of one count in a row, ascending, so
+// every line of the map is written in parts once per count, by whichever XCD, and the memory takes some 60 such requests a ns.  By
+// buckets every line is written once:
+//   split   every tile of 4096 ranks hands its (node, rank) pairs to the buckets of 2^shift neighbouring nodes that they belong to;
+//           a bucket's pairs lie where its nodes' ranks will (a permutation fills it exactly);
+//   place   a workgroup per bucket puts the ranks in order in LDS and writes them out, and a place that got none is a hole.
+// Measured, us by scattered stores / by buckets, for the hotness order of a power law (and a random order):
+//   1 M nodes 13.2/14.2 (18.4/19.9)   2 M 23.8/19.1 (34.5/30.5; the line)   3 M 33.7/23.4 (49.7/39.4)   8 M 80/38 (116/81)   16 M 144/69 (216/144)
+// An order that ascends by ID throughout, where every count is the same, is the one that scattered stores write whole lines for: 8 M 26.7/37.2.
+// The buckets take 8 bytes of scratch per node, so they are used where the context has that from making a hotness order; and above 16.7 M
+// nodes a bucket would not fit LDS.  (Four ranks per thread in the split; with eight 39.8 at 8 M, with sixteen 55: one chain of LDS additions.)
+constexpr int kInvertBlock = 1024;
+constexpr int kInvertItems = 4;
+constexpr uint32_t kInvertTile = kInvertBlock * kInvertItems;
+constexpr uint32_t kInvertBuckets = 512;
+constexpr uint32_t kInvertMaxShift = 15;               // 32768 ranks: 128 KB of LDS
+constexpr int64_t kInvertMin = 2000000;
+constexpr int64_t kInvertMax = static_cast<int64_t>(kInvertBuckets) << kInvertMaxShift;
+
+__global__ __launch_bounds__(kInvertBlock) void rank_zero_kernel(uint32_t* cursors, int64_t* holes) {
+    if (threadIdx.x < kInvertBuckets) cursors[threadIdx.x] = 0;
+    if (threadIdx.x == 0) *holes = 0;
+}
+
+__global__ __launch_bounds__(kInvertBlock) void rank_split_kernel(const int32_t* __restrict__ order, uint32_t n, uint32_t shift, uint32_t* cursors,
+                                                                  unsigned long long* pairs, int32_t* err) {
+    __shared__ uint32_t s_count[kInvertBuckets], s_base[kInvertBuckets], s_unused[kWave];
+    const uint32_t r0 = blockIdx.x * kInvertTile + threadIdx.x, lane = static_cast<uint32_t>(lane_id());
+    uint32_t v[kInvertItems], at[kInvertItems], lead[kInvertItems];
+    uint64_t same[kInvertItems];
+#pragma unroll
+    for (int k = 0; k < kInvertItems; ++k) v[k] = static_cast<uint32_t>(order[r0 + k * kInvertBlock < n ? r0 + k * kInvertBlock : 0]);
+    if (threadIdx.x < kInvertBuckets) s_count[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kInvertItems; ++k) {
+        const bool here = r0 + k * kInvertBlock < n;
+        if (here && v[k] >= n) raise(err, kErrData);
+        if (!here || v[k] >= n) v[k] = ~0u;
+        const uint32_t bucket = v[k] >> shift;
+        // In a hotness order the nodes of a wave are mostly neighbours: those that go where the first goes are counted at once, by
+        // the first.  (Every lane adds somewhere, so that the additions of all items are on their way together.)
+        const uint64_t there = __ballot(v[k] != ~0u);
+        lead[k] = there ? static_cast<uint32_t>(__ffsll(static_cast<long long>(there)) - 1) : 0u;
+        same[k] = __ballot(bucket == lane_value(bucket, lead[k])) & there;
+        const bool leads = lane == lead[k], counts = v[k] != ~0u && (leads || !((same[k] >> lane) & 1u));
+        at[k] = atomicAdd(counts ? s_count + bucket : s_unused + lane, leads ? static_cast<uint32_t>(__popcll(same[k])) : 1u);
+    }
+#pragma unroll
+    for (int k = 0; k < kInvertItems; ++k)
+        if ((same[k] >> lane) & 1u) at[k] = lane_value(at[k], lead[k]) + rank_in_mask(same[k]);
+    __syncthreads();
+    if (threadIdx.x < kInvertBuckets) {
+        const uint32_t c = s_count[threadIdx.x];
+        s_base[threadIdx.x] = c ? atomicAdd(cursors + threadIdx.x, c) : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kInvertItems; ++k) {
+        if (v[k] == ~0u) continue;
+        const uint32_t bucket = v[k] >> shift, place = s_base[bucket] + at[k], nodes = min(n - (bucket << shift), 1u << shift);
+        // (more pairs than nodes: some node is there twice; the bucket's workgroup then goes by the order itself)
+        if (place < nodes) pairs[(bucket << shift) + place] = (static_cast<unsigned long long>(v[k]) << 32) | (r0 + k * kInvertBlock);
+    }
+}
+
+template <uint32_t MOST>
+__global__ __launch_bounds__(kInvertBlock) void rank_place_kernel(const int32_t* __restrict__ order, uint32_t n, uint32_t shift,
+                                                                  const uint32_t* __restrict__ cursors, const unsigned long long* __restrict__ pairs,
+                                                                  int32_t* rank, int64_t* holes, int32_t* err) {
+    __shared__ int32_t s_rank[1u << MOST];               // (shift <= MOST)
+    const uint32_t first = blockIdx.x << shift, nodes = min(n - first, 1u << shift), count = cursors[blockIdx.x];
+    for (uint32_t i = threadIdx.x; i < nodes; i += kInvertBlock) s_rank[i] = -1;
+    __syncthreads();
+    if (count <= nodes) {
+        for (uint32_t i0 = threadIdx.x; i0 < count; i0 += kInvertTile) {
+            unsigned long long pair[kInvertItems];
+#pragma unroll
+            for (int k = 0; k < kInvertItems; ++k) pair[k] = pairs[first + (i0 + k * kInvertBlock < count ? i0 + k * kInvertBlock : 0)];
+#pragma unroll
+            for (int k = 0; k < kInvertItems; ++k) {
+                const uint32_t place = static_cast<uint32_t>(pair[k] >> 32) - first;
+                if (i0 + k * kInvertBlock < count && place < nodes) s_rank[place] = static_cast<int32_t>(static_cast<uint32_t>(pair[k]));
+            }
+        }
+    } else {                                             // (an order that is no permutation)
+        for (uint32_t r = threadIdx.x; r < n; r += kInvertBlock) {
+            const uint32_t place = static_cast<uint32_t>(order[r]) - first;
+            if (place < nodes) s_rank[place] = static_cast<int32_t>(r);
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < nodes; i += kInvertBlock) {
+        const int32_t r = s_rank[i];
+        rank[first + i] = r;
+        if (r < 0) {
+            *holes = 1;
+            raise(err, kErrData);
+        }
+    }
 }
 
 struct PartitionArgs {
@@ -237,7 +342,23 @@ unsigned grid_for(int64_t n, unsigned cap_blocks) {
 
 }  // namespace
 
-hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int64_t* holes, int32_t* err) {
+hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int64_t* holes, void* scratch,
+                             size_t scratch_bytes, int32_t* err) {
+    const size_t pairs_at = sizeof(uint32_t) * kInvertBuckets;
+    if (scratch && n_nodes >= kInvertMin && n_nodes <= kInvertMax && scratch_bytes >= pairs_at + sizeof(unsigned long long) * static_cast<size_t>(n_nodes)) {
+        uint32_t shift = kInvertMaxShift;                // 256 buckets or more, so that every CU has one or two
+        while (shift > 10 && (n_nodes >> shift) < 256) --shift;
+        const uint32_t n = static_cast<uint32_t>(n_nodes);
+        uint32_t* cursors = static_cast<uint32_t*>(scratch);
+        unsigned long long* pairs = reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(scratch) + pairs_at);
+        const dim3 block(kInvertBlock);
+        hipLaunchKernelGGL(rank_zero_kernel, dim3(1), block, 0, stream, cursors, holes);
+        hipLaunchKernelGGL(rank_split_kernel, dim3((n + kInvertTile - 1) / kInvertTile), block, 0, stream, order, n, shift, cursors, pairs, err);
+        const dim3 buckets((n + (1u << shift) - 1) >> shift);
+        if (shift == kInvertMaxShift) hipLaunchKernelGGL(rank_place_kernel<kInvertMaxShift>, buckets, block, 0, stream, order, n, shift, cursors, pairs, rank, holes, err);
+        else hipLaunchKernelGGL(rank_place_kernel<kInvertMaxShift - 1>, buckets, block, 0, stream, order, n, shift, cursors, pairs, rank, holes, err);
+        return hipGetLastError();
+    }
     const dim3 grid(grid_for(n_nodes, 8192)), block(kBlock);
     hipLaunchKernelGGL(rank_fill_kernel, grid, block, 0, stream, rank, n_nodes, holes);
     hipLaunchKernelGGL(rank_scatter_kernel, grid, block, 0, stream, order, n_nodes, rank, err);

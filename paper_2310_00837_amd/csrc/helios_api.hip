@@ -968,7 +968,8 @@ int helios_cache_build(helios_ctx* c, const int32_t* order, int64_t hbm_rows, in
         HIP_TRY(c, hipMalloc(&c->rank, sizeof(int32_t) * (n > 0 ? n : 1)));
         c->rank_cap = n;
     }
-    if (n > 0) HIP_TRY(c, launch_rank_build(c->stream, order, n, c->rank, c->cnt + kCntHoles, c->err));
+    // (the scratch of a hotness order that the context has made, if any)
+    if (n > 0) HIP_TRY(c, launch_rank_build(c->stream, order, n, c->rank, c->cnt + kCntHoles, c->hot_temp, c->hot_temp_bytes, c->err));
     c->n_hbm = hbm_rows;
     c->n_host = host_rows;
     c->row_bytes = row_bytes;

@@ -45,3 +45,57 @@ def test_hotness_order_in_the_memory_of_the_counts(oracle, kind, n):
         h.sync()
         assert np.array_equal(order.cpu().numpy(), want)
     h.close()
+
+
+@pytest.mark.parametrize("kind", ["random", "ascending", "descending", "hot", "repeats", "a bucket too full"])
+@pytest.mark.parametrize("n", [1_999_999, 2_000_000, 2_097_153, 8_388_607])      # buckets of 4096, 4096 (the line), 8192, 32768 nodes
+def test_cache_map_by_buckets(kind, n):
+    """The map that helios_cache_build makes of an order, read back by a gather whose rows are the ranks: by scattered stores below
+    2 M nodes and by buckets from there on, which use the scratch of a hotness order; and orders that are no permutation."""
+    from paper_2310_00837_amd import helios
+    print("cache map", kind, n, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    h = helios.Helios(0)
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    counts = torch.randint(0, 9, (n,), device="cuda", generator=gen).int()
+    order = torch.empty(n, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    h.hotness_order(counts, order)
+    h.sync()
+    if kind in ("random", "repeats", "a bucket too full"):
+        order = torch.randperm(n, device="cuda", generator=gen).int()
+    elif kind != "hot":
+        order = torch.arange(n, device="cuda").int()
+        if kind == "descending":
+            order = order.flip(0).contiguous()
+    bad = kind in ("repeats", "a bucket too full")
+    if kind == "repeats":
+        order[5::1000] = order[4::1000][:order[5::1000].numel()]
+        order[77] = -3
+    if kind == "a bucket too full":
+        order[1000:30_000] = 4099
+    at = torch.arange(n, device="cuda")
+    node = (order >= 0) & (order < n)
+    times = torch.zeros(n, dtype=torch.int64, device="cuda").index_add_(0, order[node].long(), torch.ones_like(at[node]))
+    table = torch.zeros((n, 2), dtype=torch.int64, device="cuda")
+    table[:, 0] = at
+    out = torch.empty((n, 2), dtype=torch.int64, device="cuda")
+    lists, stats = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(3)], torch.zeros(4, dtype=torch.int64).pin_memory()
+    ids = at.int()
+    for _ in range(2):
+        out.fill_(-9)
+        torch.cuda.synchronize()
+        h.cache_build(order, n, 0, 16, table, None, None)
+        h.gather(ids, out, *lists, stats)
+        if bad:
+            with pytest.raises(helios.HeliosError) as e:
+                h.sync()
+            assert e.value.code == helios.EDATA
+        else:
+            h.sync()
+        known = times > 0
+        assert stats.tolist() == [n, int(known.sum()), 0, 0]
+        got = out[:, 0]
+        assert torch.equal(order[got[known]].long(), at[known])          # (any of its ranks for a node that is there twice)
+        assert bool((got[~known] == -9).all())
+    h.close()
