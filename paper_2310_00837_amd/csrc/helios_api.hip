@@ -301,11 +301,16 @@ int64_t expected_hbm_rows(const helios_ctx* c) {
 // with the grid that follows the list / with this one: three hops of 1024 seeds, 243 k rows of 512 bytes 93.7/83.8 (153/148), of 2 KB
 // 188/175 (245/248); 71 k rows of 400 bytes 52.9/50.1 (113/114), of 1 KB 66.1/60.7 (130/127); two members with rows of 1 KB 46.1/44.4, four
 // with rows of 512 bytes 58.5/57.8.  With four per CU 2 KB rows take 257 alone, with eight the 512-byte rows 90.
-unsigned hbm_role_blocks(const helios_ctx* c, int64_t n_max) {
+// Not beside a copy over the link: the CUs that hold link waves copy next to nothing from HBM, so equal shares would wait for theirs
+// (243 k rows of 2 KB beside 13 k over the link, one batch alone 591/620 us), while short-lived workgroups go to the CUs that get on.  That
+// launch is bound by the link anyway.  The members of a gang then take their share of workgroups, at least 1024, unless the list
+// fills the chip by itself.
+unsigned hbm_role_blocks(const helios_ctx* c, int64_t n_max, bool beside_link) {
     const int32_t chunks = c->row_bytes / 16;
-    const unsigned alone = copy_role_blocks(chunks, false, n_max, c->hbm_blocks, expected_hbm_rows(c));
-    const unsigned most = chunks > 64 ? 6 * 256 : 5 * 256;
-    return c->hbm_blocks > 0 ? alone : std::min(alone, std::max(384u, most / static_cast<unsigned>(c->link_share)));
+    const unsigned alone = copy_role_blocks(chunks, false, n_max, c->hbm_blocks, expected_hbm_rows(c)), share = static_cast<unsigned>(c->link_share);
+    if (c->hbm_blocks > 0) return alone;
+    if (beside_link) return share <= 1 || alone >= 16384 ? alone : std::min(alone, std::max(1024u, alone / share));
+    return std::min(alone, std::max(384u, (chunks > 64 ? 6 * 256u : 5 * 256u) / share));
 }
 
 // The two row copies as kernels of their own over the per-tier lists that a lookup has left behind
@@ -585,7 +590,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             miss.stamps = take_stamps(c, HELIOS_ROLE_COPY_STANDIN, stage, miss_blocks);
         }
         if (c->n_hbm > 0 && u_max > 0) {
-            hbm_blocks = hbm_role_blocks(c, u_max);
+            hbm_blocks = hbm_role_blocks(c, u_max, c->n_host > 0 || served_max > 0);
             hbm = tier_copy_args(c, 0, nullptr, Count{c->cnt + kCntTier + 0, u_max}, b->out, take_stamps(c, HELIOS_ROLE_COPY_HBM, stage, hbm_blocks));
         }
         if (c->n_host > 0 && u_max > 0) {
