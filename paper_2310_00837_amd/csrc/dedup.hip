@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kSplitBlock) void dedup_split_kernel(const int32_t*
 // One workgroup per bucket.  A bucket with more distinct IDs than its table takes is gone through class by class of the lowest
 // bits of the hash, a class for 2048 entries and then twice as many, until every class fits.  At 1024 classes it does: the hash is
 // one-to-one, so the IDs of a bucket and class then differ in the 13 bits between, which are their places in the table.
-__global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch s, uint32_t n_tiles) {
+__global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch s, uint32_t n_tiles, int32_t* err) {
     __shared__ PartTable table;
     __shared__ uint32_t s_before[kMaxPartTiles], s_from[kMaxPartTiles];     // of a tile's piece: entries before it, where it begins
     __shared__ uint32_t s_wave[kMaxPartTiles / kWave];
@@ -238,9 +238,14 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
     const uint32_t t = threadIdx.x;
     uint32_t len = 0, from = 0;
     if (t < n_tiles) {
+        // (Calls that overlap on the static array of helios_dedup_noalloc may each have written one of the two words.  What lies
+        // within a tile is taken, so every place below is one of the tile's own.)
         const uint16_t* starts = s.starts + static_cast<size_t>(t) * (kParts + 1) + blockIdx.x;
-        from = starts[0];
-        len = starts[1] - from;
+        const uint32_t begin = starts[0], end = starts[1];
+        const bool piece = begin <= end && end <= kPartTile;
+        if (!piece) raise(err, kErrInternal);
+        from = piece ? begin : 0u;
+        len = piece ? end - begin : 0u;
     }
     const uint32_t inc = dpp_inclusive_scan(len);
     if (t < kMaxPartTiles && lane_id() == kWave - 1) s_wave[wave_id()] = inc;
@@ -402,7 +407,7 @@ hipError_t launch_dedup_by_parts(hipStream_t stream, const CompactArgs& a, int64
     if (n < 1 || n > kPartsMax) return hipErrorInvalidValue;
     const unsigned tiles = static_cast<unsigned>((n + kPartTile - 1) / kPartTile);
     hipLaunchKernelGGL(dedup_split_kernel, dim3(tiles), dim3(kSplitBlock), 0, stream, a.ids, static_cast<uint32_t>(n), n_nodes, s, a.err);
-    hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, stream, s, tiles);
+    hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, stream, s, tiles, a.err);
     hipLaunchKernelGGL(dedup_compact_parts_kernel, dim3(tiles), dim3(kScanBlock), 0, stream, a, s);
     return hipGetLastError();
 }

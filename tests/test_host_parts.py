@@ -1,0 +1,160 @@
+"""The kernels that take a long list apart by hash, compiled for the host: their results, and what they do with scratch memory that
+another call has written into (calls of helios_dedup_noalloc that overlap on one GPU share it, and may only spoil each other's
+results).  Every buffer lies between pages that cannot be touched, so an access out of bounds ends the program."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2310_00837_amd", "csrc")
+CLANG = "/opt/rocm/llvm/bin/clang++"
+PROGRAM = r"""
+#include "dedup.hip"
+#include <sys/mman.h>
+#include <string.h>
+#include <algorithm>
+#include <string>
+#include <unordered_map>
+using namespace helios;
+
+// n elements that end where a page that cannot be touched begins, with 32 GiB of such pages on either side
+template <class T>
+T* guarded(size_t n) {
+    const size_t guard = size_t{32} << 30, bytes = (n * sizeof(T) + 4095) / 4096 * 4096;
+    char* p = static_cast<char*>(mmap(nullptr, guard + bytes + guard, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0));
+    if (p == MAP_FAILED || mprotect(p + guard, bytes, PROT_READ | PROT_WRITE) != 0) abort();
+    memset(p + guard, 0x5a, bytes);
+    return reinterpret_cast<T*>(p + guard + bytes - n * sizeof(T));
+}
+
+constexpr int64_t kNodes = 0x7fffffff;
+struct Call {
+    int64_t n, tiles;
+    int32_t *ids, *unique, *inverse, *iof;
+    PartScratch s;
+    unsigned long long* status;
+    unsigned long long* ticket;
+    int64_t* counters;
+    int32_t* err;
+    CompactArgs a{};
+    explicit Call(const std::vector<int32_t>& list, int64_t cap, bool in_place = false) : n(list.size()), tiles((n + kPartTile - 1) / kPartTile) {
+        ids = guarded<int32_t>(n);
+        unique = in_place ? ids : guarded<int32_t>(cap);
+        inverse = guarded<int32_t>(n);
+        iof = guarded<int32_t>(n);
+        const size_t room = tiles * kPartTile;
+        s = PartScratch{guarded<int32_t>(room), guarded<uint16_t>(room), guarded<uint32_t>(room), guarded<uint16_t>(room),
+                        guarded<uint16_t>(split_starts_bytes(n) / 2)};
+        status = guarded<unsigned long long>(tiles);
+        ticket = guarded<unsigned long long>(1);
+        counters = guarded<int64_t>(2);
+        err = guarded<int32_t>(2);
+        memcpy(ids, list.data(), 4 * n);
+        memset(status, 0, 8 * tiles);
+        *ticket = 0;
+        err[0] = 0;
+        a.ids = ids;
+        a.n_nodes = kNodes;
+        a.len = Count{nullptr, n};
+        a.n_total_dev = counters;
+        a.s = DedupScratch{nullptr, 0, nullptr, iof};
+        a.unique = unique;
+        a.unique_cap = cap;
+        a.last = true;
+        a.n_unique_dev = counters + 1;
+        a.inverse = inverse;
+        a.scan = ScanState{status, reinterpret_cast<uint32_t*>(ticket), static_cast<uint32_t>(tiles), 1, nullptr};
+        a.err = err;
+    }
+    void split() const {
+        hipLaunchKernelGGL(dedup_split_kernel, dim3(tiles), dim3(kSplitBlock), 0, nullptr, a.ids, static_cast<uint32_t>(n), kNodes, s, err);
+    }
+    void buckets() const { hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, nullptr, s, static_cast<uint32_t>(tiles), err); }
+    void compact() const { hipLaunchKernelGGL(dedup_compact_parts_kernel, dim3(tiles), dim3(kScanBlock), 0, nullptr, a, s); }
+};
+
+void check(bool ok, const char* what) {
+    if (ok) return;
+    printf("wrong: %s\n", what);
+    exit(1);
+}
+
+void results(const std::vector<int32_t>& list, int64_t cap, bool in_place) {
+    Call c(list, cap, in_place);
+    launch_dedup_by_parts(nullptr, c.a, c.n, kNodes, c.s);
+    launch_dedup_end(nullptr, InverseArgs{Count{c.counters, c.n}, c.iof, BatchTables{}, nullptr, c.inverse, false, Stamps{nullptr}}, c.n,
+                     ClearJob{nullptr, 0}, nullptr, 0);
+    std::unordered_map<int32_t, int32_t> at;
+    std::vector<int32_t> want;
+    bool bad = false;
+    for (int64_t j = 0; j < c.n; ++j) {
+        if (list[j] < 0 || list[j] >= kNodes) {
+            bad = true;
+            check(c.inverse[j] == -1, "inverse of an entry that is no node");
+            continue;
+        }
+        if (at.emplace(list[j], static_cast<int32_t>(want.size())).second) want.push_back(list[j]);
+        check(c.inverse[j] == at[list[j]], "inverse");
+    }
+    const int64_t u = want.size();
+    check(c.counters[1] == u, "n_unique");
+    check(std::equal(want.begin(), want.begin() + std::min(u, cap), c.unique), "unique");
+    check(c.err[0] == (u > cap ? kErrCapacity : bad ? kErrData : 0), "error");
+    check(*c.ticket == 0, "ticket");
+}
+
+uint32_t next_random() {
+    static uint64_t x = 88172645463325252ull;
+    x ^= x << 13, x ^= x >> 7, x ^= x << 17;
+    return static_cast<uint32_t>(x >> 16);
+}
+int main(int argc, char** argv) {
+    const std::string what = argv[1];
+    if (what == "results") {
+        for (int64_t n : {1, 4096, 8195}) {
+            std::vector<int32_t> few(n);
+            for (int64_t j = 0; j < n; ++j) few[j] = next_random() % (n / 3 + 1);
+            if (n > 1) results(few, n, true);            // `unique` in the memory of the IDs
+            if (n != 4096) results(few, n / 5, false);
+            if (n == 4096) continue;
+            few[0] = -1, few[n / 2] = kNodes, few[n - 1] = INT32_MIN;
+            results(few, n, n % 2);
+        }
+    } else if (what == "pieces") {                       // the words of two calls side by side, as their waves write them, and any words
+        const int n = 32 * kPartTile;
+        std::vector<int32_t> one(n, 77), distinct(n);
+        for (int j = 0; j < n; ++j) distinct[j] = j;
+        Call a(distinct, n), b(one, n);
+        a.split();
+        b.split();
+        for (int64_t t = 0; t < a.tiles; ++t)
+            for (int w = 64; w <= kParts; ++w)
+                if ((w / 64) % 2) a.s.starts[t * (kParts + 1) + w] = b.s.starts[t * (kParts + 1) + w];
+        a.buckets();
+        check(a.err[0] == kErrInternal, "the call has to notice");
+        for (int64_t q = 0; q < split_starts_bytes(n) / 2; ++q) a.s.starts[q] = static_cast<uint16_t>(next_random());
+        a.buckets();
+        a.compact();                                     // (the bound of a tile's entries is such a word too)
+    } else {
+        return 3;
+    }
+    printf("ok\n");
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("parts")
+    (d / "main.cpp").write_text(PROGRAM)
+    subprocess.run([CLANG, "-std=c++17", "-O0", "-w", "-U_FORTIFY_SOURCE", "-I", os.path.join(HERE, "hip_on_the_host"), "-I", CSRC,
+                    str(d / "main.cpp"), "-o", str(d / "main")], check=True, timeout=100)
+    return str(d / "main")
+
+
+@pytest.mark.parametrize("what", ["results", "pieces"])
+def test_list_by_parts(program, what):
+    r = subprocess.run([program, what], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout == "ok\n", (r.returncode, r.stdout)
