@@ -318,6 +318,10 @@ __global__ __launch_bounds__(kScanBlock) void dedup_compact_parts_kernel(Compact
     const uint32_t n = static_cast<uint32_t>(a.len.get()), n_tiles = (n + kPartTile - 1) / kPartTile;
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.n_total_dev) *a.n_total_dev = n;
     const uint32_t tile = Scan::take_ticket(scan, n_tiles, n_tiles, lds);          // (a workgroup per tile)
+    if (tile >= n_tiles) {                       // (calls that overlap on the static array of helios_dedup_noalloc draw from one counter)
+        if (threadIdx.x == 0) raise(a.err, kErrInternal);
+        return;
+    }
     const uint32_t base = tile * kPartTile, there = s.starts[static_cast<size_t>(tile) * (kParts + 1) + kParts];
     uint32_t first_of[kMergeItems], pos[kMergeItems], in_tile[kMergeItems];
     int32_t id[kMergeItems];

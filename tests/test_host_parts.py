@@ -136,6 +136,18 @@ int main(int argc, char** argv) {
         for (int64_t q = 0; q < split_starts_bytes(n) / 2; ++q) a.s.starts[q] = static_cast<uint16_t>(next_random());
         a.buckets();
         a.compact();                                     // (the bound of a tile's entries is such a word too)
+    } else if (what == "tickets") {                      // two calls draw tickets from one counter
+        std::vector<int32_t> v(3 * kPartTile - 5);
+        for (size_t j = 0; j < v.size(); ++j) v[j] = static_cast<int32_t>(j / 2);
+        for (unsigned drawn : {3u, 4u, 40u}) {
+            Call c(v, v.size());
+            c.split();
+            c.buckets();
+            for (int64_t t = 0; t < c.tiles; ++t) c.status[t] = scan_pack(1, kFlagPrefix, 0);     // (what the other call has published)
+            *c.ticket = drawn;
+            c.compact();
+            check(c.err[0] == kErrInternal, "the call has to notice");
+        }
     } else {
         return 3;
     }
@@ -154,7 +166,7 @@ def program(tmp_path_factory):
     return str(d / "main")
 
 
-@pytest.mark.parametrize("what", ["results", "pieces"])
+@pytest.mark.parametrize("what", ["results", "pieces", "tickets"])
 def test_list_by_parts(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", (r.returncode, r.stdout)
