@@ -119,10 +119,9 @@ constexpr int kBucketBlock = 1024;
 constexpr int kBucketItems = 4;                        // entries per thread that stay in registers
 constexpr uint32_t kPartSlots = 8192;                  // of an LDS table: keys, and the lowest position that holds the key
 constexpr uint32_t kPartProbes = 128;                  // more than that at one ID: a bucket's table counts as full
-constexpr uint32_t kBucketClasses = 1024;
 constexpr uint32_t kMaxPartTiles = 512;
 constexpr uint16_t kNoPlace = 0xffff;
-static_assert(kPartBits + 13 + 10 == 32 && kPartSlots == 1u << 13 && kBucketClasses == 1u << 10, "all bits of the hash tell IDs apart");
+static_assert((kPartSlots & (kPartSlots - 1)) == 0 && kPartProbes <= kPartSlots, "odd steps come by every slot once");
 static_assert(kPartsMax == static_cast<int64_t>(kMaxPartTiles) * kPartTile && kMaxPartTiles <= kBucketBlock, "a thread per tile");
 static_assert(kParts <= kSplitBlock && kMergeItems * kScanWaves <= kWave, "a thread per bucket; one step scans a tile");
 
@@ -134,7 +133,7 @@ __device__ __forceinline__ void part_clear(PartTable& t, uint32_t threads) {
     words4* w = reinterpret_cast<words4*>(&t);
     for (uint32_t q = threadIdx.x; q < sizeof(PartTable) / 16; q += threads) w[q] = words4{~0u, ~0u, ~0u, ~0u};
 }
-// the whole hash: the highest bits are the bucket, the next the place in the table, the lowest the class
+// the whole hash: the highest bits are the bucket, the next the place in the table, the lowest the step
 __device__ __forceinline__ uint32_t part_hash(uint32_t id) { return hash_id(id, 0xffffffffu); }
 // The tables are half full at most, and a wave waits for the longest of its 64 searches: steps of the ID's own, odd ones, which
 // come by every slot, keep those short.
@@ -227,14 +226,19 @@ __global__ __launch_bounds__(kSplitBlock) void dedup_split_kernel(const int32_t*
     }
 }
 
-// One workgroup per bucket.  A bucket with more distinct IDs than its table takes is gone through class by class of the lowest
-// bits of the hash, a class for 2048 entries and then twice as many, until every class fits.  At 1024 classes it does: the hash is
-// one-to-one, so the IDs of a bucket and class then differ in the 13 bits between, which are their places in the table.
-__global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch s, uint32_t n_tiles, int32_t* err) {
+// A bucket whose distinct IDs don't fit the table in LDS goes by a stretch of the call's table in memory, which no other bucket
+// uses: two slots for each of its entries, behind two for each entry of the buckets before it.  The stretch is emptied first, and
+// left empty.  Only lists made against the hash get there (of IDs in strides, in blocks and in a row a bucket gets at most 1.25
+// times its share of lists this long): 1 M IDs of one bucket, 78 k of them distinct, take 3.4 ms, all of it one workgroup's, where the
+// inserts into a table for all take 0.1; with one LDS table after the other, class by class of the hash, it was 606.
+__device__ __forceinline__ uint32_t stretch_slot(uint32_t id, uint32_t size) { return __umulhi(part_hash(~id), size); }
+
+__global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch s, uint32_t n_tiles, unsigned long long* table_in_memory,
+                                                                    uint32_t n_slots, int32_t* err) {
     __shared__ PartTable table;
     __shared__ uint32_t s_before[kMaxPartTiles], s_from[kMaxPartTiles];     // of a tile's piece: entries before it, where it begins
     __shared__ uint32_t s_wave[kMaxPartTiles / kWave];
-    __shared__ uint32_t s_full;
+    __shared__ uint32_t s_full, s_lower;                                    // s_lower: entries of the buckets before this one
     const uint32_t t = threadIdx.x;
     uint32_t len = 0, from = 0;
     if (t < n_tiles) {
@@ -249,6 +253,8 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
     }
     const uint32_t inc = dpp_inclusive_scan(len);
     if (t < kMaxPartTiles && lane_id() == kWave - 1) s_wave[wave_id()] = inc;
+    if (t == 0) s_full = s_lower = 0;
+    part_clear(table, kBucketBlock);
     __syncthreads();
     uint32_t at = inc - len, total = 0;
 #pragma unroll
@@ -260,53 +266,97 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
         s_before[t] = t < n_tiles ? at : ~0u;
         s_from[t] = t * kPartTile + from;
     }
+    __syncthreads();
     uint32_t place[kBucketItems], pos[kBucketItems], id[kBucketItems], slot[kBucketItems];
     const uint32_t chunks = (total + kBucketBlock * kBucketItems - 1) / (kBucketBlock * kBucketItems);
-    for (uint32_t classes = 1;;) {
-        __syncthreads();
-        if (t == 0) s_full = 0;
-        for (uint32_t c = 0; c < classes; ++c) {
-            part_clear(table, kBucketBlock);
-            __syncthreads();
-            for (uint32_t step = 0; step < 2 * chunks; ++step) {            // first all inserts, then all answers
-                const bool answer = step >= chunks;
-                const uint32_t e0 = (answer ? step - chunks : step) * (kBucketBlock * kBucketItems) + t;
-                if (step == chunks) __syncthreads();
-                if (chunks > 1 || (step == 0 && c == 0)) {                  // (one chunk stays in registers)
+    const auto entries = [&](uint32_t chunk) {                              // where they are (~0: there is none), and what
 #pragma unroll
-                    for (int k = 0; k < kBucketItems; ++k) {
-                        const uint32_t e = e0 + k * kBucketBlock;
-                        uint32_t lo = 0;                                    // the last tile with at most e entries before its piece
+        for (int k = 0; k < kBucketItems; ++k) {
+            const uint32_t e = (chunk * kBucketItems + k) * kBucketBlock + t;
+            uint32_t lo = 0;                                                // the last tile with at most e entries before its piece
 #pragma unroll
-                        for (uint32_t half = kMaxPartTiles / 2; half > 0; half /= 2)
-                            if (s_before[lo + half] <= e) lo += half;
-                        place[k] = e < total ? s_from[lo] + (e - s_before[lo]) : ~0u;
-                        pos[k] = lo * kPartTile;
-                    }
-#pragma unroll
-                    for (int k = 0; k < kBucketItems; ++k) {
-                        const uint32_t p = place[k] != ~0u ? place[k] : 0u;
-                        id[k] = static_cast<uint32_t>(s.id[p]);
-                        pos[k] += s.pos[p];
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < kBucketItems; ++k) {
-                    if (place[k] == ~0u) continue;
-                    const uint32_t h = part_hash(id[k]);
-                    if ((h & (classes - 1)) != c) continue;
-                    if (!answer || chunks > 1) slot[k] = part_slot(table, id[k], h, kPartProbes);
-                    if (slot[k] == kNoSlot) s_full = 1;
-                    else if (answer) s.first[place[k]] = part_low(table, slot[k]);
-                    else if (part_low(table, slot[k]) > pos[k]) atomicMin(table.low + slot[k], pos[k]);
-                }
-            }
-            __syncthreads();
+            for (uint32_t half = kMaxPartTiles / 2; half > 0; half /= 2)
+                if (s_before[lo + half] <= e) lo += half;
+            place[k] = e < total ? s_from[lo] + (e - s_before[lo]) : ~0u;
+            pos[k] = lo * kPartTile;
         }
-        if (s_full == 0) break;                                             // (the same in all threads: behind a barrier)
-        do classes *= 2;
-        while (classes < kBucketClasses && classes * 2048 < total);
+#pragma unroll
+        for (int k = 0; k < kBucketItems; ++k) {
+            const uint32_t p = place[k] != ~0u ? place[k] : 0u;
+            id[k] = static_cast<uint32_t>(s.id[p]);
+            pos[k] += s.pos[p];
+        }
+    };
+    for (uint32_t chunk = 0; chunk < chunks; ++chunk) {
+        if (__hip_atomic_load(&s_full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0) break;
+        entries(chunk);
+#pragma unroll
+        for (int k = 0; k < kBucketItems; ++k) {
+            if (place[k] == ~0u) continue;
+            slot[k] = part_slot(table, id[k], part_hash(id[k]), kPartProbes);
+            if (slot[k] == kNoSlot) s_full = 1;
+            else if (part_low(table, slot[k]) > pos[k]) atomicMin(table.low + slot[k], pos[k]);
+        }
     }
+    __syncthreads();
+    if (s_full == 0) {
+        for (uint32_t chunk = 0; chunk < chunks; ++chunk) {
+            if (chunks > 1) {                                               // (one chunk is still in registers)
+                entries(chunk);
+#pragma unroll
+                for (int k = 0; k < kBucketItems; ++k)
+                    if (place[k] != ~0u) slot[k] = part_slot(table, id[k], part_hash(id[k]), kPartProbes);
+            }
+#pragma unroll
+            for (int k = 0; k < kBucketItems; ++k)
+                if (place[k] != ~0u) s.first[place[k]] = slot[k] != kNoSlot ? part_low(table, slot[k]) : ~0u;
+        }
+        return;
+    }
+    if (t < n_tiles) atomicAdd(&s_lower, from);
+    __syncthreads();
+    const uint32_t size = 2 * total;
+    if (2 * s_lower + size > n_slots) {                                     // (only if another call writes to the same memory)
+        if (t == 0) raise(err, kErrInternal);
+        return;
+    }
+    unsigned long long* stretch = table_in_memory + 2 * s_lower;
+    for (uint32_t w = t; w < size; w += kBucketBlock) scan_store(stretch + w, kEmptySlot);
+    __syncthreads();
+    for (uint32_t chunk = 0; chunk < chunks; ++chunk) {
+        entries(chunk);
+#pragma unroll
+        for (int k = 0; k < kBucketItems; ++k) {
+            if (place[k] == ~0u) continue;
+            const unsigned long long mine = (static_cast<unsigned long long>(id[k]) << 32) | pos[k];
+            uint32_t q = stretch_slot(id[k], size), left = size;
+            for (; left > 0; --left, q = q + 1 < size ? q + 1 : 0) {
+                unsigned long long cur = scan_load(stretch + q);            // (a plain read first, as in part_slot)
+                if (cur == kEmptySlot) cur = atomicCAS(stretch + q, kEmptySlot, mine);
+                if (cur != kEmptySlot && cur >> 32 != id[k]) continue;
+                if (mine < cur && cur != kEmptySlot) atomicMin(stretch + q, mine);
+                break;
+            }
+            if (left == 0) raise(err, kErrInternal);                        // (as above)
+        }
+    }
+    __syncthreads();
+    for (uint32_t chunk = 0; chunk < chunks; ++chunk) {
+        entries(chunk);
+#pragma unroll
+        for (int k = 0; k < kBucketItems; ++k) {
+            if (place[k] == ~0u) continue;
+            uint32_t q = stretch_slot(id[k], size), left = size;
+            unsigned long long cur = kEmptySlot;
+            for (; left > 0; --left, q = q + 1 < size ? q + 1 : 0) {
+                cur = scan_load(stretch + q);
+                if (cur == kEmptySlot || cur >> 32 == id[k]) break;
+            }
+            s.first[place[k]] = static_cast<uint32_t>(cur);                 // (it is there, unless another call wrote)
+        }
+    }
+    __syncthreads();
+    for (uint32_t w = t; w < size; w += kBucketBlock) scan_store(stretch + w, kEmptySlot);
 }
 
 // The compaction of a list that came by parts: like compact_tiles, but the first positions come from the split tile.
@@ -408,10 +458,10 @@ hipError_t launch_dedup_insert(hipStream_t stream, const int32_t* ids, Count n, 
 }
 
 hipError_t launch_dedup_by_parts(hipStream_t stream, const CompactArgs& a, int64_t n, int64_t n_nodes, const PartScratch& s) {
-    if (n < 1 || n > kPartsMax) return hipErrorInvalidValue;
+    if (n < 1 || n > kPartsMax || !a.s.table || a.s.n_slots < 2 * n) return hipErrorInvalidValue;
     const unsigned tiles = static_cast<unsigned>((n + kPartTile - 1) / kPartTile);
     hipLaunchKernelGGL(dedup_split_kernel, dim3(tiles), dim3(kSplitBlock), 0, stream, a.ids, static_cast<uint32_t>(n), n_nodes, s, a.err);
-    hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, stream, s, tiles, a.err);
+    hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, stream, s, tiles, a.s.table, a.s.n_slots, a.err);
     hipLaunchKernelGGL(dedup_compact_parts_kernel, dim3(tiles), dim3(kScanBlock), 0, stream, a, s);
     return hipGetLastError();
 }

@@ -126,7 +126,8 @@ hipError_t launch_dedup_insert(hipStream_t stream, const int32_t* ids, Count n, 
                                const DedupScratch& s, int32_t* err);
 // Second pass over the whole list.
 hipError_t launch_dedup_compact_plain(hipStream_t stream, const CompactArgs& a, int64_t n_max);
-// Both passes for a list of kPartsMin to kPartsMax IDs, without the table (see dedup.hip).  a.len is n, known on the host.
+// Both passes for a list of kPartsMin to kPartsMax IDs (see dedup.hip).  a.len is n, known on the host.  The table may hold anything and
+// is not used but by lists that hash unevenly; what they use of it is left empty.
 constexpr int64_t kPartsMin = 98304, kPartsMax = 2097152;
 struct PartScratch {             // all of n entries, but starts: split_starts_bytes(n)
     int32_t* id;                 // the distinct IDs of every tile in order of bucket

@@ -182,6 +182,7 @@ inline int __ffsll(long long v) { return __builtin_ffsll(v); }
 inline uint64_t wall_clock64() { return 0; }
 template <class T>
 T min(T a, T b) { return a < b ? a : b; }
+inline uint32_t __umulhi(uint32_t a, uint32_t b) { return static_cast<uint32_t>((static_cast<uint64_t>(a) * b) >> 32); }
 #define __HIP_MEMORY_SCOPE_WORKGROUP 0
 #define __HIP_MEMORY_SCOPE_AGENT 0
 #define __HIP_MEMORY_SCOPE_SYSTEM 0

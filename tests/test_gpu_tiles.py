@@ -328,3 +328,30 @@ def test_gather_with_its_miss_list_in_the_memory_of_the_ids(h, which, n_ids):
         assert torch.equal(out[r < n_hbm], table[r[r < n_hbm]]) and bool((out[at] == 0xA5).all())
         for got, w in zip(lists, want):
             assert torch.equal(got[:at.numel()].long(), w)
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_dedup_of_uneven_lists_leaves_the_table_empty(h, helios, noalloc):
+    """A list by parts whose buckets do not fit LDS goes by the call's table in memory; lists that go by the table altogether follow."""
+    rng = np.random.default_rng(int(noalloc))
+    n = 100_000_000
+    pool = np.arange(40_000_000)
+    many, some = pool[_hash(pool) >> np.uint32(23) == 5], pool[_hash(pool) >> np.uint32(23) == 300][:9_000]
+    uneven = np.concatenate([many, some, rng.choice(some, 20_000), rng.integers(0, n, 60_000)])
+    rng.shuffle(uneven)
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    call = h.dedup_noalloc if noalloc else h.dedup
+    for ids in (uneven, uneven[:98_303], uneven, rng.integers(0, n, 90_000), uneven[5:300]):
+        print("uneven", noalloc, ids.size, flush=True)
+        values, first, back = np.unique(ids, return_index=True, return_inverse=True)
+        order = np.argsort(first)
+        place = np.empty_like(order)
+        place[order] = np.arange(order.size)
+        t = torch.from_numpy(ids.astype(np.int32)).cuda()
+        uniq, inv, nu = torch.empty_like(t), torch.empty_like(t), torch.zeros(1, dtype=torch.int64).pin_memory()
+        torch.cuda.synchronize()
+        call(t, uniq, inv, nu)
+        h.sync()
+        assert int(nu[0]) == values.size
+        assert np.array_equal(uniq[:values.size].cpu().numpy(), values[order])
+        assert np.array_equal(inv.cpu().numpy(), place[back])

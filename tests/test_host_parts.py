@@ -33,7 +33,8 @@ struct Call {
     int64_t n, tiles;
     int32_t *ids, *unique, *inverse, *iof;
     PartScratch s;
-    unsigned long long* status;
+    uint32_t n_slots;
+    unsigned long long *table, *status;
     unsigned long long* ticket;
     int64_t* counters;
     int32_t* err;
@@ -46,11 +47,14 @@ struct Call {
         const size_t room = tiles * kPartTile;
         s = PartScratch{guarded<int32_t>(room), guarded<uint16_t>(room), guarded<uint32_t>(room), guarded<uint16_t>(room),
                         guarded<uint16_t>(split_starts_bytes(n) / 2)};
+        for (n_slots = 1024; n_slots < 2 * n;) n_slots *= 2;
+        table = guarded<unsigned long long>(n_slots);
         status = guarded<unsigned long long>(tiles);
         ticket = guarded<unsigned long long>(1);
         counters = guarded<int64_t>(2);
         err = guarded<int32_t>(2);
         memcpy(ids, list.data(), 4 * n);
+        memset(table, 0xff, 8 * size_t{n_slots});
         memset(status, 0, 8 * tiles);
         *ticket = 0;
         err[0] = 0;
@@ -58,7 +62,7 @@ struct Call {
         a.n_nodes = kNodes;
         a.len = Count{nullptr, n};
         a.n_total_dev = counters;
-        a.s = DedupScratch{nullptr, 0, nullptr, iof};
+        a.s = DedupScratch{table, n_slots, nullptr, iof};
         a.unique = unique;
         a.unique_cap = cap;
         a.last = true;
@@ -70,7 +74,8 @@ struct Call {
     void split() const {
         hipLaunchKernelGGL(dedup_split_kernel, dim3(tiles), dim3(kSplitBlock), 0, nullptr, a.ids, static_cast<uint32_t>(n), kNodes, s, err);
     }
-    void buckets() const { hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, nullptr, s, static_cast<uint32_t>(tiles), err); }
+    void buckets() const { hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, nullptr, s, static_cast<uint32_t>(tiles), table, n_slots, err); }
+    bool table_empty() const { return std::all_of(table, table + n_slots, [](unsigned long long w) { return w == kEmptySlot; }); }
     void compact() const { hipLaunchKernelGGL(dedup_compact_parts_kernel, dim3(tiles), dim3(kScanBlock), 0, nullptr, a, s); }
 };
 
@@ -101,7 +106,7 @@ void results(const std::vector<int32_t>& list, int64_t cap, bool in_place) {
     check(c.counters[1] == u, "n_unique");
     check(std::equal(want.begin(), want.begin() + std::min(u, cap), c.unique), "unique");
     check(c.err[0] == (u > cap ? kErrCapacity : bad ? kErrData : 0), "error");
-    check(*c.ticket == 0, "ticket");
+    check(*c.ticket == 0 && c.table_empty(), "left as found");
 }
 
 uint32_t next_random() {
@@ -109,6 +114,13 @@ uint32_t next_random() {
     x ^= x << 13, x ^= x >> 7, x ^= x << 17;
     return static_cast<uint32_t>(x >> 16);
 }
+std::vector<int32_t> hashing_to(size_t n, uint32_t mask, uint32_t value) {
+    std::vector<int32_t> v;
+    for (int32_t id = 0; v.size() < n; ++id)
+        if ((part_hash(static_cast<uint32_t>(id)) & mask) == value) v.push_back(id);
+    return v;
+}
+
 int main(int argc, char** argv) {
     const std::string what = argv[1];
     if (what == "results") {
@@ -121,6 +133,14 @@ int main(int argc, char** argv) {
             few[0] = -1, few[n / 2] = kNodes, few[n - 1] = INT32_MIN;
             results(few, n, n % 2);
         }
+    } else if (what == "uneven") {                       // more in two buckets than fits their tables, repeats among them
+        std::vector<int32_t> v = hashing_to(18000, 0xff800000u, 5u << 23);
+        const std::vector<int32_t> w = hashing_to(9000, 0xff800000u, 200u << 23);
+        v.insert(v.end(), w.begin(), w.end());
+        for (int j = 0; j < 3000; ++j) v.push_back(v[next_random() % v.size()]);
+        for (int j = 0; j < 3000; ++j) v.push_back(static_cast<int32_t>(next_random() >> 1));
+        for (size_t j = v.size() - 1; j > 0; --j) std::swap(v[j], v[next_random() % (j + 1)]);
+        results(v, v.size(), false);
     } else if (what == "pieces") {                       // the words of two calls side by side, as their waves write them, and any words
         const int n = 32 * kPartTile;
         std::vector<int32_t> one(n, 77), distinct(n);
@@ -148,6 +168,19 @@ int main(int argc, char** argv) {
             c.compact();
             check(c.err[0] == kErrInternal, "the call has to notice");
         }
+    } else if (what == "foreign") {                      // a bucket's piece holds another call's IDs, all of one class of the hash
+        const int n = 16 * kPartTile;
+        std::vector<int32_t> v(n, 77);
+        Call c(v, n);
+        c.split();
+        const std::vector<int32_t> same = hashing_to(n, 1023, 3);
+        memcpy(c.s.id, same.data(), 4 * n);
+        for (int j = 0; j < n; ++j) c.s.pos[j] = j % kPartTile;
+        for (int64_t t = 0; t < c.tiles; ++t)
+            for (int w = 0; w <= kParts; ++w) c.s.starts[t * (kParts + 1) + w] = w > 9 ? kPartTile : 0;      // all in bucket 9
+        c.buckets();
+        check(c.table_empty(), "left as found");
+        for (int j = 0; j < n; ++j) check(c.s.first[j] == static_cast<uint32_t>(j), "first position");
     } else {
         return 3;
     }
@@ -166,7 +199,7 @@ def program(tmp_path_factory):
     return str(d / "main")
 
 
-@pytest.mark.parametrize("what", ["results", "pieces", "tickets"])
+@pytest.mark.parametrize("what", ["results", "uneven", "pieces", "tickets", "foreign"])
 def test_list_by_parts(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", (r.returncode, r.stdout)
