@@ -1085,10 +1085,11 @@ int helios_gather(helios_ctx* c, const int32_t* ids, int64_t n_ids, void* out, i
     if (rc) return rc;
     const TierLists lists{{c->list_pos[0], c->list_pos[1]}, {c->list_slot[0], c->list_slot[1]}, c->cnt + kCntTier};
     // Timed calls keep the copy in a kernel of its own, whose time it then is; so do calls with a launch shape of the caller's, and
-    // those whose miss list is written over the IDs, which the copy beside the lookup reads by itself.
+    // those that write an output over the IDs, which the copy beside the lookup reads by itself.
     const int64_t miss_bytes = static_cast<int64_t>(sizeof(int32_t)) * miss_cap, id_bytes = static_cast<int64_t>(sizeof(int32_t)) * n_ids;
     const bool in_place = overlap(ids, id_bytes, miss_pos, miss_bytes) || overlap(ids, id_bytes, miss_id, miss_bytes) ||
-                          overlap(ids, id_bytes, miss_slot, miss_bytes);
+                          overlap(ids, id_bytes, miss_slot, miss_bytes) || overlap(ids, id_bytes, out, n_ids * c->row_bytes) ||
+                          overlap(ids, id_bytes, stats, static_cast<int64_t>(sizeof(helios_gather_stats)));
     const bool direct = c->timing == 0 && c->hbm_blocks == 0 && c->n_hbm > 0 && !in_place &&
                         copy_beside_lookup(n_ids, c->g.n_nodes, c->n_hbm, c->row_bytes / 16);
     HIP_TRY(c, launch_lookup_partition(c->stream, ids, n_ids, rank_or_any(c), c->g.n_nodes, c->n_hbm, c->n_host,

@@ -355,3 +355,35 @@ def test_dedup_of_uneven_lists_leaves_the_table_empty(h, helios, noalloc):
         assert int(nu[0]) == values.size
         assert np.array_equal(uniq[:values.size].cpu().numpy(), values[order])
         assert np.array_equal(inv.cpu().numpy(), place[back])
+
+
+@pytest.mark.parametrize("share", [1.0, 0.9])
+@pytest.mark.parametrize("n_ids", [3_000, 600_000, 2_200_000])
+def test_gather_with_its_rows_in_the_memory_of_the_ids(h, share, n_ids):
+    """The IDs lie in the first rows of `out`, or under the stats (all nodes in HBM, and not all)."""
+    gen = torch.Generator(device="cuda").manual_seed(n_ids)
+    n, row = 40_000, 64
+    n_hbm = int(share * n)
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    order = torch.randperm(n, device="cuda", generator=gen).int()
+    rank = torch.empty(n, dtype=torch.int64, device="cuda")
+    rank[order.long()] = torch.arange(n, device="cuda")
+    table = torch.randint(0, 256, (n_hbm, row), dtype=torch.uint8, device="cuda", generator=gen)
+    h.cache_build(order, n_hbm, 0, row, table, None, None)
+    for stats_too in (False, True):
+        room = torch.empty(n_ids * row + 64, dtype=torch.uint8, device="cuda")
+        want = torch.randint(0, n, (n_ids,), dtype=torch.int32, device="cuda", generator=gen)
+        ids = room[:4 * n_ids].view(torch.int32)
+        ids.copy_(want)
+        if stats_too:                                         # rows of their own, the stats over the first IDs
+            out, stats = torch.zeros((n_ids, row), dtype=torch.uint8, device="cuda"), room[:32].view(torch.int64)
+        else:
+            out, stats = room[:n_ids * row].view(n_ids, row), torch.zeros(4, dtype=torch.int64).pin_memory()
+        lists = [torch.empty(n_ids, dtype=torch.int32, device="cuda") for _ in range(3)]
+        torch.cuda.synchronize()
+        h.gather(ids, out, *lists, stats)
+        h.sync()
+        r = rank[want.long()]
+        hit = r < n_hbm
+        assert torch.equal(out[hit], table[r[hit]])
+        assert stats.tolist() == [n_ids, int(hit.sum()), 0, int((~hit).sum())]
