@@ -973,8 +973,16 @@ int helios_cache_build(helios_ctx* c, const int32_t* order, int64_t hbm_rows, in
         HIP_TRY(c, hipMalloc(&c->rank, sizeof(int32_t) * (n > 0 ? n : 1)));
         c->rank_cap = n;
     }
-    // (the scratch of a hotness order that the context has made, if any)
-    if (n > 0) HIP_TRY(c, launch_rank_build(c->stream, order, n, c->rank, c->cnt + kCntHoles, c->hot_temp, c->hot_temp_bytes, c->err));
+    // (With the scratch of a hotness order that the context has made, if any; not in a capture, whose replays may come after another
+    // hotness order has replaced that scratch by a larger one.)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (c->hot_temp && hipStreamIsCapturing(c->stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        capture = hipStreamCaptureStatusActive;
+    }
+    const bool borrow = c->hot_temp && capture == hipStreamCaptureStatusNone;
+    if (n > 0)
+        HIP_TRY(c, launch_rank_build(c->stream, order, n, c->rank, c->cnt + kCntHoles, borrow ? c->hot_temp : nullptr, borrow ? c->hot_temp_bytes : 0, c->err));
     c->n_hbm = hbm_rows;
     c->n_host = host_rows;
     c->row_bytes = row_bytes;

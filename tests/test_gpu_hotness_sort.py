@@ -99,3 +99,42 @@ def test_cache_map_by_buckets(kind, n):
         assert torch.equal(order[got[known]].long(), at[known])          # (any of its ranks for a node that is there twice)
         assert bool((got[~known] == -9).all())
     h.close()
+
+
+def test_captured_cache_build_outlives_the_scratch_of_a_hotness_order():
+    """A cache map captured after a hotness order and replayed after a larger one, which frees the scratch of the first."""
+    from paper_2310_00837_amd import helios
+    n, larger = 2_100_000, 3_000_000
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    stream = torch.cuda.Stream()
+    h = helios.Helios(0, stream=stream)
+    off, idx = torch.zeros(larger + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    counts, order = torch.zeros(larger, dtype=torch.int32, device="cuda"), torch.empty(larger, dtype=torch.int32, device="cuda")
+    at = torch.arange(n, device="cuda")
+    table = torch.zeros((n, 2), dtype=torch.int64, device="cuda")
+    table[:, 0] = at
+    given = torch.arange(n, device="cuda").int()
+    torch.cuda.synchronize()
+    h.csr_load(off[:n + 1], idx)
+    h.hotness_order(counts[:n], order[:n])
+    h.cache_build(given, n, 0, 16, table, None, None)              # (the map's own memory is there before the capture)
+    h.sync()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        h.cache_build(given, n, 0, 16, table, None, None)
+    h.csr_load(off, idx)
+    h.hotness_order(counts, order)
+    h.csr_load(off[:n + 1], idx)
+    h.cache_build(given, n, 0, 16, table, None, None)
+    h.sync()
+    ids, out = at.int(), torch.empty((n, 2), dtype=torch.int64, device="cuda")
+    lists, stats = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(3)], torch.zeros(4, dtype=torch.int64).pin_memory()
+    for _ in range(3):
+        given.copy_(torch.randperm(n, device="cuda", generator=gen))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            graph.replay()
+        h.gather(ids, out, *lists, stats)
+        h.sync()
+        assert stats.tolist() == [n, n, 0, 0] and torch.equal(given[out[:, 0]].long(), at)
+    h.close()
