@@ -51,10 +51,14 @@ __global__ __launch_bounds__(kBlock) void rank_check_kernel(const int32_t* __res
 // buckets every line is written once:
 //   split   every tile of 4096 ranks hands its (node, rank) pairs to the buckets of 2^shift neighbouring nodes that they belong to;
 //           a bucket's pairs lie where its nodes' ranks will (a permutation fills it exactly);
-//   place   a workgroup per bucket puts the ranks in order in LDS and writes them out, and a place that got none is a hole.
-// Measured, us by scattered stores / by buckets, for the hotness order of a power law (and a random order):
-//   1 M nodes 13.2/14.2 (18.4/19.9)   2 M 23.8/19.1 (34.5/30.5; the line)   3 M 33.7/23.4 (49.7/39.4)   8 M 80/38 (116/81)   16 M 144/69 (216/144)
-// An order that ascends by ID throughout, where every count is the same, is the one that scattered stores write whole lines for: 8 M 26.7/37.2.
+//   place   a workgroup per bucket puts the ranks in order in LDS and writes them out.
+// Where an order goes through neighbouring nodes (all of one count, as those that no batch has met; nodes numbered by locality) its stores are
+// whole lines to begin with: the split then stores them itself, and place only looks whether the order has the node there.
+// Measured, us by scattered stores / by buckets: the hotness order of a power law (and a random order)
+//   1 M nodes 13.2/14.2 (18.4/19.9)   2 M 25/19 (36/33; the line)   3 M 34/23 (48/41)   8 M 78/38 (114/83)   16 M 142/66 (216/143)
+// of counts that are 0 for 99 of 100 nodes (and for 9 of 10; and all the same)
+//   2 M 14.5/15.1 (15.2/18.0; 12.0/13.4)   3 M 17.2/17.4 (19.6/21.3; 13.2/16.7)   8 M 28/30 (39/37; 27/28)   16 M 49/54 (64/67; 46/51)
+// and with every wave handing out pairs 18, 22, 37 and 66, whatever the order.  The nodes in random blocks of 64: 8 M 27/29 (with pairs 59).
 // The buckets take 8 bytes of scratch per node, so they are used where the context has that from making a hotness order; and above 16.7 M
 // nodes a bucket would not fit LDS.  (Four ranks per thread in the split; with eight 39.8 at 8 M, with sixteen 55: one chain of LDS additions.)
 constexpr int kInvertBlock = 1024;
@@ -62,6 +66,8 @@ constexpr int kInvertItems = 4;
 constexpr uint32_t kInvertTile = kInvertBlock * kInvertItems;
 constexpr uint32_t kInvertBuckets = 512;
 constexpr uint32_t kInvertMaxShift = 15;               // 32768 ranks: 128 KB of LDS
+constexpr int kPlaceItems = 8;                         // one at a time: 16 M by pairs 33.5 us in place, with eight 31
+constexpr uint32_t kNear = 96;                         // three lines of ranks (every other node of a row, 128, is as quick by pairs)
 constexpr int64_t kInvertMin = 2000000;
 constexpr int64_t kInvertMax = static_cast<int64_t>(kInvertBuckets) << kInvertMaxShift;
 
@@ -71,7 +77,7 @@ __global__ __launch_bounds__(kInvertBlock) void rank_zero_kernel(uint32_t* curso
 }
 
 __global__ __launch_bounds__(kInvertBlock) void rank_split_kernel(const int32_t* __restrict__ order, uint32_t n, uint32_t shift, uint32_t* cursors,
-                                                                  unsigned long long* pairs, int32_t* err) {
+                                                                  unsigned long long* pairs, int32_t* rank, int32_t* err) {
     __shared__ uint32_t s_count[kInvertBuckets], s_base[kInvertBuckets], s_unused[kWave];
     const uint32_t r0 = blockIdx.x * kInvertTile + threadIdx.x, lane = static_cast<uint32_t>(lane_id());
     uint32_t v[kInvertItems], at[kInvertItems], lead[kInvertItems];
@@ -85,6 +91,20 @@ __global__ __launch_bounds__(kInvertBlock) void rank_split_kernel(const int32_t*
         const bool here = r0 + k * kInvertBlock < n;
         if (here && v[k] >= n) raise(err, kErrData);
         if (!here || v[k] >= n) v[k] = ~0u;
+    }
+    // A wave whose nodes ascend or descend by little: the first and the last one of its first 64 lie close together.  They are
+    // stored at once, and are no pairs from here on.  (If the others don't, it only takes longer.  Asked of all 256, an order without
+    // such waves took 1 us longer.)
+    const uint32_t v0 = lane_value(v[0], 0), v1 = lane_value(v[0], kWave - 1);
+    if ((v0 < v1 ? v1 - v0 : v0 - v1) < kNear && v1 != ~0u) {
+#pragma unroll
+        for (int k = 0; k < kInvertItems; ++k) {
+            if (v[k] != ~0u) rank[v[k]] = static_cast<int32_t>(r0 + k * kInvertBlock);
+            v[k] = ~0u;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kInvertItems; ++k) {
         const uint32_t bucket = v[k] >> shift;
         // In a hotness order the nodes of a wave are mostly neighbours: those that go where the first goes are counted at once, by
         // the first.  (Every lane adds somewhere, so that the additions of all items are on their way together.)
@@ -138,10 +158,36 @@ __global__ __launch_bounds__(kInvertBlock) void rank_place_kernel(const int32_t*
         }
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < nodes; i += kInvertBlock) {
-        const int32_t r = s_rank[i];
-        rank[first + i] = r;
-        if (r < 0) {
+    bool missing = false;
+    for (uint32_t i0 = threadIdx.x; i0 < nodes; i0 += kPlaceItems * kInvertBlock) {
+        int32_t r[kPlaceItems];
+#pragma unroll
+        for (int k = 0; k < kPlaceItems; ++k) r[k] = s_rank[min(i0 + k * kInvertBlock, nodes - 1)];
+#pragma unroll
+        for (int k = 0; k < kPlaceItems; ++k) {
+            if (r[k] >= 0) rank[first + min(i0 + k * kInvertBlock, nodes - 1)] = r[k];
+            missing = missing || r[k] < 0;
+        }
+    }
+    if (!missing) return;
+    // What the split has stored itself has no pair.  Such a node's word is right if the order has the node at that rank, whatever
+    // the word held before; else the node has no rank.
+    for (uint32_t i0 = threadIdx.x; i0 < nodes; i0 += kPlaceItems * kInvertBlock) {
+        uint32_t stored[kPlaceItems], there[kPlaceItems];
+        bool none[kPlaceItems];
+#pragma unroll
+        for (int k = 0; k < kPlaceItems; ++k) {                    // (unguarded: all in flight together)
+            const uint32_t i = min(i0 + k * kInvertBlock, nodes - 1);
+            none[k] = s_rank[i] < 0;
+            stored[k] = static_cast<uint32_t>(rank[first + (none[k] ? i : 0)]);
+        }
+#pragma unroll
+        for (int k = 0; k < kPlaceItems; ++k) there[k] = static_cast<uint32_t>(order[none[k] && stored[k] < n ? stored[k] : 0]);
+#pragma unroll
+        for (int k = 0; k < kPlaceItems; ++k) {
+            const uint32_t i = min(i0 + k * kInvertBlock, nodes - 1);
+            if (!none[k] || (stored[k] < n && there[k] == first + i)) continue;
+            rank[first + i] = -1;
             *holes = 1;
             raise(err, kErrData);
         }
@@ -353,7 +399,7 @@ hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n
         unsigned long long* pairs = reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(scratch) + pairs_at);
         const dim3 block(kInvertBlock);
         hipLaunchKernelGGL(rank_zero_kernel, dim3(1), block, 0, stream, cursors, holes);
-        hipLaunchKernelGGL(rank_split_kernel, dim3((n + kInvertTile - 1) / kInvertTile), block, 0, stream, order, n, shift, cursors, pairs, err);
+        hipLaunchKernelGGL(rank_split_kernel, dim3((n + kInvertTile - 1) / kInvertTile), block, 0, stream, order, n, shift, cursors, pairs, rank, err);
         const dim3 buckets((n + (1u << shift) - 1) >> shift);
         if (shift == kInvertMaxShift) hipLaunchKernelGGL(rank_place_kernel<kInvertMaxShift>, buckets, block, 0, stream, order, n, shift, cursors, pairs, rank, holes, err);
         else hipLaunchKernelGGL(rank_place_kernel<kInvertMaxShift - 1>, buckets, block, 0, stream, order, n, shift, cursors, pairs, rank, holes, err);

@@ -138,3 +138,58 @@ def test_captured_cache_build_outlives_the_scratch_of_a_hotness_order():
         h.sync()
         assert stats.tolist() == [n, n, 0, 0] and torch.equal(given[out[:, 0]].long(), at)
     h.close()
+
+
+@pytest.mark.parametrize("kind", ["sparse counts", "blocks", "blocks with repeats", "ascending with repeats", "descending with a gap"])
+@pytest.mark.parametrize("n", [2_000_003, 8_388_609])
+def test_cache_map_of_neighbouring_nodes(kind, n):
+    """Orders in which neighbouring nodes follow each other, whose ranks are stored without the buckets: every node's rank is one at
+    which the order has it, also where the map held that of another order before; a node that no rank points to has none."""
+    from paper_2310_00837_amd import helios
+    print("neighbouring nodes", kind, n, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    h = helios.Helios(0)
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    at = torch.arange(n, device="cuda")
+    counts = torch.where(torch.rand(n, device="cuda", generator=gen) < 0.03, torch.randint(1, 50, (n,), device="cuda", generator=gen), 0).int()
+    order = torch.empty(n, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    h.hotness_order(counts, order)
+    h.sync()
+    orders = [torch.randperm(n, device="cuda", generator=gen).int(), order]
+    if kind.startswith("blocks"):
+        size = 64
+        blocks = torch.randperm(n // size, device="cuda", generator=gen)[:, None] * size + torch.arange(size, device="cuda")
+        order = torch.cat([blocks.flatten(), at[n // size * size:]]).int()
+    elif kind.startswith("ascending"):
+        order = at.int()
+    elif kind.startswith("descending"):
+        order = at.flip(0).int()
+    if kind.endswith("repeats"):
+        order[5::1000] = order[4::1000][:order[5::1000].numel()]
+        order[100_000:100_064] = order[300_000:300_064]
+    if kind.endswith("gap"):
+        order[n // 2] = -7
+    orders += [order, order]
+    table = torch.zeros((n, 2), dtype=torch.int64, device="cuda")
+    table[:, 0] = at
+    ids, out = at.int(), torch.empty((n, 2), dtype=torch.int64, device="cuda")
+    lists, stats = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(3)], torch.zeros(4, dtype=torch.int64).pin_memory()
+    for order in orders:
+        known = torch.zeros(n, dtype=torch.bool, device="cuda")
+        known[order[(order >= 0) & (order < n)].long()] = True
+        whole = bool(known.all())
+        out.fill_(-9)
+        torch.cuda.synchronize()
+        h.cache_build(order, n, 0, 16, table, None, None)
+        h.gather(ids, out, *lists, stats)
+        if whole:
+            h.sync()
+        else:
+            with pytest.raises(helios.HeliosError) as e:
+                h.sync()
+            assert e.value.code == helios.EDATA
+        assert stats.tolist() == [n, int(known.sum()), 0, 0]
+        got = out[:, 0]
+        assert torch.equal(order[got[known]].long(), at[known]) and bool((got[~known] == -9).all())
+    h.close()
