@@ -301,6 +301,10 @@ int64_t expected_hbm_rows(const helios_ctx* c) {
 // with the grid that follows the list / with this one: three hops of 1024 seeds, 243 k rows of 512 bytes 93.7/83.8 (153/148), of 2 KB
 // 188/175 (245/248); 71 k rows of 400 bytes 52.9/50.1 (113/114), of 1 KB 66.1/60.7 (130/127); two members with rows of 1 KB 46.1/44.4, four
 // with rows of 512 bytes 58.5/57.8.  With four per CU 2 KB rows take 257 alone, with eight the 512-byte rows 90.
+// A member of a gang has at least 384, so four of them have six per CU together: rows of 1 KB, 256 / 320 / 384 / 448 for each member,
+// 144/140/139/139 alone and 86/89/90/91 in flight; of 512 bytes 116/114/115/114 and 67/65/66/67.
+// Rows of more than 2 KB keep the grid that follows the list: they gained 0 to 3 % in flight and lost 2 to 3 % alone (243 k rows of 8 KB
+// 322/314 and 363/373, of 4 KB 163/162 and 231/235; 56 k of 8 KB 117/117 and 163/167).
 // Not beside a copy over the link: the CUs that hold link waves copy next to nothing from HBM, so equal shares would wait for theirs
 // (243 k rows of 2 KB beside 13 k over the link, one batch alone 591/620 us), while short-lived workgroups go to the CUs that get on.  That
 // launch is bound by the link anyway.  The members of a gang then take their share of workgroups, at least 1024, unless the list
@@ -309,7 +313,7 @@ unsigned hbm_role_blocks(const helios_ctx* c, int64_t n_max, bool beside_link) {
     const int32_t chunks = c->row_bytes / 16;
     const unsigned alone = copy_role_blocks(chunks, false, n_max, c->hbm_blocks, expected_hbm_rows(c)), share = static_cast<unsigned>(c->link_share);
     if (c->hbm_blocks > 0) return alone;
-    if (beside_link) return share <= 1 || alone >= 16384 ? alone : std::min(alone, std::max(1024u, alone / share));
+    if (beside_link || chunks > 128) return share <= 1 || alone >= 16384 ? alone : std::min(alone, std::max(1024u, alone / share));
     return std::min(alone, std::max(384u, (chunks > 64 ? 6 * 256u : 5 * 256u) / share));
 }
 

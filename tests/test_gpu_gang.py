@@ -418,3 +418,52 @@ def test_roles_of_a_gang_are_timed_per_member(helios, oracle, small):
     gang.destroy()
     for h in ctxs:
         h.close()
+
+
+def _resident(helios, row_bytes, ctxs, host_rows=None):
+    """A batch of about 45 k unique IDs for every context, cached whole: (sets, seeds, what must stay alive); host_rows[m] of member
+    m's nodes in the host tier."""
+    n, deg, n_seeds, fan = 60_000, 10, 1024, [10, 10]
+    gen = torch.Generator(device="cuda").manual_seed(row_bytes)
+    off = torch.arange(n + 1, device="cuda") * deg
+    idx = torch.randint(0, n, (n * deg,), dtype=torch.int32, device="cuda", generator=gen)
+    order = torch.arange(n, device="cuda").int()
+    table = torch.zeros((n, row_bytes), dtype=torch.uint8, device="cuda")
+    sets, seeds, keep = [], [], [off, idx, order, table]
+    for m, h in enumerate(ctxs):
+        k = host_rows[m] if host_rows else 0
+        host = torch.zeros((k, row_bytes), dtype=torch.uint8).pin_memory() if k else None
+        hops = helios.alloc_hops(n_seeds, fan, "cuda")
+        cap = n_seeds + sum(hb.flat.numel() for hb in hops)
+        ints = [torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(4)]
+        b = helios.BatchBuffers(hops=hops, sizes=torch.zeros(4, dtype=torch.int64).pin_memory(), unique=ints[0],
+                                inverse=torch.empty(cap, dtype=torch.int32, device="cuda"), n_unique=torch.zeros(1, dtype=torch.int64).pin_memory(),
+                                out=torch.empty((n, row_bytes), dtype=torch.uint8, device="cuda"), miss_pos=ints[1], miss_id=ints[2],
+                                miss_slot=ints[3], stats=torch.zeros(4, dtype=torch.int64).pin_memory())
+        sets.append(b)
+        seeds.append(torch.randperm(n, device="cuda", generator=gen)[:n_seeds].int())
+        torch.cuda.synchronize()
+        h.csr_load(off, idx)
+        h.cache_build(order, n - k, k, row_bytes, table, host, None)
+        h.reserve(cap)
+        h.set_timing(1)
+        for _ in range(2):                                    # the second knows from the first how many rows to expect
+            h.prepare_batch(seeds[m], fan, 5 + m, b.hops, b.sizes, b.unique, b.inverse, b.n_unique, b.out, b.miss_pos, b.miss_id, b.miss_slot, b.stats)
+            h.sync()
+        keep.append(host)
+    return sets, seeds, keep
+
+
+def _copy_workgroups(helios, h):
+    return [w for kind, _, w, _, _ in h.batch_ticks()[0] if kind == helios.ROLE_COPY_HBM]
+
+
+@pytest.mark.parametrize("row_bytes,at_most", [(512, 1280), (1024, 1280), (1040, 1536), (2048, 1536), (2064, None), (4096, None)])
+def test_workgroups_of_a_resident_row_copy(helios, row_bytes, at_most):
+    """Rows of up to 2 KB are copied by a fixed number of workgroups, longer ones by as many as the list has steps (of four rows)."""
+    h = helios.Helios(0, stream=torch.cuda.Stream())
+    sets, _, keep = _resident(helios, row_bytes, [h])
+    got, = _copy_workgroups(helios, h)
+    rows = int(sets[0].stats[1])
+    assert rows > 40_000 and (got == at_most if at_most else got >= rows // 4), (row_bytes, got, rows)
+    h.close()
