@@ -128,6 +128,7 @@ struct helios_ctx {
 
     std::vector<helios::PendingStep>* defer = nullptr;   // set while a gang is recorded: where the pipeline's launches go
     int link_share = 1;                        // batches whose host-tier copies share the link in every launch (a gang's members)
+    bool beside_link = false;                  // a member of the gang being recorded copies over the link in its last launch
 
     // what the last batch left behind for helios_make_blocks
     bool blocks_ready = false;

@@ -594,7 +594,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             miss.stamps = take_stamps(c, HELIOS_ROLE_COPY_STANDIN, stage, miss_blocks);
         }
         if (c->n_hbm > 0 && u_max > 0) {
-            hbm_blocks = hbm_role_blocks(c, u_max, c->n_host > 0 || served_max > 0);
+            hbm_blocks = hbm_role_blocks(c, u_max, c->n_host > 0 || served_max > 0 || c->beside_link);
             hbm = tier_copy_args(c, 0, nullptr, Count{c->cnt + kCntTier + 0, u_max}, b->out, take_stamps(c, HELIOS_ROLE_COPY_HBM, stage, hbm_blocks));
         }
         if (c->n_host > 0 && u_max > 0) {
@@ -1265,6 +1265,9 @@ int helios_gang_create(helios_ctx* const* ctxs, int32_t n_members, int64_t n_see
         g->member[m] = new_plan(ctxs[m]);
         if (!g->member[m]) rc = fail(c0, HELIOS_EHIP, "no pinned memory for a member's error word");
     }
+    bool beside_link = false;            // whether any member copies over the link in the shared last launch
+    for (int m = 0; m < n_members; ++m)
+        beside_link = beside_link || ctxs[m]->n_host > 0 || (ctxs[m]->serve_misses && ctxs[m]->n_hbm < ctxs[m]->g.n_nodes && buffers[m].miss_cap > 0);
     std::vector<PendingStep> steps[kMaxGang];
     bool was_ready[kMaxGang] = {false, false, false, false};
     hipError_t e = hipSuccess;
@@ -1276,6 +1279,7 @@ int helios_gang_create(helios_ctx* const* ctxs, int32_t n_members, int64_t n_see
             c->err_now = g->member[m]->err;
             c->defer = &steps[m];
             c->link_share = n_members;
+            c->beside_link = beside_link;
             was_ready[m] = c->blocks_ready;
         }
         e = hipStreamBeginCapture(c0->stream, hipStreamCaptureModeThreadLocal);
@@ -1322,6 +1326,7 @@ int helios_gang_create(helios_ctx* const* ctxs, int32_t n_members, int64_t n_see
             c->err_now = c->err;
             c->defer = nullptr;
             c->link_share = 1;
+            c->beside_link = false;
             c->blocks_ready = was_ready[m];          // nothing has run
         }
     }

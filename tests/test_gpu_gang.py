@@ -467,3 +467,20 @@ def test_workgroups_of_a_resident_row_copy(helios, row_bytes, at_most):
     rows = int(sets[0].stats[1])
     assert rows > 40_000 and (got == at_most if at_most else got >= rows // 4), (row_bytes, got, rows)
     h.close()
+
+
+@pytest.mark.parametrize("host_rows,beside_link", [([0, 0], False), ([0, 30_000], True), ([30_000, 0], True)])
+def test_workgroups_of_a_row_copy_beside_another_members_link_copy(helios, host_rows, beside_link):
+    """A copy over the link in one member's last launch is in all members' last launch: none holds its HBM copy back then."""
+    st = torch.cuda.Stream()
+    ctxs = [helios.Helios(0, stream=st) for _ in host_rows]
+    sets, seeds, keep = _resident(helios, 512, ctxs, host_rows)
+    gang = helios.Gang(ctxs, 1024, [10, 10], sets)
+    gang.launch(seeds, [11, 12])
+    assert gang.wait() == [0, 0]
+    for h in ctxs:
+        got, = _copy_workgroups(helios, h)
+        assert got >= 1024 if beside_link else got == 640, got
+    gang.destroy()
+    for h in ctxs:
+        h.close()
