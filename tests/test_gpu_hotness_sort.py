@@ -48,7 +48,8 @@ def test_hotness_order_in_the_memory_of_the_counts(oracle, kind, n):
 
 
 @pytest.mark.parametrize("kind", ["random", "ascending", "descending", "hot", "repeats", "a bucket too full"])
-@pytest.mark.parametrize("n", [1_999_999, 2_000_000, 2_097_153, 8_388_607])      # buckets of 4096, 4096 (the line), 8192, 32768 nodes
+@pytest.mark.parametrize("n", [1_999_999, 2_000_000, 2_097_153, 8_388_607, 8_388_609, 16_777_216, 16_777_217])
+# (scattered stores; buckets of 4096, 8192, 16384 and 32768 nodes, all 512 buckets of 32768; scattered stores again)
 def test_cache_map_by_buckets(kind, n):
     """The map that helios_cache_build makes of an order, read back by a gather whose rows are the ranks: by scattered stores below
     2 M nodes and by buckets from there on, which use the scratch of a hotness order; and orders that are no permutation."""

@@ -387,3 +387,45 @@ def test_gather_with_its_rows_in_the_memory_of_the_ids(h, share, n_ids):
         hit = r < n_hbm
         assert torch.equal(out[hit], table[r[hit]])
         assert stats.tolist() == [n_ids, int(hit.sum()), 0, int((~hit).sum())]
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("n_ids", [98_304, 100_003, 262_144])
+def test_dedup_by_parts_in_place_cut_off_and_with_bad_ids(h, helios, n_ids, noalloc):
+    """Lists by parts through both calls: `unique` in the memory of the IDs, the inverse there, no inverse, a `unique` that is too
+    short, and IDs that are no nodes."""
+    rng = np.random.default_rng(n_ids)
+    n = 1_000_000
+    h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    call = h.dedup_noalloc if noalloc else h.dedup
+    good = (n * rng.random(n_ids) ** 3).astype(np.int32)
+    bad = good.copy()
+    bad[[0, n_ids // 2, n_ids - 1]] = [-1, n, -2**31]
+    for kind in ("unique over ids", "inverse over ids", "no inverse", "short", "bad"):
+        print("in place", n_ids, noalloc, kind, flush=True)
+        ids = bad if kind == "bad" else good
+        node = (ids >= 0) & (ids < n)
+        values, first, back = np.unique(ids[node], return_index=True, return_inverse=True)
+        order = np.argsort(first)
+        place = np.empty_like(order)
+        place[order] = np.arange(order.size)
+        want = np.full(n_ids, -1, np.int64)
+        want[node] = place[back]
+        for _ in range(2):
+            t = torch.from_numpy(ids).cuda()
+            cap = values.size // 3 if kind == "short" else n_ids
+            uniq = t if kind == "unique over ids" else torch.full((cap,), -9, dtype=torch.int32, device="cuda")
+            inv = None if kind == "no inverse" else t if kind == "inverse over ids" else torch.full((n_ids,), -9, dtype=torch.int32, device="cuda")
+            nu = torch.full((1,), -9, dtype=torch.int64).pin_memory()
+            torch.cuda.synchronize()
+            call(t, uniq, inv, nu)
+            if kind in ("short", "bad"):
+                with pytest.raises(helios.HeliosError) as e:
+                    h.sync()
+                assert e.value.code == (helios.ECAPACITY if kind == "short" else helios.EDATA)
+            else:
+                h.sync()
+            assert int(nu[0]) == values.size
+            fits = min(cap, values.size)
+            assert np.array_equal(uniq[:fits].cpu().numpy(), values[order][:fits])
+            assert inv is None or np.array_equal(inv.cpu().numpy(), want)
