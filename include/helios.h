@@ -100,7 +100,9 @@ int helios_csr_load(helios_ctx *ctx, int64_t n_nodes, int64_t n_edges,
  *   standin_table pinned mapped host,  row t <-> rank hbm_rows + host_rows + t
  * (the stand-in replaces the SSD array of Sec. 3.1; it may be NULL if
  * helios_gather_miss is never called).  A table with zero rows may be NULL.
- * Requires helios_csr_load first (for n_nodes). */
+ * Requires helios_csr_load first (for n_nodes).  Maps of 2 M to 16.7 M nodes are
+ * made quicker where the context has made a hotness order before (the call then
+ * works in that order's scratch), except in a capture. */
 int helios_cache_build(helios_ctx *ctx, const int32_t *hotness_order,
                        int64_t hbm_rows, int64_t host_rows, int32_t row_bytes,
                        const void *hbm_table, const void *host_table, const void *standin_table);
@@ -152,9 +154,10 @@ int helios_dedup(helios_ctx *ctx, const int32_t *ids, int64_t n_ids,
 /* helios_dedup for callers that cannot allocate: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same
  * results and same errors as helios_dedup, but the call allocates and frees
- * nothing: all its scratch (hash table, per-input slots, scan state, counters)
- * is a fixed array of about 6 MiB in the library's device image, which every
- * GPU the library runs on holds until the process ends.  At most
+ * nothing: all its scratch (hash table, per-input slots, the parts that a long
+ * list is taken into, scan state, counters) is a fixed array of about 9 MiB in
+ * the library's device image, which every GPU the library runs on holds until
+ * the process ends.  At most
  * HELIOS_DEDUP_NOALLOC_MAX_IDS IDs per call, more is HELIOS_EINVAL.  All
  * contexts of a GPU share that array, which every call leaves empty, so
  * calls that overlap on one GPU (different streams or host threads) race: the
@@ -249,7 +252,7 @@ int helios_make_blocks(helios_ctx *ctx, const helios_hop_out *hops, int32_t n_ho
  * caller before the epoch).  helios_hotness_order writes the nodes by counter
  * descending, ties by ascending ID, to order (device int32[n_nodes], which may
  * be the counters' own memory): the hotness_order argument of
- * helios_cache_build.  Its scratch (about 13 bytes
+ * helios_cache_build.  Its scratch (12 to 13 bytes
  * per node) is allocated on the first call and kept by the context. */
 int helios_hotness_add(helios_ctx *ctx, const int32_t *ids, int64_t n_max, const int64_t *n_dev,
                        int32_t *counts);

@@ -436,7 +436,7 @@ bool copy_beside_lookup(int64_t n, int64_t n_nodes, int64_t n_hbm, int32_t chunk
     if (n_hbm == n_nodes) return chunks <= 128 || chunks > 256 || steps <= 16384;
     if (10 * n_hbm < 9 * n_nodes) return n <= 262144 && steps <= (chunks >= 128 && 10 * n_hbm >= 3 * n_nodes ? 8192 : 4096);
     if (chunks > 128 && chunks <= 256) return steps <= 8192;
-    return chunks >= 128 || steps <= (n_hbm < n_nodes ? 8192 : 16384);
+    return chunks >= 128 || steps <= 8192;
 }
 
 hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, int64_t n,

@@ -102,12 +102,14 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_long_kernel(const int32_t
 //   buckets   a workgroup per bucket gathers its pieces of all tiles, finds the first position of every ID in an LDS table, and
 //             leaves it where it has read the ID;
 //   compact   a tile's first positions go back into input order (LDS), and from there on it is the compaction as above.
-// All of it is streams in pieces of 32 bytes and more.  A tile drops its repeats so that no bucket is much longer than the
-// others: of an ID that fills the list a bucket gets one entry per tile.
+// All of it is streams, the buckets' reads in pieces of about 32 bytes (IDs, first positions) and 16 (places), shorter where the tiles
+// have dropped repeats.  They drop them so that no bucket is much longer than the others: of an ID that fills the list a bucket gets
+// one entry per tile.
 // Measured, whole call, us with the table / by parts, IDs by a power law (uniform ones differ by less than 4):
-//   65 k 23.9/24.5   100 k 26.0/25.2 (the line)   131 k 30.6/25.6   262 k 43/28.5   400 k 54/31.8   1.1 M 102/45.7   2 M 165/68
-// (1.1 M: split 12.2, buckets 14.1, compact 13.4, inverse 5.7); one ID throughout, 131 k: 1900/20.  Above 2 M a bucket would have more
-// IDs than half its table, and the list goes by the table.  256 buckets of 1024 threads with eight entries each, 64-bit words and
+//   65 k 23.9/24.5   98 k 26.7/24.5 (the line)   131 k 31.1/25.0   262 k 41/28.5   400 k 54/31.8   1.1 M 102/42.6   2 M 165/66
+// (1.1 M: split 11.9, buckets 13.2, compact 13.8, inverse 5.8); one ID throughout, 131 k: 1900/20.  Of few distinct IDs without hubs the table is
+// the quicker way a little longer: 12 k distinct ones, 98 k 21.5/24.3, 131 k 24.2/25.2, 200 k 28.3/27.  Above 2 M a bucket would have
+// more IDs than half its table, and the list goes by the table.  256 buckets of 1024 threads with eight entries each, 64-bit words and
 // a second search for the answers: buckets 44 us at 1.1 M; linear probing and 512 threads in the split: 15.
 constexpr int kPartTile = 4096;
 constexpr int kPartBits = 9;
@@ -135,8 +137,8 @@ __device__ __forceinline__ void part_clear(PartTable& t, uint32_t threads) {
 }
 // the whole hash: the highest bits are the bucket, the next the place in the table, the lowest the step
 __device__ __forceinline__ uint32_t part_hash(uint32_t id) { return hash_id(id, 0xffffffffu); }
-// The tables are half full at most, and a wave waits for the longest of its 64 searches: steps of the ID's own, odd ones, which
-// come by every slot, keep those short.
+// The split's table is half full at most, a bucket's about that in the longest lists, and a wave waits for the longest of its 64
+// searches: steps of the ID's own, odd ones, which come by every slot, keep those short.
 __device__ __forceinline__ uint32_t part_step(uint32_t h) { return (h << 1) | 1u; }
 // The ID's slot, claimed if need be; kNoSlot after probes_max others.  (A plain read before the atomic: the entries of a hub would
 // take their turns at its word.)

@@ -1066,7 +1066,8 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
         // (the tier lists are scratch of a lookup: no call leaves anything in them for another)
         const PartScratch parts{c->list_slot[0], reinterpret_cast<uint16_t*>(c->list_pos[0]), reinterpret_cast<uint32_t*>(c->list_slot[1]),
                                 reinterpret_cast<uint16_t*>(c->list_pos[0]) + c->cap_ids, reinterpret_cast<uint16_t*>(c->list_pos[1])};
-        if (split_starts_bytes(n_ids) > static_cast<int64_t>(sizeof(int32_t)) * c->cap_ids) return fail(c, HELIOS_EINTERNAL, "scratch too small for a list by parts");
+        if (split_starts_bytes(n_ids) > static_cast<int64_t>(sizeof(int32_t)) * c->cap_ids || (n_ids + 4095) / 4096 * 4096 > c->cap_ids)
+            return fail(c, HELIOS_EINTERNAL, "scratch too small for a list by parts");
         HIP_TRY(c, launch_dedup_by_parts(c->stream, a, n_ids, c->g.n_nodes, parts));
         HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{nullptr, 0}, nullptr, 0));
         return HELIOS_OK;

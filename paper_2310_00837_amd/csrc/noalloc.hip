@@ -41,14 +41,15 @@ constexpr size_t kOffTicket = kOffSmall, kOffCounters = kOffSmall + 64;
 constexpr uint32_t kEndZeroWords = static_cast<uint32_t>((kOffTicket + sizeof(unsigned long long) - kOffStatus) / sizeof(unsigned long long));
 static_assert(kOffStatus + kEndZeroWords * sizeof(unsigned long long) >= kOffTicket + sizeof(uint32_t) &&
               kOffStatus + kEndZeroWords * sizeof(unsigned long long) <= kOffCounters, "the ticket is in, the counters are not");
-// a long list is taken apart by hash in memory of its own (the table stays empty)
+// a long list is taken apart by hash in memory of its own (and uses the table, if at all, as other calls do: it leaves it empty)
 constexpr size_t kOffPartId = kOffSmall + kSmallBytes;
 constexpr size_t kOffPartFirst = kOffPartId + sizeof(int32_t) * kMaxIds;
 constexpr size_t kOffPartPos = kOffPartFirst + sizeof(uint32_t) * kMaxIds;
 constexpr size_t kOffPartLocal = kOffPartPos + sizeof(uint16_t) * kMaxIds;
 constexpr size_t kOffPartStarts = kOffPartLocal + sizeof(uint16_t) * kMaxIds;
 constexpr size_t kScratchBytes = kOffPartStarts + static_cast<size_t>(split_starts_bytes(kMaxIds));
-static_assert(kMaxIds <= kPartsMax, "the longest list can be taken apart");
+static_assert(kMaxIds <= kPartsMax && kMaxIds % 4096 == 0, "the longest list can be taken apart, and its last tile has all its places");
+static_assert(kScratchBytes < (9u << 20) + (256u << 10), "include/helios.h says how large the array is");
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 

@@ -135,10 +135,11 @@ __device__ __forceinline__ uint32_t scan_lookback(const ScanState& st, uint32_t 
 }
 
 // NP rows of per-wave totals feed NC counters: counter c is row c, except that with NC == NP + 1 the last row holds two
-// counters of 16 bits (a tile has at most 2048 items).
+// counters of 16 bits.
 template <int NP, int NC, int K>
 struct TileScan {
     static_assert(NC == NP || NC == NP + 1, "one row may be a pair");
+    static_assert(NC == NP || K * kScanBlock < 65536, "a tile's items can be counted in half a word");
     struct Lds {
         uint32_t total[NP][K * kScanWaves];
         uint32_t excl[NC], agg[NC];
