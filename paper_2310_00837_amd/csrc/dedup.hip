@@ -123,6 +123,7 @@ constexpr uint32_t kPartSlots = 8192;                  // of an LDS table: keys,
 constexpr uint32_t kPartProbes = 128;                  // more than that at one ID: a bucket's table counts as full
 constexpr uint32_t kMaxPartTiles = 512;
 constexpr uint16_t kNoPlace = 0xffff;
+constexpr uint32_t kForeign = 2;                       // (of s_full) a stretch of the table full of another call's words: no search goes on
 static_assert((kPartSlots & (kPartSlots - 1)) == 0 && kPartProbes <= kPartSlots, "odd steps come by every slot once");
 static_assert(kPartsMax == static_cast<int64_t>(kMaxPartTiles) * kPartTile && kMaxPartTiles <= kBucketBlock, "a thread per tile");
 static_assert(kParts <= kSplitBlock && kMergeItems * kScanWaves <= kWave, "a thread per bucket; one step scans a tile");
@@ -326,6 +327,7 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
     for (uint32_t w = t; w < size; w += kBucketBlock) scan_store(stretch + w, kEmptySlot);
     __syncthreads();
     for (uint32_t chunk = 0; chunk < chunks; ++chunk) {
+        if (__hip_atomic_load(&s_full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == kForeign) break;
         entries(chunk);
 #pragma unroll
         for (int k = 0; k < kBucketItems; ++k) {
@@ -339,11 +341,15 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
                 if (mine < cur && cur != kEmptySlot) atomicMin(stretch + q, mine);
                 break;
             }
-            if (left == 0) raise(err, kErrInternal);                        // (as above)
+            if (left == 0) {                                                // (as above)
+                s_full = kForeign;
+                raise(err, kErrInternal);
+            }
         }
     }
     __syncthreads();
     for (uint32_t chunk = 0; chunk < chunks; ++chunk) {
+        if (__hip_atomic_load(&s_full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == kForeign) break;
         entries(chunk);
 #pragma unroll
         for (int k = 0; k < kBucketItems; ++k) {
@@ -354,6 +360,7 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
                 cur = scan_load(stretch + q);
                 if (cur == kEmptySlot || cur >> 32 == id[k]) break;
             }
+            if (left == 0) s_full = kForeign;
             s.first[place[k]] = static_cast<uint32_t>(cur);                 // (it is there, unless another call wrote)
         }
     }
