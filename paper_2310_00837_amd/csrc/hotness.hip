@@ -10,21 +10,22 @@
 // a pass whose digit is the same in all counts is left out: the first reading
 // of the counts finds out which bits vary, and every kernel of the later passes
 // looks there.  Counters of a pre-sampling epoch are at most its number of
-// batches, so that one pass is the rule up to 2048 batches.  A pass is three launches:
+// batches, so that one pass is the rule up to 2048 batches.  A pass has three phases:
 //   count    every group of consecutive tiles of 8192 pairs counts its digits (LDS);
 //   scan     per digit, a prefix sum over the groups, 16 digits to a workgroup;
 //   scatter  a group goes through its tiles: a tile ranks its pairs (wave ballots find
 //            the lanes with the same digit, a counter per wave and digit in LDS carries
 //            the rank along), puts their places into order in LDS and writes them out as runs.
 // Bins are numbered from the highest digit down, so each pass goes out in
-// descending digit order.  Nothing waits for another workgroup.
+// descending digit order.  The first pass takes three launches, each of the others one, in which the workgroups draw
+// the jobs of all phases in order (sort_pass_kernel), because an idle launch costs 2.7 us and there would be six of them.
 //
 // What bounds it: the scatter's ballots and LDS traffic first, memory second.
 // Measured at 8 M nodes with counts up to 512: count 10 us, scan 7.5, scatter 35
-// (its 64 MB would take 11 us), and 2-4 us for each launch of a pass that is left
-// out; 64 us in all, three passes 225, 111 M nodes 565.  With a row of counters per
-// tile, one copy of the count's counters and a scatter of one workgroup per CU it took
-// 82 (17, 9.6 and 45), 287 and 858 us.
+// (its 64 MB would take 11 us); 58 us in all, 111 M nodes 552.  With three launches for each of the other passes, too, 64 and 564 us
+// (20 000 nodes 33.5, now 27), and where those passes run 8 M nodes 146 (two passes; now 152) and 229 (three; now 241).
+// With a row of counters per tile, one copy of the count's counters and a scatter of one workgroup per CU it took
+// 82 (17, 9.6 and 45) at 8 M and 858 us.
 //
 // Why groups of tiles: one row of counters per group, of which there are at most 512, keeps the table at 4 MB whatever the
 // length of the list, and a scan thread has its rows in registers.
@@ -34,15 +35,15 @@
 // leave out the bits that do not vary it was slower (52 us).  1024 groups, or tiles of 4096, made no difference or 5 us more.
 #include "kernels.hpp"
 
+#include <algorithm>
+
 namespace helios {
 
 namespace {
 
-constexpr int kSortBlock = 1024;                          // count and scan
-constexpr int kSortWaves = kSortBlock / kWave;
+constexpr int kSortBlock = 1024;                          // count and scan of the first pass
 constexpr int kSortTile = 8192;                           // pairs
-constexpr int kCountItems = kSortTile / kSortBlock;
-constexpr int kPlaceBlock = 512;                          // scatter
+constexpr int kPlaceBlock = 512;                          // scatter, and all phases of the other passes
 constexpr int kPlaceWaves = kPlaceBlock / kWave;
 constexpr int kPlaceItems = kSortTile / kPlaceBlock;
 constexpr int kPlaceBits = 13;                            // a place in the tile
@@ -50,10 +51,13 @@ constexpr int kDigitBits = 11;
 constexpr int kBins = 1 << kDigitBits;
 constexpr int kSortPasses = 3;
 constexpr int kScanBins = 16;                             // bins per workgroup of the scan
-constexpr int kWalkers = kSortBlock / kScanBins;          // each takes a share of the groups
 constexpr uint32_t kSortMaxGroups = 512;
 constexpr int kCopies = 4;                                // of the count's counters: lanes that meet on a digit spread over them
-static_assert(kWalkers == kWave && kSortWaves == kScanBins, "one wave scans the walkers of one bin");
+constexpr uint32_t kScanSlices = kBins / kScanBins;       // workgroups (or jobs) of a scan
+constexpr int kControlStride = 32;                        // words: what is counted or waited for lies 128 bytes apart
+constexpr int kGoLines = 32;                              // copies of the word that is waited for
+constexpr int kControlPass = (3 + 2 * kGoLines) * kControlStride;       // ticket, groups counted, slices scanned; go (scan), go (scatter)
+constexpr int kControlWords = (kSortPasses - 1) * kControlPass;
 static_assert(kSortTile == 1 << kPlaceBits && kBins == 4 * kPlaceBlock, "a thread of the scatter has four bins");
 
 __global__ __launch_bounds__(kBlock) void hotness_add_kernel(const int32_t* __restrict__ ids, Count n_in, int64_t n_nodes,
@@ -77,7 +81,7 @@ struct SortArgs {
     uint32_t* totals;            // [kBins]
     uint32_t* group_bits;        // [n_groups][2]: bits set in some count, bits clear in some count
     uint32_t* varying;           // bits that are not the same in all counts (from the first pass's scan on)
-    int pass;
+    uint32_t* control;           // [kControlWords], of the passes after the first
     int32_t* err;
 };
 
@@ -106,120 +110,160 @@ __device__ __forceinline__ uint32_t bin_of(int32_t key, int pass) {
     return kBins - 1 - ((static_cast<uint32_t>(key) >> (pass * kDigitBits)) & (kBins - 1));
 }
 
+// Words that one job of a launch writes for later ones of the same launch (SHARED) go past the L2s of the XCDs, both ways.
+template <bool SHARED>
+__device__ __forceinline__ uint32_t get_word(const uint32_t* p) {
+    return SHARED ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+template <bool SHARED>
+__device__ __forceinline__ void put_word(uint32_t* p, uint32_t v) {
+    if (SHARED) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+
+// threadIdx.x; in a loop over jobs, what is worked out from it is to be forgotten after the job (kept, it would fill the registers)
+template <bool SHARED>
+__device__ __forceinline__ uint32_t thread_now() {
+    uint32_t t = threadIdx.x;
+    if (SHARED) asm volatile("" : "+v"(t));
+    return t;
+}
+
 // Bound by the LDS atomics: most counts are one of a few small numbers, and lanes that add to one word take their turns.
 // Four copies of the counters, by lane, cut the queues to a quarter: 17.3 -> 10.2 us for 8 M counts (eight copies: no difference).
-__global__ __launch_bounds__(kSortBlock) void sort_count_kernel(SortArgs a) {
-    __shared__ uint32_t s_hist[kBins * kCopies];
-    __shared__ uint32_t s_set, s_clear;
-    const SortStep step(a.pass, a.pass == 0 ? 0u : *a.varying);
-    if (!step.active) return;
-    const int32_t* keys = step.before == 0 ? a.counts : a.keys[(step.before - 1) & 1];
-    for (int q = threadIdx.x; q < kBins * kCopies; q += kSortBlock) s_hist[q] = 0;
-    if (threadIdx.x == 0) s_set = s_clear = 0;
+struct CountLds {
+    uint32_t hist[kBins * kCopies];
+    uint32_t set, clear;
+};
+template <int B, bool SHARED>
+__device__ __forceinline__ void count_group(const SortArgs& a, int pass, const int32_t* keys, uint32_t group, CountLds& s) {
+    const uint32_t t = thread_now<SHARED>();
+    constexpr int kItems = kSortTile / B;
+    for (uint32_t q = t; q < kBins * kCopies; q += B) s.hist[q] = 0;
+    if (t == 0) s.set = s.clear = 0;
     __syncthreads();
-    const uint32_t tile1 = min((blockIdx.x + 1) * a.group_tiles, a.n_tiles);
+    const uint32_t tile1 = min((group + 1) * a.group_tiles, a.n_tiles);
     uint32_t set = 0, clear = 0;
-    for (uint32_t tile = blockIdx.x * a.group_tiles; tile < tile1; ++tile) {
-        const uint32_t i0 = tile * kSortTile + threadIdx.x;
-        int32_t key[kCountItems];
+    for (uint32_t tile = group * a.group_tiles; tile < tile1; ++tile) {
+        const uint32_t i0 = tile * kSortTile + t;
+        int32_t key[kItems];
 #pragma unroll
-        for (int k = 0; k < kCountItems; ++k) key[k] = keys[i0 + k * kSortBlock < a.n ? i0 + k * kSortBlock : a.n - 1];
+        for (int k = 0; k < kItems; ++k) key[k] = keys[i0 + k * B < a.n ? i0 + k * B : a.n - 1];
 #pragma unroll
-        for (int k = 0; k < kCountItems; ++k) {
+        for (int k = 0; k < kItems; ++k) {
             set |= static_cast<uint32_t>(key[k]);
             clear |= ~static_cast<uint32_t>(key[k]);
-            if (i0 + k * kSortBlock < a.n) atomicAdd(s_hist + bin_of(key[k], a.pass) * kCopies + threadIdx.x % kCopies, 1u);
+            if (i0 + k * B < a.n) atomicAdd(s.hist + bin_of(key[k], pass) * kCopies + t % kCopies, 1u);
         }
     }
-    if (a.pass == 0) {
+    if (pass == 0) {
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) {
             set |= __shfl_xor(set, d, kWave);
             clear |= __shfl_xor(clear, d, kWave);
         }
         if (lane_id() == 0) {
-            atomicOr(&s_set, set);
-            atomicOr(&s_clear, clear);
+            atomicOr(&s.set, set);
+            atomicOr(&s.clear, clear);
         }
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < kBins; q += kSortBlock) {
+    for (uint32_t q = t; q < kBins; q += B) {
         uint32_t sum = 0;
 #pragma unroll
-        for (int k = 0; k < kCopies; ++k) sum += s_hist[q * kCopies + k];
-        a.group_counts[static_cast<size_t>(blockIdx.x) * kBins + q] = sum;
+        for (int k = 0; k < kCopies; ++k) sum += s.hist[q * kCopies + k];
+        put_word<SHARED>(a.group_counts + static_cast<size_t>(group) * kBins + q, sum);
     }
-    if (a.pass == 0 && threadIdx.x == 0) {
-        a.group_bits[2 * blockIdx.x] = s_set;
-        a.group_bits[2 * blockIdx.x + 1] = s_clear;
+    if (pass == 0 && t == 0) {
+        a.group_bits[2 * group] = s.set;
+        a.group_bits[2 * group + 1] = s.clear;
     }
 }
 
-// Workgroup b: the bins [16 b, 16 b + 16) over all groups, by 64 walkers that take consecutive groups each.  In the first
-// pass one workgroup more gathers which bits vary.
-__global__ __launch_bounds__(kSortBlock) void sort_scan_kernel(SortArgs a) {
-    __shared__ uint32_t s_sum[kWalkers][kScanBins + 1];
-    __shared__ uint32_t s_set, s_clear;
-    if (blockIdx.x == kBins / kScanBins) {
-        if (threadIdx.x == 0) s_set = s_clear = 0;
-        __syncthreads();
-        uint32_t set = 0, clear = 0;
-        for (uint32_t t = threadIdx.x; t < a.n_groups; t += kSortBlock) {
-            set |= a.group_bits[2 * t];
-            clear |= a.group_bits[2 * t + 1];
-        }
-        atomicOr(&s_set, set);
-        atomicOr(&s_clear, clear);
-        __syncthreads();
-        if (threadIdx.x == 0) *a.varying = s_set & s_clear;
-        return;
-    }
-    if (a.pass > 0 && !SortStep(a.pass, *a.varying).active) return;
-    const uint32_t walker = threadIdx.x / kScanBins, bin = threadIdx.x % kScanBins;
-    constexpr uint32_t kPer = kSortMaxGroups / kWalkers;
-    uint32_t* column = a.group_counts + blockIdx.x * kScanBins + bin;
+__global__ __launch_bounds__(kSortBlock) void sort_count_kernel(SortArgs a) {
+    __shared__ CountLds s;
+    if (blockIdx.x == 0)
+        for (uint32_t w = threadIdx.x; w < kControlWords; w += kSortBlock) a.control[w] = 0;
+    count_group<kSortBlock, false>(a, 0, a.counts, blockIdx.x, s);
+}
+
+// Slice b: the bins [16 b, 16 b + 16) over all groups, by walkers that take consecutive groups each.
+template <int B>
+struct ScanLds {
+    uint32_t sum[B / kScanBins][kScanBins + 1];
+};
+template <int B, bool SHARED>
+__device__ __forceinline__ void scan_slice(const SortArgs& a, uint32_t slice, ScanLds<B>& s) {
+    const uint32_t t = thread_now<SHARED>();
+    constexpr uint32_t kWalkers = B / kScanBins, kPer = kSortMaxGroups / kWalkers;
+    static_assert(kWalkers <= kWave, "one wave scans the walkers of one bin");
+    const uint32_t walker = t / kScanBins, bin = t % kScanBins;
+    uint32_t* column = a.group_counts + slice * kScanBins + bin;
     uint32_t v[kPer], sum = 0;
 #pragma unroll
     for (uint32_t q = 0; q < kPer; ++q) {            // (unguarded: all in flight together)
         const uint32_t g = walker * kPer + q;
-        v[q] = column[static_cast<size_t>(g < a.n_groups ? g : 0) * kBins];
+        v[q] = get_word<SHARED>(column + static_cast<size_t>(g < a.n_groups ? g : 0) * kBins);
     }
 #pragma unroll
     for (uint32_t q = 0; q < kPer; ++q) {
         if (walker * kPer + q >= a.n_groups) v[q] = 0;
         sum += v[q];
     }
-    s_sum[walker][bin] = sum;
+    s.sum[walker][bin] = sum;
     __syncthreads();
-    {
-        const uint32_t b = static_cast<uint32_t>(wave_id()), w = static_cast<uint32_t>(lane_id());      // one wave per bin
-        const uint32_t mine = s_sum[w][b], inc = dpp_inclusive_scan(mine);
-        s_sum[w][b] = inc - mine;
-        if (w == kWalkers - 1) a.totals[blockIdx.x * kScanBins + b] = inc;
+    for (uint32_t b = static_cast<uint32_t>(wave_id()); b < kScanBins; b += B / kWave) {      // one wave per bin
+        const uint32_t w = static_cast<uint32_t>(lane_id());
+        const uint32_t mine = w < kWalkers ? s.sum[w][b] : 0u, inc = dpp_inclusive_scan(mine);
+        if (w < kWalkers) s.sum[w][b] = inc - mine;
+        if (w == kWave - 1) put_word<SHARED>(a.totals + slice * kScanBins + b, inc);
     }
     __syncthreads();
-    uint32_t run = s_sum[walker][bin];
+    uint32_t run = s.sum[walker][bin];
 #pragma unroll
     for (uint32_t q = 0; q < kPer; ++q) {
         const uint32_t g = walker * kPer + q;
-        if (g < a.n_groups) column[static_cast<size_t>(g) * kBins] = run;
+        if (g < a.n_groups) put_word<SHARED>(column + static_cast<size_t>(g) * kBins, run);
         run += v[q];
     }
 }
 
-__global__ __launch_bounds__(kPlaceBlock) void sort_scatter_kernel(SortArgs a) {
+// One workgroup more than slices: it gathers which bits vary.
+__global__ __launch_bounds__(kSortBlock) void sort_scan_kernel(SortArgs a) {
+    __shared__ ScanLds<kSortBlock> s;
+    __shared__ uint32_t s_set, s_clear;
+    if (blockIdx.x < kScanSlices) {
+        scan_slice<kSortBlock, false>(a, blockIdx.x, s);
+        return;
+    }
+    if (threadIdx.x == 0) s_set = s_clear = 0;
+    __syncthreads();
+    uint32_t set = 0, clear = 0;
+    for (uint32_t t = threadIdx.x; t < a.n_groups; t += kSortBlock) {
+        set |= a.group_bits[2 * t];
+        clear |= a.group_bits[2 * t + 1];
+    }
+    atomicOr(&s_set, set);
+    atomicOr(&s_clear, clear);
+    __syncthreads();
+    if (threadIdx.x == 0) *a.varying = s_set & s_clear;
+}
+
+struct PlaceLds {
     // the ranks' counters (one per wave and bin) and, once the ranks are known, the tile in order share their memory
-    // (pointers by condition and no a.keys[i], or the arguments end up in scratch memory)
-    __shared__ union {
+    union {
         uint16_t count[kPlaceWaves][kBins];
         unsigned long long four[kPlaceWaves][kBins / 4];      // a thread's bins
         uint32_t out[kSortTile];                              // {bin : 11 | place in the tile : 13}
-    } s;
-    __shared__ uint32_t s_to[kBins];                          // where a bin goes in the output, minus where it begins in the tile
-    __shared__ int32_t s_word[kSortTile];
-    __shared__ uint32_t s_wave[kPlaceWaves];
-    const SortStep step(a.pass, *a.varying);
-    if (!step.active) return;
+    };
+    uint32_t to[kBins];                                       // where a bin goes in the output, minus where it begins in the tile
+    int32_t word[kSortTile];
+    uint32_t wave[kPlaceWaves];
+};
+template <bool SHARED>
+__device__ __forceinline__ void scatter_group(const SortArgs& a, int pass, const SortStep& step, uint32_t group, PlaceLds& s) {
+    const uint32_t t = thread_now<SHARED>();
+    // (pointers by condition and no a.keys[i], or the arguments end up in scratch memory)
     const int32_t* keys_in = step.before == 0 ? a.counts : step.before == 1 ? a.keys[0] : a.keys[1];
     const int32_t* vals_in = step.before == 0 ? nullptr : step.to_order ? a.vals1 : a.order;
     int32_t* keys_out = step.last ? nullptr : step.before == 0 ? a.keys[0] : a.keys[1];
@@ -232,9 +276,9 @@ __global__ __launch_bounds__(kPlaceBlock) void sort_scatter_kernel(SortArgs a) {
 #pragma unroll
         for (int q = 0; q < kPer; ++q) mine += v[q];
         const uint32_t inc = dpp_inclusive_scan(mine);
-        if (lane == kWave - 1) s_wave[wave] = inc;
+        if (lane == kWave - 1) s.wave[wave] = inc;
         __syncthreads();
-        const uint32_t w = lane < kPlaceWaves ? s_wave[lane] : 0u;
+        const uint32_t w = lane < kPlaceWaves ? s.wave[lane] : 0u;
         const uint32_t upto = dpp_inclusive_scan(w);
         uint32_t at = lane_value(upto, wave) - lane_value(w, wave) + inc - mine;
 #pragma unroll
@@ -247,20 +291,20 @@ __global__ __launch_bounds__(kPlaceBlock) void sort_scatter_kernel(SortArgs a) {
     const uint32_t n = a.n;
     uint32_t total[kPer], next[kPer];            // next: where the tile's pairs of the bin go in the output
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) total[q] = a.totals[threadIdx.x * kPer + q];
+    for (int q = 0; q < kPer; ++q) total[q] = get_word<SHARED>(a.totals + t * kPer + q);
     scan_bins(total, next);
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) next[q] += a.group_counts[static_cast<size_t>(blockIdx.x) * kBins + threadIdx.x * kPer + q];
-    const uint32_t tile1 = min((blockIdx.x + 1) * a.group_tiles, a.n_tiles);
-    for (uint32_t tile = blockIdx.x * a.group_tiles; tile < tile1; ++tile) {
+    for (int q = 0; q < kPer; ++q) next[q] += get_word<SHARED>(a.group_counts + static_cast<size_t>(group) * kBins + t * kPer + q);
+    const uint32_t tile1 = min((group + 1) * a.group_tiles, a.n_tiles);
+    for (uint32_t tile = group * a.group_tiles; tile < tile1; ++tile) {
         // a wave owns 1024 consecutive pairs, 64 per round
         const uint32_t base = tile * kSortTile, here = min(n - base, static_cast<uint32_t>(kSortTile));
         const uint32_t at0 = wave * (kPlaceItems * kWave) + lane;
         uint32_t item[kPlaceItems];              // the bin, then {bin : 11 | rank : 13}
 #pragma unroll
-        for (int k = 0; k < kPlaceItems; ++k) item[k] = bin_of(keys_in[base + (at0 + k * kWave < here ? at0 + k * kWave : 0)], a.pass);
+        for (int k = 0; k < kPlaceItems; ++k) item[k] = bin_of(keys_in[base + (at0 + k * kWave < here ? at0 + k * kWave : 0)], pass);
 #pragma unroll
-        for (int w = 0; w < kPlaceWaves; ++w) s.four[w][threadIdx.x] = 0;
+        for (int w = 0; w < kPlaceWaves; ++w) s.four[w][t] = 0;
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kPlaceItems; ++k) {
@@ -290,7 +334,7 @@ __global__ __launch_bounds__(kPlaceBlock) void sort_scatter_kernel(SortArgs a) {
 #pragma unroll
         for (int w = 0; w < kPlaceWaves; ++w) {
             before[w] = sum;
-            sum += s.four[w][threadIdx.x];
+            sum += s.four[w][t];
         }
         uint32_t in_tile[kPer], start[kPer];
         unsigned long long begins = 0;
@@ -300,11 +344,11 @@ __global__ __launch_bounds__(kPlaceBlock) void sort_scatter_kernel(SortArgs a) {
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
             begins |= static_cast<unsigned long long>(start[q]) << (16 * q);
-            s_to[threadIdx.x * kPer + q] = next[q] - start[q];
+            s.to[t * kPer + q] = next[q] - start[q];
             next[q] += in_tile[q];
         }
 #pragma unroll
-        for (int w = 0; w < kPlaceWaves; ++w) s.four[w][threadIdx.x] = before[w] + begins;
+        for (int w = 0; w < kPlaceWaves; ++w) s.four[w][t] = before[w] + begins;
         __syncthreads();
         uint32_t place[kPlaceItems];
 #pragma unroll
@@ -316,7 +360,7 @@ __global__ __launch_bounds__(kPlaceBlock) void sort_scatter_kernel(SortArgs a) {
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kPlaceItems; ++k) {
-            const uint32_t p = threadIdx.x + k * kPlaceBlock, e = s.out[p < here ? p : 0], to = s_to[e >> kPlaceBits] + p;
+            const uint32_t p = t + k * kPlaceBlock, e = s.out[p < here ? p : 0], to = s.to[e >> kPlaceBits] + p;
             if (p < here && to >= n) raise(a.err, kErrInternal);         // never, unless the counts changed between the kernels
             if (p < here && to < n && !vals_in) vals_out[to] = static_cast<int32_t>(base + (e & (kSortTile - 1)));
         }
@@ -324,19 +368,73 @@ __global__ __launch_bounds__(kPlaceBlock) void sort_scatter_kernel(SortArgs a) {
         const auto move = [&](const int32_t* in, int32_t* out) {
 #pragma unroll
             for (int k = 0; k < kPlaceItems; ++k) {
-                const uint32_t p = threadIdx.x + k * kPlaceBlock;
-                s_word[p] = in[base + (p < here ? p : 0)];
+                const uint32_t p = t + k * kPlaceBlock;
+                s.word[p] = in[base + (p < here ? p : 0)];
             }
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < kPlaceItems; ++k) {
-                const uint32_t p = threadIdx.x + k * kPlaceBlock, e = s.out[p < here ? p : 0], to = s_to[e >> kPlaceBits] + p;
-                if (p < here && to < n) out[to] = s_word[e & (kSortTile - 1)];
+                const uint32_t p = t + k * kPlaceBlock, e = s.out[p < here ? p : 0], to = s.to[e >> kPlaceBits] + p;
+                if (p < here && to < n) out[to] = s.word[e & (kSortTile - 1)];
             }
             __syncthreads();
         };
         if (vals_in) move(vals_in, vals_out);
         if (keys_out) move(keys_in, keys_out);
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(kPlaceBlock) void sort_scatter_kernel(SortArgs a) {
+    __shared__ PlaceLds s;
+    scatter_group<false>(a, 0, SortStep(0, *a.varying), blockIdx.x, s);
+}
+
+// A pass after the first, if it runs.  The jobs (a group to count, a slice to scan, a group to scatter) are numbered phase by phase,
+// and a workgroup draws the next number from a counter until there is none.  A job waits until all jobs of the phase before it
+// are done; those have lower numbers, so workgroups that run already hold them, and the lowest job that is not done waits for
+// nothing: however few workgroups the GPU has room for, the launch ends.  Between the phases only the counts and their sums
+// change hands, as words that go past the L2s (put_word): a wave waits until its own are there before its job counts as done.
+// Whoever finishes a phase says so in 32 places, as hundreds that look at one word keep those away that add to it (10 ns each;
+// 8 M nodes, a second pass: 120 us when they did).
+template <int PASS>
+__global__ __launch_bounds__(kPlaceBlock, 4) void sort_pass_kernel(SortArgs a) {
+    __shared__ union {
+        CountLds count;
+        ScanLds<kPlaceBlock> scan;
+        PlaceLds place;
+    } s;
+    __shared__ uint32_t s_job;
+    const SortStep step(PASS, *a.varying);
+    if (!step.active) return;
+    const uint32_t n_jobs = 2 * a.n_groups + kScanSlices;
+    uint32_t* ticket = a.control + (PASS - 1) * kControlPass;
+    if (threadIdx.x == 0) s_job = atomicAdd(ticket, 1u);
+    __syncthreads();
+    for (uint32_t job; (job = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(s_job)))) < n_jobs;) {
+        const uint32_t phase = job < a.n_groups ? 0u : job < a.n_groups + kScanSlices ? 1u : 2u;
+        if (phase > 0) {
+            if (threadIdx.x == 0) {
+                const uint32_t* go = ticket + (3 + (phase - 1) * kGoLines + job % kGoLines) * kControlStride;
+                uint32_t budget = kScanSpinBudget;
+                while (__hip_atomic_load(go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 && --budget > 0) __builtin_amdgcn_s_sleep(4);
+                if (budget == 0) raise(a.err, kErrInternal);       // gave up: report, and let the launch drain
+            }
+            __syncthreads();
+        }
+        if (phase == 0) count_group<kPlaceBlock, true>(a, PASS, step.before == 1 ? a.keys[0] : a.keys[1], job, s.count);
+        else if (phase == 1) scan_slice<kPlaceBlock, true>(a, job - a.n_groups, s.scan);
+        else scatter_group<true>(a, PASS, step, job - a.n_groups - kScanSlices, s.place);
+        if (phase < 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            if (phase < 2 && atomicAdd(ticket + (phase + 1) * kControlStride, 1u) + 1 == (phase == 0 ? a.n_groups : kScanSlices))
+                for (int q = 0; q < kGoLines; ++q)
+                    put_word<true>(ticket + (3 + phase * kGoLines + q) * kControlStride, 1u);
+            s_job = atomicAdd(ticket, 1u);
+        }
+        // (The loop has to end with a barrier: with that `if` as its end the compiler makes two loops of it, and the lanes beside lane 0
+        // go round without it.)
         __syncthreads();
     }
 }
@@ -358,7 +456,7 @@ hipError_t launch_hotness_add(hipStream_t stream, const int32_t* ids, Count n, i
 
 namespace {
 struct SortLayout {              // scratch of the hotness order, in bytes
-    size_t tiles, group_tiles, groups, totals, varying, bits, counts, keys1, keys2, vals1, bytes;
+    size_t tiles, group_tiles, groups, totals, varying, control, bits, counts, keys1, keys2, vals1, bytes;
     explicit SortLayout(int64_t n) {
         const auto up = [](size_t b) { return (b + 255) / 256 * 256; };
         tiles = static_cast<size_t>((n + kSortTile - 1) / kSortTile);
@@ -368,7 +466,8 @@ struct SortLayout {              // scratch of the hotness order, in bytes
         const size_t ints = up(sizeof(int32_t) * static_cast<size_t>(n));
         totals = 0;
         varying = totals + up(sizeof(uint32_t) * kBins);
-        bits = varying + 256;
+        control = varying + 256;
+        bits = control + up(sizeof(uint32_t) * kControlWords);
         counts = bits + up(sizeof(uint32_t) * 2 * groups);
         keys1 = counts + up(sizeof(uint32_t) * kBins * groups);
         keys2 = keys1 + ints;
@@ -399,6 +498,7 @@ hipError_t launch_hotness_order(hipStream_t stream, const int32_t* counts, int64
     a.totals = reinterpret_cast<uint32_t*>(p + at.totals);
     a.group_bits = reinterpret_cast<uint32_t*>(p + at.bits);
     a.varying = reinterpret_cast<uint32_t*>(p + at.varying);
+    a.control = reinterpret_cast<uint32_t*>(p + at.control);
     a.err = err;
     // With one pass or three the first one already writes to `order`.  If that is (part of) the counters' own memory, the pass
     // reads a copy, in the buffer that no pass writes before the second has begun.
@@ -409,12 +509,12 @@ hipError_t launch_hotness_order(hipStream_t stream, const int32_t* counts, int64
         a.counts = a.keys[1];
     }
     const dim3 groups(a.n_groups), block(kSortBlock);
-    for (int pass = 0; pass < kSortPasses; ++pass) {
-        a.pass = pass;
-        hipLaunchKernelGGL(sort_count_kernel, groups, block, 0, stream, a);
-        hipLaunchKernelGGL(sort_scan_kernel, dim3(kBins / kScanBins + (pass == 0 ? 1 : 0)), block, 0, stream, a);
-        hipLaunchKernelGGL(sort_scatter_kernel, groups, dim3(kPlaceBlock), 0, stream, a);
-    }
+    hipLaunchKernelGGL(sort_count_kernel, groups, block, 0, stream, a);
+    hipLaunchKernelGGL(sort_scan_kernel, dim3(kScanSlices + 1), block, 0, stream, a);
+    hipLaunchKernelGGL(sort_scatter_kernel, groups, dim3(kPlaceBlock), 0, stream, a);
+    const dim3 workers(std::max(a.n_groups, kScanSlices));
+    hipLaunchKernelGGL(sort_pass_kernel<1>, workers, dim3(kPlaceBlock), 0, stream, a);
+    hipLaunchKernelGGL(sort_pass_kernel<2>, workers, dim3(kPlaceBlock), 0, stream, a);
     return hipGetLastError();
 }
 
