@@ -20,10 +20,11 @@
 // descending digit order.  The first pass takes three launches, each of the others one, in which the workgroups draw
 // the jobs of all phases in order (sort_pass_kernel), because an idle launch costs 2.7 us and there would be six of them.
 //
-// What bounds it: the scatter's ballots and LDS traffic first, memory second.
-// Measured at 8 M nodes with counts up to 512: count 10 us, scan 7.5, scatter 35
-// (its 64 MB would take 11 us); 58 us in all, 111 M nodes 552.  With three launches for each of the other passes, too, 64 and 564 us
-// (20 000 nodes 33.5, now 27), and where those passes run 8 M nodes 146 (two passes; now 152) and 229 (three; now 241).
+// What bounds it: the chain of steps of the scatter's two tiles per workgroup, its ballots and its LDS traffic; memory second.
+// Measured at 8 M nodes with counts up to 512: count 10 us, scan 8, scatter 29
+// (its 64 MB would take 11 us); 54 us in all, 111 M nodes 521.  With three launches for each of the other passes, too, and a scatter
+// that looked at all bits (35 us) it took 64 and 561 us, 20 000 nodes 33.5 (now 27); and where those passes run, 8 M nodes 146
+// (two passes; now 150) and 229 (three; now 240), 111 M 1808 (1767) and 2991 (2951).
 // With a row of counters per tile, one copy of the count's counters and a scatter of one workgroup per CU it took
 // 82 (17, 9.6 and 45) at 8 M and 858 us.
 //
@@ -31,8 +32,10 @@
 // length of the list, and a scan thread has its rows in registers.
 // Why 512 threads with 16 pairs each in the scatter: its counters then take 32 KB (16 waves of 8 pairs: 64 KB), and with the
 // order kept as {digit, place in the tile}, 4 bytes a pair, two workgroups fit a CU (74 KB and 128 registers each), so that one has
-// its memory traffic while the other ranks.  A digit's bit costs the ranking five instructions of a wave for 64 pairs; as branches that
-// leave out the bits that do not vary it was slower (52 us).  1024 groups, or tiles of 4096, made no difference or 5 us more.
+// its memory traffic while the other ranks.  A digit's bit costs the ranking four instructions of a wave for 64 pairs, and the five
+// higher bits are left out where a wave's 64 agree on them: 35 -> 29 us (a branch for every bit 52; the
+// lower bits four or five in number 94.4 and 93.2 us for the cache set-up, six 92.4).  The next tile's keys asked for ahead, or a full tile
+// without its bounds checks: no difference.  1024 groups, or tiles of 4096, made no difference or 5 us more.
 #include "kernels.hpp"
 
 #include <algorithm>
@@ -51,6 +54,7 @@ constexpr int kDigitBits = 11;
 constexpr int kBins = 1 << kDigitBits;
 constexpr int kSortPasses = 3;
 constexpr int kScanBins = 16;                             // bins per workgroup of the scan
+constexpr int kLowBits = 6;                               // of a digit, that are always looked at
 constexpr uint32_t kSortMaxGroups = 512;
 constexpr int kCopies = 4;                                // of the count's counters: lanes that meet on a digit spread over them
 constexpr uint32_t kScanSlices = kBins / kScanBins;       // workgroups (or jobs) of a scan
@@ -249,10 +253,29 @@ __global__ __launch_bounds__(kSortBlock) void sort_scan_kernel(SortArgs a) {
     if (threadIdx.x == 0) *a.varying = s_set & s_clear;
 }
 
+// The lanes of a wave that hold the same bin as this one.
+struct Peers {
+    uint32_t lo, hi;
+    template <int FROM, int TO>
+    __device__ __forceinline__ void agree(uint32_t bin) {          // those that agree on the bits too; four instructions for each
+#pragma unroll
+        for (int b = FROM; b < TO; ++b) {
+            uint32_t mine = static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(bin), b, 1));
+            asm("" : "+v"(mine));                                  // (or the comparison gets a shift of its own)
+            const uint64_t ones = __ballot(mine != 0);
+            lo = __builtin_amdgcn_bitop3_b32(lo, static_cast<uint32_t>(ones), mine, 0x90);      // x & ~(y ^ z)
+            hi = __builtin_amdgcn_bitop3_b32(hi, static_cast<uint32_t>(ones >> 32), mine, 0x90);
+        }
+    }
+    __device__ __forceinline__ uint32_t rank() const { return __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u)); }
+    __device__ __forceinline__ uint32_t count() const { return static_cast<uint32_t>(__popc(lo) + __popc(hi)); }
+};
+
 struct PlaceLds {
     // the ranks' counters (one per wave and bin) and, once the ranks are known, the tile in order share their memory
     union {
         uint16_t count[kPlaceWaves][kBins];
+        uint32_t two[kPlaceWaves][kBins / 2];
         unsigned long long four[kPlaceWaves][kBins / 4];      // a thread's bins
         uint32_t out[kSortTile];                              // {bin : 11 | place in the tile : 13}
     };
@@ -310,21 +333,17 @@ __device__ __forceinline__ void scatter_group(const SortArgs& a, int pass, const
         for (int k = 0; k < kPlaceItems; ++k) {
             const uint32_t bin = item[k];
             const uint64_t there = __ballot(at0 + k * kWave < here);
-            uint32_t lo = static_cast<uint32_t>(there), hi = static_cast<uint32_t>(there >> 32);
-#pragma unroll
-            for (int b = 0; b < kDigitBits; ++b) {                // peers: the lanes that agree on the bit (four instructions)
-                const uint32_t mine = static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int>(bin), b, 1));
-                const uint64_t ones = __ballot(mine != 0);
-                lo &= ~(static_cast<uint32_t>(ones) ^ mine);
-                hi &= ~(static_cast<uint32_t>(ones >> 32) ^ mine);
-            }
-            const uint64_t peers = (static_cast<uint64_t>(hi) << 32) | lo;
-            const uint32_t among = rank_in_mask(peers);
-            const uint32_t seen = s.count[wave][bin];
-            item[k] = (bin << kPlaceBits) | (seen + among);
+            Peers peers{static_cast<uint32_t>(there), static_cast<uint32_t>(there >> 32)};
+            peers.agree<0, kLowBits>(bin);
+            // (most counts are small)
+            if (__ballot((bin ^ static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bin)))) >> kLowBits != 0) != 0) peers.agree<kLowBits, kDigitBits>(bin);
+            const uint32_t among = peers.rank();
+            // The wave's counter of the bin is read and then added to, two of them to a word; LDS works a wave's requests off in order,
+            // so that nothing has to wait in between.
+            item[k] = (bin << kPlaceBits) | (s.count[wave][bin] + among);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
-            if (among == 0 && at0 + k * kWave < here) s.count[wave][bin] = static_cast<uint16_t>(seen + __popcll(peers));
+            if (among == 0 && at0 + k * kWave < here) __hip_atomic_fetch_add(&s.two[wave][bin / 2], peers.count() << (16 * (bin % 2)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }

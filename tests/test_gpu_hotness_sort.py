@@ -9,14 +9,15 @@ SIZES = [1, 2, 65, 8191, 8192, 8193, 70_001]
 KINDS = {"zero": lambda r, n: np.zeros(n), "equal": lambda r, n: np.full(n, 123_456_789), "low": lambda r, n: r.integers(0, 2048, n),
          "few": lambda r, n: r.poisson(0.7, n), "middle": lambda r, n: r.integers(0, 2048, n) << 11,
          "high": lambda r, n: r.integers(0, 512, n) << 22, "low and high": lambda r, n: (r.integers(0, 3, n) << 29) | r.integers(0, 9, n),
-         "all": lambda r, n: r.integers(0, 1 << 31, n), "low and middle": lambda r, n: r.integers(0, 1 << 14, n)}
+         "all": lambda r, n: r.integers(0, 1 << 31, n), "low and middle": lambda r, n: r.integers(0, 1 << 14, n),
+         "few and hubs": lambda r, n: np.where(r.random(n) < 0.01, r.integers(0, 5000, n), r.poisson(0.7, n))}      # waves with and without high bits
 
 
 @pytest.mark.parametrize("kind", KINDS)
 def test_hotness_order_at_tile_edges(oracle, kind):
     from paper_2310_00837_amd import helios
     h = helios.Helios(0)
-    for n in SIZES + ([8192 * 512 + 77] if kind in ("few", "all") else []):        # the last: more tiles than workgroups
+    for n in SIZES + ([8192 * 512 + 77] if kind in ("few", "all", "few and hubs") else []):        # the last: more tiles than workgroups
         print("hotness order", kind, n, flush=True)
         counts = KINDS[kind](np.random.default_rng(n), n).astype(np.int32)
         h.csr_load(torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
