@@ -49,21 +49,28 @@ __global__ __launch_bounds__(kBlock) void rank_check_kernel(const int32_t* __res
 // The scattered stores are bound by the parts of lines that they write: a hotness order has the nodes of one count in a row, ascending, so
 // every line of the map is written in parts once per count, by whichever XCD, and the memory takes some 60 such requests a ns.  By
 // buckets every line is written once:
-//   split   every tile of 4096 ranks hands its (node, rank) pairs to the buckets of 2^shift neighbouring nodes that they belong to;
-//           a bucket's pairs lie where its nodes' ranks will (a permutation fills it exactly);
+//   split   every tile of 4096 ranks hands its nodes to the buckets of 2^shift neighbouring nodes that they belong to; what a bucket
+//           gets lies where its nodes' ranks will (a permutation fills it exactly).  64 nodes of one wave that all go to one bucket,
+//           the rule in a hotness order, are a run: their ranks are consecutive, so the first rank and the 64 places in the bucket,
+//           of 2 bytes, say it all.  Other nodes go as pairs {node, rank} of 8 bytes;
 //   place   a workgroup per bucket puts the ranks in order in LDS and writes them out.
 // Where an order goes through neighbouring nodes (all of one count, as those that no batch has met; nodes numbered by locality) its stores are
 // whole lines to begin with: the split then stores them itself, and place only looks whether the order has the node there.
-// Measured, us by scattered stores / by buckets: the hotness order of a power law (and a random order)
-//   1 M nodes 13.2/14.2 (18.4/19.9)   2 M 25/19 (36/33; the line)   3 M 34/23 (48/41)   8 M 78/38 (114/83)   16 M 142/66 (216/143)
-// of counts that are 0 for 99 of 100 nodes (and for 9 of 10; and all the same)
-//   2 M 14.5/15.1 (15.2/18.0; 12.0/13.4)   3 M 17.2/17.4 (19.6/21.3; 13.2/16.7)   8 M 28/30 (39/37; 27/28)   16 M 49/54 (64/67; 46/51)
-// and with every wave handing out pairs 18, 22, 37 and 66, whatever the order.  The nodes in random blocks of 64: 8 M 27/29 (with pairs 59).
+// Measured, us by scattered stores / by buckets with pairs only / with runs: the hotness order of a power law
+//   1 M nodes 13.2/14.2/-   2 M 25/19.7/15.3 (the line)   3 M 34/23.6/19.0   8 M 78/38.0/29.1   16 M 142/66.2/52.4
+// (a random order 8 M 114/83/80, 3 M 48/41/39), of counts that are 0 for 99 of 100 nodes (and for 9 of 10; and all the same)
+//   2 M 14.5/15.1/13.4 (15.2/17.3/16.2; 12.0/11.6/10.0)   3 M 17.2/17.5/15.5 (19.6/20.6/19.0; 13.2/17.3/15.5)
+//   8 M 28/30/27.1 (39/35.9/33.9; 27/28/25.2)   16 M 49/53/49 (64/64.5/62.5; 46/51/47)
+// and the nodes in random blocks of 64: 8 M 27/28/25.4.  (With runs there is a launch less, too: 2 us.)  8 M of a power law by kernels: split 20.8 with pairs, 16.7 with runs, place 16.3 and 12.1.
 // The buckets take 8 bytes of scratch per node, so they are used where the context has that from making a hotness order; and above 16.7 M
-// nodes a bucket would not fit LDS.  (Four ranks per thread in the split; with eight 39.8 at 8 M, with sixteen 55: one chain of LDS additions.)
+// nodes a bucket would not fit LDS.  (Four ranks per thread in the split: with 512 or 256 threads, or eight ranks, 0 to 4 us slower, random orders
+// up to 50; workgroups that go through several tiles, the next one asked for ahead, 2 us slower.)
 constexpr int kInvertBlock = 1024;
 constexpr int kInvertItems = 4;
 constexpr uint32_t kInvertTile = kInvertBlock * kInvertItems;
+constexpr int kHandBlock = 1024;                       // split
+constexpr int kHandItems = 4;
+constexpr uint32_t kHandTile = kHandBlock * kHandItems;
 constexpr uint32_t kInvertBuckets = 512;
 constexpr uint32_t kInvertMaxShift = 15;               // 32768 ranks: 128 KB of LDS
 constexpr int kPlaceItems = 8;                         // one at a time: 16 M by pairs 33.5 us in place, with eight 31
@@ -71,84 +78,136 @@ constexpr uint32_t kNear = 96;                         // three lines of ranks (
 constexpr int64_t kInvertMin = 2000000;
 constexpr int64_t kInvertMax = static_cast<int64_t>(kInvertBuckets) << kInvertMaxShift;
 
-__global__ __launch_bounds__(kInvertBlock) void rank_zero_kernel(uint32_t* cursors, int64_t* holes) {
-    if (threadIdx.x < kInvertBuckets) cursors[threadIdx.x] = 0;
-    if (threadIdx.x == 0) *holes = 0;
-}
+// What a bucket is handed lies where its nodes are among all nodes, 8 bytes for each: the places of its runs (64 nodes of one wave, so 64
+// consecutive ranks) from the front, 2 bytes a node, and its pairs from the back.  Of a permutation a bucket gets as many nodes as it
+// has, so the two do not meet.
+struct InvertScratch {
+    uint32_t* cursors;           // [2][kInvertBuckets]: pairs and runs that a bucket has been handed so far; zero between calls
+    unsigned long long* pairs;   // [n] {node : 32 | rank : 32}
+    uint32_t* run_rank;          // [n / 64] rank of a run's first node
+    __device__ __forceinline__ uint16_t* places(uint32_t first) const { return reinterpret_cast<uint16_t*>(pairs + first); }
+};
+constexpr int kRunsAhead = 4;
+static_assert(2 * kInvertBuckets == kMapCursors, "the context's counters");
 
-__global__ __launch_bounds__(kInvertBlock) void rank_split_kernel(const int32_t* __restrict__ order, uint32_t n, uint32_t shift, uint32_t* cursors,
-                                                                  unsigned long long* pairs, int32_t* rank, int32_t* err) {
-    __shared__ uint32_t s_count[kInvertBuckets], s_base[kInvertBuckets], s_unused[kWave];
-    const uint32_t r0 = blockIdx.x * kInvertTile + threadIdx.x, lane = static_cast<uint32_t>(lane_id());
-    uint32_t v[kInvertItems], at[kInvertItems], lead[kInvertItems];
-    uint64_t same[kInvertItems];
+__global__ __launch_bounds__(kHandBlock) void rank_split_kernel(const int32_t* __restrict__ order, uint32_t n, uint32_t shift, InvertScratch s,
+                                                                  int32_t* rank, int64_t* holes, int32_t* err) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *holes = 0;
+    // of pairs [0, 512) and of runs [512, 1024): how many this tile has for a bucket, and where they go
+    __shared__ uint32_t s_count[2 * kInvertBuckets], s_base[2 * kInvertBuckets], s_unused[kWave];
+    const uint32_t r0 = blockIdx.x * kHandTile + threadIdx.x, lane = static_cast<uint32_t>(lane_id());
+    uint32_t v[kHandItems];
 #pragma unroll
-    for (int k = 0; k < kInvertItems; ++k) v[k] = static_cast<uint32_t>(order[r0 + k * kInvertBlock < n ? r0 + k * kInvertBlock : 0]);
-    if (threadIdx.x < kInvertBuckets) s_count[threadIdx.x] = 0;
+    for (int k = 0; k < kHandItems; ++k) v[k] = static_cast<uint32_t>(order[min(r0 + k * kHandBlock, n - 1)]);
+    for (uint32_t c = threadIdx.x; c < 2 * kInvertBuckets; c += kHandBlock) s_count[c] = 0;
     __syncthreads();
+    bool bad = false;
 #pragma unroll
-    for (int k = 0; k < kInvertItems; ++k) {
-        const bool here = r0 + k * kInvertBlock < n;
-        if (here && v[k] >= n) raise(err, kErrData);
-        if (!here || v[k] >= n) v[k] = ~0u;
+    for (int k = 0; k < kHandItems; ++k) {
+        const bool here = r0 + k * kHandBlock < n, node = v[k] < n;
+        bad = bad || (here && !node);
+        v[k] = here && node ? v[k] : ~0u;
     }
+    if (bad) raise(err, kErrData);
     // A wave whose nodes ascend or descend by little: the first and the last one of its first 64 lie close together.  They are
     // stored at once, and are no pairs from here on.  (If the others don't, it only takes longer.  Asked of all 256, an order without
     // such waves took 1 us longer.)
     const uint32_t v0 = lane_value(v[0], 0), v1 = lane_value(v[0], kWave - 1);
     if ((v0 < v1 ? v1 - v0 : v0 - v1) < kNear && v1 != ~0u) {
 #pragma unroll
-        for (int k = 0; k < kInvertItems; ++k) {
-            if (v[k] != ~0u) rank[v[k]] = static_cast<int32_t>(r0 + k * kInvertBlock);
+        for (int k = 0; k < kHandItems; ++k) {
+            if (v[k] != ~0u) rank[v[k]] = static_cast<int32_t>(r0 + k * kHandBlock);
             v[k] = ~0u;
         }
     }
+    // In a hotness order the nodes of a wave are mostly of one bucket, and then a run.  Lane k has the bucket of the wave's k-th run and
+    // its number, so that one addition counts them all.
+    bool run[kHandItems], all_runs = true;
+    uint32_t run_bucket = ~0u, nth = 0;
 #pragma unroll
-    for (int k = 0; k < kInvertItems; ++k) {
-        const uint32_t bucket = v[k] >> shift;
-        // In a hotness order the nodes of a wave are mostly neighbours: those that go where the first goes are counted at once, by
-        // the first.  (Every lane adds somewhere, so that the additions of all items are on their way together.)
-        const uint64_t there = __ballot(v[k] != ~0u);
-        lead[k] = there ? static_cast<uint32_t>(__ffsll(static_cast<long long>(there)) - 1) : 0u;
-        same[k] = __ballot(bucket == lane_value(bucket, lead[k])) & there;
-        const bool leads = lane == lead[k], counts = v[k] != ~0u && (leads || !((same[k] >> lane) & 1u));
-        at[k] = atomicAdd(counts ? s_count + bucket : s_unused + lane, leads ? static_cast<uint32_t>(__popcll(same[k])) : 1u);
+    for (int k = 0; k < kHandItems; ++k) {
+        const uint32_t head = lane_value(v[k], 0);
+        run[k] = __ballot(v[k] >> shift == head >> shift) == ~0ull && head != ~0u;
+        all_runs = all_runs && (run[k] || __ballot(v[k] != ~0u) == 0);
+        if (lane == static_cast<uint32_t>(k) && run[k]) run_bucket = head >> shift;
+    }
+    if (run_bucket != ~0u) nth = atomicAdd(s_count + kInvertBuckets + run_bucket, 1u);
+    uint32_t at[kHandItems];
+    if (!all_runs) {
+        uint32_t lead[kHandItems];
+        uint64_t same[kHandItems];
+#pragma unroll
+        for (int k = 0; k < kHandItems; ++k) {
+            const uint32_t bucket = v[k] >> shift;
+            // Those that go where the first goes are counted at once, by the first.  (Every lane adds somewhere, so that the additions of
+            // all items are on their way together.)
+            const uint64_t there = run[k] ? 0 : __ballot(v[k] != ~0u);
+            lead[k] = there ? static_cast<uint32_t>(__ffsll(static_cast<long long>(there)) - 1) : 0u;
+            same[k] = __ballot(bucket == lane_value(bucket, lead[k])) & there;
+            const bool leads = lane == lead[k], counts = ((there >> lane) & 1u) && (leads || !((same[k] >> lane) & 1u));
+            at[k] = atomicAdd(counts ? s_count + bucket : s_unused + lane, leads ? static_cast<uint32_t>(__popcll(same[k])) : 1u);
+        }
+#pragma unroll
+        for (int k = 0; k < kHandItems; ++k) {
+            const uint32_t from = lane_value(at[k], lead[k]);
+            if ((same[k] >> lane) & 1u) at[k] = from + rank_in_mask(same[k]);
+        }
+    }
+    __syncthreads();
+    for (uint32_t c = threadIdx.x; c < 2 * kInvertBuckets; c += kHandBlock)
+        if (s_count[c] != 0) s_base[c] = atomicAdd(s.cursors + c, s_count[c]);
+    __syncthreads();
+    // (More than the bucket has nodes: some node is there twice.  What does not fit is left out, and the bucket's workgroup goes by the
+    // order itself.)
+    if (run_bucket != ~0u) {
+        const uint32_t first = run_bucket << shift, nodes = min(n - first, 1u << shift);
+        nth += s_base[kInvertBuckets + run_bucket];
+        if ((nth + 1) * kWave > nodes) nth = ~0u;
+        else s.run_rank[first / kWave + nth] = r0 - lane + lane * kHandBlock;
     }
 #pragma unroll
-    for (int k = 0; k < kInvertItems; ++k)
-        if ((same[k] >> lane) & 1u) at[k] = lane_value(at[k], lead[k]) + rank_in_mask(same[k]);
-    __syncthreads();
-    if (threadIdx.x < kInvertBuckets) {
-        const uint32_t c = s_count[threadIdx.x];
-        s_base[threadIdx.x] = c ? atomicAdd(cursors + threadIdx.x, c) : 0u;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < kInvertItems; ++k) {
-        if (v[k] == ~0u) continue;
-        const uint32_t bucket = v[k] >> shift, place = s_base[bucket] + at[k], nodes = min(n - (bucket << shift), 1u << shift);
-        // (more pairs than nodes: some node is there twice; the bucket's workgroup then goes by the order itself)
-        if (place < nodes) pairs[(bucket << shift) + place] = (static_cast<unsigned long long>(v[k]) << 32) | (r0 + k * kInvertBlock);
+    for (int k = 0; k < kHandItems; ++k) {
+        if (run[k]) {
+            const uint32_t first = lane_value(run_bucket, k) << shift, to = lane_value(nth, k);
+            if (to != ~0u) s.places(first)[to * kWave + lane] = static_cast<uint16_t>(v[k] - first);
+        } else if (!all_runs && v[k] != ~0u) {
+            const uint32_t bucket = v[k] >> shift, first = bucket << shift, nodes = min(n - first, 1u << shift), place = s_base[bucket] + at[k];
+            if (place < nodes) s.pairs[first + nodes - 1 - place] = (static_cast<unsigned long long>(v[k]) << 32) | (r0 + k * kHandBlock);
+        }
     }
 }
 
 template <uint32_t MOST>
 __global__ __launch_bounds__(kInvertBlock) void rank_place_kernel(const int32_t* __restrict__ order, uint32_t n, uint32_t shift,
-                                                                  const uint32_t* __restrict__ cursors, const unsigned long long* __restrict__ pairs,
-                                                                  int32_t* rank, int64_t* holes, int32_t* err) {
+                                                                  InvertScratch s, int32_t* rank, int64_t* holes, int32_t* err) {
     __shared__ int32_t s_rank[1u << MOST];               // (shift <= MOST)
-    const uint32_t first = blockIdx.x << shift, nodes = min(n - first, 1u << shift), count = cursors[blockIdx.x];
+    const uint32_t first = blockIdx.x << shift, nodes = min(n - first, 1u << shift);
+    const uint32_t n_pairs = s.cursors[blockIdx.x], n_runs = s.cursors[kInvertBuckets + blockIdx.x];
     for (uint32_t i = threadIdx.x; i < nodes; i += kInvertBlock) s_rank[i] = -1;
     __syncthreads();
-    if (count <= nodes) {
-        for (uint32_t i0 = threadIdx.x; i0 < count; i0 += kInvertTile) {
+    if (threadIdx.x < 2) s.cursors[threadIdx.x * kInvertBuckets + blockIdx.x] = 0;
+    if (n_pairs <= nodes && n_runs <= nodes / kWave && n_pairs + n_runs * kWave <= nodes) {
+        const uint32_t lane = static_cast<uint32_t>(lane_id()), wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(wave_id()));
+        for (uint32_t w0 = wave; w0 < n_runs; w0 += kRunsAhead * (kInvertBlock / kWave)) {
+            uint32_t r[kRunsAhead], place[kRunsAhead];
+#pragma unroll
+            for (int k = 0; k < kRunsAhead; ++k) {
+                const uint32_t w = min(w0 + k * (kInvertBlock / kWave), n_runs - 1);
+                r[k] = s.run_rank[first / kWave + w] + lane;
+                place[k] = s.places(first)[w * kWave + lane];
+            }
+#pragma unroll
+            for (int k = 0; k < kRunsAhead; ++k)         // (a run that is there already once more)
+                if (place[k] < nodes) s_rank[place[k]] = static_cast<int32_t>(r[k]);
+        }
+        for (uint32_t i0 = threadIdx.x; i0 < n_pairs; i0 += kInvertTile) {
             unsigned long long pair[kInvertItems];
 #pragma unroll
-            for (int k = 0; k < kInvertItems; ++k) pair[k] = pairs[first + (i0 + k * kInvertBlock < count ? i0 + k * kInvertBlock : 0)];
+            for (int k = 0; k < kInvertItems; ++k) pair[k] = s.pairs[first + nodes - 1 - (i0 + k * kInvertBlock < n_pairs ? i0 + k * kInvertBlock : 0)];
 #pragma unroll
             for (int k = 0; k < kInvertItems; ++k) {
                 const uint32_t place = static_cast<uint32_t>(pair[k] >> 32) - first;
-                if (i0 + k * kInvertBlock < count && place < nodes) s_rank[place] = static_cast<int32_t>(static_cast<uint32_t>(pair[k]));
+                if (i0 + k * kInvertBlock < n_pairs && place < nodes) s_rank[place] = static_cast<int32_t>(static_cast<uint32_t>(pair[k]));
             }
         }
     } else {                                             // (an order that is no permutation)
@@ -388,21 +447,20 @@ unsigned grid_for(int64_t n, unsigned cap_blocks) {
 
 }  // namespace
 
-hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int64_t* holes, void* scratch,
+hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int64_t* holes, uint32_t* cursors, void* scratch,
                              size_t scratch_bytes, int32_t* err) {
-    const size_t pairs_at = sizeof(uint32_t) * kInvertBuckets;
-    if (scratch && n_nodes >= kInvertMin && n_nodes <= kInvertMax && scratch_bytes >= pairs_at + sizeof(unsigned long long) * static_cast<size_t>(n_nodes)) {
+    const size_t nodes = static_cast<size_t>(n_nodes), runs_at = sizeof(unsigned long long) * nodes, bytes = runs_at + sizeof(uint32_t) * (nodes / kWave);
+    if (scratch && n_nodes >= kInvertMin && n_nodes <= kInvertMax && scratch_bytes >= bytes) {
         uint32_t shift = kInvertMaxShift;                // 256 buckets or more, so that every CU has one or two
         while (shift > 10 && (n_nodes >> shift) < 256) --shift;
         const uint32_t n = static_cast<uint32_t>(n_nodes);
-        uint32_t* cursors = static_cast<uint32_t*>(scratch);
-        unsigned long long* pairs = reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(scratch) + pairs_at);
+        unsigned char* p = static_cast<unsigned char*>(scratch);
+        const InvertScratch s{cursors, reinterpret_cast<unsigned long long*>(p), reinterpret_cast<uint32_t*>(p + runs_at)};
         const dim3 block(kInvertBlock);
-        hipLaunchKernelGGL(rank_zero_kernel, dim3(1), block, 0, stream, cursors, holes);
-        hipLaunchKernelGGL(rank_split_kernel, dim3((n + kInvertTile - 1) / kInvertTile), block, 0, stream, order, n, shift, cursors, pairs, rank, err);
+        hipLaunchKernelGGL(rank_split_kernel, dim3((n + kHandTile - 1) / kHandTile), dim3(kHandBlock), 0, stream, order, n, shift, s, rank, holes, err);
         const dim3 buckets((n + (1u << shift) - 1) >> shift);
-        if (shift == kInvertMaxShift) hipLaunchKernelGGL(rank_place_kernel<kInvertMaxShift>, buckets, block, 0, stream, order, n, shift, cursors, pairs, rank, holes, err);
-        else hipLaunchKernelGGL(rank_place_kernel<kInvertMaxShift - 1>, buckets, block, 0, stream, order, n, shift, cursors, pairs, rank, holes, err);
+        if (shift == kInvertMaxShift) hipLaunchKernelGGL(rank_place_kernel<kInvertMaxShift>, buckets, block, 0, stream, order, n, shift, s, rank, holes, err);
+        else hipLaunchKernelGGL(rank_place_kernel<kInvertMaxShift - 1>, buckets, block, 0, stream, order, n, shift, s, rank, holes, err);
         return hipGetLastError();
     }
     const dim3 grid(grid_for(n_nodes, 8192)), block(kBlock);

@@ -142,6 +142,8 @@ struct helios_ctx {
     // scratch of helios_hotness_order, kept between calls
     void* hot_temp = nullptr;
     size_t hot_temp_bytes = 0;
+    uint32_t* map_cursors = nullptr;           // device [kMapCursors], behind the scan tickets: zero between calls
+    bool map_cursors_used = false;             // a build of the map has failed half way
 };
 
 namespace helios {

@@ -869,7 +869,7 @@ int helios_create(helios_ctx** out, int device, void* hip_stream) {
               hipMalloc(&c->cnt, sizeof(int64_t) * kNumCounters) == hipSuccess &&
               hipMalloc(&c->claims, sizeof(uint32_t) * HELIOS_MAX_HOPS * kSampleMaxWorkgroups * kWavesPerBlock) == hipSuccess &&
               hipMalloc(&c->vars, sizeof(BatchVars)) == hipSuccess &&
-              hipMalloc(&c->scan_ticket, 128) == hipSuccess &&
+              hipMalloc(&c->scan_ticket, 128 + sizeof(uint32_t) * kMapCursors) == hipSuccess &&
               hipMalloc(&c->batches_run, 64) == hipSuccess &&
               hipHostMalloc(reinterpret_cast<void**>(&c->vars_ring), sizeof(BatchVars) * kVarsRing,
                             hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
@@ -883,9 +883,10 @@ int helios_create(helios_ctx** out, int device, void* hip_stream) {
         if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0) c->clock_khz = khz;
         c->err[0] = c->err[1] = 0;
         c->err_now = c->err;
+        c->map_cursors = c->scan_ticket + 32;
         for (int k = 0; k < 4; ++k) c->learn[k] = 0;
         ok = hipMemsetAsync(c->cnt, 0, sizeof(int64_t) * kNumCounters, c->stream) == hipSuccess &&
-             hipMemsetAsync(c->scan_ticket, 0, 128, c->stream) == hipSuccess &&
+             hipMemsetAsync(c->scan_ticket, 0, 128 + sizeof(uint32_t) * kMapCursors, c->stream) == hipSuccess &&
              hipMemsetAsync(c->batches_run, 0, 64, c->stream) == hipSuccess &&
              hipStreamSynchronize(c->stream) == hipSuccess;
     }
@@ -985,8 +986,12 @@ int helios_cache_build(helios_ctx* c, const int32_t* order, int64_t hbm_rows, in
         capture = hipStreamCaptureStatusActive;
     }
     const bool borrow = c->hot_temp && capture == hipStreamCaptureStatusNone;
+    if (borrow && c->map_cursors_used) HIP_TRY(c, hipMemsetAsync(c->map_cursors, 0, sizeof(uint32_t) * kMapCursors, c->stream));
+    c->map_cursors_used = borrow;
     if (n > 0)
-        HIP_TRY(c, launch_rank_build(c->stream, order, n, c->rank, c->cnt + kCntHoles, borrow ? c->hot_temp : nullptr, borrow ? c->hot_temp_bytes : 0, c->err));
+        HIP_TRY(c, launch_rank_build(c->stream, order, n, c->rank, c->cnt + kCntHoles, c->map_cursors, borrow ? c->hot_temp : nullptr,
+                                     borrow ? c->hot_temp_bytes : 0, c->err));
+    c->map_cursors_used = false;
     c->n_hbm = hbm_rows;
     c->n_host = host_rows;
     c->row_bytes = row_bytes;

@@ -145,9 +145,10 @@ hipError_t launch_dedup_end(hipStream_t stream, const InverseArgs& inv, int64_t 
 
 // ---- cache.hip
 // rank[order[r]] = r; *holes (device) = 1 if that leaves a node without a rank, else 0.  scratch (nullable): device memory
-// that may be used, 8 bytes per node and 2 KB.
-hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int64_t* holes, void* scratch,
-                             size_t scratch_bytes, int32_t* err);
+// that may be used, 8 1/16 bytes per node.  cursors: kMapCursors device words, zero before and after.
+constexpr uint32_t kMapCursors = 1024;
+hipError_t launch_rank_build(hipStream_t stream, const int32_t* order, int64_t n_nodes, int32_t* rank, int64_t* holes, uint32_t* cursors,
+                             void* scratch, size_t scratch_bytes, int32_t* err);
 
 // Lookup of ids[0, n) and partition into the per-tier lists and the miss list.  With copy_table, the rows of the HBM tier are copied
 // in the same launch (out[j] = copy_table[rank[ids[j]]], rows of `chunks` 16-byte pieces), and that tier gets no list; its count
