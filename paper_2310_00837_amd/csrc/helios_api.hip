@@ -1074,7 +1074,6 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
         if (split_starts_bytes(n_ids) > static_cast<int64_t>(sizeof(int32_t)) * c->cap_ids || (n_ids + 4095) / 4096 * 4096 > c->cap_ids)
             return fail(c, HELIOS_EINTERNAL, "scratch too small for a list by parts");
         HIP_TRY(c, launch_dedup_by_parts(c->stream, a, n_ids, c->g.n_nodes, parts));
-        HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{nullptr, 0}, nullptr, 0));
         return HELIOS_OK;
     }
     c->batch_dirty[which] = s.n_slots;

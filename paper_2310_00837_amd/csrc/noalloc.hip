@@ -156,7 +156,7 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
         HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, c->err));
         HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
     }
-    const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse, false,
+    const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{}, nullptr, by_parts ? nullptr : inverse, false,
                           Stamps{nullptr}};
     HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, by_parts ? ClearJob{nullptr, 0} : ClearJob{table, slots}, status,
                                 kEndZeroWords));

@@ -177,6 +177,7 @@ T __shfl_up(T v, unsigned d, int) {
     const int64_t* all = on_host::exchange(v, &lanes);
     return lane < d ? v : static_cast<T>(all[lane - d]);
 }
+inline int __popc(uint32_t v) { return __builtin_popcount(v); }
 inline int __popcll(uint64_t v) { return __builtin_popcountll(v); }
 inline int __ffsll(long long v) { return __builtin_ffsll(v); }
 inline uint64_t wall_clock64() { return 0; }

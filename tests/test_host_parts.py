@@ -76,7 +76,7 @@ struct Call {
     }
     void buckets() const { hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, nullptr, s, static_cast<uint32_t>(tiles), table, n_slots, err); }
     bool table_empty() const { return std::all_of(table, table + n_slots, [](unsigned long long w) { return w == kEmptySlot; }); }
-    void compact() const { hipLaunchKernelGGL(dedup_compact_parts_kernel, dim3(tiles), dim3(kScanBlock), 0, nullptr, a, s); }
+    void compact() const { hipLaunchKernelGGL(dedup_compact_parts_kernel, dim3(tiles), dim3(kMergeBlock), 0, nullptr, a, s); }
 };
 
 void check(bool ok, const char* what) {
