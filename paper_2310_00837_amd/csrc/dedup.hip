@@ -33,7 +33,7 @@ namespace helios {
 namespace {
 
 __global__ __launch_bounds__(kBlock) void dedup_insert_kernel(const int32_t* __restrict__ ids, Count n_in, int64_t n_nodes,
-                                                              DedupScratch s, int32_t* err) {
+                                                              DedupScratch s, unsigned long long* zero, uint32_t n_zero, int32_t* err) {
     // The first ID is fetched before the device-side count has arrived (the buffer holds n_in.host
     // entries, so the read is in bounds whatever the count turns out to be).
     const int64_t j0 = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
@@ -42,6 +42,7 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_kernel(const int32_t* __r
     const int64_t n = n_in.get();
     const uint32_t mask = s.n_slots - 1;
     uint32_t claims = 0;
+    for (uint32_t w = static_cast<uint32_t>(j0); w < n_zero; w += gridDim.x * kBlock) zero[w] = 0ull;
     for (int64_t j = j0; j < n; j += static_cast<int64_t>(gridDim.x) * kBlock) {
         const int32_t id = j == j0 ? early : ids[j];
         if (id < 0 || static_cast<int64_t>(id) >= n_nodes) {
@@ -96,47 +97,46 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_long_kernel(const int32_t
 // ---- a long list by parts, without the table
 //
 // The inserts of a long list are bound by the atomics of the memory (25 a ns) and its compaction by as many random reads.  So a
-// list of kPartsMin to kPartsMax IDs is taken apart by hash instead, until a part fits a table in LDS:
-//   split     a tile of 4096 IDs drops its repeats (LDS table), and the rest is put into order of 512 buckets and written out so,
+// list is taken apart by hash instead, until a part fits a table in LDS:
+//   split     a tile (see PartShape) drops its repeats (LDS table), and the rest is put into order of 512 buckets and written out so,
 //             with where the buckets begin;
 //   buckets   a workgroup per bucket gathers its pieces of all tiles, finds the first position of every ID in an LDS table, and
 //             leaves it where it has read the ID;
-//   compact   a tile's first positions go back into input order (LDS), and from there on it is the compaction as above.
-// All of it is streams, the buckets' reads in pieces of about 32 bytes (IDs, first positions) and 16 (places), shorter where the tiles
-// have dropped repeats.  They drop them so that no bucket is much longer than the others: of an ID that fills the list a bucket gets
-// one entry per tile.
-// Measured, whole call, us with the table / by parts, IDs by a power law (uniform ones differ by less than 4):
-//   65 k 23.9/24.5   98 k 26.7/24.5 (the line)   131 k 31.1/25.0   262 k 41/28.5   400 k 54/31.8   1.1 M 102/42.6   2 M 165/66
-// (1.1 M: split 11.9, buckets 13.2, compact 13.8, inverse 5.8); one ID throughout, 131 k: 1900/20.  Of few distinct IDs without hubs the table is
-// the quicker way a little longer: 12 k distinct ones, 98 k 21.5/24.3, 131 k 24.2/25.2, 200 k 28.3/27.  Above 2 M a bucket would have
-// more IDs than half its table, and the list goes by the table.  256 buckets of 1024 threads with eight entries each, 64-bit words and
+//   compact   a tile's first positions go back into input order (LDS), and from there on it is a compaction that also writes the
+//             inverse map.
+// All of it is streams, the buckets' reads in pieces of about 32 bytes (IDs, first positions) and 16 (places), shorter where the list is
+// short or the tiles have dropped repeats.  They drop them so that no bucket is much longer than the others: of an ID that fills the list
+// a bucket gets one entry per tile.
+// What bounds it is a workgroup's chain of steps, LDS searches above all, so the tiles are as small as 256 workgroups allow: 1.1 M IDs
+// 253 tiles of 4352 38.1 us (split 13.5, buckets 12, compact 12), 269 of 4096, so that 13 CUs have two, 41.0, 506 of 2176 43.8;
+// 98 k 256 tiles of 1024 18.2, of 512 20.5, 24 of 4096 22.2.  Each number of rounds has an instance of its own: with guards in one for
+// all 1.1 M took 40.2, with six rounds always 38.7.  256 buckets of 1024 threads with eight entries each, 64-bit words and
 // a second search for the answers: buckets 44 us at 1.1 M; linear probing and 512 threads in the split: 15.
-constexpr int kPartTile = 4096;
+// When it pays against the table: dedup_by_parts.
+constexpr int kPartTile = kMaxPartTile;
 constexpr int kPartBits = 9;
 constexpr int kParts = 1 << kPartBits;
 constexpr int kSplitBlock = 1024;
-constexpr int kSplitItems = kPartTile / kSplitBlock;
 constexpr int kMergeBlock = 1024;                      // compaction
 constexpr int kMergeWaves = kMergeBlock / kWave;
-constexpr int kMergeItems = kPartTile / kMergeBlock;
 constexpr int kBucketBlock = 1024;
 constexpr int kBucketItems = 4;                        // entries per thread that stay in registers
 constexpr uint32_t kPartSlots = 8192;                  // of an LDS table: keys, and the lowest position that holds the key
 constexpr uint32_t kPartProbes = 128;                  // more than that at one ID: a bucket's table counts as full
-constexpr uint32_t kMaxPartTiles = 512;
 constexpr uint16_t kNoPlace = 0xffff;
 constexpr uint32_t kForeign = 2;                       // (of s_full) a stretch of the table full of another call's words: no search goes on
 static_assert((kPartSlots & (kPartSlots - 1)) == 0 && kPartProbes <= kPartSlots, "odd steps come by every slot once");
-static_assert(kPartsMax == static_cast<int64_t>(kMaxPartTiles) * kPartTile && kMaxPartTiles <= kBucketBlock, "a thread per tile");
-static_assert(kParts <= kSplitBlock && kMergeItems * kMergeWaves == kWave, "a thread per bucket; one step scans a tile");
+static_assert(kPartsMax == kMaxPartTiles * 4096 && kMaxPartTiles <= kBucketBlock && kMaxPartTiles <= kMergeBlock, "a thread per tile");
+static_assert(kParts <= kSplitBlock && kPartTile / kMergeBlock * kMergeWaves <= 2 * kWave, "a thread per bucket; two steps scan a tile");
+static_assert(kSplitBlock == kMergeBlock && kPartTile == 6 * kMergeBlock && kPartTile < kPartSlots, "one to six rounds of all threads; the split's table never fills");
 
 struct PartTable {
     uint32_t key[kPartSlots], low[kPartSlots];         // ~0: empty (IDs are below 2^31)
 };
-__device__ __forceinline__ void part_clear(PartTable& t, uint32_t threads) {
+__device__ __forceinline__ void part_clear(PartTable& t, uint32_t slots, uint32_t threads) {
     typedef uint32_t words4 __attribute__((ext_vector_type(4)));
-    words4* w = reinterpret_cast<words4*>(&t);
-    for (uint32_t q = threadIdx.x; q < sizeof(PartTable) / 16; q += threads) w[q] = words4{~0u, ~0u, ~0u, ~0u};
+    words4 *keys = reinterpret_cast<words4*>(t.key), *lows = reinterpret_cast<words4*>(t.low);
+    for (uint32_t q = threadIdx.x; q < slots / 4; q += threads) keys[q] = lows[q] = words4{~0u, ~0u, ~0u, ~0u};
 }
 // the whole hash: the highest bits are the bucket, the next the place in the table, the lowest the step
 __device__ __forceinline__ uint32_t part_hash(uint32_t id) { return hash_id(id, 0xffffffffu); }
@@ -145,13 +145,13 @@ __device__ __forceinline__ uint32_t part_hash(uint32_t id) { return hash_id(id, 
 __device__ __forceinline__ uint32_t part_step(uint32_t h) { return (h << 1) | 1u; }
 // The ID's slot, claimed if need be; kNoSlot after probes_max others.  (A plain read before the atomic: the entries of a hub would
 // take their turns at its word.)
-__device__ __forceinline__ uint32_t part_slot(PartTable& t, uint32_t id, uint32_t h, uint32_t probes_max) {
-    uint32_t slot = (h >> 10) % kPartSlots;
+__device__ __forceinline__ uint32_t part_slot(PartTable& t, uint32_t slots, uint32_t id, uint32_t h, uint32_t probes_max) {
+    uint32_t slot = (h >> 10) & (slots - 1);
     for (uint32_t probes = 0; probes < probes_max; ++probes) {
         uint32_t cur = __hip_atomic_load(t.key + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (cur == ~0u) cur = atomicCAS(t.key + slot, ~0u, id);
         if (cur == ~0u || cur == id) return slot;
-        slot = (slot + part_step(h)) % kPartSlots;
+        slot = (slot + part_step(h)) & (slots - 1);
     }
     return kNoSlot;
 }
@@ -159,41 +159,42 @@ __device__ __forceinline__ uint32_t part_low(const PartTable& t, uint32_t slot) 
     return __hip_atomic_load(t.low + slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-__global__ __launch_bounds__(kSplitBlock) void dedup_split_kernel(const int32_t* __restrict__ ids, uint32_t n, int64_t n_nodes, PartScratch s,
-                                                                  int32_t* err) {
+// ITEMS: rounds of all threads that go through a tile
+template <int ITEMS>
+__global__ __launch_bounds__(kSplitBlock) void dedup_split_kernel(const int32_t* __restrict__ ids, PartShape shape, int64_t n_nodes,
+                                                                  PartScratch s, int32_t* err) {
     __shared__ union {
         PartTable table;
-        struct { int32_t id[kPartTile]; uint16_t pos[kPartTile]; } out;
+        struct { int32_t id[ITEMS * kSplitBlock]; uint16_t pos[ITEMS * kSplitBlock]; } out;
     } m;
     __shared__ uint32_t s_count[kParts], s_wave[kParts / kWave];
-    const uint32_t tile = blockIdx.x, base = tile * kPartTile;
-    int32_t id[kSplitItems];
-    uint32_t slot[kSplitItems], rank[kSplitItems];
+    const uint32_t tile = blockIdx.x, base = tile * shape.tile, entries = min(shape.n - base, shape.tile);
+    int32_t id[ITEMS];
+    uint32_t slot[ITEMS], rank[ITEMS];
 #pragma unroll
-    for (int k = 0; k < kSplitItems; ++k) {
-        const uint32_t j = base + k * kSplitBlock + threadIdx.x;
-        id[k] = ids[j < n ? j : base];
-    }
-    part_clear(m.table, kSplitBlock);
+    for (int k = 0; k < ITEMS; ++k) id[k] = ids[base + min(k * kSplitBlock + threadIdx.x, entries - 1)];
+    if (s.clear && tile == 0)
+        for (uint32_t w = threadIdx.x; w < s.n_clear; w += kSplitBlock) s.clear[w] = 0ull;
+    part_clear(m.table, shape.split_slots, kSplitBlock);
     if (threadIdx.x < kParts) s_count[threadIdx.x] = 0;
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kSplitItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const uint32_t p = k * kSplitBlock + threadIdx.x;
-        const bool here = base + p < n, node = id[k] >= 0 && static_cast<int64_t>(id[k]) < n_nodes;
+        const bool here = p < entries, node = id[k] >= 0 && static_cast<int64_t>(id[k]) < n_nodes;
         if (here && !node) raise(err, kErrData);
         slot[k] = kNoSlot;
         if (!here || !node) continue;
-        const uint32_t at = part_slot(m.table, static_cast<uint32_t>(id[k]), part_hash(static_cast<uint32_t>(id[k])), kPartSlots);
-        slot[k] = at;                                  // (there is one: at most 4096 IDs in 8192 slots)
+        const uint32_t at = part_slot(m.table, shape.split_slots, static_cast<uint32_t>(id[k]), part_hash(static_cast<uint32_t>(id[k])), shape.split_slots);
+        slot[k] = at;                                  // (there is one: the tile has fewer IDs than the table slots)
         if (part_low(m.table, at) > p) atomicMin(m.table.low + at, p);
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kSplitItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const uint32_t p = k * kSplitBlock + threadIdx.x;
         const uint32_t low = slot[k] != kNoSlot ? part_low(m.table, slot[k]) : kNoPlace;
-        if (base + p < n) s.local[base + p] = static_cast<uint16_t>(low);
+        if (p < entries) s.local[base + p] = static_cast<uint16_t>(low);
         slot[k] = low == p ? part_hash(static_cast<uint32_t>(id[k])) >> (32 - kPartBits) : kNoSlot;      // from here on the bucket
         rank[k] = low == p ? atomicAdd(s_count + slot[k], 1u) : 0u;
     }
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(kSplitBlock) void dedup_split_kernel(const int32_t*
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kSplitItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         if (slot[k] == kNoSlot) continue;
         const uint32_t to = s_count[slot[k]] + rank[k];
         m.out.id[to] = id[k];
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(kSplitBlock) void dedup_split_kernel(const int32_t*
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kSplitItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const uint32_t p = k * kSplitBlock + threadIdx.x;
         if (p >= there) continue;
         s.id[base + p] = m.out.id[p];
@@ -238,20 +239,20 @@ __global__ __launch_bounds__(kSplitBlock) void dedup_split_kernel(const int32_t*
 // inserts into a table for all take 0.1; with one LDS table after the other, class by class of the hash, it was 606.
 __device__ __forceinline__ uint32_t stretch_slot(uint32_t id, uint32_t size) { return __umulhi(part_hash(~id), size); }
 
-__global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch s, uint32_t n_tiles, unsigned long long* table_in_memory,
+__global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch s, PartShape shape, unsigned long long* table_in_memory,
                                                                     uint32_t n_slots, int32_t* err) {
     __shared__ PartTable table;
     __shared__ uint32_t s_before[kMaxPartTiles], s_from[kMaxPartTiles];     // of a tile's piece: entries before it, where it begins
     __shared__ uint32_t s_wave[kMaxPartTiles / kWave];
     __shared__ uint32_t s_full, s_lower;                                    // s_lower: entries of the buckets before this one
-    const uint32_t t = threadIdx.x;
+    const uint32_t t = threadIdx.x, n_tiles = shape.n_tiles;
     uint32_t len = 0, from = 0;
     if (t < n_tiles) {
         // (Calls that overlap on the static array of helios_dedup_noalloc may each have written one of the two words.  What lies
         // within a tile is taken, so every place below is one of the tile's own.)
         const uint16_t* starts = s.starts + static_cast<size_t>(t) * (kParts + 1) + blockIdx.x;
         const uint32_t begin = starts[0], end = starts[1];
-        const bool piece = begin <= end && end <= kPartTile;
+        const bool piece = begin <= end && end <= min(shape.n - t * shape.tile, shape.tile);
         if (!piece) raise(err, kErrInternal);
         from = piece ? begin : 0u;
         len = piece ? end - begin : 0u;
@@ -259,7 +260,7 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
     const uint32_t inc = dpp_inclusive_scan(len);
     if (t < kMaxPartTiles && lane_id() == kWave - 1) s_wave[wave_id()] = inc;
     if (t == 0) s_full = s_lower = 0;
-    part_clear(table, kBucketBlock);
+    part_clear(table, shape.bucket_slots, kBucketBlock);
     __syncthreads();
     uint32_t at = inc - len, total = 0;
 #pragma unroll
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
     }
     if (t < kMaxPartTiles) {
         s_before[t] = t < n_tiles ? at : ~0u;
-        s_from[t] = t * kPartTile + from;
+        s_from[t] = t * shape.tile + from;
     }
     __syncthreads();
     uint32_t place[kBucketItems], pos[kBucketItems], id[kBucketItems], slot[kBucketItems];
@@ -283,7 +284,7 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
             for (uint32_t half = kMaxPartTiles / 2; half > 0; half /= 2)
                 if (s_before[lo + half] <= e) lo += half;
             place[k] = e < total ? s_from[lo] + (e - s_before[lo]) : ~0u;
-            pos[k] = lo * kPartTile;
+            pos[k] = lo * shape.tile;
         }
 #pragma unroll
         for (int k = 0; k < kBucketItems; ++k) {
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
 #pragma unroll
         for (int k = 0; k < kBucketItems; ++k) {
             if (place[k] == ~0u) continue;
-            slot[k] = part_slot(table, id[k], part_hash(id[k]), kPartProbes);
+            slot[k] = part_slot(table, shape.bucket_slots, id[k], part_hash(id[k]), kPartProbes);
             if (slot[k] == kNoSlot) s_full = 1;
             else if (part_low(table, slot[k]) > pos[k]) atomicMin(table.low + slot[k], pos[k]);
         }
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
                 entries(chunk);
 #pragma unroll
                 for (int k = 0; k < kBucketItems; ++k)
-                    if (place[k] != ~0u) slot[k] = part_slot(table, id[k], part_hash(id[k]), kPartProbes);
+                    if (place[k] != ~0u) slot[k] = part_slot(table, shape.bucket_slots, id[k], part_hash(id[k]), kPartProbes);
             }
 #pragma unroll
             for (int k = 0; k < kBucketItems; ++k)
@@ -379,11 +380,12 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
 // repeat's tile read from the chain's words, at memory, by every repeat: 48.9.)
 __device__ __forceinline__ uint32_t first_word(uint32_t before, uint32_t mask) { return (before << 16) | (mask & 0xffffu); }
 
-__global__ __launch_bounds__(kMergeBlock) void dedup_compact_parts_kernel(CompactArgs a, PartScratch s) {
-    __shared__ uint32_t s_first[kPartTile], s_total[kMergeItems * kMergeWaves], s_upto[kMaxPartTiles], s_wave[kMaxPartTiles / kWave], s_ticket;
+template <int ITEMS>
+__global__ __launch_bounds__(kMergeBlock) void dedup_compact_parts_kernel(CompactArgs a, PartScratch s, PartShape shape) {
+    __shared__ uint32_t s_first[ITEMS * kMergeBlock], s_total[ITEMS * kMergeWaves], s_upto[kMaxPartTiles], s_wave[kMaxPartTiles / kWave], s_ticket;
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(wave_id())), lane = static_cast<uint32_t>(lane_id());
     const ScanState scan = scan_resolve(a.scan);
-    const uint32_t n = static_cast<uint32_t>(a.len.get()), n_tiles = (n + kPartTile - 1) / kPartTile;
+    const uint32_t n = shape.n, n_tiles = shape.n_tiles;
     uint32_t* words = reinterpret_cast<uint32_t*>(a.s.index_of_first);
     if (blockIdx.x == 0 && threadIdx.x == 0 && a.n_total_dev) *a.n_total_dev = n;
     if (threadIdx.x == 0) {
@@ -400,43 +402,47 @@ __global__ __launch_bounds__(kMergeBlock) void dedup_compact_parts_kernel(Compac
         if (threadIdx.x == 0) raise(a.err, kErrInternal);
         return;
     }
-    const uint32_t base = tile * kPartTile, there = s.starts[static_cast<size_t>(tile) * (kParts + 1) + kParts];
-    uint32_t first_of[kMergeItems], pos[kMergeItems], in_tile[kMergeItems];
-    int32_t id[kMergeItems];
+    const uint32_t base = tile * shape.tile, entries = min(n - base, shape.tile);
+    const uint32_t there = min(static_cast<uint32_t>(s.starts[static_cast<size_t>(tile) * (kParts + 1) + kParts]), entries);
+    uint32_t first_of[ITEMS], pos[ITEMS], in_tile[ITEMS];
+    int32_t id[ITEMS];
 #pragma unroll
-    for (int k = 0; k < kMergeItems; ++k) {
+    for (int k = 0; k < ITEMS; ++k) {
         const uint32_t p = k * kMergeBlock + threadIdx.x, at = base + (p < there ? p : 0);
         first_of[k] = s.first[at];
         pos[k] = s.pos[at];
-        in_tile[k] = s.local[base + p < n ? base + p : base];
-        id[k] = a.ids[base + p < n ? base + p : base];
+        in_tile[k] = s.local[base + min(p, entries - 1)];
+        id[k] = a.ids[base + min(p, entries - 1)];
         asm volatile("" : "+v"(id[k]));          // (read before the tile's total goes out: `unique` may lie over the IDs)
     }
 #pragma unroll
-    for (int k = 0; k < kMergeItems; ++k)
-        if (k * kMergeBlock + threadIdx.x < there) s_first[pos[k] % kPartTile] = first_of[k];
+    for (int k = 0; k < ITEMS; ++k)
+        if (k * kMergeBlock + threadIdx.x < there) s_first[pos[k] % (ITEMS * kMergeBlock)] = first_of[k];
     __syncthreads();
-    uint32_t before[kMergeItems], local[kMergeItems], total[kMergeItems];
-    uint64_t firsts[kMergeItems];
-    bool first[kMergeItems];
+    uint32_t before[ITEMS], local[ITEMS], total[ITEMS];
+    uint64_t firsts[ITEMS];
+    bool first[ITEMS];
 #pragma unroll
-    for (int k = 0; k < kMergeItems; ++k) {
-        const uint32_t j = base + k * kMergeBlock + threadIdx.x;
-        first_of[k] = in_tile[k] != kNoPlace ? s_first[in_tile[k] % kPartTile] : ~0u;        // (~0: no node)
-        first[k] = j < n && first_of[k] == j;
+    for (int k = 0; k < ITEMS; ++k) {
+        const uint32_t p = k * kMergeBlock + threadIdx.x, j = base + p;
+        first_of[k] = in_tile[k] != kNoPlace ? s_first[in_tile[k] % (ITEMS * kMergeBlock)] : ~0u;        // (~0: no node)
+        first[k] = p < entries && first_of[k] == j;
         firsts[k] = __ballot(first[k]);
         local[k] = rank_in_mask(firsts[k]);
         total[k] = static_cast<uint32_t>(__popcll(firsts[k]));
         if (lane == 0) s_total[k * kMergeWaves + wave] = total[k];
     }
     __syncthreads();
-    const uint32_t inc = dpp_inclusive_scan(s_total[lane]), in_all = lane_value(inc, kWave - 1);
+    constexpr uint32_t kRuns = ITEMS * kMergeWaves, kFirstItems = kWave / kMergeWaves;
+    const uint32_t inc = dpp_inclusive_scan(lane < kRuns ? s_total[lane] : 0u);
+    const uint32_t more = kRuns > kWave ? dpp_inclusive_scan(kWave + lane < kRuns ? s_total[kWave + lane] : 0u) : 0u;
+    const uint32_t in_first = lane_value(inc, kWave - 1), in_all = in_first + lane_value(more, kWave - 1);
 #pragma unroll
-    for (int k = 0; k < kMergeItems; ++k) {
-        before[k] = lane_value(inc, k * kMergeWaves + wave) - total[k];
-        const uint32_t mask = static_cast<uint32_t>(firsts[k] >> (lane % 4 * 16)), j = base + k * kMergeBlock + wave * kWave + lane * 16;
+    for (int k = 0; k < ITEMS; ++k) {
+        before[k] = (k < kFirstItems ? lane_value(inc, k * kMergeWaves + wave) : in_first + lane_value(more, (k - kFirstItems) * kMergeWaves + wave)) - total[k];
+        const uint32_t mask = static_cast<uint32_t>(firsts[k] >> (lane % 4 * 16)), p = k * kMergeBlock + wave * kWave + lane * 16;
         const uint32_t below = static_cast<uint32_t>(__popcll(firsts[k] & ((1ull << (lane % 4 * 16)) - 1)));
-        if (a.inverse && lane < 4 && j < n) __hip_atomic_store(words + j / 16, first_word(before[k] + below, mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (a.inverse && lane < 4 && p < entries) __hip_atomic_store(words + (base + p) / 16, first_word(before[k] + below, mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // (they go past the L2: now they are there for all)
     __syncthreads();
@@ -466,14 +472,16 @@ __global__ __launch_bounds__(kMergeBlock) void dedup_compact_parts_kernel(Compac
     if (threadIdx.x < kMaxPartTiles) s_upto[threadIdx.x] = sums - mine;
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kMergeItems; ++k) {
-        const uint32_t j = base + k * kMergeBlock + threadIdx.x;
-        if (j >= n) continue;
+    for (int k = 0; k < ITEMS; ++k) {
+        const uint32_t p = k * kMergeBlock + threadIdx.x, j = base + p;
+        if (p >= entries) continue;
         const uint32_t at = excl + before[k] + local[k], of = first_of[k];
         if (a.inverse && of < j) {
             // (complete, and the same for the rest of the launch: it may come from the L2)
             const uint32_t word = __hip_atomic_load(words + of / 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            a.inverse[j] = static_cast<int32_t>(s_upto[of / kPartTile] + (word >> 16) + static_cast<uint32_t>(__popc(word & ((1u << (of % 16)) - 1))));
+            uint32_t in = __umulhi(of, shape.per_tile);         // the tile, or one more
+            if (in * shape.tile > of) --in;
+            a.inverse[j] = static_cast<int32_t>(s_upto[in] + (word >> 16) + static_cast<uint32_t>(__popc(word & ((1u << (of % 16)) - 1))));
         } else if (a.inverse) {
             a.inverse[j] = first[k] ? static_cast<int32_t>(at) : -1;
         }
@@ -495,8 +503,6 @@ __global__ __launch_bounds__(kScanBlock) void dedup_compact_kernel(CompactArgs a
 struct EndArgs {
     InverseArgs inv;
     ClearJob clear;
-    unsigned long long* zero;
-    uint32_t n_zero;
     Role r_inv, r_clear;
 };
 __global__ __launch_bounds__(kBlock) void dedup_end_kernel(EndArgs a) {
@@ -506,7 +512,6 @@ __global__ __launch_bounds__(kBlock) void dedup_end_kernel(EndArgs a) {
     }
     const uint32_t step = a.r_clear.blocks * kBlock, first = a.r_clear.rb() * kBlock + threadIdx.x;
     for (uint32_t w = first; a.clear.table && w < a.clear.n_slots; w += step) a.clear.table[w] = kEmptySlot;
-    for (uint32_t w = first; w < a.n_zero; w += step) a.zero[w] = 0ull;
 }
 
 unsigned grid_for(int64_t n_max, unsigned cap_blocks) {
@@ -519,19 +524,33 @@ unsigned grid_for(int64_t n_max, unsigned cap_blocks) {
 }  // namespace
 
 hipError_t launch_dedup_insert(hipStream_t stream, const int32_t* ids, Count n, int64_t n_max, int64_t n_nodes,
-                               const DedupScratch& s, int32_t* err) {
+                               const DedupScratch& s, unsigned long long* zero, uint32_t n_zero, int32_t* err) {
+    if (n_max > kPartsMax && n_zero > 0) return hipErrorInvalidValue;
     if (n_max > kPartsMax)
         hipLaunchKernelGGL(dedup_insert_long_kernel, dim3(kInsertLongWorkgroups), dim3(kBlock), 0, stream, ids, n, n_nodes, s, err);
-    else hipLaunchKernelGGL(dedup_insert_kernel, dim3(grid_for(n_max, 4096)), dim3(kBlock), 0, stream, ids, n, n_nodes, s, err);
+    else hipLaunchKernelGGL(dedup_insert_kernel, dim3(grid_for(n_max, 4096)), dim3(kBlock), 0, stream, ids, n, n_nodes, s, zero, n_zero, err);
     return hipGetLastError();
 }
 
 hipError_t launch_dedup_by_parts(hipStream_t stream, const CompactArgs& a, int64_t n, int64_t n_nodes, const PartScratch& s) {
     if (n < 1 || n > kPartsMax || !a.s.table || a.s.n_slots < 2 * n) return hipErrorInvalidValue;
-    const unsigned tiles = static_cast<unsigned>((n + kPartTile - 1) / kPartTile);
-    hipLaunchKernelGGL(dedup_split_kernel, dim3(tiles), dim3(kSplitBlock), 0, stream, a.ids, static_cast<uint32_t>(n), n_nodes, s, a.err);
-    hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, stream, s, tiles, a.s.table, a.s.n_slots, a.err);
-    hipLaunchKernelGGL(dedup_compact_parts_kernel, dim3(tiles), dim3(kMergeBlock), 0, stream, a, s);
+    const PartShape shape(n);
+#define HELIOS_CALL_(ITEMS)                                                                                                          \
+    do {                                                                                                                             \
+        hipLaunchKernelGGL(dedup_split_kernel<ITEMS>, dim3(shape.n_tiles), dim3(kSplitBlock), 0, stream, a.ids, shape, n_nodes, s, a.err); \
+        hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, stream, s, shape, a.s.table, a.s.n_slots, a.err); \
+        hipLaunchKernelGGL(dedup_compact_parts_kernel<ITEMS>, dim3(shape.n_tiles), dim3(kMergeBlock), 0, stream, a, s, shape);       \
+    } while (0)
+    switch ((shape.tile + kMergeBlock - 1) / kMergeBlock) {
+        case 1: HELIOS_CALL_(1); break;
+        case 2: HELIOS_CALL_(2); break;
+        case 3: HELIOS_CALL_(3); break;
+        case 4: HELIOS_CALL_(4); break;
+        case 5: HELIOS_CALL_(5); break;
+        case 6: HELIOS_CALL_(6); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef HELIOS_CALL_
     return hipGetLastError();
 }
 
@@ -540,13 +559,12 @@ hipError_t launch_dedup_compact_plain(hipStream_t stream, const CompactArgs& a, 
     return hipGetLastError();
 }
 
-hipError_t launch_dedup_end(hipStream_t stream, const InverseArgs& inv, int64_t n_max, const ClearJob& clear, unsigned long long* zero,
-                            uint32_t n_zero) {
-    EndArgs a{inv, clear, zero, n_zero, Role{0, 0}, Role{0, 0}};
+hipError_t launch_dedup_end(hipStream_t stream, const InverseArgs& inv, int64_t n_max, const ClearJob& clear) {
+    EndArgs a{inv, clear, Role{0, 0}, Role{0, 0}};
     a.r_inv.blocks = inv.inverse ? grid_for(n_max, 2048) : 0u;
     a.r_clear.first = a.r_inv.blocks;
     // eight slots per thread up to a grid that fills the chip
-    a.r_clear.blocks = clear.table || n_zero ? grid_for((static_cast<int64_t>(clear.n_slots) + 7) / 8, 1024) : 0u;
+    a.r_clear.blocks = clear.table ? grid_for((static_cast<int64_t>(clear.n_slots) + 7) / 8, 1024) : 0u;
     const unsigned blocks = a.r_inv.blocks + a.r_clear.blocks;
     if (blocks == 0) return hipSuccess;
     hipLaunchKernelGGL(dedup_end_kernel, dim3(blocks), dim3(kBlock), 0, stream, a);

@@ -583,7 +583,7 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
             HIP_TRY(c, launch_gather_rows(c->stream, miss_args, served_max, true, true, c->host_blocks, 0, nullptr, nullptr, nullptr));
         // (a recording with split copies leaves the emptying of the next table to helios_plan_launch)
         const ClearJob clear = !rec && clear_slots ? ClearJob{batch_table(c, next), clear_slots} : ClearJob{nullptr, 0};
-        HIP_TRY(c, launch_dedup_end(c->stream, inv, p.cat_max, clear, nullptr, 0));
+        HIP_TRY(c, launch_dedup_end(c->stream, inv, p.cat_max, clear));
     } else {
         const int stage = n_hops - 1;
         GatherArgs hbm{}, link{}, miss{};
@@ -1042,13 +1042,14 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     if (rc) return rc;
     // the table (and its lists) that the context's next batch would use: not one that helios_make_blocks may still need
     const uint32_t which = static_cast<uint32_t>(c->batch_seq % kBatchTables);
-    const bool by_parts = n_ids >= kPartsMin && n_ids <= kPartsMax;
+    const uint32_t slots = list_slots(n_ids, c->table_slots);
+    const bool by_parts = dedup_by_parts(n_ids, slots);
     rc = by_parts ? HELIOS_OK : clean_for_call(c, static_cast<int>(which));
     if (rc) return rc;
     uint32_t epoch;
     rc = next_epoch(c, &epoch);
     if (rc) return rc;
-    const DedupScratch s{batch_table(c, which), dedup_slots(c, n_ids), batch_slots(c, which), batch_iof(c, which)};
+    const DedupScratch s{batch_table(c, which), slots, batch_slots(c, which), batch_iof(c, which)};
     const Count n{nullptr, n_ids};
     CompactArgs a{};
     a.ids = ids;
@@ -1065,23 +1066,23 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     a.inverse = inverse;
     a.scan = scan_state(c, epoch, kScanRowsLook);
     a.err = c->err;
-    const InverseArgs inv{Count{c->cnt + kCntCat, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse, false,
-                          Stamps{nullptr}};
     if (by_parts) {
         // (the tier lists are scratch of a lookup: no call leaves anything in them for another)
         const PartScratch parts{c->list_slot[0], reinterpret_cast<uint16_t*>(c->list_pos[0]), reinterpret_cast<uint32_t*>(c->list_slot[1]),
-                                reinterpret_cast<uint16_t*>(c->list_pos[0]) + c->cap_ids, reinterpret_cast<uint16_t*>(c->list_pos[1])};
-        if (split_starts_bytes(n_ids) > static_cast<int64_t>(sizeof(int32_t)) * c->cap_ids || (n_ids + 4095) / 4096 * 4096 > c->cap_ids)
+                                reinterpret_cast<uint16_t*>(c->list_pos[0]) + c->cap_ids, reinterpret_cast<uint16_t*>(c->list_pos[1]), nullptr, 0};
+        if (split_starts_bytes(PartShape(n_ids).n_tiles) > static_cast<int64_t>(sizeof(int32_t)) * c->cap_ids || n_ids > c->cap_ids)
             return fail(c, HELIOS_EINTERNAL, "scratch too small for a list by parts");
         HIP_TRY(c, launch_dedup_by_parts(c->stream, a, n_ids, c->g.n_nodes, parts));
         return HELIOS_OK;
     }
     c->batch_dirty[which] = s.n_slots;
     c->batch_listed[which] = false;
-    HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, c->err));
+    HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, nullptr, 0, c->err));
     HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
     // the call leaves its table as it found it: empty
-    HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{s.table, s.n_slots}, nullptr, 0));
+    const InverseArgs inv{Count{c->cnt + kCntCat, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse, false,
+                          Stamps{nullptr}};
+    HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{s.table, s.n_slots}));
     c->batch_dirty[which] = 0;
     return HELIOS_OK;
 }

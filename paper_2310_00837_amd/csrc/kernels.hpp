@@ -120,28 +120,60 @@ hipError_t launch_clock_publish(hipStream_t stream, const uint64_t* clock, const
                                 uint64_t* host_out);
 
 // ---- dedup.hip (the stand-alone de-duplication)
+// Slots of the table for a list of n IDs, if there are `most`: eight for each, so that a wave, which waits for the longest of its 64
+// searches, rarely looks at more than two (each a round trip to memory).  Two or more slots / eight, us: 8 192 IDs 15.7/13.1, 16 384
+// drawn evenly 23.4/14.4, 41 237 17.9/17.4 (19.7/16.2).  Emptying them costs less: 4 MB 0.7 us.
+inline uint32_t list_slots(int64_t n, uint32_t most) {
+    uint32_t slots = 1024;
+    while (slots < most && static_cast<int64_t>(slots) < 8 * n) slots <<= 1;
+    return slots;
+}
 // First pass as a kernel of its own (for IDs that no kernel of this library produced): inserts ids[0, n)
-// into s.table, which must be empty.
+// into s.table, which must be empty.  Beside it zero[0, n_zero) (nullable) is set to zero.
 hipError_t launch_dedup_insert(hipStream_t stream, const int32_t* ids, Count n, int64_t n_max, int64_t n_nodes,
-                               const DedupScratch& s, int32_t* err);
+                               const DedupScratch& s, unsigned long long* zero, uint32_t n_zero, int32_t* err);
 // Second pass over the whole list.
 hipError_t launch_dedup_compact_plain(hipStream_t stream, const CompactArgs& a, int64_t n_max);
-// Both passes for a list of kPartsMin to kPartsMax IDs (see dedup.hip).  a.len is n, known on the host.  The table may hold anything and
+// Both passes for a list of up to kPartsMax IDs (see dedup.hip), and whether that is the quicker way.  a.len is n, known on the host.  The table may hold anything and
 // is not used but by lists that hash unevenly; what they use of it is left empty.
-constexpr int64_t kPartsMin = 98304, kPartsMax = 2097152;
-struct PartScratch {             // all of n entries, but starts: split_starts_bytes(n)
+constexpr int64_t kPartsMax = 2097152;
+// Measured, us for the call with a table of two slots an ID / of eight / by parts, IDs by a power law (drawn evenly):
+//   4 k 12.8/12.9/17 (13.5/12.5/17)   8 k 15.5/12.8/15.7 (18/13/15.6)   16 k 16-17/13.5/15.7 (23.7/14/16.5)   25 k 16.3/14.7/15.8 (18.5/14.8/16)
+//   32 k 19.5/16.0/16.1 (25.5/16.6/16.2)   41 k 18.0/17.2/16.3 (19.3/16.1/16.7)   50 k 19/18.3/16.6 (20.5/17.5/16.7)   65 k 22/20.5/17 (24.5/19.7/17)
+//   98 k 24.5/-/18.2   262 k 41/-/23   1.1 M 102/-/38   2 M 165/-/57
+// and one ID throughout 8 k 135/145/15.3, 65 k 1050/1050/15.  Above 2 M a bucket would have more IDs than half its table.
+inline bool dedup_by_parts(int64_t n, uint32_t slots) { return n >= (slots >= 8 * n ? 32768 : 8192) && n <= kPartsMax; }
+// The list is cut into tiles, one to a workgroup: 256 of them, so that every CU has one, but of 1024 entries or more; and 512 if 256
+// would have more than 6144 each.
+constexpr uint32_t kMinPartTile = 1024, kMaxPartTile = 6144;
+struct PartShape {
+    uint32_t n, tile, n_tiles;   // entries, entries of a tile (a multiple of 64), tiles
+    uint32_t per_tile;           // 2^32 / tile, rounded up
+    uint32_t split_slots, bucket_slots;      // of the tables in LDS: 8192, or twice the entries of a tile and four times those of a bucket
+    explicit PartShape(int64_t ids) : n(static_cast<uint32_t>(ids)) {
+        const uint32_t most = ids <= 256 * kMaxPartTile ? 256 : 512;
+        tile = (n + most * 64 - 1) / (most * 64) * 64;
+        if (tile < kMinPartTile) tile = kMinPartTile;
+        n_tiles = (n + tile - 1) / tile;
+        per_tile = 0xffffffffu / tile + 1;
+        for (split_slots = 1024; split_slots < 8192 && split_slots < 2 * tile;) split_slots *= 2;
+        for (bucket_slots = 1024; bucket_slots < 8192 && bucket_slots < n / 128;) bucket_slots *= 2;
+    }
+};
+constexpr int64_t kMaxPartTiles = 512;
+struct PartScratch {             // all of n entries, but starts: split_starts_bytes(PartShape(n).n_tiles)
     int32_t* id;                 // the distinct IDs of every tile in order of bucket
     uint16_t* pos;               // their places in the tile
     uint32_t* first;             // the first positions of those IDs in the list
     uint16_t* local;             // for every input, the place in its tile where its ID is first, or 0xffff
     uint16_t* starts;            // [tile][513]: where a bucket begins in the tile
+    unsigned long long* clear;   // n_clear words that the first launch sets to zero (nullable)
+    uint32_t n_clear;
 };
-constexpr int64_t split_starts_bytes(int64_t n) { return (n + 4095) / 4096 * 513 * 2; }
+constexpr int64_t split_starts_bytes(int64_t n_tiles) { return n_tiles * 513 * 2; }
 hipError_t launch_dedup_by_parts(hipStream_t stream, const CompactArgs& a, int64_t n, int64_t n_nodes, const PartScratch& s);
-// The optional third pass (inv.inverse nullable), and in the same launch the emptying of a table and the zeroing of n_zero words,
-// neither of which that pass reads.
-hipError_t launch_dedup_end(hipStream_t stream, const InverseArgs& inv, int64_t n_max, const ClearJob& clear, unsigned long long* zero,
-                            uint32_t n_zero);
+// The optional third pass (inv.inverse nullable), and in the same launch the emptying of a table, which that pass does not read.
+hipError_t launch_dedup_end(hipStream_t stream, const InverseArgs& inv, int64_t n_max, const ClearJob& clear);
 
 // ---- cache.hip
 // rank[order[r]] = r; *holes (device) = 1 if that leaves a node without a rank, else 0.  scratch (nullable): device memory

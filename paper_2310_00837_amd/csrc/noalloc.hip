@@ -5,15 +5,15 @@
 // occurrence, scan status words, counters) from memory the context allocates and grows.  Here all
 // of it lives in one file-scope device array of fixed size, so the call enqueues kernels and
 // nothing else.  The array exists once per GPU the library runs on.  It is filled once, when the
-// first context of that GPU is created, and every call leaves it as it found it: its last launch
-// empties the table and zeroes the scan status and the ticket beside the inverse map, which reads none
-// of them (a launch of its own at the start of every call took 3 us).  So a captured call can be replayed.
-// Only a call that a launch error has cut short leaves it in use; the next call fills it first.
+// first context of that GPU is created.  The first launch of every call zeroes the scan status and the ticket, and the
+// last one leaves the table empty, beside work that uses none of them (a launch of its own at the start of every call
+// took 3 us).  So a captured call can be replayed.
+// Only a call that a launch error has cut short leaves the table in use; the next call fills the array first.
 // All calls on one GPU share the array, so calls that overlap on one GPU (two streams, two
 // contexts, two host threads) race; callers serialise them.  Calls that did overlap spoil each other and no
-// later one: whatever a call has put into the array, also while another was at work in it, its own last launch,
-// which is behind its own writes on its stream, takes out again (the ticket above all: two scans that draw
-// from it at the same time may both miss the draw that puts it back to zero).
+// later one: what a call has put into the table, also while another was at work in it, its own last launch,
+// which is behind its own writes on its stream, takes out again, and status and ticket a call never takes over from
+// another (two scans that draw from the ticket at the same time may both miss the draw that puts it back to zero).
 #include "context.hpp"
 #include "noalloc.hpp"
 
@@ -37,18 +37,20 @@ constexpr size_t kStatusBytes = (sizeof(unsigned long long) * 3 * kStride + 255)
 constexpr size_t kOffSmall = kOffStatus + kStatusBytes;     // ticket (uint32) at +0, counters (int64[2]) at +64
 constexpr size_t kSmallBytes = 256;
 constexpr size_t kOffTicket = kOffSmall, kOffCounters = kOffSmall + 64;
-// what the last launch of a call zeroes: the scan status and the ticket right behind it (not the counters, which it reads)
-constexpr uint32_t kEndZeroWords = static_cast<uint32_t>((kOffTicket + sizeof(unsigned long long) - kOffStatus) / sizeof(unsigned long long));
-static_assert(kOffStatus + kEndZeroWords * sizeof(unsigned long long) >= kOffTicket + sizeof(uint32_t) &&
-              kOffStatus + kEndZeroWords * sizeof(unsigned long long) <= kOffCounters, "the ticket is in, the counters are not");
-// a long list is taken apart by hash in memory of its own (and uses the table, if at all, as other calls do: it leaves it empty)
+// what the first launch of a call zeroes: the scan status and the ticket right behind it
+constexpr uint32_t kZeroWords = static_cast<uint32_t>((kOffTicket + sizeof(unsigned long long) - kOffStatus) / sizeof(unsigned long long));
+static_assert(kOffStatus + kZeroWords * sizeof(unsigned long long) >= kOffTicket + sizeof(uint32_t) &&
+              kOffStatus + kZeroWords * sizeof(unsigned long long) <= kOffCounters, "the ticket is in, the counters are not");
+// A long list is taken apart by hash in memory of its own (and uses the table, if at all, as other calls do: it leaves it empty).
+// Of the index of every first occurrence it uses 1/16, and where its buckets begin stands behind that.
 constexpr size_t kOffPartId = kOffSmall + kSmallBytes;
 constexpr size_t kOffPartFirst = kOffPartId + sizeof(int32_t) * kMaxIds;
 constexpr size_t kOffPartPos = kOffPartFirst + sizeof(uint32_t) * kMaxIds;
 constexpr size_t kOffPartLocal = kOffPartPos + sizeof(uint16_t) * kMaxIds;
-constexpr size_t kOffPartStarts = kOffPartLocal + sizeof(uint16_t) * kMaxIds;
-constexpr size_t kScratchBytes = kOffPartStarts + static_cast<size_t>(split_starts_bytes(kMaxIds));
-static_assert(kMaxIds <= kPartsMax && kMaxIds % 4096 == 0, "the longest list can be taken apart, and its last tile has all its places");
+constexpr size_t kScratchBytes = kOffPartLocal + sizeof(uint16_t) * kMaxIds;
+constexpr size_t kOffPartStarts = kOffIndexOfFirst + sizeof(uint32_t) * (kMaxIds / 16);
+static_assert(kMaxIds <= kPartsMax && kMaxIds <= 256 * 4096 && kOffPartStarts + static_cast<size_t>(split_starts_bytes(256)) <= kOffStatus,
+              "the longest list can be taken apart, into 256 tiles at most");
 static_assert(kScratchBytes < (9u << 20) + (256u << 10), "include/helios.h says how large the array is");
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -121,13 +123,11 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     unsigned long long* status = reinterpret_cast<unsigned long long*>(base + kOffStatus);
     uint32_t* ticket = reinterpret_cast<uint32_t*>(base + kOffTicket);
     int64_t* counters = reinterpret_cast<int64_t*>(base + kOffCounters);
-    // a table no larger than this call needs: cheaper to empty, and it stays in cache
-    uint32_t slots = 1024;
-    while (static_cast<int64_t>(slots) < 2 * n_ids) slots <<= 1;
+    const uint32_t slots = list_slots(n_ids, kSlots);
     const DedupScratch s{table, slots, reinterpret_cast<int32_t*>(base + kOffSlotOf),
                          reinterpret_cast<int32_t*>(base + kOffIndexOfFirst)};
     if (fill) HIP_TRY(c, launch_reset(c->stream, base, kSlots));
-    // the status words are zero, so any epoch but zero reads them as unpublished; the same value every
+    // the first launch zeroes the status words, so any epoch but zero reads them as unpublished; the same value every
     // call keeps a captured call replayable
     const ScanState scan{status, ticket, kStride, 1u, nullptr};
     const Count n{nullptr, n_ids};
@@ -146,20 +146,18 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     a.inverse = inverse;
     a.scan = scan;
     a.err = c->err;
-    const bool by_parts = n_ids >= kPartsMin;
+    const bool by_parts = dedup_by_parts(n_ids, slots);
     if (by_parts) {
         const PartScratch parts{reinterpret_cast<int32_t*>(base + kOffPartId), reinterpret_cast<uint16_t*>(base + kOffPartPos),
                                 reinterpret_cast<uint32_t*>(base + kOffPartFirst), reinterpret_cast<uint16_t*>(base + kOffPartLocal),
-                                reinterpret_cast<uint16_t*>(base + kOffPartStarts)};
+                                reinterpret_cast<uint16_t*>(base + kOffPartStarts), status, kZeroWords};
         HIP_TRY(c, launch_dedup_by_parts(c->stream, a, n_ids, c->g.n_nodes, parts));
     } else {
-        HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, c->err));
+        HIP_TRY(c, launch_dedup_insert(c->stream, ids, n, n_ids, c->g.n_nodes, s, status, kZeroWords, c->err));
         HIP_TRY(c, launch_dedup_compact_plain(c->stream, a, n_ids));
+        const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{}, nullptr, inverse, false, Stamps{nullptr}};
+        HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, ClearJob{table, slots}));
     }
-    const InverseArgs inv{Count{counters + 0, n_ids}, s.index_of_first, BatchTables{}, nullptr, by_parts ? nullptr : inverse, false,
-                          Stamps{nullptr}};
-    HIP_TRY(c, launch_dedup_end(c->stream, inv, n_ids, by_parts ? ClearJob{nullptr, 0} : ClearJob{table, slots}, status,
-                                kEndZeroWords));
     // A call that is being captured has not run.  It found the array clean, and leaves it so, unless the filling was
     // captured with it: then the next call still has to do that.
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;

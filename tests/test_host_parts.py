@@ -30,6 +30,7 @@ T* guarded(size_t n) {
 
 constexpr int64_t kNodes = 0x7fffffff;
 struct Call {
+    PartShape shape;
     int64_t n, tiles;
     int32_t *ids, *unique, *inverse, *iof;
     PartScratch s;
@@ -39,14 +40,13 @@ struct Call {
     int64_t* counters;
     int32_t* err;
     CompactArgs a{};
-    explicit Call(const std::vector<int32_t>& list, int64_t cap, bool in_place = false) : n(list.size()), tiles((n + kPartTile - 1) / kPartTile) {
+    explicit Call(const std::vector<int32_t>& list, int64_t cap, bool in_place = false) : shape(list.size()), n(list.size()), tiles(shape.n_tiles) {
         ids = guarded<int32_t>(n);
         unique = in_place ? ids : guarded<int32_t>(cap);
         inverse = guarded<int32_t>(n);
         iof = guarded<int32_t>(n);
-        const size_t room = tiles * kPartTile;
-        s = PartScratch{guarded<int32_t>(room), guarded<uint16_t>(room), guarded<uint32_t>(room), guarded<uint16_t>(room),
-                        guarded<uint16_t>(split_starts_bytes(n) / 2)};
+        s = PartScratch{guarded<int32_t>(n), guarded<uint16_t>(n), guarded<uint32_t>(n), guarded<uint16_t>(n),
+                        guarded<uint16_t>(split_starts_bytes(tiles) / 2), nullptr, 0};
         for (n_slots = 1024; n_slots < 2 * n;) n_slots *= 2;
         table = guarded<unsigned long long>(n_slots);
         status = guarded<unsigned long long>(tiles);
@@ -72,11 +72,11 @@ struct Call {
         a.err = err;
     }
     void split() const {
-        hipLaunchKernelGGL(dedup_split_kernel, dim3(tiles), dim3(kSplitBlock), 0, nullptr, a.ids, static_cast<uint32_t>(n), kNodes, s, err);
+        hipLaunchKernelGGL(dedup_split_kernel<6>, dim3(tiles), dim3(kSplitBlock), 0, nullptr, a.ids, shape, kNodes, s, err);
     }
-    void buckets() const { hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, nullptr, s, static_cast<uint32_t>(tiles), table, n_slots, err); }
+    void buckets() const { hipLaunchKernelGGL(dedup_bucket_kernel, dim3(kParts), dim3(kBucketBlock), 0, nullptr, s, shape, table, n_slots, err); }
     bool table_empty() const { return std::all_of(table, table + n_slots, [](unsigned long long w) { return w == kEmptySlot; }); }
-    void compact() const { hipLaunchKernelGGL(dedup_compact_parts_kernel, dim3(tiles), dim3(kMergeBlock), 0, nullptr, a, s); }
+    void compact() const { hipLaunchKernelGGL(dedup_compact_parts_kernel<6>, dim3(tiles), dim3(kMergeBlock), 0, nullptr, a, s, shape); }
 };
 
 void check(bool ok, const char* what) {
@@ -88,8 +88,6 @@ void check(bool ok, const char* what) {
 void results(const std::vector<int32_t>& list, int64_t cap, bool in_place) {
     Call c(list, cap, in_place);
     launch_dedup_by_parts(nullptr, c.a, c.n, kNodes, c.s);
-    launch_dedup_end(nullptr, InverseArgs{Count{c.counters, c.n}, c.iof, BatchTables{}, nullptr, c.inverse, false, Stamps{nullptr}}, c.n,
-                     ClearJob{nullptr, 0}, nullptr, 0);
     std::unordered_map<int32_t, int32_t> at;
     std::vector<int32_t> want;
     bool bad = false;
@@ -153,18 +151,18 @@ int main(int argc, char** argv) {
                 if ((w / 64) % 2) a.s.starts[t * (kParts + 1) + w] = b.s.starts[t * (kParts + 1) + w];
         a.buckets();
         check(a.err[0] == kErrInternal, "the call has to notice");
-        for (int64_t q = 0; q < split_starts_bytes(n) / 2; ++q) a.s.starts[q] = static_cast<uint16_t>(next_random());
+        for (int64_t q = 0; q < split_starts_bytes(a.tiles) / 2; ++q) a.s.starts[q] = static_cast<uint16_t>(next_random());
         a.buckets();
         a.compact();                                     // (the bound of a tile's entries is such a word too)
     } else if (what == "tickets") {                      // two calls draw tickets from one counter
         std::vector<int32_t> v(3 * kPartTile - 5);
         for (size_t j = 0; j < v.size(); ++j) v[j] = static_cast<int32_t>(j / 2);
-        for (unsigned drawn : {3u, 4u, 40u}) {
+        for (unsigned drawn : {0u, 1u, 40u}) {
             Call c(v, v.size());
             c.split();
             c.buckets();
             for (int64_t t = 0; t < c.tiles; ++t) c.status[t] = scan_pack(1, kFlagPrefix, 0);     // (what the other call has published)
-            *c.ticket = drawn;
+            *c.ticket = c.tiles + drawn;
             c.compact();
             check(c.err[0] == kErrInternal, "the call has to notice");
         }
@@ -175,9 +173,9 @@ int main(int argc, char** argv) {
         c.split();
         const std::vector<int32_t> same = hashing_to(n, 1023, 3);
         memcpy(c.s.id, same.data(), 4 * n);
-        for (int j = 0; j < n; ++j) c.s.pos[j] = j % kPartTile;
+        for (int j = 0; j < n; ++j) c.s.pos[j] = j % c.shape.tile;
         for (int64_t t = 0; t < c.tiles; ++t)
-            for (int w = 0; w <= kParts; ++w) c.s.starts[t * (kParts + 1) + w] = w > 9 ? kPartTile : 0;      // all in bucket 9
+            for (int w = 0; w <= kParts; ++w) c.s.starts[t * (kParts + 1) + w] = w > 9 ? std::min<int64_t>(c.shape.tile, n - t * c.shape.tile) : 0;      // all in bucket 9
         c.buckets();
         check(c.table_empty(), "left as found");
         for (int j = 0; j < n; ++j) check(c.s.first[j] == static_cast<uint32_t>(j), "first position");
