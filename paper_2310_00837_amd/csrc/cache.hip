@@ -264,7 +264,6 @@ struct PartitionArgs {
     int64_t* stats_out;          // device-accessible int64[4], nullable
     int64_t* learn;              // pinned int64[4], nullable: a copy of the stats for the host's grid sizing
     bool hbm_direct;             // no list is wanted for the HBM tier
-    const int64_t* holes;        // device word: not 0 if some node has no rank
     ScanState scan;
     int32_t* err;
 };
@@ -351,25 +350,40 @@ __device__ __forceinline__ void partition_role(const PartitionArgs& a, uint32_t 
 // map has found out, the ranks need not be read for it.  Call on 100 k rows of 64 bytes, copied beside it: 12.0 us with the partition,
 // 10.1 with a count that reads the ranks, 7.5 with this; 243 k rows of 2 KB 174.3 -> 167.2.
 constexpr unsigned kCountWorkgroups = 64;              // (a word that all add to takes about 10 ns for each)
-__device__ __forceinline__ void count_role(const PartitionArgs& a, uint32_t rb, uint32_t nrb) {
+struct CountCopyArgs {
+    const int32_t* ids;
+    const int32_t* rank;
+    const chunk16* table;
+    chunk16* out;
+    int64_t *count, *stats_out, *learn;
+    const int64_t* holes;
+    unsigned long long* word;    // zero between launches (the scan's ticket)
+    int32_t* err;
+    uint32_t n, n_nodes;         // (all nodes are in HBM)
+    int32_t chunks;
+    uint32_t count_blocks;       // the workgroups before those that copy
+};
+// (a launch with 128 bytes of arguments or more costs the host 0.5 us more)
+static_assert(sizeof(CountCopyArgs) <= 112, "arguments of a cheap launch");
+__device__ __forceinline__ void count_role(const CountCopyArgs& a) {
     __shared__ uint32_t s_hits[kScanWaves];
     constexpr int kAhead = 4;
-    const uint32_t n = static_cast<uint32_t>(a.n.get()), step = nrb * kScanBlock;
+    const uint32_t n = a.n, nrb = a.count_blocks, step = nrb * kScanBlock;
     const bool whole = *a.holes == 0;
     uint32_t hits = 0;
-    for (uint64_t j0 = rb * kScanBlock + threadIdx.x; j0 < n; j0 += static_cast<uint64_t>(kAhead) * step) {
+    for (uint64_t j0 = blockIdx.x * kScanBlock + threadIdx.x; j0 < n; j0 += static_cast<uint64_t>(kAhead) * step) {
         int32_t id[kAhead], r[kAhead];
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) id[k] = a.ids[j0 + static_cast<uint64_t>(k) * step < n ? j0 + static_cast<uint64_t>(k) * step : j0];
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
-            const bool ok = id[k] >= 0 && static_cast<int64_t>(id[k]) < a.n_nodes;
+            const bool ok = static_cast<uint32_t>(id[k]) < a.n_nodes;
             if (!ok) raise(a.err, kErrData);
             r[k] = ok ? 0 : -1;
             if (!whole && ok) r[k] = a.rank[id[k]];
         }
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) hits += j0 + static_cast<uint64_t>(k) * step < n && static_cast<uint32_t>(r[k]) < static_cast<uint32_t>(a.n_hbm) ? 1u : 0u;
+        for (int k = 0; k < kAhead; ++k) hits += j0 + static_cast<uint64_t>(k) * step < n && static_cast<uint32_t>(r[k]) < a.n_nodes ? 1u : 0u;
     }
     const uint32_t sum = dpp_sum(hits);
     if (lane_id() == 0) s_hits[wave_id()] = sum;
@@ -378,12 +392,11 @@ __device__ __forceinline__ void count_role(const PartitionArgs& a, uint32_t rb, 
     unsigned long long mine = 1ull << 40;              // {workgroups done : 24 | hits : 40}
 #pragma unroll
     for (int w = 0; w < kScanWaves; ++w) mine += s_hits[w];
-    unsigned long long* word = reinterpret_cast<unsigned long long*>(a.scan.ticket);       // zero between launches, as the ticket is
-    const unsigned long long all = atomicAdd(word, mine) + mine;
+    const unsigned long long all = atomicAdd(a.word, mine) + mine;
     if (all >> 40 != nrb) return;
-    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int64_t c0 = static_cast<int64_t>(all & ((1ull << 40) - 1));
-    a.lists.count[0] = c0; a.lists.count[1] = a.lists.count[2] = 0;
+    a.count[0] = c0; a.count[1] = a.count[2] = 0;
     if (a.stats_out) { a.stats_out[0] = n; a.stats_out[1] = c0; a.stats_out[2] = 0; a.stats_out[3] = 0; }
     if (a.learn) { a.learn[0] = n; a.learn[1] = c0; a.learn[2] = 0; a.learn[3] = 0; }
 }
@@ -427,15 +440,24 @@ __device__ __forceinline__ void direct_rows(const DirectArgs& a, uint32_t rb, ui
 // Lookup and partition, and beside it, if r_copy has workgroups, the copy of the HBM tier's rows.  As two launches the copy
 // waited 8 to 13 us for lists it does not need: 243 k rows of 2 KB 179.1 -> 174.5 us for the call, 100 k rows of 64 bytes
 // 15.0 -> 12.0.  (One row per group and step: with two 177.0 and 13.4 us, with four 184.2 and 13.7.)  When it does not pay:
-// copy_beside_lookup below.  K = 0: the count in place of the partition.
+// copy_beside_lookup below.
 template <int K, int L, int CPL>
 __global__ __launch_bounds__(kScanBlock) void lookup_copy_kernel(PartitionArgs a, DirectArgs d, Role r_part, Role r_copy) {
     if (r_part.mine()) {
-        if constexpr (K == 0) count_role(a, r_part.rb(), r_part.blocks);
-        else partition_role<K>(a, r_part.rb(), r_part.blocks);
+        partition_role<K>(a, r_part.rb(), r_part.blocks);
         return;
     }
     direct_rows<L, CPL>(d, r_copy.rb(), r_copy.blocks);
+}
+
+// The same with all nodes in HBM: the count, and beside it the copy.
+template <int L, int CPL>
+__global__ __launch_bounds__(kScanBlock) void count_copy_kernel(CountCopyArgs a) {
+    if (blockIdx.x < a.count_blocks) {
+        count_role(a);
+        return;
+    }
+    direct_rows<L, CPL>(DirectArgs{a.ids, a.rank, a.n, a.n_nodes, a.n_nodes, a.table, a.out, a.chunks}, blockIdx.x - a.count_blocks, gridDim.x - a.count_blocks);
 }
 
 unsigned grid_for(int64_t n, unsigned cap_blocks) {
@@ -505,10 +527,12 @@ hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, int64
                                    int32_t chunks) {
     const bool copy = copy_table && n > 0 && n_hbm > 0;
     const PartitionArgs a{ids, Count{nullptr, n}, rank, n_nodes, n_hbm, n_host, lists, miss_pos, miss_id, miss_slot, miss_cap,
-                          stats_out, learn, copy, holes, scan, err};
+                          stats_out, learn, copy, scan, err};
     const DirectArgs d{ids, rank, static_cast<uint32_t>(n), static_cast<uint32_t>(n_nodes), static_cast<uint32_t>(n_hbm), copy_table, copy_out, chunks};
     const bool count_only = copy && n_hbm == n_nodes;
     const Role r_part{0, scan_workgroups(n, count_only ? kCountWorkgroups : kScanMaxWorkgroups)};
+    const CountCopyArgs counting{ids, rank, copy_table, copy_out, lists.count, stats_out, learn, holes, reinterpret_cast<unsigned long long*>(scan.ticket), err,
+                                 static_cast<uint32_t>(n), static_cast<uint32_t>(n_nodes), chunks, r_part.blocks};
     const dim3 block(kScanBlock);
     // One row per group and step, and as many workgroups as the list has steps: short-lived workgroups on consecutive rows copy
     // fastest (gather_dev.hpp).
@@ -519,7 +543,7 @@ hipError_t launch_lookup_partition(hipStream_t stream, const int32_t* ids, int64
         if (nb > kMaxRoleBlocks) nb = kMaxRoleBlocks;                                                                        \
         const Role r_copy{r_part.blocks, static_cast<uint32_t>(nb)};                                                         \
         const dim3 grid(r_part.blocks + r_copy.blocks);                                                                      \
-        if (count_only) hipLaunchKernelGGL((lookup_copy_kernel<0, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy);   \
+        if (count_only) hipLaunchKernelGGL((count_copy_kernel<L, CPL>), grid, block, 0, stream, counting);                   \
         else if (n <= kScanOneItemMax) hipLaunchKernelGGL((lookup_copy_kernel<1, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy); \
         else hipLaunchKernelGGL((lookup_copy_kernel<kScanMaxItems, L, CPL>), grid, block, 0, stream, a, d, r_part, r_copy);  \
     } while (0)

@@ -146,6 +146,10 @@ def _dev(t: torch.Tensor, dtype: torch.dtype, what: str) -> torch.Tensor:
     return t
 
 
+def _dev_ptr(t: torch.Tensor, dtype: torch.dtype, what: str) -> int:
+    return _dev(t, dtype, what).data_ptr()
+
+
 def _dev_accessible(t: torch.Tensor, dtype: torch.dtype, what: str) -> torch.Tensor:
     if t.dtype != dtype or not t.is_contiguous() or not (t.is_cuda or _is_pinned(t)):
         raise TypeError(f"{what}: expected a contiguous {dtype} tensor on the GPU or in pinned host memory")
@@ -518,41 +522,45 @@ class Helios:
     # ---- S2
     def dedup(self, ids: torch.Tensor, unique: torch.Tensor, inverse: Optional[torch.Tensor],
               n_unique: torch.Tensor, n_ids: Optional[int] = None) -> None:
-        _dev(ids, torch.int32, "ids"), _dev(unique, torch.int32, "unique")
+        p_ids, p_unique = _dev_ptr(ids, torch.int32, "ids"), _dev_ptr(unique, torch.int32, "unique")
         _dev_accessible(n_unique, torch.int64, "n_unique")
         n = ids.numel() if n_ids is None else n_ids
+        p_inverse = None
         if inverse is not None:
-            _dev(inverse, torch.int32, "inverse")
+            p_inverse = _dev_ptr(inverse, torch.int32, "inverse")
             assert inverse.numel() >= n
-        self._check(_lib.helios_dedup(self._h, _ptr(ids), n, _ptr(unique), unique.numel(), _ptr(inverse),
-                                      _ptr(n_unique)))
+        rc = _lib.helios_dedup(self._h, p_ids, n, p_unique, unique.numel(), p_inverse, n_unique.data_ptr())
+        if rc != OK:
+            self._check(rc)
 
     def dedup_noalloc(self, ids: torch.Tensor, unique: torch.Tensor, inverse: Optional[torch.Tensor],
                       n_unique: torch.Tensor, n_ids: Optional[int] = None) -> None:
         """helios_dedup on the library's fixed scratch array: allocates nothing (at most DEDUP_NOALLOC_MAX_IDS IDs)."""
-        _dev(ids, torch.int32, "ids"), _dev(unique, torch.int32, "unique")
+        p_ids, p_unique = _dev_ptr(ids, torch.int32, "ids"), _dev_ptr(unique, torch.int32, "unique")
         _dev_accessible(n_unique, torch.int64, "n_unique")
         n = ids.numel() if n_ids is None else n_ids
+        p_inverse = None
         if inverse is not None:
-            _dev(inverse, torch.int32, "inverse")
+            p_inverse = _dev_ptr(inverse, torch.int32, "inverse")
             assert inverse.numel() >= n
-        self._check(_lib.helios_dedup_noalloc(self._h, _ptr(ids), n, _ptr(unique), unique.numel(), _ptr(inverse),
-                                              _ptr(n_unique)))
+        rc = _lib.helios_dedup_noalloc(self._h, p_ids, n, p_unique, unique.numel(), p_inverse, n_unique.data_ptr())
+        if rc != OK:
+            self._check(rc)
 
     # ---- S3 + S4 + S5
     def gather(self, ids: torch.Tensor, out: torch.Tensor, miss_pos: torch.Tensor, miss_id: torch.Tensor,
                miss_slot: torch.Tensor, stats: torch.Tensor, n_ids: Optional[int] = None) -> None:
-        _dev(ids, torch.int32, "ids")
+        p_ids = _dev_ptr(ids, torch.int32, "ids")
         n = ids.numel() if n_ids is None else n_ids
         if not out.is_cuda or not out.is_contiguous() or out.numel() * out.element_size() < n * self.row_bytes:
             raise TypeError("out must be a contiguous GPU tensor of n_ids x row_bytes")
-        for t in (miss_pos, miss_id, miss_slot):
-            _dev(t, torch.int32, "miss list")
+        p_pos, p_id, p_slot = [_dev_ptr(t, torch.int32, "miss list") for t in (miss_pos, miss_id, miss_slot)]
         _dev_accessible(stats, torch.int64, "stats")
         assert stats.numel() >= 4
         cap = min(miss_pos.numel(), miss_id.numel(), miss_slot.numel())
-        self._check(_lib.helios_gather(self._h, _ptr(ids), n, _ptr(out), _ptr(miss_pos), _ptr(miss_id),
-                                       _ptr(miss_slot), cap, _ptr(stats)))
+        rc = _lib.helios_gather(self._h, p_ids, n, out.data_ptr(), p_pos, p_id, p_slot, cap, stats.data_ptr())
+        if rc != OK:
+            self._check(rc)
 
     # ---- S6
     def gather_miss(self, miss_pos: torch.Tensor, miss_slot: torch.Tensor, n_miss_max: int,
