@@ -435,13 +435,17 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
     const bool fold = n_seeds <= kFoldMaxSeeds;
     if (c->defer && (!fold || !b || c->split_copies || c->missq || c->timing > 1))
         return fail(c, HELIOS_EINTERNAL, "this call cannot be part of a gang");       // (refused earlier, with the reason)
+    unsigned counted_waves = 0;
+    const unsigned counted_blocks = fold ? 0u : sample_counted_blocks(fanouts[0], n_seeds, c->scan_stride, &counted_waves);
+    ScanState count_scan{};
     if (!fold) {
         uint32_t epoch;
         int rc = next_epoch(c, &epoch);
         if (rc) return rc;
-        HIP_TRY(c, launch_frontier_count(c->stream, c->g, seeds, feed, hops[0].frontier, Count{nullptr, n_seeds}, n_seeds,
-                                         fanouts[0], hops[0].indptr, hops[0].flat_cap, c->cnt + kCntFlat + 0, sizes,
-                                         scan_state(c, epoch, kScanRowsHop), err));
+        count_scan = scan_state(c, epoch, kScanRowsHop);
+        if (counted_blocks == 0)
+            HIP_TRY(c, launch_frontier_count(c->stream, c->g, seeds, feed, hops[0].frontier, Count{nullptr, n_seeds}, n_seeds,
+                                             fanouts[0], hops[0].indptr, hops[0].flat_cap, c->cnt + kCntFlat + 0, sizes, count_scan, err));
     }
     Count nf{nullptr, n_seeds};
     uint32_t n_claims = 0;
@@ -453,7 +457,8 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
         ha.indices = c->g.indices;
         ha.n_nodes = c->g.n_nodes;
         ha.fold = h == 0 && fold;
-        ha.frontier = ha.fold ? seeds : hops[h].frontier;
+        const bool counted = h == 0 && counted_blocks > 0;
+        ha.frontier = ha.fold || counted ? seeds : hops[h].frontier;
         ha.indptr = hops[h].indptr;
         ha.n_frontier = nf;
         ha.fanout = fanouts[h];
@@ -469,17 +474,17 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
         ha.n_seeds = n_seeds;
         ha.cat_begin = b && h > 0 ? stage_words(c, h - 1) + kStageEnd : nullptr;
         ha.err = err;
-        if (ha.fold) {
+        if (ha.fold || counted) {
             ha.feed = feed;
             ha.frontier_out = hops[0].frontier;
             ha.indptr_out = hops[0].indptr;
             ha.n_flat_dev = c->cnt + kCntFlat + 0;
             ha.size_out = sizes;
         }
-        const unsigned hop_blocks = sample_role_blocks(fanouts[h], p.frontier_max[h], c->link_share);
+        const unsigned hop_blocks = counted ? counted_blocks : sample_role_blocks(fanouts[h], p.frontier_max[h], c->link_share);
         if (b) {
             ha.claims = c->claims + n_claims;
-            n_claims += hop_blocks * kWavesPerBlock;
+            n_claims += hop_blocks * (counted ? counted_waves : kWavesPerBlock);
         }
         ha.stamps = take_stamps(c, HELIOS_ROLE_SAMPLE, h, hop_blocks);
         GatherArgs link{};
@@ -492,8 +497,12 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
                                   Count{stage_words(c, stage) + kStageHostCopy, u_max}, b->out,
                                   take_stamps(c, HELIOS_ROLE_COPY_HOST, stage, link_blocks));
         }
-        int rs = emit_sample(c, SampleJob{ha, hop_blocks, link, link_blocks});
-        if (rs) return rs;
+        if (counted) {
+            HIP_TRY(c, launch_sample_counted(c->stream, ha, count_scan));
+        } else {
+            const int rs = emit_sample(c, SampleJob{ha, hop_blocks, link, link_blocks});
+            if (rs) return rs;
+        }
         const Count flat{c->cnt + kCntFlat + h, p.flat_max[h]};
 
         // ---- compaction: this hop's samples into the next frontier, and stage h of the batch's ID list

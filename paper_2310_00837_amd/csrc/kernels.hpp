@@ -26,6 +26,11 @@ hipError_t launch_frontier_count(hipStream_t stream, const CsrView& g, const int
                                  int32_t* frontier_out, Count n, int64_t n_max, int32_t fanout, int64_t* indptr,
                                  int64_t flat_cap, int64_t* n_flat_dev, int64_t* size_out, const ScanState& scan, int32_t* err);
 
+// Count and sampling of hop 0 in one launch: sample_counted_blocks workgroups of `waves` waves (0: the list is too long, or the fan-out too
+// large); stride: the scan's status words.  a as for a folded hop; scan.vars is not used.
+unsigned sample_counted_blocks(int32_t fanout, int64_t n, uint32_t stride, unsigned* waves);
+hipError_t launch_sample_counted(hipStream_t stream, const HopArgs& a, const ScanState& scan);
+
 // ---- pipeline.hip: the launches of the sampling / whole-path pipeline; each carries one or more roles
 // Every launch takes the jobs of n mini-batches (1 <= n <= kMaxGang), one per member of a gang; the
 // members' roles share the launch.

@@ -89,12 +89,14 @@ __device__ __forceinline__ void put_id(SampleTables& t, int64_t n_nodes, int32_t
     }
 }
 
-// What the folded count pass leaves in LDS for the nodes that this workgroup samples.
-struct OwnNodes {
-    int64_t base[kBlock / 8];
-    int32_t v[kBlock / 8], deg[kBlock / 8];
-    uint32_t out[kBlock / 8];
+// What the count pass, where the sampling kernel does it, leaves in LDS for the nodes that this workgroup samples.
+template <int N>
+struct OwnNodesOf {
+    int64_t base[N];
+    int32_t v[N], deg[N];
+    uint32_t out[N];
 };
+using OwnNodes = OwnNodesOf<kBlock / 8>;
 
 // The count pass of a frontier of at most K * kBlock nodes, redone by every workgroup: item k of a thread is node
 // k * kBlock + threadIdx.x.  All loads of a step are issued before the first is used.
@@ -174,6 +176,21 @@ __device__ __forceinline__ void floyd_settle(int f, bool floyd, int l, int32_t t
             if (floyd && l > i && si == t) s = j;
         }
     }
+}
+
+// The position in v's row of the l-th sample, of a group of G lanes for one node; f <= G.
+template <int G>
+__device__ __forceinline__ int32_t pick(uint64_t rng_seed, int32_t v, int32_t hop, int32_t deg, int f, int l) {
+    int32_t pos = l;                                  // deg <= f: the whole row, CSR order
+    const bool floyd = deg > f && l < f;
+    const int32_t j = deg - f + l;                    // position looked at in step l
+    int32_t s = pos;
+    if (__ballot(floyd) != 0) {                       // about half the nodes have no more neighbours than the fan-out
+        if (floyd) pos = static_cast<int32_t>(bounded(node_draw(rng_seed, v, hop, static_cast<uint32_t>(l)), static_cast<uint32_t>(j) + 1u));
+        s = pos;
+        floyd_settle<G>(f, floyd, l, pos, j, s);
+    }
+    return s;
 }
 
 // What bounds the role: for a short frontier the chain of dependent reads and instructions (batch variables, seeds, row bounds,
@@ -268,15 +285,7 @@ __device__ __forceinline__ void sample_role(const HopArgs& a, uint32_t rb, uint3
             const int64_t room = a.flat_cap - out;   // samples of this node that fit
 
             if (f <= G) {
-                int32_t pos = l;                                  // deg <= f: the whole row, CSR order
-                const bool floyd = deg > f && l < f;
-                const int32_t j = deg - f + l;                    // position looked at in step l
-                int32_t s = pos;
-                if (__ballot(floyd) != 0) {                       // about half the nodes have no more neighbours than the fan-out
-                    if (floyd) pos = static_cast<int32_t>(bounded(node_draw(rng_seed, v, a.hop, static_cast<uint32_t>(l)), static_cast<uint32_t>(j) + 1u));
-                    s = pos;
-                    floyd_settle<G>(f, floyd, l, pos, j, s);
-                }
+                const int32_t s = pick<G>(rng_seed, v, a.hop, deg, f, l);
                 const bool sample = l < cnt && out_ok && l < room;
                 const uint32_t at = static_cast<uint32_t>(out) + l;
                 if (!seeds_too) {

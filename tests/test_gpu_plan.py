@@ -125,6 +125,30 @@ def test_two_batches_queued_per_context(helios, oracle):
     first.close()
 
 
+@pytest.mark.parametrize("n_seeds,fanouts", [(3_000, [25, 2]), (9_000, [40, 1])])
+def test_recorded_batches_of_long_seed_lists(helios, oracle, n_seeds, fanouts):
+    """More seeds than the sampling pass counts by itself, in recordings: counted and sampled in one launch, and in two."""
+    rng = np.random.default_rng(n_seeds)
+    n, n_hbm, n_host = 50_000, 20_000, 20_000
+    off = np.concatenate([[0], np.cumsum(rng.integers(0, 60, n))]).astype(np.int64)
+    idx = rng.integers(0, n, off[-1]).astype(np.int32)
+    feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
+    order = torch.from_numpy(rng.permutation(n).astype(np.int32))
+    by_rank = to_bytes(feats)[order.numpy()]
+    tabs = [np.ascontiguousarray(x) for x in (by_rank[:n_hbm], by_rank[n_hbm:n_hbm + n_host], by_rank[n_hbm + n_host:])]
+    tabs_dev = (torch.from_numpy(tabs[0]).cuda(), torch.from_numpy(tabs[1]).pin_memory(), torch.from_numpy(tabs[2]).pin_memory())
+    seeds = [rng.integers(0, n, n_seeds).astype(np.int32) for _ in range(9)]
+    jobs = [(torch.from_numpy(s).cuda(), 70 + k) for k, s in enumerate(seeds)]
+    torch.cuda.synchronize()
+    got = lanes_in_flight(helios, torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda(), order.cuda(), n_hbm, n_host, 16, tabs_dev, n_seeds,
+                          fanouts, jobs, per_lane=2)
+    rank = oracle.rank_build(order.numpy())
+    for k, s in enumerate(seeds):
+        want = oracle_path(oracle, off, idx, s, fanouts, 70 + k, rank, n_hbm, n_host, *tabs, 16)
+        del want["out"]
+        assert_same(got[k], want)
+
+
 @pytest.mark.parametrize("params", [dict(split=1), dict(split=0, hbm_blocks=7, host_blocks=3), dict(split=1, hbm_blocks=8192, host_blocks=1), dict(split=0, hbm_blocks=1, host_blocks=300)])
 def test_launch_parameters_do_not_change_results(helios, oracle, params):
     """The tuning parameters (tier copies as kernels of their own or as roles of the batch's other launches, grid

@@ -98,10 +98,11 @@ def test_dedup_reports_bad_ids_and_keeps_the_rest(h, helios, oracle, n_ids):
     assert np.array_equal(got[good], wi) and (got[bad] == -1).all()
 
 
-@pytest.mark.parametrize("n_seeds,fanouts", [(2_048, [4, 3]), (2_049, [4, 3]), (ONE_ITEM_MAX + 5, [1, 2]), (60_000, [4, 2]),
+@pytest.mark.parametrize("n_seeds,fanouts", [(2_048, [4, 3]), (2_049, [4, 3]), (2_049, [25, 3]), (8_192, [33, 2]), (8_193, [33, 2]), (16_384, [32, 1]),
+                                              (16_385, [32, 1]), (32_768, [9, 1]), (32_769, [9, 1]), (32_768, [8, 1]), (4_000, [64, 1]), (4_000, [65, 1]), (ONE_ITEM_MAX + 5, [1, 2]), (60_000, [4, 2]),
                                               (150_000, [4, 4]), (512 * 2048 + 1, [1, 1])])
 def test_whole_path_with_long_lists(h, helios, oracle, n_seeds, fanouts):
-    """Seed lists on both sides of the folded count pass, stages and hops longer than one item per thread serves, and such
+    """Seed lists on both sides of the folded count pass and of the launch that counts and samples (512 tiles by lane group), stages and hops longer than one item per thread serves, and such
     that have more tiles than workgroups (the last two: stages of about 0.5 to 2 M items; 513 tiles in the last one's count pass)."""
     print("long lists", n_seeds, fanouts, flush=True)
     rng = np.random.default_rng(n_seeds)
