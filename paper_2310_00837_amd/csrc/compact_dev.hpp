@@ -382,6 +382,7 @@ __device__ __forceinline__ void compact_role(const CompactArgs& a, uint32_t rb, 
     }
     if (static_cast<uint64_t>(rb) * kScanBlock < n) {
         if (n <= kScanOneItemMax) compact_tiles<MODE, 1>(a, s, scan, prev, begin, n, rb, nrb);
+        else if (n <= 2 * kScanOneItemMax) compact_tiles<MODE, 2>(a, s, scan, prev, begin, n, rb, nrb);
         else compact_tiles<MODE, kScanMaxItems>(a, s, scan, prev, begin, n, rb, nrb);
     }
     stamp_end(a.stamps, rb, nrb);
