@@ -57,6 +57,12 @@ uint32_t pow2_at_least(int64_t n) {
     return p;
 }
 
+// Slots of a batch's table for at most n IDs: two for each, and eight where that is no more than 32 k (256 KB), because a wave
+// waits for the longest of its 64 searches, each step of which is a round trip to memory: 128 seeds with fan-outs 5 and 5, launched
+// directly, 41.1 us with two, 39.8.  With eight for longer lists, too, a gang of four pays more for the emptying than it gains
+// (57.0/57.9).  The bounds are several times what batches bring, so longer lists are rarely crowded.
+uint32_t batch_slots_for(int64_t n) { return std::max(pow2_at_least(2 * n), pow2_at_least(8 * std::min<int64_t>(n, 4096))); }
+
 void free_scratch(helios_ctx* c) {
     (void)hipFree(c->batch_tables);
     (void)hipFree(c->batch_iof);
@@ -95,7 +101,8 @@ int ensure_capacity(helios_ctx* c, int64_t n) {
     free_scratch(c);
     c->blocks_ready = false;
     const int64_t cap = (n + 4095) / 4096 * 4096;
-    const uint32_t slots = pow2_at_least(2 * cap);
+    // (a stand-alone list of up to 64 k IDs finds eight slots for each, see list_slots; 4 MB)
+    const uint32_t slots = std::max(pow2_at_least(2 * cap), pow2_at_least(8 * std::min<int64_t>(cap, 65536)));
     const uint32_t stride = scan_row_stride(cap);
     HIP_TRY(c, hipMalloc(&c->batch_tables, sizeof(unsigned long long) * slots * kBatchTables));
     HIP_TRY(c, hipMalloc(&c->batch_iof, sizeof(int32_t) * cap * kBatchTables));
@@ -195,7 +202,7 @@ int plan_hops(helios_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_
 // slots of the hash table a de-duplication of up to n_max IDs uses (no more than it needs: a smaller
 // table is cheaper to empty and stays in cache)
 uint32_t dedup_slots(const helios_ctx* c, int64_t n_max) {
-    const uint32_t want = pow2_at_least(2 * n_max);
+    const uint32_t want = batch_slots_for(n_max);
     return want < c->table_slots ? want : c->table_slots;
 }
 
@@ -1052,7 +1059,7 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     // the table (and its lists) that the context's next batch would use: not one that helios_make_blocks may still need
     const uint32_t which = static_cast<uint32_t>(c->batch_seq % kBatchTables);
     const uint32_t slots = list_slots(n_ids, c->table_slots);
-    const bool by_parts = dedup_by_parts(n_ids, slots);
+    const bool by_parts = dedup_by_parts(n_ids);
     rc = by_parts ? HELIOS_OK : clean_for_call(c, static_cast<int>(which));
     if (rc) return rc;
     uint32_t epoch;

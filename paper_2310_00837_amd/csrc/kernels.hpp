@@ -142,12 +142,11 @@ hipError_t launch_dedup_compact_plain(hipStream_t stream, const CompactArgs& a, 
 // Both passes for a list of up to kPartsMax IDs (see dedup.hip), and whether that is the quicker way.  a.len is n, known on the host.  The table may hold anything and
 // is not used but by lists that hash unevenly; what they use of it is left empty.
 constexpr int64_t kPartsMax = 2097152;
-// Measured, us for the call with a table of two slots an ID / of eight / by parts, IDs by a power law (drawn evenly):
-//   4 k 12.8/12.9/17 (13.5/12.5/17)   8 k 15.5/12.8/15.7 (18/13/15.6)   16 k 16-17/13.5/15.7 (23.7/14/16.5)   25 k 16.3/14.7/15.8 (18.5/14.8/16)
-//   32 k 19.5/16.0/16.1 (25.5/16.6/16.2)   41 k 18.0/17.2/16.3 (19.3/16.1/16.7)   50 k 19/18.3/16.6 (20.5/17.5/16.7)   65 k 22/20.5/17 (24.5/19.7/17)
-//   98 k 24.5/-/18.2   262 k 41/-/23   1.1 M 102/-/38   2 M 165/-/57
-// and one ID throughout 8 k 135/145/15.3, 65 k 1050/1050/15.  Above 2 M a bucket would have more IDs than half its table.
-inline bool dedup_by_parts(int64_t n, uint32_t slots) { return n >= (slots >= 8 * n ? 32768 : 8192) && n <= kPartsMax; }
+// Measured, us for the call with a table of eight slots an ID / by parts, IDs by a power law (drawn evenly; one ID throughout):
+//   4 k 12.9/17 (12.5/17)   8 k 12.9/15.7 (13/15.6; 145/15.3)   16 k 13.5/15.7 (14/16.5)   25 k 14.7/15.8 (14.8/16)   32 k 16.0/16.1 (16.6/16.2; 510/16)
+//   41 k 17.2/16.3 (16.1/16.7)   50 k 18.3/16.6 (17.5/16.7)   65 k 20.5/17 (19.7/17; 1050/15); with two slots an ID 98 k 24.5/18.2   262 k 41/23
+//   1.1 M 102/38   2 M 165/57.  Above 2 M a bucket would have more IDs than half its table.
+inline bool dedup_by_parts(int64_t n) { return n >= 32768 && n <= kPartsMax; }
 // The list is cut into tiles, one to a workgroup: 256 of them, so that every CU has one, but of 1024 entries or more; and 512 if 256
 // would have more than 6144 each.
 constexpr uint32_t kMinPartTile = 1024, kMaxPartTile = 6144;
