@@ -101,8 +101,9 @@ int ensure_capacity(helios_ctx* c, int64_t n) {
     free_scratch(c);
     c->blocks_ready = false;
     const int64_t cap = (n + 4095) / 4096 * 4096;
-    // (a stand-alone list of up to 64 k IDs finds eight slots for each, see list_slots; 4 MB)
-    const uint32_t slots = std::max(pow2_at_least(2 * cap), pow2_at_least(8 * std::min<int64_t>(cap, 65536)));
+    // (A stand-alone list of up to 8192 IDs finds eight slots for each, see list_slots.  Tables of more than 512 KB would take 25 us or more
+    // longer to allocate.)
+    const uint32_t slots = std::max(pow2_at_least(2 * cap), pow2_at_least(8 * std::min<int64_t>(cap, 8192)));
     const uint32_t stride = scan_row_stride(cap);
     HIP_TRY(c, hipMalloc(&c->batch_tables, sizeof(unsigned long long) * slots * kBatchTables));
     HIP_TRY(c, hipMalloc(&c->batch_iof, sizeof(int32_t) * cap * kBatchTables));
@@ -1059,7 +1060,7 @@ int helios_dedup(helios_ctx* c, const int32_t* ids, int64_t n_ids, int32_t* uniq
     // the table (and its lists) that the context's next batch would use: not one that helios_make_blocks may still need
     const uint32_t which = static_cast<uint32_t>(c->batch_seq % kBatchTables);
     const uint32_t slots = list_slots(n_ids, c->table_slots);
-    const bool by_parts = dedup_by_parts(n_ids);
+    const bool by_parts = dedup_by_parts(n_ids, slots);
     rc = by_parts ? HELIOS_OK : clean_for_call(c, static_cast<int>(which));
     if (rc) return rc;
     uint32_t epoch;

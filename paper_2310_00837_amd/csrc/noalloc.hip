@@ -146,7 +146,7 @@ extern "C" int helios_dedup_noalloc(helios_ctx* c, const int32_t* ids, int64_t n
     a.inverse = inverse;
     a.scan = scan;
     a.err = c->err;
-    const bool by_parts = dedup_by_parts(n_ids);
+    const bool by_parts = dedup_by_parts(n_ids, slots);
     if (by_parts) {
         const PartScratch parts{reinterpret_cast<int32_t*>(base + kOffPartId), reinterpret_cast<uint16_t*>(base + kOffPartPos),
                                 reinterpret_cast<uint32_t*>(base + kOffPartFirst), reinterpret_cast<uint16_t*>(base + kOffPartLocal),

@@ -219,9 +219,9 @@ def _hash(x):
 
 
 @pytest.mark.parametrize("kind", ["one", "distinct", "one bucket", "one bucket and class", "bad", "few repeats far apart"])
-@pytest.mark.parametrize("n_ids", [32_767, 32_768, 98_303, 98_304, 98_305, 262_145, 524_289, 1_000_003, 1_048_577, 1_572_864, 1_572_865, 2_097_152, 2_097_153])
+@pytest.mark.parametrize("n_ids", [19_999, 20_000, 32_767, 32_768, 98_303, 98_304, 98_305, 262_145, 524_289, 1_000_003, 1_048_577, 1_572_864, 1_572_865, 2_097_152, 2_097_153])
 def test_dedup_of_long_lists_by_parts(h, helios, kind, n_ids):
-    """Long lists (32 768 to 2 097 152 IDs are taken apart by hash) whose parts are as uneven as can be, against numpy."""
+    """Long lists (32 768 to 2 097 152 IDs are taken apart by hash, from 20 000 on if the table is small) whose parts are as uneven as can be, against numpy."""
     print("by parts", kind, n_ids, flush=True)
     rng = np.random.default_rng(n_ids)
     n = 100_000_000
