@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kBlock) void dedup_insert_long_kernel(const int32_t
 // a bucket gets one entry per tile.
 // What bounds it is a workgroup's chain of steps, LDS searches above all, so the tiles are as small as 256 workgroups allow: 1.1 M IDs
 // 253 tiles of 4352 38.1 us (split 13.5, buckets 12, compact 12), 269 of 4096, so that 13 CUs have two, 41.0, 506 of 2176 43.8;
-// 98 k 256 tiles of 1024 18.2, of 512 20.5, 24 of 4096 22.2.  Each number of rounds has an instance of its own: with guards in one for
+// 98 k 96 tiles of 1024 18.2, 24 of 4096 22.2.  Each number of rounds has an instance of its own: with guards in one for
 // all 1.1 M took 40.2, with six rounds always 38.7.  256 buckets of 1024 threads with eight entries each, 64-bit words and
 // a second search for the answers: buckets 44 us at 1.1 M; linear probing and 512 threads in the split: 15.
 // When it pays against the table: dedup_by_parts.
