@@ -430,3 +430,42 @@ def test_dedup_by_parts_in_place_cut_off_and_with_bad_ids(h, helios, n_ids, noal
             fits = min(cap, values.size)
             assert np.array_equal(uniq[:fits].cpu().numpy(), values[order][:fits])
             assert inv is None or np.array_equal(inv.cpu().numpy(), want)
+
+
+def test_launches_that_wait_on_several_streams(helios, oracle):
+    """Hotness orders of all passes, lists by parts and long seed lists of four contexts in flight on four streams: launches whose
+    workgroups wait for others of theirs, side by side."""
+    rng = np.random.default_rng(31)
+    n, m, n_seeds, fan = 1_200_000, 700_001, 9_001, [25]
+    off, idx = _graph(rng, n, 5)
+    off_d, idx_d = torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda()
+    units = []
+    for k in range(4):
+        h = helios.Helios(0, stream=torch.cuda.Stream())
+        h.csr_load(off_d, idx_d)
+        h.reserve(m)
+        counts = rng.integers(0, 1 << 31, n).astype(np.int32)
+        ids = rng.integers(0, n, m).astype(np.int32)
+        seeds = rng.integers(0, n, n_seeds).astype(np.int32)
+        units.append(dict(h=h, counts=counts, ids=ids, seeds=seeds, counts_d=torch.from_numpy(counts).cuda(), ids_d=torch.from_numpy(ids).cuda(),
+                          seeds_d=torch.from_numpy(seeds).cuda(), order=torch.empty(n, dtype=torch.int32, device="cuda"),
+                          uniq=torch.empty(m, dtype=torch.int32, device="cuda"), inv=torch.empty(m, dtype=torch.int32, device="cuda"),
+                          nu=torch.zeros(1, dtype=torch.int64).pin_memory(), hops=helios.alloc_hops(n_seeds, fan, "cuda"),
+                          sizes=torch.zeros(2, dtype=torch.int64).pin_memory()))
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for u in units:
+            u["h"].hotness_order(u["counts_d"], u["order"])
+            u["h"].dedup(u["ids_d"], u["uniq"], u["inv"], u["nu"])
+            u["h"].sample(u["seeds_d"], fan, 5, u["hops"], u["sizes"])
+    for u in units:
+        u["h"].sync()
+    for u in units:
+        assert np.array_equal(u["order"].cpu().numpy(), oracle.hotness_order(u["counts"]))
+        wu, wi = oracle.dedup(n, u["ids"])
+        assert int(u["nu"][0]) == wu.size and np.array_equal(u["uniq"][:wu.size].cpu().numpy(), wu)
+        assert np.array_equal(u["inv"].cpu().numpy(), wi)
+        indptr = np.concatenate([[0], np.cumsum(np.minimum(np.diff(off)[u["seeds"]], fan[0]))])
+        assert u["sizes"].tolist() == [n_seeds, int(indptr[-1])]
+        assert np.array_equal(u["hops"][0].indptr.cpu().numpy(), indptr)
+        u["h"].close()
