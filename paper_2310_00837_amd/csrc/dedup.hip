@@ -130,7 +130,7 @@ static_assert(kPartsMax == kMaxPartTiles * 4096 && kMaxPartTiles <= kBucketBlock
 static_assert(kParts <= kSplitBlock && kPartTile / kMergeBlock * kMergeWaves <= 2 * kWave, "a thread per bucket; two steps scan a tile");
 static_assert(kSplitBlock == kMergeBlock && kPartTile == 6 * kMergeBlock && kPartTile < kPartSlots, "one to six rounds of all threads; the split's table never fills");
 
-struct PartTable {
+struct alignas(16) PartTable {                         // (part_clear stores 16 bytes at a time)
     uint32_t key[kPartSlots], low[kPartSlots];         // ~0: empty (IDs are below 2^31)
 };
 __device__ __forceinline__ void part_clear(PartTable& t, uint32_t slots, uint32_t threads) {

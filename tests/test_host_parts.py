@@ -18,6 +18,8 @@ PROGRAM = r"""
 #include <unordered_map>
 using namespace helios;
 
+static_assert(alignof(PartTable) >= 16, "it is cleared 16 bytes at a time");
+
 // n elements that end where a page that cannot be touched begins, with 32 GiB of such pages on either side
 template <class T>
 T* guarded(size_t n) {
