@@ -372,8 +372,8 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
 }
 
 // The compaction of a list that came by parts: like compact_tiles, but the first positions come from the split tile, and it writes the
-// whole inverse map.  Which of a tile's entries are first occurrences goes out, 16 to a word with how many of the tile come before them,
-// before the tile's total does.  A workgroup waits for the totals of all tiles before its own and sums them up, which gives it the place of
+// whole inverse map.  Which of a tile's entries are first occurrences goes out, 16 to a word with how many of the tile come before them (a
+// tile's words begin a line, see PartShape), before the tile's total does.  A workgroup waits for the totals of all tiles before its own and sums them up, which gives it the place of
 // its own first occurrences and of everybody's before; a repeat then finds its index as what the tiles before its first occurrence's
 // have, what the word says, and the bits below.  With marks in the inverse map and a launch more that
 // looks them up, the totals chained from tile to tile and 512 threads: 400 k IDs 30.7 us, now 27.5, 1.1 M 43.2 and 41.0.  (The sum up to a
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(kMergeBlock) void dedup_compact_parts_kernel(Compac
         before[k] = (k < kFirstItems ? lane_value(inc, k * kMergeWaves + wave) : in_first + lane_value(more, (k - kFirstItems) * kMergeWaves + wave)) - total[k];
         const uint32_t mask = static_cast<uint32_t>(firsts[k] >> (lane % 4 * 16)), p = k * kMergeBlock + wave * kWave + lane * 16;
         const uint32_t below = static_cast<uint32_t>(__popcll(firsts[k] & ((1ull << (lane % 4 * 16)) - 1)));
-        if (a.inverse && lane < 4 && p < entries) __hip_atomic_store(words + (base + p) / 16, first_word(before[k] + below, mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (a.inverse && lane < 4 && p < entries) __hip_atomic_store(words + tile * shape.row + p / 16, first_word(before[k] + below, mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // (they go past the L2: now they are there for all)
     __syncthreads();
@@ -477,10 +477,12 @@ __global__ __launch_bounds__(kMergeBlock) void dedup_compact_parts_kernel(Compac
         if (p >= entries) continue;
         const uint32_t at = excl + before[k] + local[k], of = first_of[k];
         if (a.inverse && of < j) {
-            // (complete, and the same for the rest of the launch: it may come from the L2)
-            const uint32_t word = __hip_atomic_load(words + of / 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             uint32_t in = __umulhi(of, shape.per_tile);         // the tile, or one more
             if (in * shape.tile > of) --in;
+            // (A tile's words are on lines of their own, and the tile is this one or one whose total has been waited for: the whole line
+            // is complete, and the same for the rest of the launch, so it may come from the L2.  A line with words of a later tile could be
+            // fetched before they are there, and stay so for whoever waits for that tile.)
+            const uint32_t word = __hip_atomic_load(words + in * shape.row + (of - in * shape.tile) / 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             a.inverse[j] = static_cast<int32_t>(s_upto[in] + (word >> 16) + static_cast<uint32_t>(__popc(word & ((1u << (of % 16)) - 1))));
         } else if (a.inverse) {
             a.inverse[j] = first[k] ? static_cast<int32_t>(at) : -1;
@@ -534,6 +536,7 @@ hipError_t launch_dedup_insert(hipStream_t stream, const int32_t* ids, Count n, 
 
 hipError_t launch_dedup_by_parts(hipStream_t stream, const CompactArgs& a, int64_t n, int64_t n_nodes, const PartScratch& s) {
     if (n < 1 || n > kPartsMax || !a.s.table || a.s.n_slots < 2 * n) return hipErrorInvalidValue;
+    if (reinterpret_cast<uintptr_t>(a.s.index_of_first) % (sizeof(uint32_t) * kLineWords) != 0) return hipErrorInvalidValue;
     const PartShape shape(n);
 #define HELIOS_CALL_(ITEMS)                                                                                                          \
     do {                                                                                                                             \

@@ -150,10 +150,11 @@ constexpr int64_t kPartsMax = 2097152;
 inline bool dedup_by_parts(int64_t n, uint32_t slots) { return n >= (slots >= 4 * n ? 32768 : 20000) && n <= kPartsMax; }
 // The list is cut into tiles, one to a workgroup: 256 of them, so that every CU has one, but of 1024 entries or more; and 512 if 256
 // would have more than 6144 each.
-constexpr uint32_t kMinPartTile = 1024, kMaxPartTile = 6144;
+constexpr uint32_t kMinPartTile = 1024, kMaxPartTile = 6144, kLineWords = 32;
 struct PartShape {
     uint32_t n, tile, n_tiles;   // entries, entries of a tile (a multiple of 64), tiles
     uint32_t per_tile;           // 2^32 / tile, rounded up
+    uint32_t row;                // words from one tile's flags to the next one's (dedup_compact_parts_kernel): whole lines of 128 bytes
     uint32_t split_slots, bucket_slots;      // of the tables in LDS: 8192, or twice the entries of a tile and four times those of a bucket
     explicit PartShape(int64_t ids) : n(static_cast<uint32_t>(ids)) {
         const uint32_t most = ids <= 256 * kMaxPartTile ? 256 : 512;
@@ -161,6 +162,7 @@ struct PartShape {
         if (tile < kMinPartTile) tile = kMinPartTile;
         n_tiles = (n + tile - 1) / tile;
         per_tile = 0xffffffffu / tile + 1;
+        row = (tile / 16 + kLineWords - 1) / kLineWords * kLineWords;      // (no more words in all than the list has entries)
         for (split_slots = 1024; split_slots < 8192 && split_slots < 2 * tile;) split_slots *= 2;
         for (bucket_slots = 1024; bucket_slots < 8192 && bucket_slots < n / 128;) bucket_slots *= 2;
     }

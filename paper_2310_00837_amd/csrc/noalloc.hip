@@ -49,8 +49,8 @@ constexpr size_t kOffPartPos = kOffPartFirst + sizeof(uint32_t) * kMaxIds;
 constexpr size_t kOffPartLocal = kOffPartPos + sizeof(uint16_t) * kMaxIds;
 constexpr size_t kScratchBytes = kOffPartLocal + sizeof(uint16_t) * kMaxIds;
 constexpr size_t kOffPartStarts = kOffIndexOfFirst + sizeof(uint32_t) * (kMaxIds / 16);
-static_assert(kMaxIds <= kPartsMax && kMaxIds <= 256 * 4096 && kOffPartStarts + static_cast<size_t>(split_starts_bytes(256)) <= kOffStatus,
-              "the longest list can be taken apart, into 256 tiles at most");
+static_assert(kMaxIds <= kPartsMax && kMaxIds <= 256 * kMinPartTile && kMinPartTile / 16 % kLineWords == 0 && kOffPartStarts + static_cast<size_t>(split_starts_bytes(256)) <= kOffStatus,
+              "the longest list can be taken apart, into 256 tiles at most, whose words leave no room between them");
 static_assert(kScratchBytes < (9u << 20) + (256u << 10), "include/helios.h says how large the array is");
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];

@@ -2,6 +2,8 @@
 // run without a GPU, on whatever its scratch memory holds.  The workgroups of a launch run one after the other; the threads of a
 // workgroup are coroutines that run until they meet a barrier or an operation of the whole wave (a ballot, a DPP move), where they
 // wait for the others of the workgroup or the wave.  __shared__ variables are static ones.  Only what the kernels under test use.
+// Of one range of memory (on_host::cached) atomic loads of a workgroup's scope see what a cache may hold: workgroup b belongs to cache b
+// modulo 8, which keeps a line of 128 bytes as it was when it was first loaded in the launch, until the same cache's workgroups store there.
 #pragma once
 #include <setjmp.h>
 #include <stdint.h>
@@ -9,7 +11,10 @@
 #include <stdlib.h>
 #include <ucontext.h>
 
+#include <string.h>
+
 #include <functional>
+#include <unordered_map>
 #include <vector>
 
 #define __device__
@@ -59,6 +64,15 @@ inline std::vector<Meeting> waves;
 inline jmp_buf scheduler;
 inline unsigned now;
 inline const std::function<void()>* body;
+
+constexpr unsigned kCaches = 8;
+constexpr uintptr_t kLine = 128;
+struct Line {
+    char bytes[kLine];
+    bool there = false;
+};
+inline std::unordered_map<const char*, Line> caches[kCaches];
+inline struct { const char *begin = nullptr, *end = nullptr; } cached;
 
 inline void give_way() {
     if (_setjmp(threads[now].at) == 0) _longjmp(scheduler, 1);
@@ -121,6 +135,7 @@ inline void run_workgroup(unsigned block, unsigned grid, unsigned size, const st
 template <class F>
 void launch(dim3 grid, dim3 block, const F& f) {
     const std::function<void()> g = f;
+    for (auto& c : caches) c.clear();
     for (unsigned b = 0; b < grid.x; ++b) run_workgroup(b, grid.x, block.x, g);
 }
 }  // namespace on_host
@@ -185,10 +200,32 @@ template <class T>
 T min(T a, T b) { return a < b ? a : b; }
 inline uint32_t __umulhi(uint32_t a, uint32_t b) { return static_cast<uint32_t>((static_cast<uint64_t>(a) * b) >> 32); }
 #define __HIP_MEMORY_SCOPE_WORKGROUP 0
-#define __HIP_MEMORY_SCOPE_AGENT 0
-#define __HIP_MEMORY_SCOPE_SYSTEM 0
-#define __hip_atomic_load(p, order, scope) (*(p))
-#define __hip_atomic_store(p, v, order, scope) (*(p) = (v))
+#define __HIP_MEMORY_SCOPE_AGENT 1
+#define __HIP_MEMORY_SCOPE_SYSTEM 2
+#define __hip_atomic_load(p, order, scope) on_host::load(p, scope)
+#define __hip_atomic_store(p, v, order, scope) on_host::store(p, v)
+namespace on_host {
+template <class T>
+T load(const T* p, int scope) {
+    const char* at = reinterpret_cast<const char*>(p);
+    if (scope != __HIP_MEMORY_SCOPE_WORKGROUP || at < cached.begin || at >= cached.end) return *p;
+    const uintptr_t offset = reinterpret_cast<uintptr_t>(p) % kLine;
+    Line& line = caches[blockIdx.x % kCaches].try_emplace(at - offset).first->second;
+    if (!line.there) memcpy(line.bytes, at - offset, kLine);
+    line.there = true;
+    T v;
+    memcpy(&v, line.bytes + offset, sizeof(T));
+    return v;
+}
+template <class T, class V>
+void store(T* p, V v) {
+    *p = v;
+    const char* at = reinterpret_cast<const char*>(p);
+    const uintptr_t offset = reinterpret_cast<uintptr_t>(p) % kLine;
+    const auto line = caches[blockIdx.x % kCaches].find(at - offset);
+    if (line != caches[blockIdx.x % kCaches].end()) memcpy(line->second.bytes + offset, p, sizeof(T));
+}
+}  // namespace on_host
 template <class T>
 T atomicAdd(T* p, T v) { const T was = *p; *p = was + v; return was; }
 template <class T>

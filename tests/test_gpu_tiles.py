@@ -432,6 +432,38 @@ def test_dedup_by_parts_in_place_cut_off_and_with_bad_ids(h, helios, n_ids, noal
             assert inv is None or np.array_equal(inv.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("n_ids", [263_000, 1_100_001, 1_600_001])
+def test_dedup_by_parts_with_repeats_at_the_ends_of_tiles(h, n_ids):
+    """Tiles whose flags fill no whole number of lines: repeats of first occurrences at the end of the same tile, and of some at the
+    beginnings of all tiles before, in another list each time (what a call leaves in the scratch is wrong for the next)."""
+    rng = np.random.default_rng(n_ids)
+    most = 256 if n_ids <= 256 * 6144 else 512
+    tile = -(-n_ids // (most * 64)) * 64
+    assert tile > 1024 and tile % 512 != 0
+    h.csr_load(torch.zeros(4 * n_ids + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"))
+    at = np.arange(n_ids)
+    inside, begin = at % tile, at - at % tile
+    near = np.nonzero(inside >= tile - 8)[0]
+    far = np.nonzero((inside >= tile // 2) & (inside < tile // 2 + 400) & (begin > 0))[0]
+    for k in range(6):
+        ids = rng.permutation(4 * n_ids)[:n_ids]
+        ids[near] = ids[near - rng.integers(8, 300, near.size)]
+        ids[far] = ids[rng.integers(0, begin[far] // tile) * tile + rng.integers(0, 400, far.size)]
+        print("ends of tiles", n_ids, k, flush=True)
+        values, first, back = np.unique(ids, return_index=True, return_inverse=True)
+        order = np.argsort(first)
+        place = np.empty_like(order)
+        place[order] = np.arange(order.size)
+        t = torch.from_numpy(ids.astype(np.int32)).cuda()
+        uniq, inv, nu = torch.empty_like(t), torch.empty_like(t), torch.zeros(1, dtype=torch.int64).pin_memory()
+        torch.cuda.synchronize()
+        h.dedup(t, uniq, inv, nu)
+        h.sync()
+        assert int(nu[0]) == values.size
+        assert np.array_equal(uniq[:values.size].cpu().numpy(), values[order])
+        assert np.array_equal(inv.cpu().numpy(), place[back])
+
+
 def test_launches_that_wait_on_several_streams(helios, oracle):
     """Hotness orders of all passes, lists by parts and long seed lists of four contexts in flight on four streams: launches whose
     workgroups wait for others of theirs, side by side."""

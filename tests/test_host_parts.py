@@ -46,7 +46,10 @@ struct Call {
         ids = guarded<int32_t>(n);
         unique = in_place ? ids : guarded<int32_t>(cap);
         inverse = guarded<int32_t>(n);
-        iof = guarded<int32_t>(n);
+        const int64_t words = (n + 31) / 32 * 32;          // (whole lines, so that it begins one)
+        iof = guarded<int32_t>(words);
+        on_host::cached.begin = reinterpret_cast<const char*>(iof);
+        on_host::cached.end = reinterpret_cast<const char*>(iof + words);
         s = PartScratch{guarded<int32_t>(n), guarded<uint16_t>(n), guarded<uint32_t>(n), guarded<uint16_t>(n),
                         guarded<uint16_t>(split_starts_bytes(tiles) / 2), nullptr, 0};
         for (n_slots = 1024; n_slots < 2 * n;) n_slots *= 2;
@@ -141,6 +144,19 @@ int main(int argc, char** argv) {
         for (int j = 0; j < 3000; ++j) v.push_back(static_cast<int32_t>(next_random() >> 1));
         for (size_t j = v.size() - 1; j > 0; --j) std::swap(v[j], v[next_random() % (j + 1)]);
         results(v, v.size(), false);
+    } else if (what == "lines") {                        // tiles that are no whole lines of flags; repeats of first occurrences of the same tile and of all before
+        for (int64_t n : {263000, 300000}) {
+            const uint32_t tile = PartShape(n).tile;
+            check(tile > kMinPartTile && tile % 512 != 0, "such tiles");
+            std::vector<int32_t> v(n);
+            for (int64_t j = 0; j < n; ++j) {
+                const int64_t in = j % tile, begin = j - in;
+                v[j] = static_cast<int32_t>(j);
+                if (in >= tile - 4) v[j] = v[j - 40];                                                   // their first occurrences in the tile's last words
+                else if (in >= tile / 2 && in < tile / 2 + 100 && j >= tile) v[j] = v[next_random() % (begin / tile) * tile + next_random() % 60];      // in a tile's first words
+            }
+            results(v, n, false);
+        }
     } else if (what == "pieces") {                       // the words of two calls side by side, as their waves write them, and any words
         const int n = 32 * kPartTile;
         std::vector<int32_t> one(n, 77), distinct(n);
@@ -199,7 +215,7 @@ def program(tmp_path_factory):
     return str(d / "main")
 
 
-@pytest.mark.parametrize("what", ["results", "uneven", "pieces", "tickets", "foreign"])
+@pytest.mark.parametrize("what", ["results", "uneven", "lines", "pieces", "tickets", "foreign"])
 def test_list_by_parts(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", (r.returncode, r.stdout)
