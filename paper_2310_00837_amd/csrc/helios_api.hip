@@ -347,6 +347,12 @@ int copy_tiers_split(helios_ctx* c, int64_t n_max, void* out, bool hbm_too) {
     return HELIOS_OK;
 }
 
+// whether hop 0's samples may be written over its seeds
+bool seeds_under_samples(const int32_t* seeds, int64_t n_seeds, const helios_hop_out& hop, int64_t flat_max) {
+    const int64_t entry = static_cast<int64_t>(sizeof(int32_t));
+    return overlap(seeds, entry * n_seeds, hop.flat, entry * flat_max);
+}
+
 // The launches of the pipeline go out at once, or, while a gang is being recorded, onto the member's list.
 int emit_sample(helios_ctx* c, const SampleJob& j) {
     if (c->defer) {
@@ -443,8 +449,11 @@ int run_pipeline(helios_ctx* c, const int32_t* seeds, int64_t n_seeds, const int
     const bool fold = n_seeds <= kFoldMaxSeeds;
     if (c->defer && (!fold || !b || c->split_copies || c->missq || c->timing > 1))
         return fail(c, HELIOS_EINTERNAL, "this call cannot be part of a gang");       // (refused earlier, with the reason)
+    // (Counted and sampled in one launch, the first seeds' samples are there before the last seeds have been read.  A recording's seeds
+    // are not known yet: see helios_plan_launch.)
     unsigned counted_waves = 0;
-    const unsigned counted_blocks = fold ? 0u : sample_counted_blocks(fanouts[0], n_seeds, c->scan_stride, &counted_waves);
+    const unsigned counted_blocks = fold || seeds_under_samples(seeds, n_seeds, hops[0], p.flat_max[0])
+                                        ? 0u : sample_counted_blocks(fanouts[0], n_seeds, c->scan_stride, &counted_waves);
     ScanState count_scan{};
     if (!fold) {
         uint32_t epoch;
@@ -797,6 +806,12 @@ int plan_prelaunch(helios_plan* pl, const int32_t* seeds, uint64_t rng_seed, uin
     if (!pl->clear_slots) c->batch_listed[next] = false;
     rc = clean_unlisted(c, next);
     if (rc) return rc;
+    // The recording may count and sample hop 0 in one launch.  Seeds that its samples would be written over are read from where the
+    // batch puts them anyway.
+    if (pl->n_seeds > kFoldMaxSeeds && seeds_under_samples(seeds, pl->n_seeds, pl->hops[0], pl->flat_max[0])) {
+        HIP_TRY(c, hipMemcpyAsync(pl->hops[0].frontier, seeds, sizeof(int32_t) * static_cast<size_t>(pl->n_seeds), hipMemcpyDefault, c->stream));
+        seeds = pl->hops[0].frontier;
+    }
     BatchVars* slot = c->vars_ring + (c->vars_next % kVarsRing);
     slot->rng_seed = rng_seed;
     slot->seeds = seeds;

@@ -149,6 +149,56 @@ def test_recorded_batches_of_long_seed_lists(helios, oracle, n_seeds, fanouts):
         assert_same(got[k], want)
 
 
+@pytest.mark.parametrize("at", [0, 1001])
+@pytest.mark.parametrize("n_seeds,fan", [(9_000, 25), (16_384, 8), (3_000, 65)])
+def test_seeds_in_the_memory_of_the_first_samples(helios, oracle, n_seeds, fan, at):
+    """More seeds than the sampling pass counts by itself, lying where hop 0's samples go: sampled alone, prepared and recorded."""
+    rng = np.random.default_rng(n_seeds + at)
+    n, n_hbm, n_host, fanouts = 50_000, 20_000, 20_000, [fan, 2]
+    off = np.concatenate([[0], np.cumsum(rng.integers(fan, fan + 20, n))]).astype(np.int64)
+    idx = rng.integers(0, n, off[-1]).astype(np.int32)
+    feats = torch.from_numpy(rng.integers(0, 1 << 30, (n, 4)).astype(np.int32))
+    order = torch.from_numpy(rng.permutation(n).astype(np.int32))
+    by_rank = to_bytes(feats)[order.numpy()]
+    tabs = [np.ascontiguousarray(x) for x in (by_rank[:n_hbm], by_rank[n_hbm:n_hbm + n_host], by_rank[n_hbm + n_host:])]
+    h = helios.Helios(0, stream=torch.cuda.Stream())
+    h.csr_load(torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda())
+    cache = GpuCache(h, feats, order, n_hbm, n_host)  # noqa: F841  (keeps the tier tables alive)
+    hops = helios.alloc_hops(n_seeds, fanouts, "cuda")
+    cap = n_seeds + sum(hb.flat.numel() for hb in hops)
+    h.reserve(cap)
+    sizes, nu, stats = torch.zeros(4, dtype=torch.int64).pin_memory(), torch.zeros(1, dtype=torch.int64).pin_memory(), torch.zeros(4, dtype=torch.int64).pin_memory()
+    uniq, inv, mp, mi, ms = (torch.zeros(cap, dtype=torch.int32, device="cuda") for _ in range(5))
+    out = torch.zeros((cap, 16), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    plan = h.plan_create(n_seeds, fanouts, hops, sizes, uniq, inv, nu, out, mp, mi, ms, stats)
+    rank = oracle.rank_build(order.numpy())
+    seeds_at = hops[0].flat[at:at + n_seeds]
+    for k, call in enumerate(("sample", "prepare", "plan", "plan", "sample", "prepare")):
+        seeds = rng.integers(0, n, n_seeds).astype(np.int32)
+        want = oracle_path(oracle, off, idx, seeds, fanouts, 90 + k, rank, n_hbm, n_host, *tabs, 16)
+        seeds_at.copy_(torch.from_numpy(seeds))
+        torch.cuda.synchronize()
+        print("seeds under samples", call, n_seeds, at, flush=True)
+        if call == "sample":
+            h.sample(seeds_at, fanouts, 90 + k, hops, sizes)
+        elif call == "prepare":
+            h.prepare_batch(seeds_at, fanouts, 90 + k, hops, sizes, uniq, inv, nu, out, mp, mi, ms, stats)
+        else:
+            plan.launch(seeds_at, 90 + k)
+            plan.wait()
+        h.sync()
+        for hop, (frontier, indptr, flat) in enumerate(want["hops"]):
+            assert sizes[2 * hop:2 * hop + 2].tolist() == [frontier.size, flat.size]
+            assert np.array_equal(hops[hop].frontier[:frontier.size].cpu().numpy(), frontier)
+            assert np.array_equal(hops[hop].indptr[:frontier.size + 1].cpu().numpy(), indptr)
+            assert np.array_equal(hops[hop].flat[:flat.size].cpu().numpy(), flat)
+        if call != "sample":
+            assert int(nu[0]) == want["unique"].size and np.array_equal(inv[:want["inverse"].size].cpu().numpy(), want["inverse"])
+    plan.destroy()
+    h.close()
+
+
 @pytest.mark.parametrize("params", [dict(split=1), dict(split=0, hbm_blocks=7, host_blocks=3), dict(split=1, hbm_blocks=8192, host_blocks=1), dict(split=0, hbm_blocks=1, host_blocks=300)])
 def test_launch_parameters_do_not_change_results(helios, oracle, params):
     """The tuning parameters (tier copies as kernels of their own or as roles of the batch's other launches, grid
