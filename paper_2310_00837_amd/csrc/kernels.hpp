@@ -125,12 +125,16 @@ hipError_t launch_clock_publish(hipStream_t stream, const uint64_t* clock, const
                                 uint64_t* host_out);
 
 // ---- dedup.hip (the stand-alone de-duplication)
+constexpr int64_t kPartsMax = 2097152;
 // Slots of the table for a list of n IDs, if there are `most`: eight for each, so that a wave, which waits for the longest of its 64
 // searches, rarely looks at more than two (each a round trip to memory).  Two or more slots / eight, us: 8 192 IDs 15.7/13.1, 16 384
-// drawn evenly 23.4/14.4, 41 237 17.9/17.4 (19.7/16.2).  Emptying them costs less: 4 MB 0.7 us.
+// drawn evenly 23.4/14.4, 41 237 17.9/17.4 (19.7/16.2).  Emptying them costs less: 4 MB 0.7 us.  Lists that are too long to be taken apart
+// (below) are bound by the memory's atomics and by the emptying instead, so two for each are enough: 2.2 M IDs drawn evenly 229 us with eight,
+// 188 with two, 3 M 291 and 254.
 inline uint32_t list_slots(int64_t n, uint32_t most) {
+    const int64_t want = n <= kPartsMax ? 8 * n : 2 * n;
     uint32_t slots = 1024;
-    while (slots < most && static_cast<int64_t>(slots) < 8 * n) slots <<= 1;
+    while (slots < most && static_cast<int64_t>(slots) < want) slots <<= 1;
     return slots;
 }
 // First pass as a kernel of its own (for IDs that no kernel of this library produced): inserts ids[0, n)
@@ -141,7 +145,6 @@ hipError_t launch_dedup_insert(hipStream_t stream, const int32_t* ids, Count n, 
 hipError_t launch_dedup_compact_plain(hipStream_t stream, const CompactArgs& a, int64_t n_max);
 // Both passes for a list of up to kPartsMax IDs (see dedup.hip), and whether that is the quicker way.  a.len is n, known on the host.  The table may hold anything and
 // is not used but by lists that hash unevenly; what they use of it is left empty.
-constexpr int64_t kPartsMax = 2097152;
 // Measured, us for the call with a table of eight slots an ID / by parts, IDs by a power law (drawn evenly; one ID throughout):
 //   4 k 12.9/17 (12.5/17)   8 k 12.9/15.7 (13/15.6; 145/15.3)   16 k 13.5/15.7 (14/16.5)   25 k 14.7/15.8 (14.8/16)   32 k 16.0/16.1 (16.6/16.2; 510/16)
 //   41 k 17.2/16.3 (16.1/16.7)   50 k 18.3/16.6 (17.5/16.7)   65 k 20.5/17 (19.7/17; 1050/15); with two slots an ID 98 k 24.5/18.2   262 k 41/23

@@ -144,6 +144,15 @@ int main(int argc, char** argv) {
         for (int j = 0; j < 3000; ++j) v.push_back(static_cast<int32_t>(next_random() >> 1));
         for (size_t j = v.size() - 1; j > 0; --j) std::swap(v[j], v[next_random() % (j + 1)]);
         results(v, v.size(), false);
+    } else if (what == "slots") {                        // of a list's table: two or more for each ID, eight up to the longest list by parts, never more than there are
+        for (int64_t n : {int64_t{1}, int64_t{1000}, int64_t{8192}, int64_t{19999}, kPartsMax, kPartsMax + 1, int64_t{3000000}, int64_t{16000000}})
+            for (uint32_t most = 1024; most >= 1024 && most <= 1u << 28; most *= 2) {
+                if (most < 2 * n) continue;
+                const uint32_t slots = list_slots(n, most);
+                check(slots <= most && slots >= 2 * n && slots >= 1024 && (slots & (slots - 1)) == 0, "a table for the list");
+                check(slots <= std::max<int64_t>(1024, (n <= kPartsMax ? 16 : 4) * n), "no larger than needed");
+                check(n > kPartsMax || slots >= 8 * n || slots == most, "eight for each");
+            }
     } else if (what == "lines") {                        // tiles that are no whole lines of flags; repeats of first occurrences of the same tile and of all before
         for (int64_t n : {263000, 300000}) {
             const uint32_t tile = PartShape(n).tile;
@@ -215,7 +224,7 @@ def program(tmp_path_factory):
     return str(d / "main")
 
 
-@pytest.mark.parametrize("what", ["results", "uneven", "lines", "pieces", "tickets", "foreign"])
+@pytest.mark.parametrize("what", ["results", "uneven", "slots", "lines", "pieces", "tickets", "foreign"])
 def test_list_by_parts(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", (r.returncode, r.stdout)
