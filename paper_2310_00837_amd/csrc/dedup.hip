@@ -133,10 +133,10 @@ static_assert(kSplitBlock == kMergeBlock && kPartTile == 6 * kMergeBlock && kPar
 struct alignas(16) PartTable {                         // (part_clear stores 16 bytes at a time)
     uint32_t key[kPartSlots], low[kPartSlots];         // ~0: empty (IDs are below 2^31)
 };
-__device__ __forceinline__ void part_clear(PartTable& t, uint32_t slots, uint32_t threads) {
+__device__ __forceinline__ void part_clear(PartTable& t, uint32_t from, uint32_t slots, uint32_t threads) {
     typedef uint32_t words4 __attribute__((ext_vector_type(4)));
     words4 *keys = reinterpret_cast<words4*>(t.key), *lows = reinterpret_cast<words4*>(t.low);
-    for (uint32_t q = threadIdx.x; q < slots / 4; q += threads) keys[q] = lows[q] = words4{~0u, ~0u, ~0u, ~0u};
+    for (uint32_t q = from / 4 + threadIdx.x; q < slots / 4; q += threads) keys[q] = lows[q] = words4{~0u, ~0u, ~0u, ~0u};
 }
 // the whole hash: the highest bits are the bucket, the next the place in the table, the lowest the step
 __device__ __forceinline__ uint32_t part_hash(uint32_t id) { return hash_id(id, 0xffffffffu); }
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kSplitBlock) void dedup_split_kernel(const int32_t*
     for (int k = 0; k < ITEMS; ++k) id[k] = ids[base + min(k * kSplitBlock + threadIdx.x, entries - 1)];
     if (s.clear && tile == 0)
         for (uint32_t w = threadIdx.x; w < s.n_clear; w += kSplitBlock) s.clear[w] = 0ull;
-    part_clear(m.table, shape.split_slots, kSplitBlock);
+    part_clear(m.table, 0, shape.split_slots, kSplitBlock);
     if (threadIdx.x < kParts) s_count[threadIdx.x] = 0;
     __syncthreads();
 #pragma unroll
@@ -236,7 +236,8 @@ __global__ __launch_bounds__(kSplitBlock) void dedup_split_kernel(const int32_t*
 // uses: two slots for each of its entries, behind two for each entry of the buckets before it.  The stretch is emptied first, and
 // left empty.  Only lists made against the hash get there (of IDs in strides, in blocks and in a row a bucket gets at most 1.25
 // times its share of lists this long): 1 M IDs of one bucket, 78 k of them distinct, take 3.4 ms, all of it one workgroup's, where the
-// inserts into a table for all take 0.1; with one LDS table after the other, class by class of the hash, it was 606.
+// inserts into a table for all take 0.1; with one LDS table after the other, class by class of the hash, it was 606.  32 k of one bucket
+// take 410 us, 98 k 768, 32 k of four buckets 178, 98 k of 14 buckets 47 (by the table altogether 21, 23, 21 and 26).
 __device__ __forceinline__ uint32_t stretch_slot(uint32_t id, uint32_t size) { return __umulhi(part_hash(~id), size); }
 
 __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch s, PartShape shape, unsigned long long* table_in_memory,
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
     const uint32_t inc = dpp_inclusive_scan(len);
     if (t < kMaxPartTiles && lane_id() == kWave - 1) s_wave[wave_id()] = inc;
     if (t == 0) s_full = s_lower = 0;
-    part_clear(table, shape.bucket_slots, kBucketBlock);
+    part_clear(table, 0, shape.bucket_slots, kBucketBlock);
     __syncthreads();
     uint32_t at = inc - len, total = 0;
 #pragma unroll
@@ -272,6 +273,11 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
         s_before[t] = t < n_tiles ? at : ~0u;
         s_from[t] = t * shape.tile + from;
     }
+    // A bucket of more than twice its share gets a larger table than the others (all entries of 131 k IDs in 16 buckets 163 us without, 29.4; in
+    // 65 buckets 102 and 20.9).
+    uint32_t slots = shape.bucket_slots;
+    while (slots < kPartSlots && slots < 2 * total) slots *= 2;
+    if (slots > shape.bucket_slots) part_clear(table, shape.bucket_slots, slots, kBucketBlock);
     __syncthreads();
     uint32_t place[kBucketItems], pos[kBucketItems], id[kBucketItems], slot[kBucketItems];
     const uint32_t chunks = (total + kBucketBlock * kBucketItems - 1) / (kBucketBlock * kBucketItems);
@@ -299,7 +305,7 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
 #pragma unroll
         for (int k = 0; k < kBucketItems; ++k) {
             if (place[k] == ~0u) continue;
-            slot[k] = part_slot(table, shape.bucket_slots, id[k], part_hash(id[k]), kPartProbes);
+            slot[k] = part_slot(table, slots, id[k], part_hash(id[k]), kPartProbes);
             if (slot[k] == kNoSlot) s_full = 1;
             else if (part_low(table, slot[k]) > pos[k]) atomicMin(table.low + slot[k], pos[k]);
         }
@@ -311,7 +317,7 @@ __global__ __launch_bounds__(kBucketBlock) void dedup_bucket_kernel(PartScratch 
                 entries(chunk);
 #pragma unroll
                 for (int k = 0; k < kBucketItems; ++k)
-                    if (place[k] != ~0u) slot[k] = part_slot(table, shape.bucket_slots, id[k], part_hash(id[k]), kPartProbes);
+                    if (place[k] != ~0u) slot[k] = part_slot(table, slots, id[k], part_hash(id[k]), kPartProbes);
             }
 #pragma unroll
             for (int k = 0; k < kBucketItems; ++k)

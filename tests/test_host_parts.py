@@ -166,6 +166,16 @@ int main(int argc, char** argv) {
             }
             results(v, n, false);
         }
+    } else if (what == "crowded") {                      // a bucket of many times its share, that a table in LDS takes: nothing goes by memory
+        std::vector<int32_t> v = hashing_to(5000, 0xff800000u, 5u << 23);
+        for (int j = 0; j < 16000; ++j) v.push_back(static_cast<int32_t>(next_random() >> 1));
+        for (size_t j = v.size() - 1; j > 0; --j) std::swap(v[j], v[next_random() % (j + 1)]);
+        results(v, v.size(), false);
+        Call c(v, v.size());
+        c.n_slots = 0;                                   // (what would use the memory raises an error)
+        c.split();
+        c.buckets();
+        check(c.err[0] == 0, "by LDS");
     } else if (what == "pieces") {                       // the words of two calls side by side, as their waves write them, and any words
         const int n = 32 * kPartTile;
         std::vector<int32_t> one(n, 77), distinct(n);
@@ -224,7 +234,7 @@ def program(tmp_path_factory):
     return str(d / "main")
 
 
-@pytest.mark.parametrize("what", ["results", "uneven", "slots", "lines", "pieces", "tickets", "foreign"])
+@pytest.mark.parametrize("what", ["results", "uneven", "slots", "lines", "crowded", "pieces", "tickets", "foreign"])
 def test_list_by_parts(program, what):
     r = subprocess.run([program, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout == "ok\n", (r.returncode, r.stdout)
