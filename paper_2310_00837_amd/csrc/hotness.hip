@@ -18,13 +18,16 @@
 //            the rank along), puts their places into order in LDS and writes them out as runs.
 // Bins are numbered from the highest digit down, so each pass goes out in
 // descending digit order.  The first pass takes three launches, each of the others one, in which the workgroups draw
-// the jobs of all phases in order (sort_pass_kernel), because an idle launch costs 2.7 us and there would be six of them.
+// the jobs of all phases (sort_pass_kernel), because an idle launch costs 2 us and there would be six of them.
 //
 // What bounds it: the chain of steps of the scatter's two tiles per workgroup, its ballots and its LDS traffic; memory second.
 // Measured at 8 M nodes with counts up to 512: count 10 us, scan 8, scatter 29
-// (its 64 MB would take 11 us); 54 us in all, 111 M nodes 521.  With three launches for each of the other passes, too, and a scatter
-// that looked at all bits (35 us) it took 64 and 561 us, 20 000 nodes 33.5 (now 27); and where those passes run, 8 M nodes 146
-// (two passes; now 150) and 229 (three; now 240), 111 M 1808 (1767) and 2991 (2951).
+// (its 64 MB would take 11 us); 52 us in all, 111 M nodes 520.  With three launches for each of the other passes, too, and a scatter
+// that looked at all bits (35 us) it took 63 and 563 us, 20 000 nodes 33 (now 26); where two passes run, 20 000 nodes 49.7 (now 45.7),
+// 1 M 56.7 (53.9), 4 M 94.8 (91.8), 8 M 145 (138), 111 M 1815 (1709); three, which takes counts of 4.2 M and more, 20 000 nodes 68.0 (69.5), 1 M 79.8
+// (82.4), 2 M 94.4 (92.4), 4 M 138 (131), 8 M 224 (221), 111 M 3010 (2942).  The launches between the phases cost about what the
+// waits do; what the one launch gains where the pass runs is the ranking of every workgroup's first tile before the sums are there
+// (8 M, two passes 141 without, three 233).
 // With a row of counters per tile, one copy of the count's counters and a scatter of one workgroup per CU it took
 // 82 (17, 9.6 and 45) at 8 M and 858 us.
 //
@@ -60,8 +63,11 @@ constexpr int kCopies = 4;                                // of the count's coun
 constexpr uint32_t kScanSlices = kBins / kScanBins;       // workgroups (or jobs) of a scan
 constexpr int kControlStride = 32;                        // words: what is counted or waited for lies 128 bytes apart
 constexpr int kGoLines = 32;                              // copies of the word that is waited for
-constexpr int kControlPass = (3 + 2 * kGoLines) * kControlStride;       // ticket, groups counted, slices scanned; go (scan), go (scatter)
+constexpr int kCountTickets = 8;                         // counters that the groups to count are drawn from
+constexpr int kControlLate = kCountTickets, kControlDone = kControlLate + 1, kControlGo = kControlDone + 2;       // lines of a pass
+constexpr int kControlPass = (kControlGo + 2 * kGoLines) * kControlStride;
 constexpr int kControlWords = (kSortPasses - 1) * kControlPass;
+static_assert(kCopies == 4, "a bin is read as one word of 16 bytes");
 static_assert(kSortTile == 1 << kPlaceBits && kBins == 4 * kPlaceBlock, "a thread of the scatter has four bins");
 
 __global__ __launch_bounds__(kBlock) void hotness_add_kernel(const int32_t* __restrict__ ids, Count n_in, int64_t n_nodes,
@@ -136,14 +142,18 @@ __device__ __forceinline__ uint32_t thread_now() {
 // Bound by the LDS atomics: most counts are one of a few small numbers, and lanes that add to one word take their turns.
 // Four copies of the counters, by lane, cut the queues to a quarter: 17.3 -> 10.2 us for 8 M counts (eight copies: no difference).
 struct CountLds {
-    uint32_t hist[kBins * kCopies];
+    alignas(16) uint32_t hist[kBins * kCopies];
     uint32_t set, clear;
 };
 template <int B, bool SHARED>
 __device__ __forceinline__ void count_group(const SortArgs& a, int pass, const int32_t* keys, uint32_t group, CountLds& s) {
     const uint32_t t = thread_now<SHARED>();
     constexpr int kItems = kSortTile / B;
-    for (uint32_t q = t; q < kBins * kCopies; q += B) s.hist[q] = 0;
+    typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+    words4* bins = reinterpret_cast<words4*>(s.hist);
+    uint32_t zero = 0;
+    if (SHARED) asm volatile("" : "+v"(zero));            // (as in thread_now)
+    for (uint32_t q = t; q < kBins; q += B) bins[q] = words4{zero, zero, zero, zero};
     if (t == 0) s.set = s.clear = 0;
     __syncthreads();
     const uint32_t tile1 = min((group + 1) * a.group_tiles, a.n_tiles);
@@ -173,9 +183,8 @@ __device__ __forceinline__ void count_group(const SortArgs& a, int pass, const i
     }
     __syncthreads();
     for (uint32_t q = t; q < kBins; q += B) {
-        uint32_t sum = 0;
-#pragma unroll
-        for (int k = 0; k < kCopies; ++k) sum += s.hist[q * kCopies + k];
+        const words4 c = bins[q];
+        const uint32_t sum = c.x + c.y + c.z + c.w;
         put_word<SHARED>(a.group_counts + static_cast<size_t>(group) * kBins + q, sum);
     }
     if (pass == 0 && t == 0) {
@@ -216,8 +225,8 @@ __device__ __forceinline__ void scan_slice(const SortArgs& a, uint32_t slice, Sc
     }
     s.sum[walker][bin] = sum;
     __syncthreads();
-    for (uint32_t b = static_cast<uint32_t>(wave_id()); b < kScanBins; b += B / kWave) {      // one wave per bin
-        const uint32_t w = static_cast<uint32_t>(lane_id());
+    for (uint32_t b = t / kWave; b < kScanBins; b += B / kWave) {                             // one wave per bin
+        const uint32_t w = t % kWave;
         const uint32_t mine = w < kWalkers ? s.sum[w][b] : 0u, inc = dpp_inclusive_scan(mine);
         if (w < kWalkers) s.sum[w][b] = inc - mine;
         if (w == kWave - 1) put_word<SHARED>(a.totals + slice * kScanBins + b, inc);
@@ -283,15 +292,16 @@ struct PlaceLds {
     int32_t word[kSortTile];
     uint32_t wave[kPlaceWaves];
 };
-template <bool SHARED>
-__device__ __forceinline__ void scatter_group(const SortArgs& a, int pass, const SortStep& step, uint32_t group, PlaceLds& s) {
+// ready: waits until the sums of the counts are there.  The first tile is ranked before that, beside the phases that make them.
+template <bool SHARED, class Ready>
+__device__ __forceinline__ void scatter_group(const SortArgs& a, int pass, const SortStep& step, uint32_t group, PlaceLds& s, const Ready& ready) {
     const uint32_t t = thread_now<SHARED>();
     // (pointers by condition and no a.keys[i], or the arguments end up in scratch memory)
     const int32_t* keys_in = step.before == 0 ? a.counts : step.before == 1 ? a.keys[0] : a.keys[1];
     const int32_t* vals_in = step.before == 0 ? nullptr : step.to_order ? a.vals1 : a.order;
     int32_t* keys_out = step.last ? nullptr : step.before == 0 ? a.keys[0] : a.keys[1];
     int32_t* vals_out = step.to_order ? a.order : a.vals1;
-    const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(wave_id())), lane = static_cast<uint32_t>(lane_id());
+    const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(t / kWave))), lane = t % kWave;
     constexpr int kPer = kBins / kPlaceBlock;    // bins per thread: consecutive ones
     // exclusive sums over the bins of the whole list
     const auto scan_bins = [&](const uint32_t (&v)[kPer], uint32_t (&before)[kPer]) {
@@ -312,12 +322,16 @@ __device__ __forceinline__ void scatter_group(const SortArgs& a, int pass, const
         __syncthreads();
     };
     const uint32_t n = a.n;
-    uint32_t total[kPer], next[kPer];            // next: where the tile's pairs of the bin go in the output
+    uint32_t next[kPer];                         // where the tile's pairs of the bin go in the output
+    const auto first_places = [&] {
+        uint32_t total[kPer];
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) total[q] = get_word<SHARED>(a.totals + t * kPer + q);
-    scan_bins(total, next);
+        for (int q = 0; q < kPer; ++q) total[q] = get_word<SHARED>(a.totals + t * kPer + q);
+        scan_bins(total, next);
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) next[q] += get_word<SHARED>(a.group_counts + static_cast<size_t>(group) * kBins + t * kPer + q);
+        for (int q = 0; q < kPer; ++q) next[q] += get_word<SHARED>(a.group_counts + static_cast<size_t>(group) * kBins + t * kPer + q);
+    };
+    if (!SHARED) first_places();
     const uint32_t tile1 = min((group + 1) * a.group_tiles, a.n_tiles);
     for (uint32_t tile = group * a.group_tiles; tile < tile1; ++tile) {
         // a wave owns 1024 consecutive pairs, 64 per round
@@ -348,6 +362,10 @@ __device__ __forceinline__ void scatter_group(const SortArgs& a, int pass, const
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
+        if (SHARED && tile == group * a.group_tiles) {
+            ready();
+            first_places();
+        }
         // four counters of 16 bits at a time: their sums over the waves, and where the bins begin, stay below 2^16
         unsigned long long sum = 0, before[kPlaceWaves];
 #pragma unroll
@@ -406,16 +424,34 @@ __device__ __forceinline__ void scatter_group(const SortArgs& a, int pass, const
 
 __global__ __launch_bounds__(kPlaceBlock) void sort_scatter_kernel(SortArgs a) {
     __shared__ PlaceLds s;
-    scatter_group<false>(a, 0, SortStep(0, *a.varying), blockIdx.x, s);
+    scatter_group<false>(a, 0, SortStep(0, *a.varying), blockIdx.x, s, [] {});
 }
 
-// A pass after the first, if it runs.  The jobs (a group to count, a slice to scan, a group to scatter) are numbered phase by phase,
-// and a workgroup draws the next number from a counter until there is none.  A job waits until all jobs of the phase before it
-// are done; those have lower numbers, so workgroups that run already hold them, and the lowest job that is not done waits for
-// nothing: however few workgroups the GPU has room for, the launch ends.  Between the phases only the counts and their sums
-// change hands, as words that go past the L2s (put_word): a wave waits until its own are there before its job counts as done.
-// Whoever finishes a phase says so in 32 places, as hundreds that look at one word keep those away that add to it (10 ns each;
-// 8 M nodes, a second pass: 120 us when they did).
+// A pass after the first, if it runs.  The jobs (a group to count, a slice to scan, a group to scatter) are done phase by phase, and
+// a workgroup draws one after the other until there is none.  The groups to count are drawn from eight counters, a workgroup's own
+// first (489 draws from one took 4 us), all other jobs, in order, from one more, and only once every group is seen to be drawn.
+// A job waits until all jobs of the phase before it are done; workgroups that run already hold those, and the lowest job that is
+// not done waits for nothing: however few workgroups the GPU has room for, the launch ends.  Between the phases only the counts
+// and their sums change hands, as words that go past the L2s (put_word): a wave waits until its own are there before its job counts
+// as done.  Whoever finishes a phase says so in 32 places, as hundreds that look at one word keep those away that add to it (10 ns
+// each; 8 M nodes, a second pass: 120 us when they did).
+__device__ __forceinline__ uint32_t draw(uint32_t* counter) {                  // (by the first wave)
+    uint32_t t = 0;
+    if (thread_now<true>() == 0) t = atomicAdd(counter, 1u);
+    return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(t)));
+}
+__device__ __forceinline__ uint32_t draw_job(uint32_t* control, uint32_t n_groups, uint64_t look) {      // look: counters to draw from at once
+    while (true) {
+        for (; look != 0; look &= look - 1) {
+            const uint32_t c = static_cast<uint32_t>(__ffsll(static_cast<long long>(look)) - 1), group = draw(control + c * kControlStride) * kCountTickets + c;
+            if (group < n_groups) return group;
+        }
+        const uint32_t c = thread_now<true>() % kCountTickets;
+        look = __ballot(get_word<true>(control + c * kControlStride) * kCountTickets + c < n_groups) & ((1u << kCountTickets) - 1);
+        if (look == 0) return n_groups + draw(control + kControlLate * kControlStride);
+    }
+}
+
 template <int PASS>
 __global__ __launch_bounds__(kPlaceBlock, 4) void sort_pass_kernel(SortArgs a) {
     __shared__ union {
@@ -427,30 +463,32 @@ __global__ __launch_bounds__(kPlaceBlock, 4) void sort_pass_kernel(SortArgs a) {
     const SortStep step(PASS, *a.varying);
     if (!step.active) return;
     const uint32_t n_jobs = 2 * a.n_groups + kScanSlices;
-    uint32_t* ticket = a.control + (PASS - 1) * kControlPass;
-    if (threadIdx.x == 0) s_job = atomicAdd(ticket, 1u);
+    uint32_t* control = a.control + (PASS - 1) * kControlPass;
+    if (threadIdx.x < kWave) s_job = draw_job(control, a.n_groups, 1u << blockIdx.x % kCountTickets);
     __syncthreads();
     for (uint32_t job; (job = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(s_job)))) < n_jobs;) {
         const uint32_t phase = job < a.n_groups ? 0u : job < a.n_groups + kScanSlices ? 1u : 2u;
-        if (phase > 0) {
+        const auto wait = [&] {                  // for the phase before this one
             if (threadIdx.x == 0) {
-                const uint32_t* go = ticket + (3 + (phase - 1) * kGoLines + job % kGoLines) * kControlStride;
+                const uint32_t* go = control + (kControlGo + (phase - 1) * kGoLines + job % kGoLines) * kControlStride;
                 uint32_t budget = kScanSpinBudget;
                 while (__hip_atomic_load(go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 && --budget > 0) __builtin_amdgcn_s_sleep(4);
                 if (budget == 0) raise(a.err, kErrInternal);       // gave up: report, and let the launch drain
             }
             __syncthreads();
-        }
+        };
+        if (phase == 1) wait();
         if (phase == 0) count_group<kPlaceBlock, true>(a, PASS, step.before == 1 ? a.keys[0] : a.keys[1], job, s.count);
         else if (phase == 1) scan_slice<kPlaceBlock, true>(a, job - a.n_groups, s.scan);
-        else scatter_group<true>(a, PASS, step, job - a.n_groups - kScanSlices, s.place);
+        else scatter_group<true>(a, PASS, step, job - a.n_groups - kScanSlices, s.place, wait);
         if (phase < 2) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (threadIdx.x == 0) {
-            if (phase < 2 && atomicAdd(ticket + (phase + 1) * kControlStride, 1u) + 1 == (phase == 0 ? a.n_groups : kScanSlices))
-                for (int q = 0; q < kGoLines; ++q)
-                    put_word<true>(ticket + (3 + phase * kGoLines + q) * kControlStride, 1u);
-            s_job = atomicAdd(ticket, 1u);
+        if (threadIdx.x < kWave) {
+            if (phase < 2 && draw(control + (kControlDone + phase) * kControlStride) + 1 == (phase == 0 ? a.n_groups : kScanSlices)) {
+                const uint32_t q = thread_now<true>();
+                if (q < kGoLines) put_word<true>(control + (kControlGo + phase * kGoLines + q) * kControlStride, 1u);
+            }
+            s_job = phase == 0 ? draw_job(control, a.n_groups, 0) : a.n_groups + draw(control + kControlLate * kControlStride);
         }
         // (The loop has to end with a barrier: with that `if` as its end the compiler makes two loops of it, and the lanes beside lane 0
         // go round without it.)

@@ -30,7 +30,12 @@ typedef int hipError_t;
 typedef void* hipStream_t;
 typedef void* hipEvent_t;
 constexpr hipError_t hipSuccess = 0, hipErrorInvalidValue = 1;
+enum hipMemcpyKind { hipMemcpyDefault = 4 };
 inline hipError_t hipGetLastError() { return hipSuccess; }
+inline hipError_t hipMemcpyAsync(void* to, const void* from, size_t bytes, hipMemcpyKind, hipStream_t) {
+    memmove(to, from, bytes);
+    return hipSuccess;
+}
 
 struct dim3 {
     unsigned x, y, z;
@@ -173,13 +178,13 @@ inline unsigned on_host_mbcnt(unsigned mask, unsigned v, unsigned first) {
     return v + static_cast<unsigned>(__builtin_popcount(mask & below));
 }
 #define __builtin_amdgcn_readlane on_host_readlane
-#define __builtin_amdgcn_readfirstlane(v) (v)                  // (used on values that are the same in all lanes)
+#define __builtin_amdgcn_readfirstlane(v) (v)                  // (used on values that are the same in all lanes, unless the test has its own)
 #define __builtin_amdgcn_update_dpp on_host_dpp
 #define __builtin_amdgcn_mbcnt_lo(mask, v) on_host_mbcnt(mask, v, 0)
 #define __builtin_amdgcn_mbcnt_hi(mask, v) on_host_mbcnt(mask, v, 32)
 #define __builtin_amdgcn_s_sleep(n) on_host::give_way()
 #define __builtin_amdgcn_fence(...) ((void)0)
-#define __builtin_amdgcn_wave_barrier() ((void)0)
+#define __builtin_amdgcn_wave_barrier() ((void)on_host::meet(on_host::waves[on_host::now / on_host::kLanes]))
 template <class T>
 T __shfl_xor(T v, int d, int) {
     uint64_t lanes;
@@ -192,6 +197,15 @@ T __shfl_up(T v, unsigned d, int) {
     const int64_t* all = on_host::exchange(v, &lanes);
     return lane < d ? v : static_cast<T>(all[lane - d]);
 }
+inline int on_host_sbfe(int v, unsigned at, unsigned bits) { return (v << (32 - at - bits)) >> (32 - bits); }
+inline uint32_t on_host_bitop3(uint32_t x, uint32_t y, uint32_t z, int table) {
+    uint32_t r = 0;
+    for (int q = 0; q < 8; ++q)
+        if ((table >> q) & 1) r |= (q & 4 ? x : ~x) & (q & 2 ? y : ~y) & (q & 1 ? z : ~z);
+    return r;
+}
+#define __builtin_amdgcn_sbfe on_host_sbfe
+#define __builtin_amdgcn_bitop3_b32 on_host_bitop3
 inline int __popc(uint32_t v) { return __builtin_popcount(v); }
 inline int __popcll(uint64_t v) { return __builtin_popcountll(v); }
 inline int __ffsll(long long v) { return __builtin_ffsll(v); }
@@ -204,6 +218,7 @@ inline uint32_t __umulhi(uint32_t a, uint32_t b) { return static_cast<uint32_t>(
 #define __HIP_MEMORY_SCOPE_SYSTEM 2
 #define __hip_atomic_load(p, order, scope) on_host::load(p, scope)
 #define __hip_atomic_store(p, v, order, scope) on_host::store(p, v)
+#define __hip_atomic_fetch_add(p, v, order, scope) atomicAdd(p, v)
 namespace on_host {
 template <class T>
 T load(const T* p, int scope) {
