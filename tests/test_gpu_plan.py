@@ -125,9 +125,10 @@ def test_two_batches_queued_per_context(helios, oracle):
     first.close()
 
 
-@pytest.mark.parametrize("n_seeds,fanouts", [(3_000, [25, 2]), (9_000, [40, 1])])
+@pytest.mark.parametrize("n_seeds,fanouts", [(3_000, [25, 2]), (9_000, [40, 1]), (16_384, [8, 1]), (3_000, [65, 1]), (16_385, [8, 1]), (32_769, [9, 1])])
 def test_recorded_batches_of_long_seed_lists(helios, oracle, n_seeds, fanouts):
-    """More seeds than the sampling pass counts by itself, in recordings: counted and sampled in one launch, and in two."""
+    """More seeds than the sampling pass counts by itself, in recordings: counted and sampled in one launch (the first three), and in
+    two (a fan-out above 64, or more seeds than fit one launch: 16 384 with fan-outs up to 8, 32 768 above)."""
     rng = np.random.default_rng(n_seeds)
     n, n_hbm, n_host = 50_000, 20_000, 20_000
     off = np.concatenate([[0], np.cumsum(rng.integers(0, 60, n))]).astype(np.int64)

@@ -99,7 +99,7 @@ def test_dedup_reports_bad_ids_and_keeps_the_rest(h, helios, oracle, n_ids):
 
 
 @pytest.mark.parametrize("n_seeds,fanouts", [(2_048, [4, 3]), (2_049, [4, 3]), (2_049, [25, 3]), (8_192, [33, 2]), (8_193, [33, 2]), (16_384, [32, 1]),
-                                              (16_385, [32, 1]), (32_768, [9, 1]), (32_769, [9, 1]), (32_768, [8, 1]), (4_000, [64, 1]), (4_000, [65, 1]), (ONE_ITEM_MAX + 5, [1, 2]), (60_000, [4, 2]),
+                                              (16_385, [32, 1]), (32_768, [9, 1]), (32_769, [9, 1]), (16_384, [8, 1]), (16_385, [8, 1]), (32_768, [8, 1]), (4_000, [64, 1]), (4_000, [65, 1]), (ONE_ITEM_MAX + 5, [1, 2]), (60_000, [4, 2]),
                                               (150_000, [4, 4]), (512 * 2048 + 1, [1, 1])])
 def test_whole_path_with_long_lists(h, helios, oracle, n_seeds, fanouts):
     """Seed lists on both sides of the folded count pass and of the launch that counts and samples (512 tiles by lane group), stages and hops longer than one item per thread serves, and such
@@ -466,38 +466,44 @@ def test_dedup_by_parts_with_repeats_at_the_ends_of_tiles(h, n_ids):
 
 def test_launches_that_wait_on_several_streams(helios, oracle):
     """Hotness orders of all passes, lists by parts and long seed lists of four contexts in flight on four streams: launches whose
-    workgroups wait for others of theirs, side by side."""
+    workgroups wait for others of theirs, side by side.  Every call has inputs of its own: what an earlier one has left in the context's
+    scratch is wrong for it."""
     rng = np.random.default_rng(31)
     n, m, n_seeds, fan = 1_200_000, 700_001, 9_001, [25]
     off, idx = _graph(rng, n, 5)
     off_d, idx_d = torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda()
-    units = []
-    for k in range(4):
+    contexts, calls = [], []
+    for _ in range(4):
         h = helios.Helios(0, stream=torch.cuda.Stream())
         h.csr_load(off_d, idx_d)
         h.reserve(m)
+        contexts.append(h)
+    for k in range(12):
         counts = rng.integers(0, 1 << 31, n).astype(np.int32)
         ids = rng.integers(0, n, m).astype(np.int32)
+        near = rng.integers(300, m, m // 4)
+        ids[near] = ids[near - rng.integers(1, 300, near.size)]           # (repeats within a tile, too)
         seeds = rng.integers(0, n, n_seeds).astype(np.int32)
-        units.append(dict(h=h, counts=counts, ids=ids, seeds=seeds, counts_d=torch.from_numpy(counts).cuda(), ids_d=torch.from_numpy(ids).cuda(),
+        calls.append(dict(h=contexts[k % 4], counts=counts, ids=ids, seeds=seeds, counts_d=torch.from_numpy(counts).cuda(), ids_d=torch.from_numpy(ids).cuda(),
                           seeds_d=torch.from_numpy(seeds).cuda(), order=torch.empty(n, dtype=torch.int32, device="cuda"),
                           uniq=torch.empty(m, dtype=torch.int32, device="cuda"), inv=torch.empty(m, dtype=torch.int32, device="cuda"),
                           nu=torch.zeros(1, dtype=torch.int64).pin_memory(), hops=helios.alloc_hops(n_seeds, fan, "cuda"),
                           sizes=torch.zeros(2, dtype=torch.int64).pin_memory()))
     torch.cuda.synchronize()
-    for _ in range(3):
-        for u in units:
-            u["h"].hotness_order(u["counts_d"], u["order"])
-            u["h"].dedup(u["ids_d"], u["uniq"], u["inv"], u["nu"])
-            u["h"].sample(u["seeds_d"], fan, 5, u["hops"], u["sizes"])
-    for u in units:
-        u["h"].sync()
-    for u in units:
+    for k, u in enumerate(calls):
+        u["h"].hotness_order(u["counts_d"], u["order"])
+        u["h"].dedup(u["ids_d"], u["uniq"], u["inv"], u["nu"])
+        u["h"].sample(u["seeds_d"], fan, 5 + k, u["hops"], u["sizes"])
+    for h in contexts:
+        h.sync()
+    for k, u in enumerate(calls):
         assert np.array_equal(u["order"].cpu().numpy(), oracle.hotness_order(u["counts"]))
         wu, wi = oracle.dedup(n, u["ids"])
         assert int(u["nu"][0]) == wu.size and np.array_equal(u["uniq"][:wu.size].cpu().numpy(), wu)
         assert np.array_equal(u["inv"].cpu().numpy(), wi)
-        indptr = np.concatenate([[0], np.cumsum(np.minimum(np.diff(off)[u["seeds"]], fan[0]))])
-        assert u["sizes"].tolist() == [n_seeds, int(indptr[-1])]
-        assert np.array_equal(u["hops"][0].indptr.cpu().numpy(), indptr)
-        u["h"].close()
+        frontier, indptr, flat = oracle.sample(off, idx, u["seeds"], fan, 5 + k)[0]
+        assert u["sizes"].tolist() == [frontier.size, flat.size]
+        for got, want in ((u["hops"][0].frontier, frontier), (u["hops"][0].indptr, indptr), (u["hops"][0].flat, flat)):
+            assert np.array_equal(got[:want.size].cpu().numpy(), want)
+    for h in contexts:
+        h.close()
