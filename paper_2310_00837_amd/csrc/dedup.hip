@@ -140,7 +140,7 @@ __device__ __forceinline__ void part_clear(PartTable& t, uint32_t from, uint32_t
 }
 // the whole hash: the highest bits are the bucket, the next the place in the table, the lowest the step
 __device__ __forceinline__ uint32_t part_hash(uint32_t id) { return hash_id(id, 0xffffffffu); }
-// The split's table is half full at most, a bucket's about that in the longest lists, and a wave waits for the longest of its 64
+// The split's table is at most three quarters full (6144 IDs), a bucket's about half in the longest lists, and a wave waits for the longest of its 64
 // searches: steps of the ID's own, odd ones, which come by every slot, keep those short.
 __device__ __forceinline__ uint32_t part_step(uint32_t h) { return (h << 1) | 1u; }
 // The ID's slot, claimed if need be; kNoSlot after probes_max others.  (A plain read before the atomic: the entries of a hub would

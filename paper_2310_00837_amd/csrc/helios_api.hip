@@ -58,9 +58,12 @@ uint32_t pow2_at_least(int64_t n) {
 }
 
 // Slots of a batch's table for at most n IDs: two for each, and eight where that is no more than 32 k (256 KB), because a wave
-// waits for the longest of its 64 searches, each step of which is a round trip to memory: 128 seeds with fan-outs 5 and 5, launched
-// directly, 41.1 us with two, 39.8.  With eight for longer lists, too, a gang of four pays more for the emptying than it gains
-// (57.0/57.9).  The bounds are several times what batches bring, so longer lists are rarely crowded.
+// waits for the longest of its 64 searches, each step of which is a round trip to memory.  Measured, us with two / with eight, launched directly
+// (recorded; a gang of four): 32 seeds with fan-outs 5 and 5 31/30 (36.9/35.2; 40.4/37.6), 128 34.7/32.0 (42.1/38.8; 46.1/41.3), 256 34.4/32.4
+// (41.8/39.3; 48.4/45.1), 512 with 5 and 3 37.0/35.2 (43.6/41.8; 51.8/50.4), 1024 with 3 and 2 39.7/37.7 (47.6/44.5; 54.0/51.1), 1024 with 3 24.3/19.9
+// (33.0/28.4; 39.1/30.7), 300 with 10 20.4/20.2 (28.9/27.4; 31.2/29.2), and where the bounds leave few of them 256 with 10 and 10 34.4/34.0 (41.5/41.0;
+// 47.9/46.6), 700 with 15, 10 and 5 65.3/65.5 (76.7/77.0; 137/138).  With eight for lists of up to 16 384 up to 3 us less for those between, but with eight for all
+// a gang of four of 1024 seeds with 25 and 10 pays more for the emptying than it gains (57.0/57.9).
 uint32_t batch_slots_for(int64_t n) { return std::max(pow2_at_least(2 * n), pow2_at_least(8 * std::min<int64_t>(n, 4096))); }
 
 void free_scratch(helios_ctx* c) {

@@ -1,7 +1,7 @@
 // Hop 0 of seed lists that are too long for the count that the sampling pass folds in (sample_dev.hpp).
 //
-// Up to 512 workgroups' worth of seeds (8 192 to 32 768 by fan-out) are counted and sampled in one launch
-// (sample_counted_kernel).  Longer lists, and fan-outs above 64, get a count pass as a kernel of its own first: every
+// Up to 16 384 seeds with fan-outs up to 8, and up to 32 768 with fan-outs of 9 to 64, are counted and sampled in one launch
+// (sample_counted_kernel), unless the samples go where the seeds are.  Longer lists, and fan-outs above 64, get a count pass as a kernel of its own first: every
 // thread reads the row bounds of its frontier nodes, the sample counts min(deg, fanout) are scanned in the workgroup
 // and chained across workgroups (TileScan in scan.hpp) into indptr, each node's place in `flat`.
 #include "kernels.hpp"
@@ -239,7 +239,10 @@ static int64_t counted_per_tile(int64_t n, uint32_t stride) {
 
 // Measured, us for helios_sample as two launches / as one: fan-outs 25 and 10, 2 049 seeds 25.2/21.9, 8 192 34.0/31.0, 16 384 45.7/42, 32 768 65.5/63;
 // 10 alone, 2 049 10.8/7.8, 16 384 10.9/7.6, 32 768 13.7/11.8; 60 alone, 10 000 13.8/11.4, 32 768 22.2/19.6; 8 alone, 16 384 11.0/7.5, 32 768 (two
-// tiles for each CU) 11.3/11.6, so that is left out.
+// tiles for each CU) 11.3/11.6, so that is left out.  Four streams at the same time, us for four calls: 9 000 seeds with 10 47/31, with 25 and 10
+// 80/71.  Recorded batches, rows of 32 bytes in HBM, one after the other (alone; three streams at the same time, for three): 2 049 seeds with 25
+// and 10 60.5/56.6 (69.0/65.0; 85.7/83.3), 9 000 99.4/96.2 (108/105; 195/193), 9 000 with 10 alone 39.7/35.0 (48.2/42.6; 60/56), 16 384 with 8
+// 47.2/42.0 (55.8/50.9; 67.6/64.3), 32 768 with 10 61.3/56.2 (69.5/64.4; 100/101), 9 000 with 60 47.9/42.0 (56.6/51.4; 70/66).
 unsigned sample_counted_blocks(int32_t fanout, int64_t n, uint32_t stride, unsigned* waves) {
     const int64_t per_tile = counted_per_tile(n, stride), lanes = group_lanes(fanout);
     *waves = lanes == 8 ? 8 : 16;
