@@ -149,6 +149,8 @@ hipError_t launch_dedup_compact_plain(hipStream_t stream, const CompactArgs& a, 
 //   4 k 12.9/17 (12.5/17)   8 k 12.9/15.7 (13/15.6; 145/15.3)   16 k 13.5/15.7 (14/16.5)   25 k 14.7/15.8 (14.8/16)   32 k 16.0/16.1 (16.6/16.2; 510/16)
 //   41 k 17.2/16.3 (16.1/16.7)   50 k 18.3/16.6 (17.5/16.7)   65 k 20.5/17 (19.7/17; 1050/15); with two slots an ID 98 k 24.5/18.2   262 k 41/23
 //   1.1 M 102/38   2 M 165/57.  Above 2 M a bucket would have more IDs than half its table.
+// Of few distinct IDs without a hub the table is the quicker way a little longer: 3 000 distinct ones, 32 k 15.4/16.9, 50 k 17.0/17.7, 65 k 18.9/18.
+// All IDs of one bucket of the hash: see dedup.hip.
 // With two to four slots an ID the table takes 20 k 16.3 (17.6), 25 k 16.3 (18.5), 32 k 19.5 (25.5), so there the line lies lower.
 inline bool dedup_by_parts(int64_t n, uint32_t slots) { return n >= (slots >= 4 * n ? 32768 : 20000) && n <= kPartsMax; }
 // The list is cut into tiles, one to a workgroup: 256 of them, so that every CU has one, but of 1024 entries or more; and 512 if 256

@@ -99,7 +99,7 @@ def test_dedup_reports_bad_ids_and_keeps_the_rest(h, helios, oracle, n_ids):
 
 
 @pytest.mark.parametrize("n_seeds,fanouts", [(2_048, [4, 3]), (2_049, [4, 3]), (2_049, [25, 3]), (8_192, [33, 2]), (8_193, [33, 2]), (16_384, [32, 1]),
-                                              (16_385, [32, 1]), (32_768, [9, 1]), (32_769, [9, 1]), (16_384, [8, 1]), (16_385, [8, 1]), (32_768, [8, 1]), (4_000, [64, 1]), (4_000, [65, 1]), (ONE_ITEM_MAX + 5, [1, 2]), (60_000, [4, 2]),
+                                              (16_385, [32, 1]), (32_768, [9, 1]), (32_769, [9, 1]), (16_384, [8, 1]), (16_385, [8, 1]), (32_768, [8, 1]), (3_000, [0, 2]), (3_000, [5, 0]), (4_000, [64, 1]), (4_000, [65, 1]), (ONE_ITEM_MAX + 5, [1, 2]), (60_000, [4, 2]),
                                               (150_000, [4, 4]), (512 * 2048 + 1, [1, 1])])
 def test_whole_path_with_long_lists(h, helios, oracle, n_seeds, fanouts):
     """Seed lists on both sides of the folded count pass and of the launch that counts and samples (512 tiles by lane group), stages and hops longer than one item per thread serves, and such
@@ -120,6 +120,39 @@ def test_whole_path_with_long_lists(h, helios, oracle, n_seeds, fanouts):
     for _ in range(2):
         assert_same(gpu_path(h, helios, torch.from_numpy(seeds), fanouts, 99, fused=True), want)
     assert_same(gpu_path(h, helios, torch.from_numpy(seeds), fanouts, 99, fused=False), want)
+
+
+@pytest.mark.parametrize("n_seeds,fan", [(2_049, 8), (9_000, 25), (3_000, 64), (3_000, 65)])
+def test_long_seed_lists_cut_off_and_with_bad_seeds(h, helios, oracle, n_seeds, fan):
+    """Samples that do not fit, and seeds that are no nodes: what there is room for is right, nothing is written behind it."""
+    rng = np.random.default_rng(n_seeds + fan)
+    n = 20_000
+    off, idx = _graph(rng, n, 90)
+    off, idx = np.concatenate([off, off[-1:]]), idx            # (node n has no neighbours)
+    h.csr_load(torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda())
+    seeds = rng.integers(0, n, n_seeds).astype(np.int32)
+    bad = seeds.copy()
+    at = [0, 700, n_seeds - 1]
+    bad[at] = [-1, n + 1, -2**31]
+    lone = seeds.copy()
+    lone[at] = n
+    for kind in ("short", "bad"):
+        print("long seed lists", n_seeds, fan, kind, flush=True)
+        frontier, indptr, flat = oracle.sample(off, idx, lone if kind == "bad" else seeds, [fan], 12)[0]
+        cap = flat.size // 3 if kind == "short" else flat.size
+        room = torch.full((flat.size + 4096,), -9, dtype=torch.int32, device="cuda")
+        hops = [helios.HopBuffers(torch.empty(n_seeds, dtype=torch.int32, device="cuda"), torch.empty(n_seeds + 1, dtype=torch.int64, device="cuda"), room[:cap])]
+        sizes = torch.zeros(2, dtype=torch.int64).pin_memory()
+        given = bad if kind == "bad" else seeds
+        t = torch.from_numpy(given).cuda()
+        torch.cuda.synchronize()
+        h.sample(t, [fan], 12, hops, sizes)
+        with pytest.raises(helios.HeliosError) as e:
+            h.sync()
+        assert e.value.code == (helios.ECAPACITY if kind == "short" else helios.EDATA)
+        assert sizes.tolist() == [n_seeds, flat.size]
+        assert np.array_equal(hops[0].frontier.cpu().numpy(), given) and np.array_equal(hops[0].indptr.cpu().numpy(), indptr)
+        assert np.array_equal(room[:cap].cpu().numpy(), flat[:cap]) and bool((room[cap:] == -9).all())
 
 
 def test_gang_with_more_tiles_than_workgroups(helios, oracle):
